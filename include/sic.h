@@ -172,12 +172,13 @@ sic_status sic_push(sic_sim *sim);
  * deposits the new positions and solves the new field, so on return the field
  * is current for the new step.  If the field is stale it is brought up to date
  * first.  Steps run as captured HIP graphs of a tracer launch and a solve
- * launch each (SIC_PATH_FUSED).  With constant segments and at most 512
- * workgroups per launch (two per compute unit) a simulation's tracer
- * launches solve the previous step's charge themselves, in every workgroup,
- * and one solve launch closes each graph of up to 32 steps
- * (SIC_PATH_SOLVE_FIRST); a small simulation (at most 32 chunks of 64 tracer
- * slots) runs its steps in one launch of a single workgroup
+ * launch each (SIC_PATH_FUSED).  With at most 512 workgroups per launch (two
+ * per compute unit; linear segments: on at most 1024 cells) a simulation's
+ * step is one launch, which solves the previous step's charge itself, in
+ * every workgroup, and one solve launch closes the call
+ * (SIC_PATH_SOLVE_FIRST); a small simulation (constant segments, at most 32
+ * chunks of 64 tracer slots) runs its steps in one launch of a single
+ * workgroup
  * (SIC_PATH_RESIDENT).  All give the bits of the fused path in the split
  * forms.  Timing mode (sic_set_timing) always takes the fused path.  Async;
  * with refinement on (l_max > 0) each step is followed by a refinement pass

@@ -146,7 +146,7 @@ struct Pool {
   InstDesc *inst = nullptr;
   int2 *slot_items = nullptr;
   Partial *partials = nullptr;
-  // P, D (and R) in rep copies of slot_cap * max_cells words each
+  // P, D (and R) in rep copies of slot_cap * max_cells words each, one block
   void *meshP = nullptr;
   void *meshD = nullptr;
   void *meshR = nullptr;  // order 1
@@ -178,9 +178,9 @@ struct Pool {
   int64_t *dr_in_off = nullptr;  // per chunk of the reservation: first staging index
   int32_t dr_sheets = 0, dr_chunks = 0;
   // solve-first steps of a single simulation (allocated on first use): two
-  // more accumulator pairs (the pool's own is the third) and a second set of
+  // more accumulator sets (the pool's own is the third) and a second set of
   // work-item partials
-  void *sf_mesh = nullptr;     // P1, D1, P2, D2: rep copies of mesh_words each
+  void *sf_mesh = nullptr;     // acc_words each
   Partial *sf_part = nullptr;  // item_cap
 
   std::vector<SlotHost> slots;
@@ -284,7 +284,7 @@ void pool_free(Pool *p) {
     if (s.d_in_off) hipFree(s.d_in_off);
   void *bufs[] = {p->xs,        p->vs,       p->halo[0],  p->halo[1],  p->halo3[0],  p->halo3[1],
                   p->links,     p->chunks,   p->items,    p->n_items,  p->inst,      p->slot_items,
-                  p->partials,  p->meshP,    p->meshD,    p->meshR,    p->meshE,     p->meshRho,
+                  p->partials,  p->meshP,    p->meshE,    p->meshRho,
                   p->hist,      p->done,     p->slot_ids, p->segq,     p->cedge,     p->edge_prev,
                   p->ref_cnt,   p->ref_mask, p->ref_off,  p->ref_w,    p->ref_v,     p->ref_c,
                   p->dr_nt,     p->dr_closed, p->dr_q,    p->dr_work,  p->dr_state,  p->dr_in_off,
@@ -363,16 +363,14 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
   p->rep = batch ? 1 : single_rep(max_cells);
   {
     const size_t mc = (size_t)slot_cap * max_cells;
-    long long *mp = nullptr, *md = nullptr;
-    ALLOC(mp, mc * p->rep);
-    p->meshP = mp;
-    ALLOC(md, mc * p->rep);
-    p->meshD = md;
-    if (order == 1) {
-      long long *mr = nullptr;
-      ALLOC(mr, mc * p->rep);
-      p->meshR = mr;
-    }
+    // one block: P, D (and R), each in rep copies.  Float64 and 64-bit integer
+    // additions to memory execute at the memory channels, so arrays and copies
+    // that follow one another lie on different channels.
+    long long *acc = nullptr;
+    ALLOC(acc, mc * p->rep * (order == 1 ? 3 : 2));
+    p->meshP = acc;
+    p->meshD = acc + mc * p->rep;
+    if (order == 1) p->meshR = acc + 2 * mc * p->rep;
     ALLOC(p->meshE, mc);
     ALLOC(p->meshRho, mc);
   }
@@ -716,6 +714,9 @@ sic_status pool_autotune(Pool *p, int32_t steps, sic_tuning *best_out, double *b
 // Words of one copy of a charge accumulator (every slot's mesh).
 int64_t mesh_words(const Pool *p) { return (int64_t)p->slot_cap * p->max_cells; }
 
+// Words of all accumulators: P, D (and R) in all copies.
+int64_t acc_words(const Pool *p) { return (p->order == 1 ? 3 : 2) * p->rep * mesh_words(p); }
+
 TracerArgs tracer_args(Pool *p, int mode, int slot) {
   TracerArgs a;
   const bool one = slot >= 0;
@@ -831,29 +832,28 @@ sic_status get_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
   return SIC_OK;
 }
 
-// Solve-first steps: a single simulation with constant segments (not timed,
-// not refining on the device) runs k steps as k tracer launches whose
-// second and later ones solve the previous step's charge in every workgroup
-// (launch_tracers_sf), then one solve launch for the last step.  The charge
-// rotates through three accumulator pairs A0 (the pool's own), A1, A2 and
-// the partials through two buffers: launch i (1-based) merges into
-// A[(i - 1) mod 3] and writes partials (i - 1) mod 2, reads A[(i - 2) mod 3]
-// and partials (i - 2) mod 2, and clears A[i mod 3], which launch i - 1 read
-// and launch i + 1 merges into after this one has ended.  The closing solve
-// clears what it reads and a zero launch the pair launch k read, so every
-// pair is clear again, as the other paths expect.  The bits are those of the
-// tracer/solve launch pairs: the same solve code, the same sums in the same
-// order.
+// Solve-first steps: a single simulation (not timed, not refining on the
+// device) runs k steps as k launches of one workgroup per item, whose second
+// and later ones solve the previous step's charge in every workgroup
+// (launch_step), then one solve launch for the last step.  The charge
+// rotates through three accumulator sets A0 (the pool's own), A1, A2 and the
+// partials through two buffers: step i of the run (from 0) merges into
+// A[i mod 3] and writes partials i mod 2, reads A[(i - 1) mod 3] and partials
+// (i - 1) mod 2, and clears A[(i + 1) mod 3], which step i - 1 read and step
+// i + 1 merges into after this one has ended.  The closing solve clears what
+// it reads and the set that the last step read, so every set is clear again,
+// as the other paths expect.  The bits are those of the tracer/solve launch
+// pairs: the same solve code, the same sums in the same order.
 bool sf_ready(Pool *p) {
-  if (p->batch || p->order != 0 || p->timing || p->dev_refine || p->tune.fused_only || p->block < kSolveThreads ||
-      p->rep != single_rep(p->max_cells))
+  if (p->batch || p->timing || p->dev_refine || p->tune.fused_only || p->block < kSolveThreads ||
+      !step_supported(p->order, p->max_cells) || p->tile > p->block)
     return false;
   // every workgroup solves first: worth it while the workgroups run in one
   // round on the machine, not when each CU works through several in turn
   // (a 33.5M-tracer job's 2048 workgroups: 400 against 290 us per step)
   if (grid_for(p, -1) > kSfMaxGrid) return false;
   if (!p->sf_mesh) {
-    const size_t bytes = sizeof(double) * 4 * (size_t)p->rep * mesh_words(p);
+    const size_t bytes = sizeof(double) * 2 * (size_t)acc_words(p);
     if (hipMalloc(&p->sf_mesh, bytes) != hipSuccess) {
       p->sf_mesh = nullptr;
       return false;
@@ -869,43 +869,69 @@ bool sf_ready(Pool *p) {
   return true;
 }
 
-sic_status enqueue_sf(Pool *p, int64_t k, hipStream_t st) {
-  // each pair's copies lie mesh_words apart, as the pool's own
-  double *m = static_cast<double *>(p->sf_mesh);
-  const size_t mc = (size_t)p->rep * mesh_words(p);
-  void *AP[3] = {p->meshP, m, m + 2 * mc};
-  void *AD[3] = {p->meshD, m + mc, m + 3 * mc};
-  Partial *PB[2] = {p->partials, p->sf_part};
-  const size_t lds = tracer_lds_size(p->prec, p->order, p->seg, p->max_cells, p->tile);
-  for (int64_t i = 1; i <= k; ++i) {
-    TracerArgs a = tracer_args(p, kPush | kDeposit, -1);
-    a.meshP = AP[(i - 1) % 3];
-    a.meshD = AD[(i - 1) % 3];
-    a.partials = PB[(i - 1) % 2];
-    if (i == 1) {
-      LAUNCHCHK(p, launch_tracers(p->prec, kPush | kDeposit, p->order, p->seg, a, grid_for(p, -1), p->block, lds, st));
-    } else {
-      a.sf_P = AP[(i - 2) % 3];
-      a.sf_D = AD[(i - 2) % 3];
-      a.sf_zP = AP[i % 3];
-      a.sf_zD = AD[i % 3];
-      a.sf_partials = PB[(i - 2) % 2];
-      a.sf = solve_args(p, kHavePush | kHaveDeposit, -1);
-      LAUNCHCHK(p, launch_tracers_sf(p->prec, p->seg, a, grid_for(p, -1), p->block, lds, p->max_cells, st));
-    }
-    p->parity ^= 1;
-  }
-  SolveArgs sa = solve_args(p, kHavePush | kHaveDeposit, -1);
-  sa.meshP = AP[(k - 1) % 3];
-  sa.meshD = AD[(k - 1) % 3];
-  sa.partials = PB[(k - 1) % 2];
-  LAUNCHCHK(p, launch_solve(p->prec, sa, p->solve_grid, p->max_cells, st));
-  if (k >= 2)
-    LAUNCHCHK(p, launch_zero_mesh(p->prec, AP[(k - 2) % 3], AD[(k - 2) % 3], nullptr, p->inst, p->slot_ids, 1, p->rep,
-                                  mesh_words(p), st));
+// Accumulator set i of the rotation.
+long long *sf_set(Pool *p, int64_t i) {
+  return i % 3 == 0 ? static_cast<long long *>(p->meshP)
+                    : static_cast<long long *>(p->sf_mesh) + (i % 3 - 1) * acc_words(p);
+}
+
+// Step i of a run of solve-first steps.
+sic_status enqueue_sf(Pool *p, int64_t i, hipStream_t st) {
+  const SlotHost &sh = p->slots[0];
+  Partial *part[2] = {p->partials, p->sf_part};
+  StepArgs a;
+  a.L = sh.L;
+  a.half_L = 0.5 * sh.L;
+  a.dx = sh.L / sh.n_cells;
+  a.inv_dx = (double)sh.n_cells / sh.L;
+  a.dt = sh.dt;
+  a.q_unit = p->prec == kFP64 ? 1.0 : 1.0 / sh.q_scale;
+  a.nc = sh.n_cells;
+  a.n_items = sh.n_items;
+  a.tile = p->tile;
+  a.chunk_begin = sh.chunk_begin;
+  a.n_chunks = sh.n_chunks;
+  a.hist_cap = p->hist_rows;
+  a.chunks = p->chunks;
+  a.links = p->links;
+  a.segq = p->segq;
+  a.cedge = p->cedge;
+  a.xs = p->xs;
+  a.vs = p->vs;
+  a.halo_in = p->order == 1 ? p->halo3[p->parity] : p->halo[p->parity];
+  a.halo_out = p->order == 1 ? p->halo3[p->parity ^ 1] : p->halo[p->parity ^ 1];
+  a.meshE = p->meshE;
+  a.acc_in = i > 0 ? sf_set(p, i - 1) : nullptr;
+  a.acc_out = sf_set(p, i);
+  a.acc_zero = i > 0 ? sf_set(p, i + 1) : nullptr;
+  a.part_in = part[(i + 1) % 2];
+  a.part_out = part[i % 2];
+  a.sf = solve_args(p, kHavePush | kHaveDeposit, -1);
+  LAUNCHCHK(p, launch_step(p->prec, p->order, p->seg, a, std::min(grid_for(p, -1), sh.n_items), p->block, st));
+  p->parity ^= 1;
   return SIC_OK;
 }
 
+// The solve launch that ends a run of k solve-first steps.
+sic_status close_sf(Pool *p, int64_t k, hipStream_t st) {
+  const int64_t arr = (int64_t)p->rep * mesh_words(p);
+  Partial *part[2] = {p->partials, p->sf_part};
+  long long *set = sf_set(p, k - 1);
+  SolveArgs sa = solve_args(p, kHavePush | kHaveDeposit, -1);
+  sa.meshP = set;
+  sa.meshD = set + arr;
+  if (p->order == 1) sa.meshR = set + 2 * arr;
+  sa.partials = part[(k - 1) % 2];
+  if (k >= 2) {
+    sa.zero = sf_set(p, k - 2);
+    sa.zero_words = acc_words(p);
+  }
+  LAUNCHCHK(p, launch_solve(p->prec, sa, p->solve_grid, p->max_cells, st));
+  return SIC_OK;
+}
+
+// A graph of k solve-first steps, the first of them step 1 (mod kSfPeriod)
+// of its run.
 sic_status get_sf_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
   auto key = std::make_tuple(k, p->parity, p->grid, p->solve_grid, 3);
   auto it = p->graphs.find(key);
@@ -915,7 +941,8 @@ sic_status get_sf_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
   }
   const int parity0 = p->parity;
   HIPCHK(p, hipStreamBeginCapture(p->cap, hipStreamCaptureModeRelaxed));
-  sic_status s = enqueue_sf(p, k, p->cap);
+  sic_status s = SIC_OK;
+  for (int64_t i = 0; i < k && s == SIC_OK; ++i) s = enqueue_sf(p, 1 + i, p->cap);
   p->parity = parity0;
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(p->cap, &g);
@@ -934,6 +961,32 @@ sic_status get_sf_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
   p->graphs[key] = ex;
   *out = ex;
   return SIC_OK;
+}
+
+// A run of n solve-first steps.  The first one is launched by itself (it
+// reads the field instead of solving for it); the graphs of the others hold
+// a multiple of the six steps after which the accumulators, the partials and
+// the halos are the same buffers again, so that one graph serves all but the
+// last of them; a few left over are launched by themselves.
+constexpr int64_t kSfGraphSteps = 36;
+constexpr int64_t kSfDirectSteps = 6;
+
+sic_status run_sf(Pool *p, int64_t n) {
+  sic_status s = enqueue_sf(p, 0, p->stream);
+  for (int64_t i = 1; i < n && s == SIC_OK;) {
+    const int64_t k = std::min<int64_t>(n - i, kSfGraphSteps);
+    if (k <= kSfDirectSteps) {
+      s = enqueue_sf(p, i++, p->stream);
+      continue;
+    }
+    hipGraphExec_t ex;
+    s = get_sf_graph(p, k, &ex);
+    if (s != SIC_OK) break;
+    HIPCHK(p, hipGraphLaunch(ex, p->stream));
+    if (k & 1) p->parity ^= 1;
+    i += k;
+  }
+  return s == SIC_OK ? close_sf(p, n, p->stream) : s;
 }
 
 sic_status run_fused(Pool *p, int64_t n) {
@@ -971,11 +1024,11 @@ sic_status run_fused(Pool *p, int64_t n) {
     p->t_solve = ts / (double)n;
     return SIC_OK;
   }
-  const bool sf = sf_ready(p);
+  if (sf_ready(p)) return run_sf(p, n);
   while (n > 0) {
     const int64_t k = std::min<int64_t>(n, kGraphSteps);
     hipGraphExec_t ex;
-    sic_status s = sf ? get_sf_graph(p, k, &ex) : get_graph(p, k, &ex);
+    sic_status s = get_graph(p, k, &ex);
     if (s != SIC_OK) return s;
     HIPCHK(p, hipGraphLaunch(ex, p->stream));
     if (k & 1) p->parity ^= 1;
@@ -1361,8 +1414,9 @@ sic_status pool_relayout(Pool *p, int32_t slot, const std::vector<int32_t> &nt, 
   sh.n_chunks = (int32_t)n_ch;
   st = place_slot_items(p, slot);
   if (st != SIC_OK) return st;
-  // captured graphs carry the tile (LDS size) and grid of their capture
-  if (p->tile != tile0 || p->grid != grid0) destroy_graphs(p);
+  // captured graphs carry the tile (LDS size) and grid of their capture, a
+  // single simulation's solve-first ones its chunk and item counts too
+  if (!p->batch || p->tile != tile0 || p->grid != grid0) destroy_graphs(p);
   hipError_t e = upload_layout(p, sh, cb, L);
   if (e == hipSuccess && step >= 0) {
     InstDesc I;

@@ -40,8 +40,10 @@ constexpr int kMaxCells = 4096;     // mirrors SIC_MAX_CELLS
 // solve-first workgroup reads all copies of the whole mesh (the reads then
 // cost more than the contention saves).  Batches, with few items per
 // simulation, keep one copy.
-constexpr int single_rep(int max_cells) { return max_cells <= 256 ? 4 : 2; }
+constexpr int kSmallMeshRep = 4;
+constexpr int single_rep(int max_cells) { return max_cells <= 256 ? kSmallMeshRep : 2; }
 constexpr int kSolveThreads = 256;  // field-solve workgroup
+constexpr int kComputeUnits = 256;  // of an MI355X
 
 enum Prec : int { kFP64 = 0, kSplitF32 = 1, kSplitU32 = 2 };
 
@@ -132,6 +134,10 @@ struct SolveArgs {
   // sums them in copy order and clears each
   int32_t rep = 1;
   int64_t rep_stride = 0;
+  // further accumulators to clear (those that the last of a run of
+  // solve-first steps read)
+  void *zero = nullptr;
+  int64_t zero_words = 0;
 };
 
 struct TracerArgs {
@@ -162,14 +168,33 @@ struct TracerArgs {
   // mesh)
   int32_t rep = 1;
   int64_t rep_stride = 0;
-  // Solve-first launches of a single simulation (launch_tracers_sf): every
-  // workgroup solves the previous step's charge for the field it pushes
-  // with, instead of reading meshE; the first also writes what a solve
-  // launch would (the diagnostics row, the step, the field and density).
-  const void *sf_P = nullptr, *sf_D = nullptr;  // the previous step's accumulators
-  void *sf_zP = nullptr, *sf_zD = nullptr;      // accumulators to clear, a slice per workgroup
-  const Partial *sf_partials = nullptr;         // the previous launch's work-item partials
-  SolveArgs sf{};                               // what the first workgroup's solve writes to
+};
+
+// A solve-first step of a single simulation (slot 0).  The accumulators of a
+// step are one block of (P, D and for linear segments R) x single_rep copies
+// x nc words.
+struct StepArgs {
+  double L, half_L, dx, inv_dx, dt, q_unit;
+  int32_t nc;
+  int32_t n_items, tile;          // item i: chunks [chunk_begin + i tile, + tile), n_chunks in all
+  int32_t chunk_begin, n_chunks;
+  int64_t hist_cap;
+  const ChunkDesc *chunks;
+  const int2 *links;              // order 1
+  const uint64_t *segq, *cedge;   // per-segment charges
+  uint64_t *xs;
+  double *vs;
+  const double2 *halo_in;         // orders 0, 2: one copy per chunk; order 1: three
+  double2 *halo_out;
+  const double *meshE;            // the field of a run's first step
+  const void *acc_in;             // the previous step's charge; NULL: a run's first step
+  void *acc_out;                  // this step's charge
+  void *acc_zero;                 // accumulators to clear, or NULL
+  const Partial *part_in;         // the previous step's work-item partials
+  Partial *part_out;
+  SolveArgs sf;                   // what the diagnostics go to
+  int32_t row_group = 0;          // set by launch_step: workgroup 0 has no item
+  int32_t zero_slice = 0;         // words of acc_zero per workgroup
 };
 
 struct IngestArgs {
@@ -271,10 +296,10 @@ struct RefinePlanArgs {
 // Launchers (sic_kernels.hip).  All return hipError_t as int.
 int launch_tracers(int prec, int mode, int order, bool seg, const TracerArgs &a, int grid, int block,
                    size_t lds_bytes, void *stream);
-// A fused step (push + deposit, constant segments) of a single simulation in
-// solve-first form (TracerArgs sf_*); max_cells sizes the solve.
-int launch_tracers_sf(int prec, bool seg, const TracerArgs &a, int grid, int block, size_t lds_bytes,
-                      int max_cells, void *stream);
+// A solve-first step of a single simulation: grid workgroups over the items,
+// of block threads, at least kSolveThreads and at least a.tile.
+int launch_step(int prec, int order, bool seg, const StepArgs &a, int grid, int block, void *stream);
+bool step_supported(int order, int max_cells);
 int set_tracer_lds_limit(int prec, int order, bool seg, size_t lds_bytes);
 size_t tracer_lds_size(int prec, int order, bool seg, int mesh_cells, int tile_cap);
 // max_cells: the largest mesh of the slots the launch may solve.

@@ -38,6 +38,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "sic_internal.h"
@@ -887,43 +888,43 @@ __device__ __forceinline__ T block_sum(T v, T *sWave) {
   return r;
 }
 
-// The solve's scan and sum over its kSolveThreads threads (four wavefronts;
-// wider workgroups' other wavefronts hold zeros and take no part), with the
+// The solve's scan and sum over its kSolveThreads threads (four wavefronts,
+// mine; a wider workgroup's other wavefronts only pass the barrier), with the
 // sums in the order of block_incl_scan and block_sum.  Each call site passes
 // four LDS words of its own, so one barrier per call suffices (nothing
 // writes them again before the next solve).
 template <class T>
-__device__ __forceinline__ T solve_incl_scan(T v, T *slot4) {
-  const int lane = threadIdx.x & 63;
+__device__ __forceinline__ T solve_incl_scan(T v, T *slot4, bool mine) {
   const int wave = threadIdx.x >> 6;
-  v = wave_incl_scan(v, [](T x, T y) { return x + y; });
-  if (lane == 63 && wave < 4) slot4[wave] = v;
+  if (mine) {
+    v = wave_incl_scan(v, [](T x, T y) { return x + y; });
+    if ((threadIdx.x & 63) == 63) slot4[wave] = v;
+  }
   __syncthreads();
   // wavefronts 0..wave-1 in order; the zeros added after them change no bits
   T base = (T)0;
+  if (mine) {
 #pragma unroll
-  for (int w = 0; w < 3; ++w) base += (w < wave) ? slot4[w] : (T)0;
+    for (int w = 0; w < 3; ++w) base += (w < wave) ? slot4[w] : (T)0;
+  }
   return v + base;
 }
 template <class T>
-__device__ __forceinline__ T solve_sum(T v, T *slot4) {
-  v = wave_sum(v);
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0 && wave < 4) slot4[wave] = v;
+__device__ __forceinline__ T solve_sum(T v, T *slot4, bool mine) {
+  if (mine) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) slot4[threadIdx.x >> 6] = v;
+  }
   __syncthreads();
   return slot4[0] + slot4[1] + slot4[2] + slot4[3];
 }
 
-
 }  // namespace
 
-// The solve of one slot by one workgroup of kSolveThreads threads: charge
-// per cell from the P/D (and R) accumulators, which it clears; mean removal,
-// Gauss's law, cell-centre field, field energy; the diagnostics row and the
-// step count.  ke, mom, ms are the slot's kinetic-energy, momentum and
-// max-segment sums of the step.  The accumulators may be the slot's global
-// mesh (k_solve) or a workgroup's LDS copy (k_resident); with sE the field is
-// also left in LDS.
+// The solve of one slot: charge per cell from the P/D (and R) accumulators
+// (cleared), mean removal, Gauss's law, cell-centre field, field energy; the
+// diagnostics row and the step count.  The accumulators may be the slot's
+// global mesh (k_solve) or a workgroup's LDS copy (k_resident, k_step).
 // The slot's constants the solve needs, read once by its caller.
 struct SlotConst {
   int nc;
@@ -987,91 +988,96 @@ __device__ __forceinline__ void solve_take(const SlotConst &kc, Acc *gP, Acc *gD
   }
 }
 
-// step0 and flags0 are the slot's step and sticky flags before this solve;
-// pv, dv this thread's accumulators from solve_take; returns the flags after
-// it (the same value in every thread).  With write_field false the field and
-// density are left in sE only (the resident kernel writes them to global
-// memory on its last step); with writer false nothing at all is written to
-// global memory (the workgroups of a launch that each solve the same charge
-// for their own use, all but one).  The field in sE is complete only after a
-// barrier following the return (without writer the solve passes none after
-// its field loop).
+// What the solve leaves for the diagnostics row: this thread's field energy
+// sum and its non-finite field values (threads of the first kSolveThreads),
+// and the total charge (every thread).
+struct FieldSums {
+  double w2, Qtot;
+  int bad;
+};
+
+// The field of pv, dv (this thread's accumulators from solve_take) and the
+// ramps, into sE (LDS, with one ghost cell on each side when ghost is set)
+// and into gE and gR (global field and density) where they are given.  The
+// cells are partitioned over kSolveThreads threads; a wider workgroup's other
+// wavefronts only pass the barriers, so the bits are those of a workgroup of
+// kSolveThreads.  The field in sE is complete after a barrier following the
+// return.
 template <int PREC, int CELLS, int REP = 1, class Acc, class T>
-__device__ __forceinline__ int solve_slot(const SolveArgs &a, int slot, const SlotConst &kc, int64_t step0,
-                                          int flags0, const T (&pv)[CELLS], const T (&dv)[CELLS], Acc *gRamp,
-                                          double ke, double mom, double ms, double *sE, bool write_field,
-                                          bool writer = true) {
+__device__ __forceinline__ FieldSums solve_field(const SlotConst &kc, const T (&pv)[CELLS], const T (&dv)[CELLS],
+                                                 Acc *gRamp, int64_t ramp_stride, double *sE, bool ghost, double *gE,
+                                                 double *gR) {
   using acc_t = typename std::conditional<PREC == kFP64, double, long long>::type;
   static_assert(std::is_same<acc_t, T>::value, "accumulator type");
-  // The cells are partitioned over kSolveThreads threads; a wider workgroup
-  // (the resident kernel's) runs the same code, its other threads holding no
-  // cells and adding zeros, so the result has the same bits.
   // LDS words of the scans and sums, four per call site
   __shared__ acc_t sA[4][4];
-  __shared__ double sF[3][4];
-  __shared__ int sBad[4];
+  __shared__ double sF[2][4];
   __shared__ double sLastF[kSolveThreads];
-  InstDesc *Ip = a.inst + slot;
   const int tid = threadIdx.x;
   const int nc = kc.nc;
-  const double L = kc.L, dx = kc.dx, dt = kc.dt;
   const double q_unit = kc.q_unit;
+  const bool mine = __builtin_amdgcn_readfirstlane(tid >> 6) < kSolveThreads / kChunk;
 
-  // 2. charge per cell: Q_j = P_j + sum_{m <= j} D_m
+  // 1. charge per cell: Q_j = P_j + sum_{m <= j} D_m
   const int per = (nc + kSolveThreads - 1) / kSolveThreads;
   const int j0 = tid * per;
-  double *gE = a.meshE + kc.mesh_off;
-  double *gR = a.meshRho + kc.mesh_off;
   acc_t dsum = (acc_t)0;
 #pragma unroll
   for (int k = 0; k < CELLS; ++k) dsum += dv[k];
-  const acc_t dbase = solve_incl_scan(dsum, sA[0]) - dsum;
+  const acc_t dbase = solve_incl_scan(dsum, sA[0], mine) - dsum;
   // Linear ramps of piecewise-linear segments: the charge adds the second
   // prefix sum of R (zero for piecewise-constant segments).
   acc_t r2[CELLS];
 #pragma unroll
   for (int k = 0; k < CELLS; ++k) r2[k] = (acc_t)0;
   if (gRamp != nullptr) {  // only piecewise-linear segments have ramps; REP copies as P and D
-#pragma unroll
-    for (int r = 0; r < REP; ++r) {
-#pragma unroll
-      for (int k = 0; k < CELLS; ++k) {
-        const int j = j0 + k;
-        const bool own = k < per && j < nc;
-        const acc_t v = (acc_t)gRamp[r * a.rep_stride + (own ? j : 0)];
-        r2[k] += own ? v : (acc_t)0;
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < REP; ++r) {
-#pragma unroll
-      for (int k = 0; k < CELLS; ++k) {
-        const int j = j0 + k;
-        if (k < per && j < nc) gRamp[r * a.rep_stride + j] = (Acc)0;
-      }
-    }
     acc_t rsum = (acc_t)0;
+    if (mine) {
 #pragma unroll
-    for (int k = 0; k < CELLS; ++k) rsum += r2[k];
-    const acc_t base1 = solve_incl_scan(rsum, sA[1]) - rsum;
-    acc_t run1 = base1, s1sum = (acc_t)0;
+      for (int r = 0; r < REP; ++r) {
 #pragma unroll
-    for (int k = 0; k < CELLS; ++k) {
-      run1 += r2[k];
-      r2[k] = run1;
-      if ((k < per) && (j0 + k < nc)) s1sum += run1;
+        for (int k = 0; k < CELLS; ++k) {
+          const int j = j0 + k;
+          const bool own = k < per && j < nc;
+          const acc_t v = (acc_t)gRamp[r * ramp_stride + (own ? j : 0)];
+          r2[k] += own ? v : (acc_t)0;
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < REP; ++r) {
+#pragma unroll
+        for (int k = 0; k < CELLS; ++k) {
+          const int j = j0 + k;
+          if (k < per && j < nc) gRamp[r * ramp_stride + j] = (Acc)0;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < CELLS; ++k) rsum += r2[k];
     }
-    const acc_t base2 = solve_incl_scan(s1sum, sA[2]) - s1sum;
-    acc_t run2 = base2;
+    const acc_t base1 = solve_incl_scan(rsum, sA[1], mine) - rsum;
+    acc_t s1sum = (acc_t)0;
+    if (mine) {
+      acc_t run1 = base1;
 #pragma unroll
-    for (int k = 0; k < CELLS; ++k) {
-      if ((k < per) && (j0 + k < nc)) run2 += r2[k];
-      r2[k] = run2;
+      for (int k = 0; k < CELLS; ++k) {
+        run1 += r2[k];
+        r2[k] = run1;
+        if ((k < per) && (j0 + k < nc)) s1sum += run1;
+      }
+    }
+    const acc_t base2 = solve_incl_scan(s1sum, sA[2], mine) - s1sum;
+    if (mine) {
+      acc_t run2 = base2;
+#pragma unroll
+      for (int k = 0; k < CELLS; ++k) {
+        if ((k < per) && (j0 + k < nc)) run2 += r2[k];
+        r2[k] = run2;
+      }
     }
   }
   double Q[CELLS];
   acc_t qsum_acc = (acc_t)0;
-  {
+  if (mine) {
     acc_t run = dbase;
 #pragma unroll
     for (int k = 0; k < CELLS; ++k) {
@@ -1083,130 +1089,153 @@ __device__ __forceinline__ int solve_slot(const SolveArgs &a, int slot, const Sl
       if (in) qsum_acc += qa;
     }
   }
-  double Qtot;
-  if constexpr (PREC == kFP64) Qtot = solve_sum(qsum_acc, sA[3]);
-  else Qtot = (double)solve_sum(qsum_acc, sA[3]) * q_unit;
+  FieldSums out;
+  if constexpr (PREC == kFP64) out.Qtot = solve_sum(qsum_acc, sA[3], mine);
+  else out.Qtot = (double)solve_sum(qsum_acc, sA[3], mine) * q_unit;
 
-  // 3. Gauss's law on faces: F_{j+1/2} = F_{j-1/2} + (Q_j - Qtot/nc),
+  // 2. Gauss's law on faces: F_{j+1/2} = F_{j-1/2} + (Q_j - Qtot/nc),
   //    F shifted to zero mean; E_j = (F_{j-1/2} + F_{j+1/2}) / 2.
-  const double qmean = Qtot / (double)nc;
+  double qmean = 0.0, rsum = 0.0;
   double F[CELLS];
-  double rsum = 0.0;
+  if (mine) {
+    qmean = out.Qtot / (double)nc;
 #pragma unroll
-  for (int k = 0; k < CELLS; ++k) {
-    const bool in = (k < per) && (j0 + k < nc);
-    const double r = in ? (Q[k] - qmean) : 0.0;
-    rsum += r;
-    F[k] = r;
+    for (int k = 0; k < CELLS; ++k) {
+      const bool in = (k < per) && (j0 + k < nc);
+      const double r = in ? (Q[k] - qmean) : 0.0;
+      rsum += r;
+      F[k] = r;
+    }
   }
-  const double fbase = solve_incl_scan(rsum, sF[0]) - rsum;
-  double fsum = 0.0;
-  {
-    double run = fbase;
+  const double fbase = solve_incl_scan(rsum, sF[0], mine) - rsum;
+  // F's mean and each thread's last face value behind one barrier; the
+  // neighbour's value is shifted by the mean after the exchange (the same
+  // subtraction, the same bits)
+  if (mine) {
+    double fsum = 0.0, run = fbase, lastF = 0.0;
 #pragma unroll
     for (int k = 0; k < CELLS; ++k) {
       const bool in = (k < per) && (j0 + k < nc);
       run += F[k];
       F[k] = in ? run : 0.0;
-      if (in) fsum += F[k];
+      if (in) {
+        fsum += F[k];
+        lastF = F[k];
+      }
     }
-  }
-  // F's mean and each thread's last face value behind one barrier; the
-  // neighbour's value is shifted by the mean after the exchange (the same
-  // subtraction, the same bits)
-  double lastF = 0.0;
-#pragma unroll
-  for (int k = 0; k < CELLS; ++k)
-    if ((k < per) && (j0 + k < nc)) lastF = F[k];
-  {
     const double fw = wave_sum(fsum);
-    const int wave = tid >> 6;
-    if ((tid & 63) == 0 && wave < 4) sF[1][wave] = fw;
-    if (tid < kSolveThreads) sLastF[tid] = lastF;
+    if ((tid & 63) == 0) sF[1][tid >> 6] = fw;
+    sLastF[tid] = lastF;
   }
   __syncthreads();
-  const double fmean = (sF[1][0] + sF[1][1] + sF[1][2] + sF[1][3]) / (double)nc;
+  out.w2 = 0.0;
+  out.bad = 0;
+  if (mine) {
+    const double fmean = (sF[1][0] + sF[1][1] + sF[1][2] + sF[1][3]) / (double)nc;
 #pragma unroll
-  for (int k = 0; k < CELLS; ++k)
-    if ((k < per) && (j0 + k < nc)) F[k] -= fmean;
-  double prevF =
-      (tid == 0) ? sLastF[(nc - 1) / per] - fmean : (tid < kSolveThreads ? sLastF[tid - 1] - fmean : 0.0);
-  double w2 = 0.0;
-  bool finite = true;
+    for (int k = 0; k < CELLS; ++k)
+      if ((k < per) && (j0 + k < nc)) F[k] -= fmean;
+    double prevF = (tid == 0) ? sLastF[(nc - 1) / per] - fmean : sLastF[tid - 1] - fmean;
+    bool finite = true;
 #pragma unroll
-  for (int k = 0; k < CELLS; ++k) {
-    const int j = j0 + k;
-    if ((k < per) && (j < nc)) {
-      const double e = 0.5 * (prevF + F[k]);
-      prevF = F[k];
-      if (sE) sE[j] = e;
-      if (write_field) {
-        gE[j] = e;
-        gR[j] = (Q[k] - qmean) / dx;
+    for (int k = 0; k < CELLS; ++k) {
+      const int j = j0 + k;
+      if ((k < per) && (j < nc)) {
+        const double e = 0.5 * (prevF + F[k]);
+        prevF = F[k];
+        if (sE) {
+          sE[j] = e;
+          if (ghost) {
+            if (j == 0) sE[nc] = e;
+            if (j == nc - 1) sE[-1] = e;
+          }
+        }
+        if (gE) {
+          gE[j] = e;
+          gR[j] = (Q[k] - qmean) / kc.dx;
+        }
+        out.w2 += e * e;
+        finite = finite && (e - e == 0.0);
       }
-      w2 += e * e;
-      finite = finite && (e - e == 0.0);
     }
+    out.bad = finite ? 0 : 1;
   }
-  // the field energy and the count of non-finite values, in one pass (only
-  // a workgroup that writes the diagnostics needs them)
-  double W = 0.0;
-  int bad = 0;
-  if (writer) {
-    w2 = wave_sum(w2);
-    const int nbad = wave_sum(finite ? 0 : 1);
-    const int wave = tid >> 6;
-    if ((tid & 63) == 0 && wave < 4) {
-      sF[2][wave] = w2;
-      sBad[wave] = nbad;
-    }
-    __syncthreads();
-    W = 0.5 * dx * (sF[2][0] + sF[2][1] + sF[2][2] + sF[2][3]);
-    bad = sBad[0] + sBad[1] + sBad[2] + sBad[3];
-  }
+  return out;
+}
 
-  // 4. diagnostics and step bookkeeping
-  const bool pushed = (a.flags & kHavePush) != 0;
-  const int64_t step = pushed ? step0 + 1 : step0;
+// Field energy and count of threads with non-finite field values, over the
+// workgroup (one barrier; the same bits in every thread).
+__device__ __forceinline__ void field_energy(const FieldSums &f, double dx, double *W, int *bad) {
+  __shared__ double sW[4];
+  __shared__ int sBad[4];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wave < kSolveThreads / kChunk) {
+    const double w = wave_sum(f.w2);
+    const int n = wave_sum(f.bad);
+    if ((threadIdx.x & 63) == 0) {
+      sW[wave] = w;
+      sBad[wave] = n;
+    }
+  }
+  __syncthreads();
+  *W = 0.5 * dx * (sW[0] + sW[1] + sW[2] + sW[3]);
+  *bad = sBad[0] + sBad[1] + sBad[2] + sBad[3];
+}
+
+// The sticky flags after a solve.
+__device__ __forceinline__ int solve_flags(int solve, int flags0, double L, double W, int bad, double ke, double mom,
+                                           double ms) {
   int f = 0;
   if (bad || !(W - W == 0.0)) f |= 1;
   // a move with a non-finite velocity (its kinetic energy or momentum)
-  if (pushed && !((ke - ke == 0.0) && (mom - mom == 0.0))) f |= 1;
-  if (a.flags & kHaveDeposit) {
+  if ((solve & kHavePush) && !((ke - ke == 0.0) && (mom - mom == 0.0))) f |= 1;
+  if (solve & kHaveDeposit) {
     if (ms != ms) f |= 1;
     else if (ms > 0.45 * L) f |= 2;
   }
-  const int flags = flags0 | f;
-  if (tid == 0 && writer) {
-    Ip->flags = flags;
-    const int64_t cap = kc.hist_cap;
-    DiagRow *H = a.hist + kc.hist_off;
-    DiagRow r;
-    r.step = step;
-    r.t = (double)step * dt;
-    r.W_E = W;
-    r.KE = __longlong_as_double(0x7ff8000000000000ll);
-    r.momentum = r.KE;
-    r.total_charge = Qtot;
-    r.max_segment = (a.flags & kHaveDeposit) ? ms : r.KE;
-    r.flags = flags;
-    H[step % cap] = r;
-    if (pushed && step >= 1) {
-      DiagRow *prev = H + (step - 1) % cap;
-      prev->KE = ke;
-      prev->momentum = mom;
-    }
-    Ip->step = step;
-    if ((a.flags & kBatchStep) && pushed && Ip->steps_left > 0) {
-      const int64_t left = Ip->steps_left - 1;
-      Ip->steps_left = left;
-      if (left == 0) {
-        Ip->active = 0;
-        a.done[slot] = 1;
-      }
+  return flags0 | f;
+}
+
+// a mod b of non-negative a, positive b: the 64-bit remainder (a long
+// instruction sequence) only where the operands need it.
+__device__ __forceinline__ int64_t row_of(int64_t a, int64_t b) {
+  if ((uint64_t)(a | b) >> 32 == 0) return (int64_t)((uint32_t)a % (uint32_t)b);
+  return a % b;
+}
+
+// The diagnostics row and the step bookkeeping, by one thread; step0 is the
+// slot's step before this solve, flags those after it.
+__device__ __forceinline__ void write_row(const SolveArgs &a, int slot, const SlotConst &kc, int64_t step0, int flags,
+                                          double W, double Qtot, double ke, double mom, double ms) {
+  InstDesc *Ip = a.inst + slot;
+  const bool pushed = (a.flags & kHavePush) != 0;
+  const int64_t step = pushed ? step0 + 1 : step0;
+  Ip->flags = flags;
+  DiagRow *H = a.hist + kc.hist_off;
+  DiagRow r;
+  r.step = step;
+  r.t = (double)step * kc.dt;
+  r.W_E = W;
+  r.KE = __longlong_as_double(0x7ff8000000000000ll);
+  r.momentum = r.KE;
+  r.total_charge = Qtot;
+  r.max_segment = (a.flags & kHaveDeposit) ? ms : r.KE;
+  r.flags = flags;
+  H[row_of(step, kc.hist_cap)] = r;
+  if (pushed && step >= 1) {
+    DiagRow *prev = H + row_of(step - 1, kc.hist_cap);
+    prev->KE = ke;
+    prev->momentum = mom;
+  }
+  Ip->step = step;
+  if ((a.flags & kBatchStep) && pushed && Ip->steps_left > 0) {
+    const int64_t left = Ip->steps_left - 1;
+    Ip->steps_left = left;
+    if (left == 0) {
+      Ip->active = 0;
+      a.done[slot] = 1;
     }
   }
-  return flags;
 }
 
 // ---------------------------------------------------------------------------
@@ -1249,27 +1278,310 @@ __device__ __forceinline__ double tracer_mass(uint64_t left, uint64_t right, dou
   }
 }
 
-// SF > 0: a solve-first launch of a single simulation (push + deposit,
-// constant segments): before its work items the workgroup solves the
-// previous step's charge (SF cells per solve thread) for the field, as a
-// solve launch would, instead of reading it.
-template <int PREC, int MODE, int ORDER, bool SEG, int SF = 0>
+// The LDS tables of a work item (layout above tracer_lds_bytes).
+template <int PREC, int ORDER, bool SEG>
+struct ItemLds {
+  using acc_t = typename std::conditional<PREC == kFP64, double, unsigned long long>::type;
+  acc_t *sP, *sD, *sR;   // sR: linear segments only
+  double *sE;            // ghost cells at -1 and nc
+  ChunkDesc *sDesc;
+  double2 *sHalo;        // orders 0, 2: the tracer after the chunk
+  uint64_t *sNextW;      // order 1: the word of the tracer after the chunk
+  LinNb *sPrevNb;        // order 1: segment before the chunk
+  LinNb *sNextNb;        // order 1: segment after its last one
+  uint64_t *sEdge;       // per-segment charges
+  double *sRed;          // 3 x 16 waves
+  __device__ __forceinline__ ItemLds(unsigned char *smem, int mesh_cells, int tile_cap) {
+    constexpr bool kLin = ORDER == 1;
+    sP = reinterpret_cast<acc_t *>(smem);
+    sD = sP + mesh_cells;
+    sR = sD + mesh_cells;
+    sE = reinterpret_cast<double *>(sR + (kLin ? mesh_cells : 0)) + 1;
+    sDesc = reinterpret_cast<ChunkDesc *>(sE + mesh_cells + 1);
+    sHalo = reinterpret_cast<double2 *>(sDesc + tile_cap);
+    sNextW = reinterpret_cast<uint64_t *>(sDesc + tile_cap);
+    sPrevNb = reinterpret_cast<LinNb *>(sNextW + tile_cap);
+    sNextNb = sPrevNb + tile_cap;
+    sEdge = kLin ? reinterpret_cast<uint64_t *>(sNextNb + tile_cap) : reinterpret_cast<uint64_t *>(sHalo + tile_cap);
+    sRed = reinterpret_cast<double *>(sEdge + (SEG ? 2 * tile_cap : 0));
+  }
+};
+
+// A halo tracer's word after this step's move (MODE with kPush) or as it is.
+template <int PREC, int MODE>
+__device__ __forceinline__ uint64_t moved_halo(double2 h, const Geo &g, const double *sE) {
+  uint64_t w = (uint64_t)__double_as_longlong(h.x);
+  if constexpr ((MODE & kPush) != 0) {
+    const double e = gather_field_ghost(sE, mesh_pos<PREC>(w, g.inv_dx), g.nc);
+    w = drift<PREC>(w, h.y + g.dt * e, g.dt, g.L, g.inv_dx, g.nc);
+  }
+  return w;
+}
+
+// The segments just outside a chunk, for the gradients of its first and last
+// segments (order 1), and the word its last segment ends at: from the
+// chunk's own first tracer (own), its partner's first (first; has_first), the
+// tracer before it (prev; has_prev) and the one after the partner's first
+// (next2; has_next), each moved here (the same functions as the lanes', so
+// the same bits).  e0, e1: the charge words of the two segments; q their
+// sheet's charge in the accumulator's units.
+template <int PREC, int MODE, bool SEG>
+__device__ __forceinline__ void stage_linear(const Geo &g, const double *sE, bool has_first, bool has_prev,
+                                             bool has_next, double2 own, double2 first, double2 prev, double2 next2,
+                                             uint64_t e0, uint64_t e1, double q, uint64_t *wn, LinNb *before,
+                                             LinNb *after) {
+  auto neighbour = [&](uint64_t wa, uint64_t wb, uint64_t cword) {
+    const SegGeo sgn = lin_geo<PREC>(wa, wb, g);
+    double qs = q;
+    if constexpr (SEG) qs = PREC == kFP64 ? __longlong_as_double((long long)cword) : (double)(long long)cword;
+    LinNb nb;
+    nb.d = sgn.d;
+    nb.r = lin_nb_density(sgn.d, lin_density(sgn, qs));
+    return nb;
+  };
+  LinNb none;
+  none.d = 0.0;
+  none.r = lin_nb_density(0.0, 0.0);
+  *before = none;
+  *after = none;
+  uint64_t wn1 = 0;
+  if (has_first) wn1 = moved_halo<PREC, MODE>(first, g, sE);
+  if (has_prev) {
+    const uint64_t wpv = moved_halo<PREC, MODE>(prev, g, sE);
+    *before = neighbour(wpv, moved_halo<PREC, MODE>(own, g, sE), e0);
+  }
+  if (has_first && has_next) *after = neighbour(wn1, moved_halo<PREC, MODE>(next2, g, sE), e1);
+  *wn = wn1;
+}
+
+// A chunk's table entry: its descriptor, the charge word of the segment that
+// ends at its first tracer (per-segment charges), the word of the tracer
+// after it (moved when the step moves) and, for linear segments, the segments
+// around it.
+struct ChunkTab {
+  ChunkDesc d;
+  uint64_t edge, next;
+  LinNb before, after;
+};
+
+// One chunk of a work item: the move (or half kick) and the deposit of its
+// segments.  halo_out: orders 0, 2 one copy per chunk, order 1 three.
+template <int PREC, int MODE, int ORDER, bool SEG>
+__device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t, const Geo &g, double q_unit,
+                                              uint64_t *xs, double *vs, double2 *halo_out, const ChunkTab &tab,
+                                              size_t chunk, int lane, uint64_t xw, double v, uint64_t cw, double &ke,
+                                              double &mom, double &ms) {
+  constexpr bool kLin = ORDER == 1;
+  constexpr bool kDep = (MODE & kDeposit) != 0;
+  constexpr bool kKick = (MODE & kKickHalf) != 0;
+  constexpr bool kField = (MODE & kPush) != 0 || kKick;
+  constexpr bool kNeedQ = SEG && (kDep || (MODE & kPush) != 0);
+  const ChunkDesc &ch = tab.d;
+  const int n_valid = __builtin_amdgcn_readfirstlane(ch.n_valid);
+  const bool valid = lane < n_valid;
+  const size_t s = chunk * kChunk + lane;
+  // Per-segment charges: this lane's segment (cw), the one ending at this
+  // tracer (cl) and, for linear segments, the next one (cn).
+  uint64_t cl = 0;
+  if constexpr (kNeedQ) {
+    const uint64_t up = lane_up1(cw);
+    cl = lane == 0 ? tab.edge : up;
+  }
+  if constexpr (kField) {
+    const double e = gather_field_ghost(t.sE, mesh_pos<PREC>(xw, g.inv_dx), g.nc);
+    if constexpr (kKick) {
+      const double vk = v - (0.5 * g.dt) * e;
+      v = valid ? vk : v;
+      vs[s] = v;
+    } else {
+      const double vn = v + g.dt * e;
+      double m;
+      if constexpr (SEG) {
+        m = tracer_mass<PREC>(cl, cw, q_unit);
+      } else {
+        // half of each segment the tracer bounds: the ends of an open
+        // sheet bound one
+        const bool end = (lane == 0 && (ch.flags & kChunkOpenStart)) || (lane == n_valid - 1 && ch.partner < 0);
+        m = end ? 0.5 * ch.q : ch.q;
+      }
+      const double qv = valid ? m : 0.0;
+      // twice the kinetic energy and momentum: the factor 1/2 is applied
+      // to the item's sums (a power of two, so the same bits)
+      ke += qv * v * vn;
+      mom += qv * (v + vn);
+      const uint64_t xn = drift<PREC>(xw, vn, g.dt, g.L, g.inv_dx, g.nc);
+      xw = valid ? xn : xw;
+      v = valid ? vn : v;
+      __builtin_nontemporal_store(xw, xs + s);
+      __builtin_nontemporal_store(v, vs + s);
+    }
+    const double2 hv2 = make_double2(__longlong_as_double((long long)xw), v);
+    if constexpr (kLin) {
+      const size_t hb = 3 * chunk;
+      if (lane == 0) halo_out[hb + kHaloFirst] = hv2;
+      if (lane == 1) halo_out[hb + kHaloSecond] = hv2;
+      if (lane == n_valid - 1) halo_out[hb + kHaloLast] = hv2;
+    } else {
+      if (lane == 0) halo_out[chunk] = hv2;
+    }
+  }
+  if constexpr (kDep && kLin) {
+    // Every lane computes its own segment's geometry and density; the
+    // gradient takes the neighbouring segments' from the lanes next to
+    // it (DPP moves), and the first and last lanes take the segments
+    // outside the chunk from the staged neighbours.
+    const bool last = lane == n_valid - 1;
+    const uint64_t dn1 = lane_down1(xw);  // all lanes active: a DPP move reads its neighbour's register
+    const uint64_t xp1 = last ? tab.next : dn1;
+    const bool has_seg = valid && (!last || ch.partner >= 0);
+    SegGeo sg = lin_geo<PREC>(xw, xp1, g);
+    if (!has_seg) sg.d = 0.0;  // a neighbour without a segment drops the gradient
+    double q0 = ch.q;
+    long long q0_fix = ch.q_fix;
+    if constexpr (SEG) {
+      if constexpr (PREC == kFP64) q0 = __longlong_as_double((long long)cw);
+      else q0_fix = (long long)cw;
+    }
+    const double r0 = lin_density(sg, PREC == kFP64 ? q0 : (double)q0_fix);
+    const double rv = lin_nb_density(sg.d, r0);
+    double dm = lane_up1(sg.d), rm = lane_up1(rv);
+    double dp = lane_down1(sg.d), rp = lane_down1(rv);
+    if (lane == 0) {
+      dm = tab.before.d;
+      rm = tab.before.r;
+    }
+    if (last) {
+      dp = tab.after.d;
+      rp = tab.after.r;
+    }
+    if (has_seg) {
+      const double grad = lin_gradient(sg.d, dm, rm, dp, rp);
+      const double len = fabs(sg.d) * g.dx;
+      if (len <= g.half_L) {
+        if constexpr (PREC == kFP64) {
+          deposit_linear_fp64(__longlong_as_double((long long)xw), sg, grad, q0, r0, g, t.sP, t.sD, t.sR);
+        } else {
+          deposit_linear_split(split_cell<PREC>(xw), split_frac<PREC>(xw), sg, grad, q0_fix, r0, g, t.sP, t.sD, t.sR);
+        }
+      }
+      ms = nan_max(ms, len);
+    }
+  }
+  if constexpr (kDep && !kLin) {
+    uint64_t pw = lane_down1(xw);
+    const bool tail = (lane == n_valid - 1);
+    bool has_seg = valid;
+    if (tail) {
+      if (ch.partner < 0) {
+        has_seg = false;  // open sheet: the last tracer ends the chain
+      } else {
+        pw = tab.next;
+      }
+    }
+    if (has_seg) {
+      double len;
+      double q0 = ch.q;
+      long long q0_fix = ch.q_fix;
+      if constexpr (SEG) {
+        if constexpr (PREC == kFP64) q0 = __longlong_as_double((long long)cw);
+        else q0_fix = (long long)cw;
+      }
+      if constexpr (ORDER == 2) {
+        // first-order weighting: geometry in mesh units, minimum image as
+        // for the constant scheme
+        double ua, dm;
+        if constexpr (PREC == kFP64) {
+          const double xa = __longlong_as_double((long long)xw);
+          double d = __longlong_as_double((long long)pw) - xa;
+          if (d >= g.half_L) d -= g.L;
+          else if (d < -g.half_L) d += g.L;
+          ua = xa * g.inv_dx;
+          dm = d * g.inv_dx;
+        } else {
+          ua = mesh_pos<PREC>(xw, g.inv_dx);
+          dm = min_image_cells(mesh_pos<PREC>(pw, g.inv_dx) - ua, 0.5 * (double)g.nc, (double)g.nc);
+        }
+        len = fabs(dm) * g.dx;
+        if (len <= g.half_L) {
+          if constexpr (PREC == kFP64) deposit_cic_fp64(ua, dm, q0, g, t.sP, t.sD);
+          else deposit_cic_split(ua, dm, q0_fix, g, t.sP, t.sD);
+        }
+      } else {
+        if constexpr (PREC == kFP64) {
+          len = deposit_fp64(__longlong_as_double((long long)xw), __longlong_as_double((long long)pw), q0, g,
+                             t.sP, t.sD);
+        } else {
+          len = deposit_split<PREC>(xw, pw, q0_fix, g, t.sP, t.sD);
+        }
+      }
+      ms = nan_max(ms, len);
+    }
+  }
+}
+
+// Work-item partial sums in a fixed order (deterministic for a fixed item
+// decomposition); holds one barrier, after which the item's deposits are
+// complete in LDS.  The last wavefront combines the wavefronts' sums: the
+// first ones go on to the merge (a small mesh occupies only those).
+template <int MODE>
+__device__ __forceinline__ void item_partial(double ke, double mom, double ms, double *sRed, Partial *out) {
+  constexpr bool kDep = (MODE & kDeposit) != 0;
+  constexpr bool kMove = (MODE & kPush) != 0;
+  const int lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (kMove) {
+    ke = wave_sum(ke);
+    mom = wave_sum(mom);
+  }
+  if constexpr (kDep) ms = wave_max(ms);
+  if (lane == 0) {
+    sRed[wave] = ke;
+    sRed[16 + wave] = mom;
+    sRed[32 + wave] = ms;
+  }
+  __syncthreads();
+  if (wave == nwaves - 1) {
+    const bool in = lane < nwaves;
+    const int l = lane & 15;
+    if constexpr (kMove) {
+      const double k = wave_sum(in ? sRed[l] : 0.0), m = wave_sum(in ? sRed[16 + l] : 0.0);
+      if (lane == 0) {
+        out->ke = 0.5 * k;
+        out->mom = 0.5 * m;
+      }
+    }
+    if constexpr (kDep) {
+      const double x = wave_max(in ? sRed[32 + l] : 0.0);
+      if (lane == 0) out->maxseg = x;
+    }
+  }
+}
+
+// Adds an item's LDS mesh to the global accumulators (gR: order 1 only), one
+// atomic per touched cell.
+template <int PREC, int ORDER, bool SEG, class Acc>
+__device__ __forceinline__ void merge_mesh(const ItemLds<PREC, ORDER, SEG> &t, Acc *gP, Acc *gD, Acc *gR, int nc) {
+  auto add = [](Acc *p, Acc v) {
+    if (v != (Acc)0) {
+      if constexpr (PREC == kFP64) unsafeAtomicAdd(p, v);
+      else atomicAdd(p, v);
+    }
+  };
+  for (int i = threadIdx.x; i < nc; i += blockDim.x) {
+    const Acc p = t.sP[i];
+    const Acc d = t.sD[i];
+    add(gP + i, p);
+    add(gD + i, d);
+    if constexpr (ORDER == 1) add(gR + i, t.sR[i]);
+  }
+}
+
+template <int PREC, int MODE, int ORDER, bool SEG>
 __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
   using acc_t = typename std::conditional<PREC == kFP64, double, unsigned long long>::type;
   extern __shared__ __align__(16) unsigned char smem[];
-  acc_t *sP = reinterpret_cast<acc_t *>(smem);
-  acc_t *sD = sP + a.mesh_cells;
   constexpr bool kLin = ORDER == 1;
-  acc_t *sR = sD + a.mesh_cells;  // linear segments only
-  double *sE = reinterpret_cast<double *>(sR + (kLin ? a.mesh_cells : 0)) + 1;  // ghost cells at -1 and nc
-  ChunkDesc *sDesc = reinterpret_cast<ChunkDesc *>(sE + a.mesh_cells + 1);
-  double2 *sHalo = reinterpret_cast<double2 *>(sDesc + a.tile_cap);     // orders 0, 2: the next tracer
-  uint64_t *sNextW = reinterpret_cast<uint64_t *>(sDesc + a.tile_cap);  // order 1: the next tracer's word
-  LinNb *sPrevNb = reinterpret_cast<LinNb *>(sNextW + a.tile_cap);      // order 1: segment before the chunk
-  LinNb *sNextNb = sPrevNb + a.tile_cap;                                // order 1: segment after its last one
-  uint64_t *sEdge = kLin ? reinterpret_cast<uint64_t *>(sNextNb + a.tile_cap)
-                         : reinterpret_cast<uint64_t *>(sHalo + a.tile_cap);  // per-segment charges
-  double *sRed = reinterpret_cast<double *>(sEdge + (SEG ? 2 * a.tile_cap : 0));  // 3 x 16 waves
+  const ItemLds<PREC, ORDER, SEG> t(smem, a.mesh_cells, a.tile_cap);
 
   if (a.gate != nullptr && *a.gate <= 0) return;
   const int tid = threadIdx.x;
@@ -1285,123 +1597,6 @@ __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
   // chunks whose state is in flight per wavefront (a deposit alone reads 8
   // bytes per tracer and keeps more of them in flight)
   constexpr int kPrefetch = kField ? 3 : 6;
-  static_assert(SF == 0 || (MODE == (kPush | kDeposit) && ORDER == 0), "solve-first: the fused step, constant segments");
-
-  if constexpr (SF > 0) {
-    // Every workgroup solves the same charge with the same arithmetic, so
-    // all hold the field the previous solve launch would have written; the
-    // first one writes it and the diagnostics row (with the previous
-    // launch's partials, summed in the order the solve launch sums them)
-    // and advances the step.  The accumulators of two steps back are
-    // cleared here, a slice per workgroup (no launch merges into them
-    // before the next one).
-    using sacc_t = typename std::conditional<PREC == kFP64, double, long long>::type;
-    // the accumulator copies of a mesh of up to SF * kSolveThreads cells
-    constexpr int kRep = single_rep(SF * kSolveThreads);
-    const int slot = a.items[0].inst;
-    const InstDesc &I0 = a.inst[slot];
-    const SlotConst kc = slot_const(I0);
-    const bool writer = blockIdx.x == 0;
-    sacc_t pv[SF], dv[SF];
-    {
-      // the copies summed in copy order, as the solve launch sums them
-      const int per = (kc.nc + kSolveThreads - 1) / kSolveThreads;
-      const int j0 = tid * per;
-#pragma unroll
-      for (int k = 0; k < SF; ++k) {
-        pv[k] = (sacc_t)0;
-        dv[k] = (sacc_t)0;
-      }
-      // the loads are unconditional (a thread past the mesh reads cell 0 and
-      // adds zero), all copies' in flight together where the registers allow
-      auto take = [&](const void *base, int r, sacc_t(&acc)[SF]) {
-        const sacc_t *g = reinterpret_cast<const sacc_t *>(base) + kc.mesh_off + r * a.rep_stride;
-#pragma unroll
-        for (int k = 0; k < SF; ++k) {
-          const int j = j0 + k;
-          const bool own = k < per && j < kc.nc;
-          const sacc_t v = g[own ? j : 0];
-          acc[k] += own ? v : (sacc_t)0;
-        }
-      };
-      if constexpr (SF * kRep <= 16) {
-#pragma unroll
-        for (int r = 0; r < kRep; ++r) {
-          take(a.sf_P, r, pv);
-          take(a.sf_D, r, dv);
-        }
-      } else {
-#pragma unroll 1
-        for (int r = 0; r < kRep; ++r) take(a.sf_P, r, pv);
-#pragma unroll 1
-        for (int r = 0; r < kRep; ++r) take(a.sf_D, r, dv);
-      }
-    }
-    {
-      // this workgroup's slice of every copy
-      const int z0 = (int)((int64_t)kc.nc * blockIdx.x / gridDim.x);
-      const int z1 = (int)((int64_t)kc.nc * (blockIdx.x + 1) / gridDim.x);
-      for (int r = 0; r < kRep; ++r) {
-        acc_t *zP = reinterpret_cast<acc_t *>(a.sf_zP) + kc.mesh_off + r * a.rep_stride;
-        acc_t *zD = reinterpret_cast<acc_t *>(a.sf_zD) + kc.mesh_off + r * a.rep_stride;
-        for (int i = z0 + tid; i < z1; i += blockDim.x) {
-          zP[i] = (acc_t)0;
-          zD[i] = (acc_t)0;
-        }
-      }
-    }
-    double ke = 0.0, mom = 0.0, ms = 0.0;
-    if (writer) {
-      // as the solve launch: threads tid < 256 sum the slot's items tid,
-      // tid + 256, ... (four at a time), then the wavefront sums and waves
-      // 0..3 in order
-      constexpr int kU = 4;
-      const int2 si = a.sf.slot_items[slot];
-      const Partial *pp = a.sf_partials + si.x;
-      if (tid < kSolveThreads) {
-        for (int i0 = tid; i0 < si.y; i0 += kU * kSolveThreads) {
-          Partial pr[kU];
-#pragma unroll
-          for (int u = 0; u < kU; ++u) {
-            const int i = i0 + u * kSolveThreads;
-            if (i < si.y) pr[u] = pp[i];
-          }
-#pragma unroll
-          for (int u = 0; u < kU; ++u) {
-            if (i0 + u * kSolveThreads < si.y) {
-              ke += pr[u].ke;
-              mom += pr[u].mom;
-              ms = nan_max(ms, pr[u].maxseg);
-            }
-          }
-        }
-      }
-      ke = wave_sum(ke);
-      mom = wave_sum(mom);
-      ms = wave_max(ms);
-      if (lane == 0) {
-        sRed[wave] = ke;
-        sRed[16 + wave] = mom;
-        sRed[32 + wave] = ms;
-      }
-      __syncthreads();
-      ke = sRed[0] + sRed[1] + sRed[2] + sRed[3];
-      mom = sRed[16] + sRed[17] + sRed[18] + sRed[19];
-      ms = nan_max(nan_max(sRed[32], sRed[33]), nan_max(sRed[34], sRed[35]));
-      __syncthreads();
-    }
-    solve_slot<PREC, SF>(a.sf, slot, kc, writer ? I0.step : 0, writer ? I0.flags : 0, pv, dv, (acc_t *)nullptr, ke,
-                         mom, ms, sE, writer, writer);
-    // the ghost cells copy cells other threads wrote: a barrier first (a
-    // workgroup that writes nothing passes none in the solve after its field
-    // loop)
-    __syncthreads();
-    if (tid == 0) {
-      sE[-1] = sE[kc.nc - 1];
-      sE[kc.nc] = sE[0];
-    }
-    __syncthreads();
-  }
 
   for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
     const Item item = a.items[it];
@@ -1451,90 +1646,53 @@ __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
     // instead of dependent reads per chunk.
     for (int i = tid; i < g.nc; i += blockDim.x) {
       if constexpr (kDep) {
-        sP[i] = (acc_t)0;
-        sD[i] = (acc_t)0;
-        if constexpr (kLin) sR[i] = (acc_t)0;
+        t.sP[i] = (acc_t)0;
+        t.sD[i] = (acc_t)0;
+        if constexpr (kLin) t.sR[i] = (acc_t)0;
       }
-      if constexpr (kField && SF == 0) sE[i] = a.meshE[I.mesh_off + i];
+      if constexpr (kField) t.sE[i] = a.meshE[I.mesh_off + i];
     }
-    if constexpr (kField && SF == 0) {
+    if constexpr (kField) {
       if (tid == 0) {
-        sE[-1] = a.meshE[I.mesh_off + g.nc - 1];
-        sE[g.nc] = a.meshE[I.mesh_off];
+        t.sE[-1] = a.meshE[I.mesh_off + g.nc - 1];
+        t.sE[g.nc] = a.meshE[I.mesh_off];
       }
     }
     for (int i = tid; i < nch; i += blockDim.x) {
-      sDesc[i] = a.chunks[cb + i];
+      t.sDesc[i] = a.chunks[cb + i];
       // the next chunk's halo, read with the descriptor: it is the partner
       // of every chunk but a sheet's last (checked below)
       if constexpr (kDep && !kLin) {
-        if (i + 1 < nch) sHalo[i] = a.halo_in[cb + i + 1];
+        if (i + 1 < nch) t.sHalo[i] = a.halo_in[cb + i + 1];
       }
       if constexpr (kNeedQ) {
-        sEdge[2 * i] = a.cedge[2 * (size_t)(cb + i)];
-        sEdge[2 * i + 1] = a.cedge[2 * (size_t)(cb + i) + 1];
+        t.sEdge[2 * i] = a.cedge[2 * (size_t)(cb + i)];
+        t.sEdge[2 * i + 1] = a.cedge[2 * (size_t)(cb + i) + 1];
       }
     }
     __syncthreads();
     if constexpr (kDep) {
+      // The tracers around each chunk, moved here (once per chunk, one
+      // thread) when this step moves, from their state before this step,
+      // rather than by a whole wavefront for its last lane.
       for (int i = tid; i < nch; i += blockDim.x) {
-        const int pc = sDesc[i].partner;
+        const int pc = t.sDesc[i].partner;
         if constexpr (kLin) {
-          // The tracers around the chunk, moved here (once per chunk, one
-          // thread) when this step moves, as for the constant scheme below:
-          // the next tracer (the partner's first), whose word the last lane's
-          // segment ends at, and the segments just outside the chunk, whose
-          // geometry and density the gradients of the first and last lanes'
-          // segments need (the same functions as the lanes', so the same bits).
-          auto moved = [&](double2 h) -> uint64_t {
-            uint64_t w = (uint64_t)__double_as_longlong(h.x);
-            if constexpr (kMove) {
-              const double e = gather_field_ghost(sE, mesh_pos<PREC>(w, g.inv_dx), g.nc);
-              w = drift<PREC>(w, h.y + g.dt * e, g.dt, g.L, g.inv_dx, g.nc);
-            }
-            return w;
-          };
-          auto neighbour = [&](uint64_t wa, uint64_t wb, uint64_t cword) {
-            const SegGeo sgn = lin_geo<PREC>(wa, wb, g);
-            double q;
-            if constexpr (SEG) q = PREC == kFP64 ? __longlong_as_double((long long)cword) : (double)(long long)cword;
-            else q = PREC == kFP64 ? sDesc[i].q : (double)sDesc[i].q_fix;
-            LinNb nb;
-            nb.d = sgn.d;
-            nb.r = lin_nb_density(sgn.d, lin_density(sgn, q));
-            return nb;
-          };
           const int2 lk = a.links[cb + i];
-          LinNb none;
-          none.d = 0.0;
-          none.r = lin_nb_density(0.0, 0.0);
-          LinNb prev = none, next = none;
-          uint64_t wn1 = 0;
-          if (pc >= 0) wn1 = moved(a.halo3_in[3 * pc + kHaloFirst]);
-          if (lk.x >= 0) {
-            const uint64_t wpv = moved(a.halo3_in[3 * (lk.x >> 2) + (lk.x & 3)]);
-            const uint64_t w0 = moved(a.halo3_in[3 * (size_t)(cb + i) + kHaloFirst]);
-            prev = neighbour(wpv, w0, SEG ? sEdge[2 * i] : 0ull);
-          }
-          if (pc >= 0 && lk.y >= 0) {
-            const uint64_t wn2 = moved(a.halo3_in[3 * (lk.y >> 2) + (lk.y & 3)]);
-            next = neighbour(wn1, wn2, SEG ? sEdge[2 * i + 1] : 0ull);
-          }
-          sNextW[i] = wn1;
-          sPrevNb[i] = prev;
-          sNextNb[i] = next;
+          auto halo3 = [&](bool has, size_t at) { return has ? a.halo3_in[at] : make_double2(0.0, 0.0); };
+          const bool hp = lk.x >= 0, hn = pc >= 0 && lk.y >= 0;
+          const double2 own = halo3(hp, 3 * (size_t)(cb + i) + kHaloFirst);
+          const double2 first = halo3(pc >= 0, 3 * (size_t)max(pc, 0) + kHaloFirst);
+          const double2 prev = halo3(hp, 3 * (size_t)(lk.x >> 2) + (lk.x & 3));
+          const double2 next2 = halo3(hn, 3 * (size_t)(lk.y >> 2) + (lk.y & 3));
+          stage_linear<PREC, MODE, SEG>(g, t.sE, pc >= 0, hp, hn, own, first, prev, next2,
+                                        SEG ? t.sEdge[2 * i] : 0ull, SEG ? t.sEdge[2 * i + 1] : 0ull,
+                                        PREC == kFP64 ? t.sDesc[i].q : (double)t.sDesc[i].q_fix, t.sNextW + i,
+                                        t.sPrevNb + i, t.sNextNb + i);
         } else if (pc >= 0) {
-          double2 h = (pc == cb + i + 1 && i + 1 < nch) ? sHalo[i] : a.halo_in[pc];
-          if constexpr (kMove) {
-            // the partner's move, from its state before this step: done here
-            // once per chunk by one thread rather than by a whole wavefront
-            // for its last lane
-            uint64_t pw = (uint64_t)__double_as_longlong(h.x);
-            const double e = gather_field_ghost(sE, mesh_pos<PREC>(pw, g.inv_dx), g.nc);
-            pw = drift<PREC>(pw, h.y + g.dt * e, g.dt, g.L, g.inv_dx, g.nc);
-            h.x = __longlong_as_double((long long)pw);
-          }
-          sHalo[i] = h;
+          double2 h = (pc == cb + i + 1 && i + 1 < nch) ? t.sHalo[i] : a.halo_in[pc];
+          h.x = __longlong_as_double((long long)moved_halo<PREC, MODE>(h, g, t.sE));
+          t.sHalo[i] = h;
         }
       }
       __syncthreads();
@@ -1545,213 +1703,327 @@ __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
     // the next two chunks is in flight while the current one is processed
     // (moving a register whose load is pending would force a wait).
     double ke = 0.0, mom = 0.0, ms = 0.0;
-    auto process = [&](int kk, uint64_t xw, double v, uint64_t cw) {
-      const ChunkDesc ch = sDesc[kk];
-      const int n_valid = __builtin_amdgcn_readfirstlane(ch.n_valid);
-      const bool valid = lane < n_valid;
-      const size_t s = (size_t)(cb + kk) * kChunk + lane;
-      // Per-segment charges: this lane's segment (cw), the one ending at this
-      // tracer (cl) and, for linear segments, the next one (cn).
-      uint64_t cl = 0, cn = 0;
-      if constexpr (kNeedQ) {
-        const uint64_t up = lane_up1(cw);
-        const uint64_t dn = lane_down1(cw);
-        cl = lane == 0 ? sEdge[2 * kk] : up;
-        cn = lane == n_valid - 1 ? sEdge[2 * kk + 1] : dn;
-      }
-      if constexpr (kField) {
-        const double e = gather_field_ghost(sE, mesh_pos<PREC>(xw, g.inv_dx), g.nc);
-        if constexpr (kKick) {
-          const double vk = v - (0.5 * g.dt) * e;
-          v = valid ? vk : v;
-          a.vs[s] = v;
-        } else {
-          const double vn = v + g.dt * e;
-          double m;
-          if constexpr (SEG) {
-            m = tracer_mass<PREC>(cl, cw, I.q_unit);
-          } else {
-            // half of each segment the tracer bounds: the ends of an open
-            // sheet bound one
-            const bool end = (lane == 0 && (ch.flags & kChunkOpenStart)) || (lane == n_valid - 1 && ch.partner < 0);
-            m = end ? 0.5 * ch.q : ch.q;
-          }
-          const double qv = valid ? m : 0.0;
-          // twice the kinetic energy and momentum: the factor 1/2 is applied
-          // to the item's sums (a power of two, so the same bits)
-          ke += qv * v * vn;
-          mom += qv * (v + vn);
-          const uint64_t xn = drift<PREC>(xw, vn, g.dt, g.L, g.inv_dx, g.nc);
-          xw = valid ? xn : xw;
-          v = valid ? vn : v;
-          __builtin_nontemporal_store(xw, a.xs + s);
-          __builtin_nontemporal_store(v, a.vs + s);
-        }
-        const double2 hv2 = make_double2(__longlong_as_double((long long)xw), v);
-        if constexpr (kLin) {
-          const size_t hb = 3 * (size_t)(cb + kk);
-          if (lane == 0) a.halo3_out[hb + kHaloFirst] = hv2;
-          if (lane == 1) a.halo3_out[hb + kHaloSecond] = hv2;
-          if (lane == n_valid - 1) a.halo3_out[hb + kHaloLast] = hv2;
-        } else {
-          if (lane == 0) a.halo_out[cb + kk] = hv2;
-        }
-      }
-      if constexpr (kDep && kLin) {
-        // Every lane computes its own segment's geometry and density; the
-        // gradient takes the neighbouring segments' from the lanes next to
-        // it (DPP moves), and the first and last lanes take the segments
-        // outside the chunk from the staged neighbours.
-        const bool last = lane == n_valid - 1;
-        const uint64_t dn1 = lane_down1(xw);  // all lanes active: a DPP move reads its neighbour's register
-        const uint64_t xp1 = last ? sNextW[kk] : dn1;
-        const bool has_seg = valid && (!last || ch.partner >= 0);
-        SegGeo sg = lin_geo<PREC>(xw, xp1, g);
-        if (!has_seg) sg.d = 0.0;  // a neighbour without a segment drops the gradient
-        double q0 = ch.q;
-        long long q0_fix = ch.q_fix;
-        if constexpr (SEG) {
-          if constexpr (PREC == kFP64) q0 = __longlong_as_double((long long)cw);
-          else q0_fix = (long long)cw;
-        }
-        const double r0 = lin_density(sg, PREC == kFP64 ? q0 : (double)q0_fix);
-        const double rv = lin_nb_density(sg.d, r0);
-        double dm = lane_up1(sg.d), rm = lane_up1(rv);
-        double dp = lane_down1(sg.d), rp = lane_down1(rv);
-        if (lane == 0) {
-          const LinNb nb = sPrevNb[kk];
-          dm = nb.d;
-          rm = nb.r;
-        }
-        if (last) {
-          const LinNb nb = sNextNb[kk];
-          dp = nb.d;
-          rp = nb.r;
-        }
-        if (has_seg) {
-          const double grad = lin_gradient(sg.d, dm, rm, dp, rp);
-          const double len = fabs(sg.d) * g.dx;
-          if (len <= g.half_L) {
-            if constexpr (PREC == kFP64) {
-              deposit_linear_fp64(__longlong_as_double((long long)xw), sg, grad, q0, r0, g, sP, sD, sR);
-            } else {
-              deposit_linear_split(split_cell<PREC>(xw), split_frac<PREC>(xw), sg, grad, q0_fix, r0, g, sP, sD,
-                                   sR);
-            }
-          }
-          ms = nan_max(ms, len);
-        }
-      }
-      if constexpr (kDep && !kLin) {
-        uint64_t pw = lane_down1(xw);
-        const bool tail = (lane == n_valid - 1);
-        bool has_seg = valid;
-        if (tail) {
-          if (ch.partner < 0) {
-            has_seg = false;  // open sheet: the last tracer ends the chain
-          } else {
-            pw = (uint64_t)__double_as_longlong(sHalo[kk].x);  // moved at staging when this step moves
-          }
-        }
-        if (has_seg) {
-          double len;
-          double q0 = ch.q;
-          long long q0_fix = ch.q_fix;
-          if constexpr (SEG) {
-            if constexpr (PREC == kFP64) q0 = __longlong_as_double((long long)cw);
-            else q0_fix = (long long)cw;
-          }
-          if constexpr (ORDER == 2) {
-            // first-order weighting: geometry in mesh units, minimum image as
-            // for the constant scheme
-            double ua, dm;
-            if constexpr (PREC == kFP64) {
-              const double xa = __longlong_as_double((long long)xw);
-              double d = __longlong_as_double((long long)pw) - xa;
-              if (d >= g.half_L) d -= g.L;
-              else if (d < -g.half_L) d += g.L;
-              ua = xa * g.inv_dx;
-              dm = d * g.inv_dx;
-            } else {
-              ua = mesh_pos<PREC>(xw, g.inv_dx);
-              dm = min_image_cells(mesh_pos<PREC>(pw, g.inv_dx) - ua, 0.5 * (double)g.nc, (double)g.nc);
-            }
-            len = fabs(dm) * g.dx;
-            if (len <= g.half_L) {
-              if constexpr (PREC == kFP64) deposit_cic_fp64(ua, dm, q0, g, sP, sD);
-              else deposit_cic_split(ua, dm, q0_fix, g, sP, sD);
-            }
-          } else {
-            if constexpr (PREC == kFP64) {
-              len = deposit_fp64(__longlong_as_double((long long)xw), __longlong_as_double((long long)pw), q0, g,
-                                 sP, sD);
-            } else {
-              len = deposit_split<PREC>(xw, pw, q0_fix, g, sP, sD);
-            }
-          }
-          ms = nan_max(ms, len);
-        }
-      }
-    };
     for (int k = wave; k < nch; k += kPrefetch * nwaves) {
 #pragma unroll
       for (int j = 0; j < kPrefetch; ++j) {
-        if (k + j * nwaves < nch) process(k + j * nwaves, xr[j], vr[j], cr_[j]);
+        const int kk = k + j * nwaves;
+        if (kk < nch) {
+          ChunkTab tab;
+          tab.d = t.sDesc[kk];
+          if constexpr (kNeedQ) tab.edge = t.sEdge[2 * kk];
+          if constexpr (kDep && kLin) {
+            tab.next = t.sNextW[kk];
+            tab.before = t.sPrevNb[kk];
+            tab.after = t.sNextNb[kk];
+          } else if constexpr (kDep) {
+            tab.next = (uint64_t)__double_as_longlong(t.sHalo[kk].x);
+          }
+          process_chunk<PREC, MODE, ORDER, SEG>(t, g, I.q_unit, a.xs, a.vs, kLin ? a.halo3_out : a.halo_out, tab,
+                                                (size_t)(cb + kk), lane, xr[j], vr[j], cr_[j], ke, mom, ms);
+        }
         load_state(k + (j + kPrefetch) * nwaves, xr[j], vr[j], cr_[j]);
       }
     }
 
-    // Work-item partial sums in a fixed order (deterministic for a fixed
-    // item decomposition).
-    if constexpr (kMove) {
-      ke = wave_sum(ke);
-      mom = wave_sum(mom);
-    }
-    if constexpr (kDep) ms = wave_max(ms);
-    if (lane == 0) {
-      sRed[wave] = ke;
-      sRed[16 + wave] = mom;
-      sRed[32 + wave] = ms;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      double kk = 0.0, m = 0.0, x = 0.0;
-      for (int w = 0; w < nwaves; ++w) {
-        kk += sRed[w];
-        m += sRed[16 + w];
-        x = nan_max(x, sRed[32 + w]);
-      }
-      if constexpr (kMove) {
-        a.partials[it].ke = 0.5 * kk;
-        a.partials[it].mom = 0.5 * m;
-      }
-      if constexpr (kDep) a.partials[it].maxseg = x;
-    }
+    item_partial<MODE>(ke, mom, ms, t.sRed, a.partials + it);
     if constexpr (kDep) {
       const int64_t roff = I.mesh_off + (int64_t)(it % a.rep) * a.rep_stride;
-      acc_t *gP = reinterpret_cast<acc_t *>(a.meshP) + roff;
-      acc_t *gD = reinterpret_cast<acc_t *>(a.meshD) + roff;
-      for (int i = tid; i < g.nc; i += blockDim.x) {
-        const acc_t p = sP[i];
-        const acc_t d = sD[i];
-        if (p != (acc_t)0) {
-          if constexpr (PREC == kFP64) unsafeAtomicAdd(gP + i, p);
-          else atomicAdd(gP + i, p);
-        }
-        if (d != (acc_t)0) {
-          if constexpr (PREC == kFP64) unsafeAtomicAdd(gD + i, d);
-          else atomicAdd(gD + i, d);
-        }
-        if constexpr (kLin) {
-          acc_t *gR = reinterpret_cast<acc_t *>(a.meshR) + roff;
-          const acc_t r = sR[i];
-          if (r != (acc_t)0) {
-            if constexpr (PREC == kFP64) unsafeAtomicAdd(gR + i, r);
-            else atomicAdd(gR + i, r);
-          }
+      merge_mesh<PREC, ORDER, SEG>(t, reinterpret_cast<acc_t *>(a.meshP) + roff,
+                                   reinterpret_cast<acc_t *>(a.meshD) + roff,
+                                   kLin ? reinterpret_cast<acc_t *>(a.meshR) + roff : (acc_t *)nullptr, g.nc);
+    }
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Solve-first step of a single simulation
+// ---------------------------------------------------------------------------
+// One launch per step: every workgroup first solves the charge that the
+// launch before merged (the same arithmetic in all of them, and in k_solve:
+// the same bits), then moves and deposits its work item; workgroup 0 also
+// writes the diagnostics row of that charge and the step.  Such a step is a
+// chain of latencies, not of bytes or operations, so the chain is kept short:
+// the simulation's constants and its item's chunk range come with the launch
+// (no reads of the item list and the slot's descriptor, each a round trip
+// that the next one waits for); the item's descriptors, halos and first
+// chunks are in flight during the solve; and every wavefront keeps the tables
+// of its own chunks in registers, one chunk per lane, with no barrier and no
+// LDS round trip.  Workgroup 0's row: with fewer items than compute units it
+// has no item (row_group) and the row holds up none; otherwise it would share
+// its compute unit with an item and hold that up by more than the row takes
+// at the end of its own (Landau, 256 items: 9.1 us per step with a row
+// workgroup, 8.1 without; 20 sheets of 64 tracers, 5 items: 8.1 with, 9.5
+// without).
+//
+// Per step, before (item list and descriptor read in turn, the row first, a
+// 64-bit division for the slice to clear; orders 1 and 2 as launch pairs) and
+// now: Landau (131072 tracers, 256 cells) 9.3 -> 8.1 us, with linear segments
+// 13.7 -> 10.1, first-order weighting on ragged sheets (47000 tracers, 200
+// cells, split U32) 11.1 -> 7.3, two-stream (2.1M tracers, 1024 cells, split
+// F32) 26 -> 26.  Of the 8.1 us of Landau's, 1.6 are the launch, 1.2 the
+// charge, 1.2 the solve, 1.7 moving and depositing one chunk per wavefront
+// and 1.2 the merge.  CELLS: cells per solve thread.
+template <int PREC, int ORDER, bool SEG, int CELLS>
+__global__ void __launch_bounds__(1024) k_step(StepArgs a) {
+  using acc_t = typename std::conditional<PREC == kFP64, double, unsigned long long>::type;
+  using sacc_t = typename std::conditional<PREC == kFP64, double, long long>::type;
+  constexpr int kMode = kPush | kDeposit;
+  constexpr bool kLin = ORDER == 1;
+  constexpr int kArrays = kLin ? 3 : 2;
+  constexpr int kRep = single_rep(CELLS * kSolveThreads);
+  constexpr int kPrefetch = 3;
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ double sRow[5][4];  // workgroup 0: the row's sums by wavefront
+  const ItemLds<PREC, ORDER, SEG> t(smem, a.nc, 0);
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nt = blockDim.x;
+  const int nwaves = nt >> 6;
+  const bool row = blockIdx.x == 0 && a.acc_in != nullptr;
+  Geo g;
+  g.L = a.L;
+  g.half_L = a.half_L;
+  g.dx = a.dx;
+  g.inv_dx = a.inv_dx;
+  g.dt = a.dt;
+  g.nc = a.nc;
+  const int nc = a.nc;
+  const SlotConst kc = {nc, a.L, a.dx, a.dt, a.q_unit, 0, 0, a.hist_cap};
+
+  const int it0 = a.row_group ? -1 : 0;  // workgroup 0's item; -1: it has none
+  int it = (int)blockIdx.x + it0;
+  int cb = 0, nch = 0;
+  auto range = [&]() {  // a workgroup without an item loads the first one's
+    const int i = max(it, 0);
+    cb = a.chunk_begin + i * a.tile;
+    nch = min(a.tile, a.n_chunks - i * a.tile);
+  };
+  // Lane i of wavefront w holds the tables of chunk w + i * waves, the i-th
+  // of the wavefront's (an item has at most 64 chunks per wavefront), until
+  // they are staged.
+  const int mine = wave + lane * nwaves;
+  ChunkDesc desc;
+  int2 lk = make_int2(-1, -1);
+  uint64_t e0 = 0, e1 = 0;
+  auto load_desc = [&]() {
+    const size_t c = (size_t)(cb + min(mine, nch - 1));
+    desc = a.chunks[c];
+    if constexpr (kLin) lk = a.links[c];
+    if constexpr (SEG) {
+      e0 = a.cedge[2 * c];
+      e1 = a.cedge[2 * c + 1];
+    }
+  };
+  double2 own, first, prev, next2;  // orders 0, 2: first alone
+  auto load_halos = [&]() {
+    const size_t c = (size_t)(cb + min(mine, nch - 1));
+    const size_t pc = desc.partner >= 0 ? (size_t)desc.partner : c;
+    if constexpr (kLin) {
+      own = a.halo_in[3 * c + kHaloFirst];
+      first = a.halo_in[3 * pc + kHaloFirst];
+      prev = a.halo_in[lk.x >= 0 ? 3 * (size_t)(lk.x >> 2) + (lk.x & 3) : 3 * c];
+      next2 = a.halo_in[lk.y >= 0 ? 3 * (size_t)(lk.y >> 2) + (lk.y & 3) : 3 * c];
+    } else {
+      first = a.halo_in[pc];
+    }
+  };
+  uint64_t xr[kPrefetch], cr_[kPrefetch];
+  double vr[kPrefetch];
+  auto load_state = [&](int kk, uint64_t &xw, double &v, uint64_t &cw) {  // as in k_tracers
+    const size_t s = kk < nch ? (size_t)(cb + kk) * kChunk + lane : (size_t)cb * kChunk;
+    xw = __builtin_nontemporal_load(a.xs + s);
+    v = __builtin_nontemporal_load(a.vs + s);
+    if constexpr (SEG) cw = a.segq[s];
+  };
+  auto load_first_states = [&]() {
+#pragma unroll
+    for (int j = 0; j < kPrefetch; ++j) {
+      xr[j] = cr_[j] = 0;
+      load_state(wave + j * nwaves, xr[j], vr[j], cr_[j]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // the moved tracers around the wavefront's chunks, one chunk per lane
+  uint64_t next = 0;
+  LinNb before, after;
+  auto move_halos = [&]() {
+    if constexpr (kLin) {
+      stage_linear<PREC, kMode, SEG>(g, t.sE, desc.partner >= 0, lk.x >= 0, lk.y >= 0, own, first, prev, next2, e0, e1,
+                                     PREC == kFP64 ? desc.q : (double)desc.q_fix, &next, &before, &after);
+    } else {
+      next = moved_halo<PREC, kMode>(first, g, t.sE);
+    }
+  };
+  // the entry of the wavefront's i-th chunk, from lane i
+  auto read_f64 = [](double x, int i) {
+    return __longlong_as_double((long long)read_lane64((uint64_t)__double_as_longlong(x), i));
+  };
+  auto entry = [&](int i) {
+    ChunkTab tab;
+    tab.d.q = SEG && PREC == kFP64 ? 0.0 : read_f64(desc.q, i);
+    tab.d.q_fix = PREC == kFP64 || SEG ? 0 : (int64_t)read_lane64((uint64_t)desc.q_fix, i);
+    tab.d.partner = __builtin_amdgcn_readlane(desc.partner, i);
+    tab.d.n_valid = __builtin_amdgcn_readlane(desc.n_valid, i);
+    tab.d.flags = __builtin_amdgcn_readlane(desc.flags, i);
+    tab.edge = SEG ? read_lane64(e0, i) : 0;
+    tab.next = read_lane64(next, i);
+    if constexpr (kLin) {
+      tab.before.d = read_f64(before.d, i);
+      tab.before.r = read_f64(before.r, i);
+      tab.after.d = read_f64(after.d, i);
+      tab.after.r = read_f64(after.r, i);
+    }
+    return tab;
+  };
+
+  range();
+  load_desc();
+  __builtin_amdgcn_sched_barrier(0);
+  FieldSums fs = {0.0, 0.0, 0};
+  Partial pr[2];  // the row: the launch before's partials tid and tid + 256
+  int64_t step0 = 0;
+  int flags0 = 0;
+  if (a.acc_in != nullptr) {
+    // The charge: cells tid, tid + threads, ... of every array, the copies
+    // summed in copy order (as the solve launch sums them) and passed to the
+    // solve's threads through the item's still unused LDS mesh, so that the
+    // reads are coalesced and spread over all wavefronts.
+    const sacc_t *in = reinterpret_cast<const sacc_t *>(a.acc_in);
+    sacc_t *sAcc = reinterpret_cast<sacc_t *>(t.sP);
+    sacc_t av[kArrays][kRep];
+    auto load_acc = [&](int j) {
+#pragma unroll
+      for (int r = 0; r < kRep; ++r)
+#pragma unroll
+        for (int k = 0; k < kArrays; ++k) av[k][r] = in[(int64_t)(k * kRep + r) * nc + j];
+    };
+    auto sum_acc = [&](int j) {
+#pragma unroll
+      for (int k = 0; k < kArrays; ++k) {
+        sacc_t sum = (sacc_t)0;
+#pragma unroll
+        for (int r = 0; r < kRep; ++r) sum += av[k][r];
+        sAcc[(int64_t)k * nc + j] = sum;
+      }
+    };
+    load_acc(min(tid, nc - 1));
+    __builtin_amdgcn_sched_barrier(0);
+    load_halos();
+    load_first_states();
+    if (row) {
+      step0 = a.sf.inst[0].step;
+      flags0 = a.sf.inst[0].flags;
+      pr[0] = a.part_in[min(tid, a.n_items - 1)];
+      pr[1] = a.part_in[min(tid + kSolveThreads, a.n_items - 1)];
+    }
+    if (tid < nc) sum_acc(tid);
+    for (int j = tid + nt; j < nc; j += nt) {
+      load_acc(j);
+      sum_acc(j);
+    }
+    __syncthreads();
+    sacc_t pv[CELLS], dv[CELLS];
+    if (wave < kSolveThreads / kChunk) {
+      const int per = (nc + kSolveThreads - 1) / kSolveThreads;
+#pragma unroll
+      for (int k = 0; k < CELLS; ++k) {
+        const int j = tid * per + k;
+        const bool in_mesh = k < per && j < nc;
+        const int at = in_mesh ? j : 0;
+        const sacc_t p = sAcc[at], d = sAcc[nc + at];
+        pv[k] = in_mesh ? p : (sacc_t)0;
+        dv[k] = in_mesh ? d : (sacc_t)0;
+      }
+    }
+    // the field and the density in global memory are written by the solve
+    // launch that ends a run of such steps
+    fs = solve_field<PREC, CELLS>(kc, pv, dv, kLin ? sAcc + 2 * (int64_t)nc : (sacc_t *)nullptr, 0, t.sE, true,
+                                  (double *)nullptr, (double *)nullptr);
+    // The accumulators that the launch before read are cleared, a slice per
+    // workgroup (the next launch merges into them).
+    acc_t *z = reinterpret_cast<acc_t *>(a.acc_zero);
+    const int z1 = min(kArrays * kRep * nc, ((int)blockIdx.x + 1) * a.zero_slice);
+    for (int i = (int)blockIdx.x * a.zero_slice + tid; i < z1; i += nt) z[i] = (acc_t)0;
+  } else {
+    // the first step of a run: the field is in global memory
+    load_halos();
+    load_first_states();
+    for (int j = tid; j < nc; j += nt) {
+      const double e = a.meshE[j];
+      t.sE[j] = e;
+      if (j == 0) t.sE[nc] = e;
+      if (j == nc - 1) t.sE[-1] = e;
+    }
+  }
+  for (;;) {
+    // the solve's threads read the charge from the LDS mesh before its first
+    // barrier (linear segments' ramps: before its second, and clear them)
+    for (int i = tid; i < nc; i += nt) {
+      t.sP[i] = (acc_t)0;
+      t.sD[i] = (acc_t)0;
+      if constexpr (kLin) t.sR[i] = (acc_t)0;
+    }
+    __syncthreads();  // the field, the cleared mesh
+    double ke = 0.0, mom = 0.0, ms = 0.0;
+    if (it >= 0) {
+      move_halos();
+      int i = 0;
+      for (int k = wave; k < nch; k += kPrefetch * nwaves) {
+#pragma unroll
+        for (int j = 0; j < kPrefetch; ++j) {
+          if (k + j * nwaves < nch)
+            process_chunk<PREC, kMode, ORDER, SEG>(t, g, a.q_unit, a.xs, a.vs, a.halo_out, entry(i++),
+                                                   (size_t)(cb + k + j * nwaves), lane, xr[j], vr[j], cr_[j], ke, mom,
+                                                   ms);
+          load_state(k + (j + kPrefetch) * nwaves, xr[j], vr[j], cr_[j]);
         }
       }
     }
+    const bool with_row = row && it == it0;
+    if (with_row && wave < kSolveThreads / kChunk) {
+      // the row's wavefront sums, in the solve launch's order: thread tid
+      // sums the items tid, tid + 256, ...
+      double pke = 0.0, pmom = 0.0, pms = 0.0;
+      auto add = [&](const Partial &p) {
+        pke += p.ke;
+        pmom += p.mom;
+        pms = nan_max(pms, p.maxseg);
+      };
+      if (tid < a.n_items) add(pr[0]);
+      if (tid + kSolveThreads < a.n_items) add(pr[1]);
+      for (int i = tid + 2 * kSolveThreads; i < a.n_items; i += kSolveThreads) add(a.part_in[i]);
+      const double w = wave_sum(fs.w2), k = wave_sum(pke), m = wave_sum(pmom), x = wave_max(pms);
+      const int bad = wave_sum(fs.bad);
+      if (lane == 0) {
+        sRow[0][wave] = w;
+        sRow[1][wave] = k;
+        sRow[2][wave] = m;
+        sRow[3][wave] = x;
+        sRow[4][wave] = (double)bad;
+      }
+    }
+    if (it >= 0) item_partial<kMode>(ke, mom, ms, t.sRed, a.part_out + it);
+    else __syncthreads();
+    if (with_row && tid == nt - 1) {
+      const double W = 0.5 * a.dx * (sRow[0][0] + sRow[0][1] + sRow[0][2] + sRow[0][3]);
+      const double k = sRow[1][0] + sRow[1][1] + sRow[1][2] + sRow[1][3];
+      const double m = sRow[2][0] + sRow[2][1] + sRow[2][2] + sRow[2][3];
+      const double x = nan_max(nan_max(sRow[3][0], sRow[3][1]), nan_max(sRow[3][2], sRow[3][3]));
+      const int bad = (int)(sRow[4][0] + sRow[4][1] + sRow[4][2] + sRow[4][3]);
+      write_row(a.sf, 0, kc, step0, solve_flags(a.sf.flags, flags0, a.L, W, bad, k, m, x), W, fs.Qtot, k, m, x);
+    }
+    if (it < 0) return;
+    acc_t *out = reinterpret_cast<acc_t *>(a.acc_out) + (int64_t)(it % kRep) * nc;
+    const int64_t arr = (int64_t)kRep * nc;
+    merge_mesh<PREC, ORDER, SEG>(t, out, out + arr, out + 2 * arr, nc);
+    it += (int)gridDim.x + it0;
+    if (it >= a.n_items) break;
+    range();
+    load_desc();
+    load_halos();
+    load_first_states();
     __syncthreads();
   }
 }
@@ -2111,8 +2383,15 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(SolveArgs a) {
   mom = sMom[0] + sMom[1] + sMom[2] + sMom[3];
   ms = nan_max(nan_max(sMs[0], sMs[1]), nan_max(sMs[2], sMs[3]));
   acc_t *gRamp = (a.order == 1 && a.meshR) ? reinterpret_cast<acc_t *>(a.meshR) + kc.mesh_off : nullptr;
-  solve_slot<PREC, CELLS, REP>(a, slot, kc, Ip->step, Ip->flags, pv, dv, gRamp, ke, mom, ms,
-                          (double *)nullptr, true);
+  const FieldSums f = solve_field<PREC, CELLS, REP>(kc, pv, dv, gRamp, a.rep_stride, (double *)nullptr, false,
+                                                    a.meshE + kc.mesh_off, a.meshRho + kc.mesh_off);
+  double W;
+  int bad;
+  field_energy(f, kc.dx, &W, &bad);
+  if (tid == 0)
+    write_row(a, slot, kc, Ip->step, solve_flags(a.flags, Ip->flags, kc.L, W, bad, ke, mom, ms), W, f.Qtot, ke, mom, ms);
+  acc_t *z = reinterpret_cast<acc_t *>(a.zero);
+  for (int64_t i = tid; i < a.zero_words; i += kSolveThreads) z[i] = (acc_t)0;
 }
 
 // ---------------------------------------------------------------------------
@@ -2293,8 +2572,15 @@ __global__ void __launch_bounds__(NT) k_resident(TracerArgs a, SolveArgs sa, int
     using sacc_t = typename std::conditional<PREC == kFP64, double, long long>::type;
     sacc_t pv[CELLS], dv[CELLS];
     solve_take<PREC, CELLS, 1>(kc, sP, sD, 0, pv, dv);
-    flags = solve_slot<PREC, CELLS>(sa, slot, kc, step_now, flags, pv, dv, (acc_t *)nullptr, ke, mom, ms, sE,
-                                    step == n_steps - 1);
+    const bool last = step == n_steps - 1;
+    const FieldSums f = solve_field<PREC, CELLS>(kc, pv, dv, (acc_t *)nullptr, 0, sE, false,
+                                                 last ? sa.meshE + kc.mesh_off : (double *)nullptr,
+                                                 last ? sa.meshRho + kc.mesh_off : (double *)nullptr);
+    double W;
+    int bad;
+    field_energy(f, kc.dx, &W, &bad);
+    flags = solve_flags(sa.flags, flags, kc.L, W, bad, ke, mom, ms);
+    if (tid == 0) write_row(sa, slot, kc, step_now, flags, W, f.Qtot, ke, mom, ms);
     step_now += 1;
     lds_barrier();
   }
@@ -2855,52 +3141,55 @@ int set_tracer_lds_limit(int prec, int order, bool seg, size_t lds) {
   return (int)e;
 }
 
-// Solve-first launches (single simulations, constant segments).
-template <int PREC, bool SEG, int SF>
-static hipError_t tracers_sf_launch(const TracerArgs &a, int grid, int block, size_t lds, hipStream_t st) {
+// Solve-first steps (single simulations).
+template <int PREC, int ORDER, bool SEG, int CELLS>
+static hipError_t step_launch(const StepArgs &a, int grid, int block, size_t lds, hipStream_t st) {
   // the dynamic LDS limit is raised to what a launch asks for, not to the
   // whole 160 KB: the solve's static LDS takes part of it
-  static size_t granted = 65536;
-  if (lds > granted) {
-    const hipError_t e = hipFuncSetAttribute((const void *)k_tracers<PREC, kPush | kDeposit, 0, SEG, SF>,
+  static std::atomic<size_t> granted{65536};
+  if (lds > granted.load()) {
+    const hipError_t e = hipFuncSetAttribute((const void *)k_step<PREC, ORDER, SEG, CELLS>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) {
       (void)hipGetLastError();  // not left for the next launch to report
       return e;
     }
-    granted = lds;
+    granted.store(lds);
   }
-  hipLaunchKernelGGL((k_tracers<PREC, kPush | kDeposit, 0, SEG, SF>), dim3(grid), dim3(block), lds, st, a);
+  hipLaunchKernelGGL((k_step<PREC, ORDER, SEG, CELLS>), dim3(grid), dim3(block), lds, st, a);
   return hipGetLastError();
 }
 
-template <int PREC, bool SEG>
-static hipError_t tracers_sf_cells(const TracerArgs &a, int grid, int block, size_t lds, int max_cells,
-                                   hipStream_t st) {
-  const int per = (max_cells + kSolveThreads - 1) / kSolveThreads;
-  if (per <= 1) return tracers_sf_launch<PREC, SEG, 1>(a, grid, block, lds, st);
-  if (per <= 4) return tracers_sf_launch<PREC, SEG, 4>(a, grid, block, lds, st);
-  return tracers_sf_launch<PREC, SEG, 16>(a, grid, block, lds, st);
+// The step of linear segments is built for meshes of up to 1024 cells: with
+// 16 cells per thread its solve's three arrays do not fit 128 registers.
+bool step_supported(int order, int max_cells) {
+  return max_cells >= 1 && max_cells <= (order == 1 ? 4 * kSolveThreads : kMaxCells);
 }
 
-int launch_tracers_sf(int prec, bool seg, const TracerArgs &a, int grid, int block, size_t lds, int max_cells,
-                      void *stream) {
-  if (grid <= 0) return 0;
-  if (max_cells < 1 || max_cells > kMaxCells || block < kSolveThreads || a.rep != single_rep(max_cells))
-    return (int)hipErrorInvalidValue;
-  hipStream_t st = (hipStream_t)stream;
-  switch (prec) {
-    case kFP64:
-      return (int)(seg ? tracers_sf_cells<kFP64, true>(a, grid, block, lds, max_cells, st)
-                       : tracers_sf_cells<kFP64, false>(a, grid, block, lds, max_cells, st));
-    case kSplitF32:
-      return (int)(seg ? tracers_sf_cells<kSplitF32, true>(a, grid, block, lds, max_cells, st)
-                       : tracers_sf_cells<kSplitF32, false>(a, grid, block, lds, max_cells, st));
-    case kSplitU32:
-      return (int)(seg ? tracers_sf_cells<kSplitU32, true>(a, grid, block, lds, max_cells, st)
-                       : tracers_sf_cells<kSplitU32, false>(a, grid, block, lds, max_cells, st));
-    default: return (int)hipErrorInvalidValue;
+template <int PREC, int ORDER, bool SEG>
+struct LaunchStep {
+  static hipError_t run(const StepArgs &a, int grid, int block, size_t lds, hipStream_t st) {
+    const int per = (a.nc + kSolveThreads - 1) / kSolveThreads;
+    if (per <= 1) return step_launch<PREC, ORDER, SEG, 1>(a, grid, block, lds, st);
+    if (per <= 4) return step_launch<PREC, ORDER, SEG, 4>(a, grid, block, lds, st);
+    if constexpr (ORDER != 1) return step_launch<PREC, ORDER, SEG, 16>(a, grid, block, lds, st);
+    return hipErrorInvalidValue;
   }
+};
+
+int launch_step(int prec, int order, bool seg, const StepArgs &a, int grid, int block, void *stream) {
+  // a wavefront stages at most 64 chunks of an item: a.tile <= block
+  if (!step_supported(order, a.nc) || block < kSolveThreads || a.tile < 1 || a.tile > block || a.n_items < 1 ||
+      grid < 1 || grid > a.n_items)
+    return (int)hipErrorInvalidValue;
+  // the chunks' tables are in registers: the mesh, the field and the sums only
+  const size_t lds = tracer_lds_size(prec, order, seg, a.nc, 0);
+  StepArgs b = a;
+  b.row_group = grid < kComputeUnits ? 1 : 0;
+  grid += b.row_group;
+  const int words = (order == 1 ? 3 : 2) * single_rep(a.nc) * a.nc;
+  b.zero_slice = (words + grid - 1) / grid;
+  return (int)dispatch<LaunchStep>(prec, order, seg, b, grid, block, lds, (hipStream_t)stream);
 }
 
 int launch_tracers(int prec, int mode, int order, bool seg, const TracerArgs &a, int grid, int block, size_t lds,
@@ -3002,7 +3291,8 @@ int launch_solve(int prec, const SolveArgs &a, int n_blocks, int max_cells, void
   if (max_cells < 1 || max_cells > kMaxCells) return (int)hipErrorInvalidValue;
   if (a.rep == 1) return (int)solve_rep_launch<1>(prec, a, n_blocks, max_cells, st);
   if (a.rep == 2) return (int)solve_rep_launch<2>(prec, a, n_blocks, max_cells, st);
-  if (a.rep == 4) return (int)solve_rep_launch<4>(prec, a, n_blocks, max_cells, st);
+  if (a.rep == kSmallMeshRep && max_cells <= kSolveThreads)
+    return (int)solve_cells_launch<1, kSmallMeshRep>(prec, a, n_blocks, st);
   return (int)hipErrorInvalidValue;
 }
 
