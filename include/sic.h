@@ -176,9 +176,9 @@ sic_status sic_push(sic_sim *sim);
  * per compute unit; linear segments: on at most 1024 cells) a simulation's
  * step is one launch, which solves the previous step's charge itself, in
  * every workgroup, and one solve launch closes the call
- * (SIC_PATH_SOLVE_FIRST); a small simulation (constant segments, at most 32
- * chunks of 64 tracer slots) runs its steps in one launch of a single
- * workgroup
+ * (SIC_PATH_SOLVE_FIRST); a small simulation (at most 32 chunks of 64 tracer
+ * slots, linear segments: on at most 1024 cells) runs its steps in one launch
+ * of a single workgroup
  * (SIC_PATH_RESIDENT).  All give the bits of the fused path in the split
  * forms.  Timing mode (sic_set_timing) always takes the fused path.  Async;
  * with refinement on (l_max > 0) each step is followed by a refinement pass

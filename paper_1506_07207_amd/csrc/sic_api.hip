@@ -1047,8 +1047,10 @@ sic_status run_resident(Pool *p, int64_t n) {
     const int64_t k = std::min<int64_t>(n, kResidentSteps);
     TracerArgs a = tracer_args(p, kPush | kDeposit, 0);
     a.halo_out = p->halo[p->parity ^ (int)(k & 1)];
+    a.halo3_out = p->halo3[p->parity ^ (int)(k & 1)];
     SolveArgs sa = solve_args(p, kHavePush | kHaveDeposit, 0);
-    LAUNCHCHK(p, launch_resident(p->prec, p->seg, a, sa, sh.chunk_begin, sh.n_chunks, sh.n_cells, k, p->stream));
+    LAUNCHCHK(p, launch_resident(p->prec, p->order, p->seg, a, sa, sh.chunk_begin, sh.n_chunks, sh.n_cells, k,
+                                 p->stream));
     if (k & 1) p->parity ^= 1;
     n -= k;
   }
@@ -2092,7 +2094,7 @@ sic_status sim_step(Pool *p, int64_t n) {
     }
     return sim_step_refining(p, n);
   }
-  if (p->order == 0 && !p->timing && !p->tune.fused_only && sh.n_chunks <= resident_max_chunks()) {
+  if (!p->timing && !p->tune.fused_only && resident_supported(p->order, sh.n_chunks, sh.n_cells)) {
     p->last_path = SIC_PATH_RESIDENT;
     return run_resident(p, n);
   }

@@ -317,11 +317,11 @@ int launch_charge_edges(const ChunkDesc *chunks, const int64_t *prev_slot, const
                         int32_t chunk_begin, int32_t n_chunks, void *stream, const int32_t *state = nullptr);
 // A small simulation's n_steps fused steps (push, deposit, solve) in one
 // launch of one workgroup; chunks [chunk_begin, chunk_begin + n_chunks) of
-// slot 0, constant segments.  a.halo_out receives the first-tracer halos of
-// the final state.
-int resident_max_chunks();
-int launch_resident(int prec, bool seg, const TracerArgs &a, const SolveArgs &sa, int chunk_begin, int n_chunks,
-                    int n_cells, int64_t n_steps, void *stream);
+// slot 0.  a.halo_out (order 1: a.halo3_out) receives the halos of the final
+// state.
+bool resident_supported(int order, int n_chunks, int n_cells);
+int launch_resident(int prec, int order, bool seg, const TracerArgs &a, const SolveArgs &sa, int chunk_begin,
+                    int n_chunks, int n_cells, int64_t n_steps, void *stream);
 // With a.state the launches cover a.n_chunks chunks (the capacity) and read
 // the count from the device.
 int launch_refine_mark(int prec, const RefineArgs &a, void *stream);

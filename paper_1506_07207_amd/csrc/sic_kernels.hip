@@ -15,6 +15,8 @@
 //              at a time.
 //   k_resident a small simulation (up to 32 chunks) stepped many times in one
 //              launch of one workgroup: state in registers, mesh in LDS.
+//   k_step     a larger single simulation's step in one launch: every
+//              workgroup solves the previous step's charge for itself.
 //   k_solve    one workgroup per simulation: finishes the deposit (prefix sum
 //              of the covered-run difference array), removes the mean density,
 //              integrates Gauss's law for the face fields, averages them to
@@ -989,11 +991,10 @@ __device__ __forceinline__ void solve_take(const SlotConst &kc, Acc *gP, Acc *gD
 }
 
 // What the solve leaves for the diagnostics row: this thread's field energy
-// sum and its non-finite field values (threads of the first kSolveThreads),
-// and the total charge (every thread).
+// sum (threads of the first kSolveThreads; not finite when one of its field
+// values is not) and the total charge (every thread).
 struct FieldSums {
   double w2, Qtot;
-  int bad;
 };
 
 // The field of pv, dv (this thread's accumulators from solve_take) and the
@@ -1129,14 +1130,12 @@ __device__ __forceinline__ FieldSums solve_field(const SlotConst &kc, const T (&
   }
   __syncthreads();
   out.w2 = 0.0;
-  out.bad = 0;
   if (mine) {
     const double fmean = (sF[1][0] + sF[1][1] + sF[1][2] + sF[1][3]) / (double)nc;
 #pragma unroll
     for (int k = 0; k < CELLS; ++k)
       if ((k < per) && (j0 + k < nc)) F[k] -= fmean;
     double prevF = (tid == 0) ? sLastF[(nc - 1) / per] - fmean : sLastF[tid - 1] - fmean;
-    bool finite = true;
 #pragma unroll
     for (int k = 0; k < CELLS; ++k) {
       const int j = j0 + k;
@@ -1155,38 +1154,29 @@ __device__ __forceinline__ FieldSums solve_field(const SlotConst &kc, const T (&
           gR[j] = (Q[k] - qmean) / kc.dx;
         }
         out.w2 += e * e;
-        finite = finite && (e - e == 0.0);
       }
     }
-    out.bad = finite ? 0 : 1;
   }
   return out;
 }
 
-// Field energy and count of threads with non-finite field values, over the
-// workgroup (one barrier; the same bits in every thread).
-__device__ __forceinline__ void field_energy(const FieldSums &f, double dx, double *W, int *bad) {
+// Field energy over the workgroup (one barrier; the same bits in every thread).
+__device__ __forceinline__ double field_energy(const FieldSums &f, double dx) {
   __shared__ double sW[4];
-  __shared__ int sBad[4];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (wave < kSolveThreads / kChunk) {
     const double w = wave_sum(f.w2);
-    const int n = wave_sum(f.bad);
-    if ((threadIdx.x & 63) == 0) {
-      sW[wave] = w;
-      sBad[wave] = n;
-    }
+    if ((threadIdx.x & 63) == 0) sW[wave] = w;
   }
   __syncthreads();
-  *W = 0.5 * dx * (sW[0] + sW[1] + sW[2] + sW[3]);
-  *bad = sBad[0] + sBad[1] + sBad[2] + sBad[3];
+  return 0.5 * dx * (sW[0] + sW[1] + sW[2] + sW[3]);
 }
 
 // The sticky flags after a solve.
-__device__ __forceinline__ int solve_flags(int solve, int flags0, double L, double W, int bad, double ke, double mom,
+__device__ __forceinline__ int solve_flags(int solve, int flags0, double L, double W, double ke, double mom,
                                            double ms) {
   int f = 0;
-  if (bad || !(W - W == 0.0)) f |= 1;
+  if (!(W - W == 0.0)) f |= 1;
   // a move with a non-finite velocity (its kinetic energy or momentum)
   if ((solve & kHavePush) && !((ke - ke == 0.0) && (mom - mom == 0.0))) f |= 1;
   if (solve & kHaveDeposit) {
@@ -1364,12 +1354,82 @@ struct ChunkTab {
   LinNb before, after;
 };
 
+// The tables of a wavefront's chunks in registers, one chunk per lane: no
+// barrier between the wavefronts and no LDS round trip.
+template <int PREC, int ORDER, bool SEG>
+struct WaveTabs {
+  ChunkDesc d;
+  int2 lk;                 // order 1
+  uint64_t e0, e1;         // per-segment charges
+  uint64_t next;           // the moved tracers around the chunk (ChunkTab)
+  LinNb before, after;
+
+  __device__ __forceinline__ void load(const ChunkDesc *chunks, const int2 *links, const uint64_t *cedge, size_t c) {
+    d = chunks[c];
+    if constexpr (ORDER == 1) lk = links[c];
+    if constexpr (SEG) {
+      e0 = cedge[2 * c];
+      e1 = cedge[2 * c + 1];
+    }
+  }
+  // The halo copies around chunk c, from halos of the chunks from base on.
+  struct Halos {
+    double2 own, first, prev, next2;  // orders 0, 2: first alone
+  };
+  __device__ __forceinline__ Halos halos(const double2 *h, size_t c, int base) const {
+    Halos r;
+    const size_t lc = c - base;
+    const size_t pc = d.partner >= 0 ? (size_t)(d.partner - base) : lc;
+    if constexpr (ORDER == 1) {
+      auto at = [&](int l) { return l >= 0 ? 3 * (size_t)((l >> 2) - base) + (l & 3) : 3 * lc; };
+      r.own = h[3 * lc + kHaloFirst];
+      r.first = h[3 * pc + kHaloFirst];
+      r.prev = h[at(lk.x)];
+      r.next2 = h[at(lk.y)];
+    } else {
+      r.first = h[pc];
+    }
+    return r;
+  }
+  __device__ __forceinline__ void move(const Halos &h, const Geo &g, const double *sE) {
+    if constexpr (ORDER == 1) {
+      stage_linear<PREC, kPush | kDeposit, SEG>(g, sE, d.partner >= 0, lk.x >= 0, lk.y >= 0, h.own, h.first, h.prev,
+                                                h.next2, e0, e1, PREC == kFP64 ? d.q : (double)d.q_fix, &next,
+                                                &before, &after);
+    } else {
+      next = moved_halo<PREC, kPush | kDeposit>(h.first, g, sE);
+    }
+  }
+  // The entry of the wavefront's i-th chunk, from lane i.
+  __device__ __forceinline__ ChunkTab entry(int i) const {
+    auto f64 = [i](double x) {
+      return __longlong_as_double((long long)read_lane64((uint64_t)__double_as_longlong(x), i));
+    };
+    ChunkTab t;
+    t.d.q = f64(d.q);
+    t.d.q_fix = PREC == kFP64 || SEG ? 0 : (int64_t)read_lane64((uint64_t)d.q_fix, i);
+    t.d.partner = __builtin_amdgcn_readlane(d.partner, i);
+    t.d.n_valid = __builtin_amdgcn_readlane(d.n_valid, i);
+    t.d.flags = __builtin_amdgcn_readlane(d.flags, i);
+    t.edge = SEG ? read_lane64(e0, i) : 0;
+    t.next = read_lane64(next, i);
+    if constexpr (ORDER == 1) {
+      t.before.d = f64(before.d);
+      t.before.r = f64(before.r);
+      t.after.d = f64(after.d);
+      t.after.r = f64(after.r);
+    }
+    return t;
+  }
+};
+
 // One chunk of a work item: the move (or half kick) and the deposit of its
-// segments.  halo_out: orders 0, 2 one copy per chunk, order 1 three.
-template <int PREC, int MODE, int ORDER, bool SEG>
+// segments.  halo_out: orders 0, 2 one copy per chunk, order 1 three.  STORE
+// false: the moved state stays in xw and v.
+template <int PREC, int MODE, int ORDER, bool SEG, bool STORE = true>
 __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t, const Geo &g, double q_unit,
                                               uint64_t *xs, double *vs, double2 *halo_out, const ChunkTab &tab,
-                                              size_t chunk, int lane, uint64_t xw, double v, uint64_t cw, double &ke,
+                                              size_t chunk, int lane, uint64_t &xw, double &v, uint64_t cw, double &ke,
                                               double &mom, double &ms) {
   constexpr bool kLin = ORDER == 1;
   constexpr bool kDep = (MODE & kDeposit) != 0;
@@ -1412,8 +1472,10 @@ __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t
       const uint64_t xn = drift<PREC>(xw, vn, g.dt, g.L, g.inv_dx, g.nc);
       xw = valid ? xn : xw;
       v = valid ? vn : v;
-      __builtin_nontemporal_store(xw, xs + s);
-      __builtin_nontemporal_store(v, vs + s);
+      if constexpr (STORE) {
+        __builtin_nontemporal_store(xw, xs + s);
+        __builtin_nontemporal_store(v, vs + s);
+      }
     }
     const double2 hv2 = make_double2(__longlong_as_double((long long)xw), v);
     if constexpr (kLin) {
@@ -1774,7 +1836,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
   constexpr int kRep = single_rep(CELLS * kSolveThreads);
   constexpr int kPrefetch = 3;
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double sRow[5][4];  // workgroup 0: the row's sums by wavefront
+  __shared__ double sRow[4][4];  // workgroup 0: the row's sums by wavefront
   const ItemLds<PREC, ORDER, SEG> t(smem, a.nc, 0);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -1801,34 +1863,10 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
     nch = min(a.tile, a.n_chunks - i * a.tile);
   };
   // Lane i of wavefront w holds the tables of chunk w + i * waves, the i-th
-  // of the wavefront's (an item has at most 64 chunks per wavefront), until
-  // they are staged.
-  const int mine = wave + lane * nwaves;
-  ChunkDesc desc;
-  int2 lk = make_int2(-1, -1);
-  uint64_t e0 = 0, e1 = 0;
-  auto load_desc = [&]() {
-    const size_t c = (size_t)(cb + min(mine, nch - 1));
-    desc = a.chunks[c];
-    if constexpr (kLin) lk = a.links[c];
-    if constexpr (SEG) {
-      e0 = a.cedge[2 * c];
-      e1 = a.cedge[2 * c + 1];
-    }
-  };
-  double2 own, first, prev, next2;  // orders 0, 2: first alone
-  auto load_halos = [&]() {
-    const size_t c = (size_t)(cb + min(mine, nch - 1));
-    const size_t pc = desc.partner >= 0 ? (size_t)desc.partner : c;
-    if constexpr (kLin) {
-      own = a.halo_in[3 * c + kHaloFirst];
-      first = a.halo_in[3 * pc + kHaloFirst];
-      prev = a.halo_in[lk.x >= 0 ? 3 * (size_t)(lk.x >> 2) + (lk.x & 3) : 3 * c];
-      next2 = a.halo_in[lk.y >= 0 ? 3 * (size_t)(lk.y >> 2) + (lk.y & 3) : 3 * c];
-    } else {
-      first = a.halo_in[pc];
-    }
-  };
+  // of the wavefront's (an item has at most 64 chunks per wavefront).
+  WaveTabs<PREC, ORDER, SEG> tabs;
+  typename WaveTabs<PREC, ORDER, SEG>::Halos halos;
+  auto lane_chunk = [&]() { return (size_t)(cb + min(wave + lane * nwaves, nch - 1)); };
   uint64_t xr[kPrefetch], cr_[kPrefetch];
   double vr[kPrefetch];
   auto load_state = [&](int kk, uint64_t &xw, double &v, uint64_t &cw) {  // as in k_tracers
@@ -1845,43 +1883,10 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // the moved tracers around the wavefront's chunks, one chunk per lane
-  uint64_t next = 0;
-  LinNb before, after;
-  auto move_halos = [&]() {
-    if constexpr (kLin) {
-      stage_linear<PREC, kMode, SEG>(g, t.sE, desc.partner >= 0, lk.x >= 0, lk.y >= 0, own, first, prev, next2, e0, e1,
-                                     PREC == kFP64 ? desc.q : (double)desc.q_fix, &next, &before, &after);
-    } else {
-      next = moved_halo<PREC, kMode>(first, g, t.sE);
-    }
-  };
-  // the entry of the wavefront's i-th chunk, from lane i
-  auto read_f64 = [](double x, int i) {
-    return __longlong_as_double((long long)read_lane64((uint64_t)__double_as_longlong(x), i));
-  };
-  auto entry = [&](int i) {
-    ChunkTab tab;
-    tab.d.q = SEG && PREC == kFP64 ? 0.0 : read_f64(desc.q, i);
-    tab.d.q_fix = PREC == kFP64 || SEG ? 0 : (int64_t)read_lane64((uint64_t)desc.q_fix, i);
-    tab.d.partner = __builtin_amdgcn_readlane(desc.partner, i);
-    tab.d.n_valid = __builtin_amdgcn_readlane(desc.n_valid, i);
-    tab.d.flags = __builtin_amdgcn_readlane(desc.flags, i);
-    tab.edge = SEG ? read_lane64(e0, i) : 0;
-    tab.next = read_lane64(next, i);
-    if constexpr (kLin) {
-      tab.before.d = read_f64(before.d, i);
-      tab.before.r = read_f64(before.r, i);
-      tab.after.d = read_f64(after.d, i);
-      tab.after.r = read_f64(after.r, i);
-    }
-    return tab;
-  };
-
   range();
-  load_desc();
+  tabs.load(a.chunks, a.links, a.cedge, lane_chunk());
   __builtin_amdgcn_sched_barrier(0);
-  FieldSums fs = {0.0, 0.0, 0};
+  FieldSums fs = {0.0, 0.0};
   Partial pr[2];  // the row: the launch before's partials tid and tid + 256
   int64_t step0 = 0;
   int flags0 = 0;
@@ -1910,7 +1915,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
     };
     load_acc(min(tid, nc - 1));
     __builtin_amdgcn_sched_barrier(0);
-    load_halos();
+    halos = tabs.halos(a.halo_in, lane_chunk(), 0);
     load_first_states();
     if (row) {
       step0 = a.sf.inst[0].step;
@@ -1948,7 +1953,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
     for (int i = (int)blockIdx.x * a.zero_slice + tid; i < z1; i += nt) z[i] = (acc_t)0;
   } else {
     // the first step of a run: the field is in global memory
-    load_halos();
+    halos = tabs.halos(a.halo_in, lane_chunk(), 0);
     load_first_states();
     for (int j = tid; j < nc; j += nt) {
       const double e = a.meshE[j];
@@ -1968,13 +1973,13 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
     __syncthreads();  // the field, the cleared mesh
     double ke = 0.0, mom = 0.0, ms = 0.0;
     if (it >= 0) {
-      move_halos();
+      tabs.move(halos, g, t.sE);
       int i = 0;
       for (int k = wave; k < nch; k += kPrefetch * nwaves) {
 #pragma unroll
         for (int j = 0; j < kPrefetch; ++j) {
           if (k + j * nwaves < nch)
-            process_chunk<PREC, kMode, ORDER, SEG>(t, g, a.q_unit, a.xs, a.vs, a.halo_out, entry(i++),
+            process_chunk<PREC, kMode, ORDER, SEG>(t, g, a.q_unit, a.xs, a.vs, a.halo_out, tabs.entry(i++),
                                                    (size_t)(cb + k + j * nwaves), lane, xr[j], vr[j], cr_[j], ke, mom,
                                                    ms);
           load_state(k + (j + kPrefetch) * nwaves, xr[j], vr[j], cr_[j]);
@@ -1995,13 +2000,11 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
       if (tid + kSolveThreads < a.n_items) add(pr[1]);
       for (int i = tid + 2 * kSolveThreads; i < a.n_items; i += kSolveThreads) add(a.part_in[i]);
       const double w = wave_sum(fs.w2), k = wave_sum(pke), m = wave_sum(pmom), x = wave_max(pms);
-      const int bad = wave_sum(fs.bad);
       if (lane == 0) {
         sRow[0][wave] = w;
         sRow[1][wave] = k;
         sRow[2][wave] = m;
         sRow[3][wave] = x;
-        sRow[4][wave] = (double)bad;
       }
     }
     if (it >= 0) item_partial<kMode>(ke, mom, ms, t.sRed, a.part_out + it);
@@ -2011,8 +2014,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
       const double k = sRow[1][0] + sRow[1][1] + sRow[1][2] + sRow[1][3];
       const double m = sRow[2][0] + sRow[2][1] + sRow[2][2] + sRow[2][3];
       const double x = nan_max(nan_max(sRow[3][0], sRow[3][1]), nan_max(sRow[3][2], sRow[3][3]));
-      const int bad = (int)(sRow[4][0] + sRow[4][1] + sRow[4][2] + sRow[4][3]);
-      write_row(a.sf, 0, kc, step0, solve_flags(a.sf.flags, flags0, a.L, W, bad, k, m, x), W, fs.Qtot, k, m, x);
+      write_row(a.sf, 0, kc, step0, solve_flags(a.sf.flags, flags0, a.L, W, k, m, x), W, fs.Qtot, k, m, x);
     }
     if (it < 0) return;
     acc_t *out = reinterpret_cast<acc_t *>(a.acc_out) + (int64_t)(it % kRep) * nc;
@@ -2021,8 +2023,8 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
     it += (int)gridDim.x + it0;
     if (it >= a.n_items) break;
     range();
-    load_desc();
-    load_halos();
+    tabs.load(a.chunks, a.links, a.cedge, lane_chunk());
+    halos = tabs.halos(a.halo_in, lane_chunk(), 0);
     load_first_states();
     __syncthreads();
   }
@@ -2385,11 +2387,9 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(SolveArgs a) {
   acc_t *gRamp = (a.order == 1 && a.meshR) ? reinterpret_cast<acc_t *>(a.meshR) + kc.mesh_off : nullptr;
   const FieldSums f = solve_field<PREC, CELLS, REP>(kc, pv, dv, gRamp, a.rep_stride, (double *)nullptr, false,
                                                     a.meshE + kc.mesh_off, a.meshRho + kc.mesh_off);
-  double W;
-  int bad;
-  field_energy(f, kc.dx, &W, &bad);
+  const double W = field_energy(f, kc.dx);
   if (tid == 0)
-    write_row(a, slot, kc, Ip->step, solve_flags(a.flags, Ip->flags, kc.L, W, bad, ke, mom, ms), W, f.Qtot, ke, mom, ms);
+    write_row(a, slot, kc, Ip->step, solve_flags(a.flags, Ip->flags, kc.L, W, ke, mom, ms), W, f.Qtot, ke, mom, ms);
   acc_t *z = reinterpret_cast<acc_t *>(a.zero);
   for (int64_t i = tid; i < a.zero_words; i += kSolveThreads) z[i] = (acc_t)0;
 }
@@ -2398,24 +2398,32 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(SolveArgs a) {
 // Resident small simulation
 // ---------------------------------------------------------------------------
 // A simulation of at most kResidentChunks chunks runs many steps in one
-// launch of one workgroup: its tracers stay in registers (each of the W
-// wavefronts owns chunks w, w + W, ...), the mesh accumulators and the field in LDS, and
-// each step is push, deposit and solve separated by workgroup barriers.  The
-// arithmetic is that of the fused step (same move, same segment deposit,
-// same solve code), so only the order of the floating-point sums of the
-// deposit and of the kinetic-energy and momentum diagnostics can differ; the
-// split forms give the same bits.  Small simulations are latency-bound: this
-// replaces two kernel launches per step with one launch per call.
+// launch of one workgroup: its tracers stay in registers (wavefront w of NW
+// owns chunks w, w + NW, ...), the mesh accumulators, the field and the
+// chunks' halos in LDS.  The arithmetic is that of the fused step (same move,
+// same segment deposit, same solve code), so only the order of the
+// floating-point sums of the deposit and of the kinetic-energy and momentum
+// diagnostics can differ; the split forms give the same bits.  Such a
+// simulation is bound by the latency of one step's chain of dependent
+// operations and barriers, so what is not part of the chain is taken out of
+// it: the move and the deposit are one pass (every wavefront moves the
+// tracers that follow its chunks itself, from the halos of the step before,
+// instead of waiting for the others' moves), and one wavefront more holds no
+// tracers and reduces and writes the diagnostics rows while the others go on
+// with the next step.  Per step (before: two passes, rows in the chain,
+// constant segments only): 1024 tracers on 128 cells 4.8 -> 3.2 us, of which
+// 1.3 the solve; 1280 tracers, linear segments, 12.2 (launch pairs) -> 5.9.
 
 constexpr int kResidentChunks = 32;  // chunks (2048 tracer slots) a resident launch holds
 
-// P, D, E; then (16-byte aligned) descriptors, new first-tracer words and
-// charge edges
-__host__ __device__ constexpr size_t resident_desc_offset(int n_cells) {
-  return ((size_t)n_cells * 24 + 15) & ~(size_t)15;
+// The LDS mesh, field and sums (ItemLds), then two sets of halo copies.
+template <int ORDER>
+__host__ __device__ constexpr size_t resident_halo_offset(int n_cells) {
+  return (tracer_lds_bytes<double, ORDER, false>(n_cells, 0) + 15) & ~(size_t)15;
 }
-__host__ __device__ constexpr size_t resident_lds_bytes(int n_cells, bool seg) {
-  return resident_desc_offset(n_cells) + (size_t)kResidentChunks * (sizeof(ChunkDesc) + 8 + (seg ? 16 : 0));
+template <int ORDER>
+__host__ __device__ constexpr size_t resident_lds_bytes(int n_cells) {
+  return resident_halo_offset<ORDER>(n_cells) + (size_t)2 * kResidentChunks * (ORDER == 1 ? 3 : 1) * sizeof(double2);
 }
 
 // A workgroup barrier that orders LDS only: global stores in flight (the
@@ -2426,27 +2434,28 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int PREC, bool SEG, int CELLS, int NT>
-__global__ void __launch_bounds__(NT) k_resident(TracerArgs a, SolveArgs sa, int chunk_begin, int n_chunks,
-                                                 int64_t n_steps) {
+template <int PREC, int ORDER, bool SEG, int CELLS, int NW>
+__global__ void __launch_bounds__((NW + 1) * kChunk) k_resident(TracerArgs a, SolveArgs sa, int chunk_begin,
+                                                               int n_chunks, int64_t n_steps) {
   using acc_t = typename std::conditional<PREC == kFP64, double, unsigned long long>::type;
-  // NT / 64 wavefronts share the chunks (wave w takes w, w + waves, ...)
-  constexpr int kResidentWaves = NT / kChunk;
-  constexpr int kResidentPerWave = kResidentChunks / kResidentWaves;
+  using sacc_t = typename std::conditional<PREC == kFP64, double, long long>::type;
+  constexpr bool kLin = ORDER == 1;
+  constexpr int kMode = kPush | kDeposit;
+  constexpr int kPer = (kResidentChunks + NW - 1) / NW;  // chunks per wavefront
+  constexpr int kHalos = kLin ? 3 : 1;        // halo copies per chunk
+  constexpr int NT = (NW + 1) * kChunk;
+  static_assert(NW * kChunk >= kSolveThreads, "the solve's threads");
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double sRed[3 * kResidentWaves];
+  __shared__ double sW2[kSolveThreads];  // the solve threads' field energy sums
+  // the threads' kinetic energy and momentum sums and longest segments
+  __shared__ double sPart[3][NW * kChunk];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int slot = 0;
-  const InstDesc *Ip = a.inst + slot;
+  const InstDesc *Ip = a.inst;
   const int nc = Ip->n_cells;
-  acc_t *sP = reinterpret_cast<acc_t *>(smem);
-  acc_t *sD = sP + nc;
-  double *sE = reinterpret_cast<double *>(sD + nc);
-  ChunkDesc *sDesc = reinterpret_cast<ChunkDesc *>(smem + resident_desc_offset(nc));
-  uint64_t *sHx = reinterpret_cast<uint64_t *>(sDesc + kResidentChunks);
-  uint64_t *sEdge = sHx + kResidentChunks;  // per-segment charges
+  const ItemLds<PREC, ORDER, SEG> t(smem, nc, 0);
+  double2 *sHalo = reinterpret_cast<double2 *>(smem + resident_halo_offset<ORDER>(nc));  // two sets
   Geo g;
   g.L = Ip->L;
   g.half_L = Ip->half_L;
@@ -2454,32 +2463,35 @@ __global__ void __launch_bounds__(NT) k_resident(TracerArgs a, SolveArgs sa, int
   g.inv_dx = Ip->inv_dx;
   g.dt = Ip->dt;
   g.nc = nc;
-  const double q_unit = Ip->q_unit;
   const SlotConst kc = slot_const(*Ip);
-  int64_t step_now = Ip->step;
+  const int64_t step0 = Ip->step;
   int flags = Ip->flags;
+  const double2 *gHaloIn = kLin ? a.halo3_in : a.halo_in;
+  double2 *gHaloOut = kLin ? a.halo3_out : a.halo_out;
 
   for (int i = tid; i < nc; i += NT) {
-    sP[i] = (acc_t)0;
-    sD[i] = (acc_t)0;
-    sE[i] = a.meshE[Ip->mesh_off + i];
+    t.sP[i] = (acc_t)0;
+    t.sD[i] = (acc_t)0;
+    if constexpr (kLin) t.sR[i] = (acc_t)0;
+    const double e = a.meshE[kc.mesh_off + i];
+    t.sE[i] = e;
+    if (i == 0) t.sE[nc] = e;
+    if (i == nc - 1) t.sE[-1] = e;
   }
-  for (int i = tid; i < n_chunks; i += NT) {
-    sDesc[i] = a.chunks[chunk_begin + i];
-    if constexpr (SEG) {
-      sEdge[2 * i] = a.cedge[2 * (size_t)(chunk_begin + i)];
-      sEdge[2 * i + 1] = a.cedge[2 * (size_t)(chunk_begin + i) + 1];
-    }
-  }
-  // the wavefront's chunks, in registers for the whole launch
-  uint64_t xr[kResidentPerWave], cwr[kResidentPerWave];
-  double vr[kResidentPerWave];
+  for (int i = tid; i < kHalos * n_chunks; i += NT) sHalo[i] = gHaloIn[kHalos * (size_t)chunk_begin + i];
+  // the wavefront's chunks, in registers for the whole launch, and their
+  // tables, chunk w + i * NW in lane i
+  const size_t lane_chunk = (size_t)(chunk_begin + min(wave + lane * NW, n_chunks - 1));
+  WaveTabs<PREC, ORDER, SEG> tabs;
+  tabs.load(a.chunks, a.links, a.cedge, lane_chunk);
+  uint64_t xr[kPer], cwr[kPer];
+  double vr[kPer];
 #pragma unroll
-  for (int j = 0; j < kResidentPerWave; ++j) {
-    const int c = wave + j * kResidentWaves;
+  for (int j = 0; j < kPer; ++j) {
+    const int c = wave + j * NW;
     xr[j] = cwr[j] = 0;
     vr[j] = 0.0;
-    if (c < n_chunks) {
+    if (wave < NW && c < n_chunks) {
       const size_t sidx = (size_t)(chunk_begin + c) * kChunk + lane;
       xr[j] = a.xs[sidx];
       vr[j] = a.vs[sidx];
@@ -2488,114 +2500,76 @@ __global__ void __launch_bounds__(NT) k_resident(TracerArgs a, SolveArgs sa, int
   }
   __syncthreads();
 
+  // the row of the step before (the last wavefront's)
+  double rk = 0.0, rm = 0.0, rx = 0.0, rq = 0.0;
+  auto finish_row = [&](int64_t step) {
+    // in the order of field_energy
+    double w[kSolveThreads / kChunk];
+#pragma unroll
+    for (int i = 0; i < kSolveThreads / kChunk; ++i) w[i] = wave_sum(sW2[i * kChunk + lane]);
+    const double W = 0.5 * kc.dx * (w[0] + w[1] + w[2] + w[3]);
+    flags = solve_flags(sa.flags, flags, kc.L, W, rk, rm, rx);
+    if (lane == 0) write_row(sa, 0, kc, step0 + step, flags, W, rq, rk, rm, rx);
+  };
+
   for (int64_t step = 0; step < n_steps; ++step) {
-    // push: gather, kick, drift; the first tracer of each chunk is
-    // published for the segment that ends at it
-    double ke = 0.0, mom = 0.0, ms = 0.0;
+    const double2 *hin = sHalo + (step & 1) * (kHalos * kResidentChunks);
+    double2 *hout = sHalo + ((step & 1) ^ 1) * (kHalos * kResidentChunks);
+    if (wave < NW) {
+      double ke = 0.0, mom = 0.0, ms = 0.0;
+      tabs.move(tabs.halos(hin, lane_chunk, chunk_begin), g, t.sE);
 #pragma unroll
-    for (int j = 0; j < kResidentPerWave; ++j) {
-      const int c = wave + j * kResidentWaves;
-      if (c < n_chunks) {
-        const ChunkDesc &ch = sDesc[c];
-        const int n_valid = __builtin_amdgcn_readfirstlane(ch.n_valid);
-        const bool valid = lane < n_valid;
-        uint64_t xw = xr[j];
-        double v = vr[j];
-        const double e = gather_field(sE, mesh_pos<PREC>(xw, g.inv_dx), g.nc);
-        const double vn = v + g.dt * e;
-        double m;
-        if constexpr (SEG) {
-          const uint64_t up = lane_up1(cwr[j]);
-          m = tracer_mass<PREC>(lane == 0 ? sEdge[2 * c] : up, cwr[j], q_unit);
-        } else {
-          const bool end =
-              (lane == 0 && (ch.flags & kChunkOpenStart)) || (lane == n_valid - 1 && ch.partner < 0);
-          m = end ? 0.5 * ch.q : ch.q;
-        }
-        const double qv = valid ? m : 0.0;
-        ke += qv * v * vn;  // twice the kinetic energy and momentum, halved below
-        mom += qv * (v + vn);
-        const uint64_t xn = drift<PREC>(xw, vn, g.dt, g.L, g.inv_dx, g.nc);
-        xr[j] = valid ? xn : xw;
-        vr[j] = valid ? vn : v;
-        if (lane == 0) sHx[c] = xr[j];
+      for (int j = 0; j < kPer; ++j) {
+        const int c = wave + j * NW;
+        if (c < n_chunks)
+          process_chunk<PREC, kMode, ORDER, SEG, false>(t, g, kc.q_unit, nullptr, nullptr, hout, tabs.entry(j),
+                                                        (size_t)c, lane, xr[j], vr[j], cwr[j], ke, mom, ms);
       }
+      sPart[0][tid] = ke;
+      sPart[1][tid] = mom;
+      sPart[2][tid] = ms;
+    } else if (step > 0) {
+      finish_row(step - 1);
     }
-    lds_barrier();
-    // deposit of the moved segments into the LDS mesh
+    lds_barrier();  // the deposit is complete
+    if (wave == NW) {
+      rk = rm = rx = 0.0;
 #pragma unroll
-    for (int j = 0; j < kResidentPerWave; ++j) {
-      const int c = wave + j * kResidentWaves;
-      if (c < n_chunks) {
-        const ChunkDesc &ch = sDesc[c];
-        const int n_valid = __builtin_amdgcn_readfirstlane(ch.n_valid);
-        const uint64_t xw = xr[j];
-        uint64_t pw = lane_down1(xw);
-        bool has_seg = lane < n_valid;
-        if (lane == n_valid - 1) {
-          if (ch.partner < 0) has_seg = false;  // open sheet: the last tracer ends the chain
-          else pw = sHx[ch.partner - chunk_begin];
-        }
-        if (has_seg) {
-          double len;
-          if constexpr (PREC == kFP64) {
-            const double q0 = SEG ? __longlong_as_double((long long)cwr[j]) : ch.q;
-            len = deposit_fp64(__longlong_as_double((long long)xw), __longlong_as_double((long long)pw), q0, g,
-                               sP, sD);
-          } else {
-            const long long q0 = SEG ? (long long)cwr[j] : ch.q_fix;
-            len = deposit_split<PREC>(xw, pw, q0, g, sP, sD);
-          }
-          ms = nan_max(ms, len);
-        }
+      for (int w = 0; w < NW; ++w) {
+        rk += sPart[0][w * kChunk + lane];
+        rm += sPart[1][w * kChunk + lane];
+        rx = nan_max(rx, sPart[2][w * kChunk + lane]);
       }
+      rk = 0.5 * wave_sum(rk);
+      rm = 0.5 * wave_sum(rm);
+      rx = wave_max(rx);
     }
-    ke = wave_sum(ke);
-    mom = wave_sum(mom);
-    ms = wave_max(ms);
-    if (lane == 0) {
-      sRed[wave] = ke;
-      sRed[kResidentWaves + wave] = mom;
-      sRed[2 * kResidentWaves + wave] = ms;
-    }
-    lds_barrier();
-    ke = mom = ms = 0.0;
-    for (int w = 0; w < kResidentWaves; ++w) {
-      ke += sRed[w];
-      mom += sRed[kResidentWaves + w];
-      ms = nan_max(ms, sRed[2 * kResidentWaves + w]);
-    }
-    ke *= 0.5;
-    mom *= 0.5;
-    // solve (clears the accumulators, leaves the field in sE; in global
+    // solve (clears the accumulators, leaves the field in LDS; in global
     // memory too after the last step)
-    using sacc_t = typename std::conditional<PREC == kFP64, double, long long>::type;
     sacc_t pv[CELLS], dv[CELLS];
-    solve_take<PREC, CELLS, 1>(kc, sP, sD, 0, pv, dv);
+    if (wave < kSolveThreads / kChunk) solve_take<PREC, CELLS, 1>(kc, t.sP, t.sD, 0, pv, dv);
     const bool last = step == n_steps - 1;
-    const FieldSums f = solve_field<PREC, CELLS>(kc, pv, dv, (acc_t *)nullptr, 0, sE, false,
+    const FieldSums f = solve_field<PREC, CELLS>(kc, pv, dv, kLin ? t.sR : (acc_t *)nullptr, 0, t.sE, true,
                                                  last ? sa.meshE + kc.mesh_off : (double *)nullptr,
                                                  last ? sa.meshRho + kc.mesh_off : (double *)nullptr);
-    double W;
-    int bad;
-    field_energy(f, kc.dx, &W, &bad);
-    flags = solve_flags(sa.flags, flags, kc.L, W, bad, ke, mom, ms);
-    if (tid == 0) write_row(sa, slot, kc, step_now, flags, W, f.Qtot, ke, mom, ms);
-    step_now += 1;
-    lds_barrier();
+    rq = f.Qtot;
+    if (tid < kSolveThreads) sW2[tid] = f.w2;
+    lds_barrier();  // the field is complete
   }
+  if (wave == NW) finish_row(n_steps - 1);
 
-  // state and first-tracer halos back to global memory
+  // state and halos back to global memory
 #pragma unroll
-  for (int j = 0; j < kResidentPerWave; ++j) {
-    const int c = wave + j * kResidentWaves;
-    if (c < n_chunks) {
+  for (int j = 0; j < kPer; ++j) {
+    const int c = wave + j * NW;
+    if (wave < NW && c < n_chunks) {
       const size_t sidx = (size_t)(chunk_begin + c) * kChunk + lane;
       a.xs[sidx] = xr[j];
       a.vs[sidx] = vr[j];
-      if (lane == 0) a.halo_out[chunk_begin + c] = make_double2(__longlong_as_double((long long)xr[j]), vr[j]);
     }
   }
+  const double2 *hend = sHalo + (n_steps & 1) * (kHalos * kResidentChunks);
+  for (int i = tid; i < kHalos * n_chunks; i += NT) gHaloOut[kHalos * (size_t)chunk_begin + i] = hend[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -3198,24 +3172,28 @@ int launch_tracers(int prec, int mode, int order, bool seg, const TracerArgs &a,
   return (int)dispatch<LaunchTracers>(prec, order, seg, mode, a, grid, block, lds, (hipStream_t)stream);
 }
 
-// Meshes of up to 1024 cells run the resident kernel with 8 wavefronts (four
-// chunks each: twice the latency hiding of four; 16 wavefronts would leave
-// 128 VGPRs and spill); larger ones, whose solve holds 16 cells per thread
-// in registers, with four.
-template <int PREC, bool SEG, int CELLS>
+// Meshes of up to 1024 cells run the resident kernel with 12 wavefronts of
+// up to three chunks each and one for the rows (a pass of 100 steps of 32
+// chunks on 128 cells: 619 us; 8 wavefronts 692, 11 674, 15 651; of one chunk:
+// 424, and 409 with 8); larger ones, whose solve holds 16 cells per thread in
+// registers, with four (2 x 1000 tracers on 4096 cells, 100 steps: 1.69 ms,
+// 1.77 as solve-first launches) and, with a third array, not with linear
+// segments.
+template <int PREC, int ORDER, bool SEG, int CELLS>
 static hipError_t resident_launch(const TracerArgs &a, const SolveArgs &sa, int chunk_begin, int n_chunks,
-                                  int64_t n_steps, size_t lds, hipStream_t st) {
-  constexpr int NT = CELLS <= 4 ? 512 : kSolveThreads;
-  static bool limit_set = false;
-  if (!limit_set) {
-    const hipError_t e = hipFuncSetAttribute((const void *)k_resident<PREC, SEG, CELLS, NT>,
+                                  int n_cells, int64_t n_steps, hipStream_t st) {
+  constexpr int NW = CELLS <= 4 ? 12 : kSolveThreads / kChunk;
+  const size_t lds = resident_lds_bytes<ORDER>(n_cells);
+  static std::atomic<bool> limit_set{false};
+  if (!limit_set.load()) {
+    const hipError_t e = hipFuncSetAttribute((const void *)k_resident<PREC, ORDER, SEG, CELLS, NW>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)resident_lds_bytes(kMaxCells, true));
+                                             (int)resident_lds_bytes<ORDER>(CELLS * kSolveThreads));
     if (e != hipSuccess) return e;
-    limit_set = true;
+    limit_set.store(true);
   }
-  hipLaunchKernelGGL((k_resident<PREC, SEG, CELLS, NT>), dim3(1), dim3(NT), lds, st, a, sa, chunk_begin,
-                     n_chunks, n_steps);
+  hipLaunchKernelGGL((k_resident<PREC, ORDER, SEG, CELLS, NW>), dim3(1), dim3((NW + 1) * kChunk), lds, st, a, sa,
+                     chunk_begin, n_chunks, n_steps);
   return hipGetLastError();
 }
 
@@ -3225,38 +3203,31 @@ static int solve_cells(int max_cells) {
   return per <= 1 ? 1 : (per <= 4 ? 4 : 16);
 }
 
-template <int PREC, bool SEG>
-static hipError_t resident_prec(const TracerArgs &a, const SolveArgs &sa, int chunk_begin, int n_chunks,
-                                int n_cells, int64_t n_steps, size_t lds, hipStream_t st) {
-  switch (solve_cells(n_cells)) {
-    case 1: return resident_launch<PREC, SEG, 1>(a, sa, chunk_begin, n_chunks, n_steps, lds, st);
-    case 4: return resident_launch<PREC, SEG, 4>(a, sa, chunk_begin, n_chunks, n_steps, lds, st);
-    default: return resident_launch<PREC, SEG, 16>(a, sa, chunk_begin, n_chunks, n_steps, lds, st);
+template <int PREC, int ORDER, bool SEG>
+struct LaunchResident {
+  static hipError_t run(const TracerArgs &a, const SolveArgs &sa, int chunk_begin, int n_chunks, int n_cells,
+                        int64_t n_steps, hipStream_t st) {
+    switch (solve_cells(n_cells)) {
+      case 1: return resident_launch<PREC, ORDER, SEG, 1>(a, sa, chunk_begin, n_chunks, n_cells, n_steps, st);
+      case 4: return resident_launch<PREC, ORDER, SEG, 4>(a, sa, chunk_begin, n_chunks, n_cells, n_steps, st);
+      default:
+        if constexpr (ORDER != 1)
+          return resident_launch<PREC, ORDER, SEG, 16>(a, sa, chunk_begin, n_chunks, n_cells, n_steps, st);
+        return hipErrorInvalidValue;
+    }
   }
+};
+
+bool resident_supported(int order, int n_chunks, int n_cells) {
+  return n_chunks >= 1 && n_chunks <= kResidentChunks && step_supported(order, n_cells);
 }
 
-int resident_max_chunks() { return kResidentChunks; }
-
-int launch_resident(int prec, bool seg, const TracerArgs &a, const SolveArgs &sa, int chunk_begin, int n_chunks,
-                    int n_cells, int64_t n_steps, void *stream) {
+int launch_resident(int prec, int order, bool seg, const TracerArgs &a, const SolveArgs &sa, int chunk_begin,
+                    int n_chunks, int n_cells, int64_t n_steps, void *stream) {
   if (n_steps <= 0) return 0;
-  if (n_chunks < 1 || n_chunks > kResidentChunks || n_cells < 1 || n_cells > kMaxCells)
-    return (int)hipErrorInvalidValue;
-  const size_t lds = resident_lds_bytes(n_cells, seg);
-  hipStream_t st = (hipStream_t)stream;
-  switch (prec) {
-    case kFP64:
-      return (int)(seg ? resident_prec<kFP64, true>(a, sa, chunk_begin, n_chunks, n_cells, n_steps, lds, st)
-                       : resident_prec<kFP64, false>(a, sa, chunk_begin, n_chunks, n_cells, n_steps, lds, st));
-    case kSplitF32:
-      return (int)(seg ? resident_prec<kSplitF32, true>(a, sa, chunk_begin, n_chunks, n_cells, n_steps, lds, st)
-                       : resident_prec<kSplitF32, false>(a, sa, chunk_begin, n_chunks, n_cells, n_steps, lds, st));
-    case kSplitU32:
-      return (int)(seg ? resident_prec<kSplitU32, true>(a, sa, chunk_begin, n_chunks, n_cells, n_steps, lds, st)
-                       : resident_prec<kSplitU32, false>(a, sa, chunk_begin, n_chunks, n_cells, n_steps, lds, st));
-    default:
-      return (int)hipErrorInvalidValue;
-  }
+  if (!resident_supported(order, n_chunks, n_cells)) return (int)hipErrorInvalidValue;
+  return (int)dispatch<LaunchResident>(prec, order, seg, a, sa, chunk_begin, n_chunks, n_cells, n_steps,
+                                       (hipStream_t)stream);
 }
 
 template <int CELLS, int REP>
