@@ -42,6 +42,8 @@ constexpr int kDefaultBatchBlock = 512;  // batches
 constexpr int kDefaultBatchTile = 256;   // chunks per batch work item (16k tracers per LDS mesh merge)
 constexpr int kLinearBatchTile = 192;    // piecewise-linear segments: three workgroups per CU in LDS
 // (batch defaults: the autotuner's choice on the 4096-instance mixed batch)
+constexpr int kBatchItems = 3072;        // work items a batch's arena is cut into at least (slot_tile)
+constexpr int kMinBatchTile = 48;
 constexpr int kMinTile = 4;             // chunks per work item, lower bound
 constexpr int kMaxTile = 256;
 
@@ -408,7 +410,13 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
 }
 
 // Work-item size in chunks for a slot of n_chunks chunks.  A batch uses one
-// size for every slot; a single simulation sizes its items to give the
+// size for every slot: its default, or, where a batch's whole arena is fewer
+// than kBatchItems such items (12 per compute unit), the size that gives it
+// that many, down to kMinBatchTile (a smaller item merges its mesh for too few
+// tracers).  Large items leave compute units idle in the last round: us per
+// step with 256 chunks and with this rule's size, 3 simulations of 10900
+// chunks in all 44 -> 19, 14 of 81000 60 -> 48, 16 of 95000 65 -> 57; 96 of
+// 508000, 222, keep 256.  A single simulation sizes its items to give the
 // machine about 2048 of them, up to the largest item (fewer, larger items
 // spend less on zeroing and merging the item's LDS mesh).  An item clears
 // and scans its whole LDS mesh, and once a sheet has folded over the box it
@@ -423,7 +431,10 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
 int slot_tile(const Pool *p, int64_t n_chunks, bool cap_items = true) {
   if (p->tune.tile_chunks > 0) return std::max(kMinTile, std::min(kMaxTile, (int)p->tune.tile_chunks));
   const int wave_min = p->block / kChunk;
-  if (p->batch) return std::max(p->order == 1 ? kLinearBatchTile : kDefaultBatchTile, wave_min);
+  if (p->batch) {
+    const int64_t fit = std::max<int64_t>(kMinBatchTile, (p->chunk_cap / kBatchItems + 7) / 8 * 8);
+    return std::max((int)std::min<int64_t>(fit, p->order == 1 ? kLinearBatchTile : kDefaultBatchTile), wave_min);
+  }
   const int64_t per = (n_chunks + 2047) / 2048;
   const int64_t mesh_min = (4 * (int64_t)p->max_cells + kChunk - 1) / kChunk;
   const int64_t max_items = std::max<int64_t>(256, (int64_t)p->max_cells * p->rep / 2);
