@@ -112,8 +112,8 @@ struct SlotHost {
   int32_t n_chunks_res = 0;  // chunks reserved from chunk_begin (room to grow by refinement)
   int32_t item_begin = 0, n_items = 0;
   std::vector<int64_t> chunk_in_off;
-  int64_t *d_in_off = nullptr;
   int state = kStale;
+  int64_t step = 0;  // a single simulation's step (a batch's slots count theirs on the device)
   // the step the diagnostics history starts at: 0, or the step a state was
   // set or loaded at (rows before it were never written by this simulation)
   int64_t hist_from = 0;
@@ -143,6 +143,7 @@ struct Pool {
   double2 *halo3[2] = {nullptr, nullptr};  // order 1
   int2 *links = nullptr;
   ChunkDesc *chunks = nullptr;
+  int64_t *in_off = nullptr;     // per chunk: first index in its slot's flat inputs and outputs
   Item *items = nullptr;
   int32_t *n_items = nullptr;
   InstDesc *inst = nullptr;
@@ -185,7 +186,13 @@ struct Pool {
   void *sf_mesh = nullptr;     // acc_words each
   Partial *sf_part = nullptr;  // item_cap
 
+  // host memory that the device writes a call's results to (allocated on
+  // first use), room for pin_rows history rows
+  unsigned char *pin = nullptr;
+  int64_t pin_rows = 0;
+
   std::vector<SlotHost> slots;
+  std::vector<Item> items_up;  // work items being uploaded
   ChunkAllocator alloc;       // tracer chunks
   ChunkAllocator item_alloc;  // work items
   std::vector<int2> slot_items_h;
@@ -282,17 +289,16 @@ void pool_free(Pool *p) {
   if (!p) return;
   hipStreamSynchronize(p->stream);  // teardown: nothing to report an error to
   destroy_graphs(p);
-  for (auto &s : p->slots)
-    if (s.d_in_off) hipFree(s.d_in_off);
   void *bufs[] = {p->xs,        p->vs,       p->halo[0],  p->halo[1],  p->halo3[0],  p->halo3[1],
                   p->links,     p->chunks,   p->items,    p->n_items,  p->inst,      p->slot_items,
                   p->partials,  p->meshP,    p->meshE,    p->meshRho,
                   p->hist,      p->done,     p->slot_ids, p->segq,     p->cedge,     p->edge_prev,
                   p->ref_cnt,   p->ref_mask, p->ref_off,  p->ref_w,    p->ref_v,     p->ref_c,
                   p->dr_nt,     p->dr_closed, p->dr_q,    p->dr_work,  p->dr_state,  p->dr_in_off,
-                  p->sf_mesh,   p->sf_part};
+                  p->sf_mesh,   p->sf_part,  p->in_off};
   for (void *b : bufs)
     if (b) hipFree(b);
+  if (p->pin) hipHostFree(p->pin);
   if (p->cap) hipStreamDestroy(p->cap);
   delete p;
 }
@@ -345,6 +351,7 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
     ALLOC(p->halo3[1], 3 * (size_t)chunk_cap);
   }
   ALLOC(p->chunks, (size_t)chunk_cap);
+  ALLOC(p->in_off, (size_t)chunk_cap);
   if (seg) {
     ALLOC(p->segq, slotsz);
     ALLOC(p->cedge, 2 * (size_t)chunk_cap);
@@ -494,16 +501,18 @@ void update_solve_grid(Pool *p) {
 }
 
 // Uploads the device-side item count (the high-water mark of the item arena).
-sic_status upload_item_count(Pool *p) {
+// wait false: the caller waits for the stream before it changes the layout
+// again.
+sic_status upload_item_count(Pool *p, bool wait = true) {
   p->n_items_h = (int32_t)p->item_alloc.used_end(p->item_cap);
   HIPCHK(p, hipMemcpyAsync(p->n_items, &p->n_items_h, sizeof(int32_t), hipMemcpyHostToDevice, p->stream));
-  HIPCHK(p, hipStreamSynchronize(p->stream));
+  if (wait) HIPCHK(p, hipStreamSynchronize(p->stream));
   apply_launch_shape(p);
   return SIC_OK;
 }
 
 // Lays out the work items of one slot in the item arena and uploads them.
-sic_status place_slot_items(Pool *p, int32_t slot) {
+sic_status place_slot_items(Pool *p, int32_t slot, bool wait = true) {
   SlotHost &s = p->slots[slot];
   p->dr_items = false;
   const int tile = slot_tile(p, s.n_chunks);
@@ -511,7 +520,8 @@ sic_status place_slot_items(Pool *p, int32_t slot) {
   const int32_t n = (s.n_chunks + tile - 1) / tile;
   const int64_t ib = p->item_alloc.alloc(n);
   if (ib < 0) return fail(p, SIC_EBUSY, "work-item arena full");
-  std::vector<Item> its((size_t)n);
+  std::vector<Item> &its = p->items_up;
+  its.resize((size_t)n);
   for (int32_t k = 0; k < n; ++k) {
     its[k].inst = slot;
     its[k].chunk_begin = s.chunk_begin + k * tile;
@@ -524,21 +534,20 @@ sic_status place_slot_items(Pool *p, int32_t slot) {
   HIPCHK(p, hipMemcpyAsync(p->items + ib, its.data(), sizeof(Item) * (size_t)n, hipMemcpyHostToDevice, p->stream));
   HIPCHK(p, hipMemcpyAsync(p->slot_items + slot, &p->slot_items_h[slot], sizeof(int2), hipMemcpyHostToDevice,
                            p->stream));
-  return upload_item_count(p);
+  return upload_item_count(p, wait);
 }
 
 // Marks a slot's items dead (the kernels skip them) and frees their range.
-sic_status clear_slot_items(Pool *p, int32_t slot) {
+sic_status clear_slot_items(Pool *p, int32_t slot) {  // waits for the stream
   SlotHost &s = p->slots[slot];
   if (s.n_items > 0) {
-    std::vector<Item> dead((size_t)s.n_items);
-    for (auto &it : dead) {
-      it.inst = -1;
-      it.chunk_begin = it.chunk_end = it.pad = 0;
-    }
+    Item none;
+    none.inst = -1;
+    none.chunk_begin = none.chunk_end = none.pad = 0;
+    std::vector<Item> &dead = p->items_up;
+    dead.assign((size_t)s.n_items, none);
     HIPCHK(p, hipMemcpyAsync(p->items + s.item_begin, dead.data(), sizeof(Item) * dead.size(), hipMemcpyHostToDevice,
                              p->stream));
-    HIPCHK(p, hipStreamSynchronize(p->stream));
     p->item_alloc.release(s.item_begin, s.n_items);
   }
   s.item_begin = 0;
@@ -1166,20 +1175,13 @@ void build_layout(int32_t slot, int64_t cb, const std::vector<int32_t> &nt, cons
 }
 
 // Uploads a layout for chunks [cb, cb + n) of a slot (ordered on the stream).
-hipError_t upload_layout(Pool *p, SlotHost &sh, int64_t cb, const Layout &L) {
+hipError_t upload_layout(Pool *p, int64_t cb, const Layout &L) {
   const size_t n = L.cd.size();
-  hipError_t e = hipSuccess;
-  if (sh.d_in_off) hipFree(sh.d_in_off);
-  sh.d_in_off = nullptr;
-  e = hipMalloc((void **)&sh.d_in_off, sizeof(int64_t) * std::max<size_t>(n, 1));
-  if (e != hipSuccess) {
-    sh.d_in_off = nullptr;
-    return e;
-  }
-  e = hipMemcpyAsync(p->chunks + cb, L.cd.data(), sizeof(ChunkDesc) * n, hipMemcpyHostToDevice, p->stream);
+  hipError_t e =
+      hipMemcpyAsync(p->chunks + cb, L.cd.data(), sizeof(ChunkDesc) * n, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(sh.d_in_off, L.in_off.data(), sizeof(int64_t) * n, hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess)
+    e = hipMemcpyAsync(p->in_off + cb, L.in_off.data(), sizeof(int64_t) * n, hipMemcpyHostToDevice, p->stream);
+  if (e == hipSuccess && p->order == 1)
     e = hipMemcpyAsync(p->links + cb, L.links.data(), sizeof(int2) * n, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess && p->seg)
     e = hipMemcpyAsync(p->edge_prev + cb, L.prev.data(), sizeof(int64_t) * n, hipMemcpyHostToDevice, p->stream);
@@ -1201,7 +1203,7 @@ int ingest_slot(Pool *p, int32_t slot, const double *x, const uint64_t *w, const
   ia.cw_in = cw;
   ia.segq = keep_charges ? nullptr : p->segq;
   ia.q_scale = sh.q_scale;
-  ia.chunk_in_off = sh.d_in_off;
+  ia.chunk_in_off = p->in_off + sh.chunk_begin;
   ia.chunk_begin = sh.chunk_begin;
   ia.n_chunks = sh.n_chunks;
   ia.chunks = p->chunks;
@@ -1313,6 +1315,7 @@ sic_status pool_admit(Pool *p, const sic_config *cfg, const sic_sheet *sheets, i
   sh.l_max = cfg->l_max;
   sh.max_tracers = reserve_tr;
   sh.hist_from = 0;
+  sh.step = 0;
   sh.chunk_begin = (int32_t)cb;
   sh.n_chunks = (int32_t)n_ch;
   sh.n_chunks_res = (int32_t)n_res;
@@ -1339,12 +1342,14 @@ sic_status pool_admit(Pool *p, const sic_config *cfg, const sic_sheet *sheets, i
   I.live = 1;
 
   auto undo = [&]() {
+    (void)hipStreamSynchronize(p->stream);  // copies in flight read host memory that is reused
     if (sh.n_items > 0) clear_slot_items(p, slot);
     p->alloc.release(cb, n_res);
     sh.live = false;
     sh.chunk_in_off.clear();
   };
-  st = place_slot_items(p, slot);
+  // the copies below are waited for together, at the end
+  st = place_slot_items(p, slot, false);
   if (st != SIC_OK) {
     undo();
     return st;
@@ -1368,13 +1373,12 @@ sic_status pool_admit(Pool *p, const sic_config *cfg, const sic_sheet *sheets, i
     dc0 = c0 ? stage + 2 * n_tr : nullptr;
   }
   const int32_t zero = 0;
-  if (e == hipSuccess) e = upload_layout(p, sh, cb, L);
+  if (e == hipSuccess) e = upload_layout(p, cb, L);
   if (e == hipSuccess) e = hipMemcpyAsync(p->inst + slot, &I, sizeof(I), hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(p->done + slot, &zero, sizeof(zero), hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
   if (e != hipSuccess) {
-    if (stage) hipFree(stage);
     undo();
+    if (stage) hipFree(stage);
     return fail(p, SIC_EDEVICE, std::string("admission copies: ") + hipGetErrorString(e));
   }
   p->used_tracers += reserve_tr;
@@ -1385,6 +1389,7 @@ sic_status pool_admit(Pool *p, const sic_config *cfg, const sic_sheet *sheets, i
   if (le == 0) le = launch_zero_mesh(p->prec, p->meshP, p->meshD, p->meshR, p->inst, p->slot_ids + slot, 1, p->rep,
                                          mesh_words(p), p->stream);
   if (le != 0) {
+    (void)hipStreamSynchronize(p->stream);
     if (stage) hipFree(stage);
     return fail(p, SIC_EDEVICE, std::string("ingest: ") + hipGetErrorString((hipError_t)le));
   }
@@ -1430,18 +1435,12 @@ sic_status pool_relayout(Pool *p, int32_t slot, const std::vector<int32_t> &nt, 
   // captured graphs carry the tile (LDS size) and grid of their capture, a
   // single simulation's solve-first ones its chunk and item counts too
   if (!p->batch || p->tile != tile0 || p->grid != grid0) destroy_graphs(p);
-  hipError_t e = upload_layout(p, sh, cb, L);
-  if (e == hipSuccess && step >= 0) {
-    InstDesc I;
-    e = hipMemcpyAsync(&I, p->inst + slot, sizeof(I), hipMemcpyDeviceToHost, p->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
-    I.step = step;
-    if (e == hipSuccess) e = hipMemcpyAsync(p->inst + slot, &I, sizeof(I), hipMemcpyHostToDevice, p->stream);
-  }
+  hipError_t e = upload_layout(p, cb, L);
+  if (step >= 0) sh.step = step;
   if (e != hipSuccess) return fail(p, SIC_EDEVICE, std::string("re-layout copies: ") + hipGetErrorString(e));
   int le = ingest_slot(p, slot, x, w, v, c, cw);
   if (le == 0) le = launch_zero_mesh(p->prec, p->meshP, p->meshD, p->meshR, p->inst, p->slot_ids + slot, 1, p->rep,
-                                         mesh_words(p), p->stream);
+                                         mesh_words(p), p->stream, step);
   if (le != 0) return fail(p, SIC_EDEVICE, std::string("re-layout ingest: ") + hipGetErrorString((hipError_t)le));
   sh.pending_push = sh.pending_dep = false;
   if (redeposit) {
@@ -1550,7 +1549,6 @@ sic_status pool_release(Pool *p, int32_t slot) {
   InstDesc I;
   std::memset(&I, 0, sizeof(I));
   HIPCHK(p, hipMemcpyAsync(p->inst + slot, &I, sizeof(I), hipMemcpyHostToDevice, p->stream));
-  HIPCHK(p, hipStreamSynchronize(p->stream));
   sic_status st = clear_slot_items(p, slot);
   if (st != SIC_OK) return st;
   p->alloc.release(sh.chunk_begin, sh.n_chunks_res);
@@ -1559,10 +1557,6 @@ sic_status pool_release(Pool *p, int32_t slot) {
   sh.live = false;
   update_solve_grid(p);
   sh.chunk_in_off.clear();
-  if (sh.d_in_off) {
-    hipFree(sh.d_in_off);
-    sh.d_in_off = nullptr;
-  }
   return SIC_OK;
 }
 
@@ -1572,37 +1566,80 @@ sic_status read_inst(Pool *p, int32_t slot, InstDesc *I) {
   return SIC_OK;
 }
 
+// History rows that the block of host memory for a call's results holds.
+constexpr int64_t kPinRows = 1024;
+
+sic_status ensure_pin(Pool *p) {
+  if (p->pin) return SIC_OK;
+  const int64_t rows = std::min(p->hist_rows, kPinRows);
+  void *ptr = nullptr;
+  HIPCHK(p, hipHostMalloc(&ptr, kExportMesh + 2 * sizeof(double) * p->max_cells + sizeof(DiagRow) * (size_t)rows,
+                          hipHostMallocDefault));
+  p->pin = static_cast<unsigned char *>(ptr);
+  p->pin_rows = rows;
+  return SIC_OK;
+}
+
+// A slot's descriptor, newest row, mesh (with mesh) and up to rows history
+// rows into p->pin; waits for the stream.
+sic_status export_slot(Pool *p, int32_t slot, bool mesh, int64_t rows, InstDesc *I) {
+  sic_status st = ensure_pin(p);
+  if (st != SIC_OK) return st;
+  const int64_t mesh_off = (int64_t)slot * p->max_cells;
+  ExportArgs a;
+  a.inst = p->inst + slot;
+  a.hist = p->hist + (int64_t)slot * p->hist_rows;
+  a.rho = mesh ? p->meshRho + mesh_off : nullptr;
+  a.E = mesh ? p->meshE + mesh_off : nullptr;
+  a.nc = mesh ? p->slots[slot].n_cells : 0;
+  a.hist_from = p->slots[slot].hist_from;
+  a.max_rows = std::min(rows, p->pin_rows);
+  a.out = p->pin;
+  LAUNCHCHK(p, launch_export(a, p->stream));
+  HIPCHK(p, hipStreamSynchronize(p->stream));
+  std::memcpy(I, p->pin, sizeof(*I));
+  return SIC_OK;
+}
+
+int64_t history_avail(const Pool *p, int32_t slot, int64_t step) {
+  return std::min<int64_t>(step + 1 - std::min(step, p->slots[slot].hist_from), p->hist_rows);
+}
+
 sic_status pool_diagnostics(Pool *p, int32_t slot, sic_diag *out, double *rho_out, double *E_out,
                             sic_diag *history_out, int64_t *history_len) {
   if (slot < 0 || slot >= p->slot_cap || !p->slots[slot].live) return fail(p, SIC_EINVAL, "slot not live");
+  if (!p->batch && !out && !rho_out && !E_out && history_len && !history_out) {
+    *history_len = history_avail(p, slot, p->slots[slot].step);
+    return SIC_OK;
+  }
   InstDesc I;
-  sic_status st = read_inst(p, slot, &I);
+  const bool mesh = rho_out || E_out;
+  sic_status st = export_slot(p, slot, mesh, history_len && history_out ? std::max<int64_t>(*history_len, 0) : 0, &I);
   if (st != SIC_OK) return st;
   const int64_t step = I.step;
   const int64_t cap = I.hist_cap;
-  const int64_t avail = std::min<int64_t>(step + 1 - std::min(step, p->slots[slot].hist_from), cap);
-  const DiagRow *H = p->hist + I.hist_off;
-  if (out) {
-    DiagRow r;
-    HIPCHK(p, hipMemcpy(&r, H + step % cap, sizeof(r), hipMemcpyDeviceToHost));
-    static_assert(sizeof(DiagRow) == sizeof(sic_diag), "row layout");
-    std::memcpy(out, &r, sizeof(r));
-  }
-  const int nc = p->slots[slot].n_cells;
-  if (rho_out) HIPCHK(p, hipMemcpy(rho_out, p->meshRho + I.mesh_off, sizeof(double) * nc, hipMemcpyDeviceToHost));
-  if (E_out) HIPCHK(p, hipMemcpy(E_out, p->meshE + I.mesh_off, sizeof(double) * nc, hipMemcpyDeviceToHost));
+  const int64_t avail = history_avail(p, slot, step);
+  const size_t nc = (size_t)p->slots[slot].n_cells;
+  static_assert(sizeof(DiagRow) == sizeof(sic_diag), "row layout");
+  if (out) std::memcpy(out, p->pin + kExportRow, sizeof(*out));
+  if (rho_out) std::memcpy(rho_out, p->pin + kExportMesh, sizeof(double) * nc);
+  if (E_out) std::memcpy(E_out, p->pin + kExportMesh + sizeof(double) * nc, sizeof(double) * nc);
   if (history_len) {
     if (history_out) {
-      const int64_t want = std::min<int64_t>(*history_len, avail);
       // the newest `want` rows, oldest first
-      std::vector<DiagRow> all((size_t)avail);
-      const int64_t first = step + 1 - avail;
-      const int64_t r0 = first % cap;
-      const int64_t n1 = std::min<int64_t>(avail, cap - r0);
-      HIPCHK(p, hipMemcpy(all.data(), H + r0, sizeof(DiagRow) * (size_t)n1, hipMemcpyDeviceToHost));
-      if (n1 < avail)
-        HIPCHK(p, hipMemcpy(all.data() + n1, H, sizeof(DiagRow) * (size_t)(avail - n1), hipMemcpyDeviceToHost));
-      std::memcpy(history_out, all.data() + (avail - want), sizeof(DiagRow) * (size_t)want);
+      const int64_t want = std::min<int64_t>(*history_len, avail);
+      if (want <= p->pin_rows) {
+        if (want > 0)
+          std::memcpy(history_out, p->pin + kExportMesh + (mesh ? 2 * sizeof(double) * nc : 0),
+                      sizeof(DiagRow) * (size_t)want);
+      } else {
+        const DiagRow *H = p->hist + I.hist_off;
+        const int64_t r0 = (step + 1 - want) % cap;
+        const int64_t n1 = std::min<int64_t>(want, cap - r0);
+        HIPCHK(p, hipMemcpy(history_out, H + r0, sizeof(DiagRow) * (size_t)n1, hipMemcpyDeviceToHost));
+        if (n1 < want)
+          HIPCHK(p, hipMemcpy(history_out + n1, H, sizeof(DiagRow) * (size_t)(want - n1), hipMemcpyDeviceToHost));
+      }
       *history_len = want;
     } else {
       *history_len = avail;
@@ -1621,7 +1658,7 @@ sic_status pool_get_state(Pool *p, int32_t slot, double *x, double *v, int64_t *
     dv = stage + sh.n_tracers;
   }
   ExtractArgs ea;
-  ea.chunk_in_off = sh.d_in_off;
+  ea.chunk_in_off = p->in_off + sh.chunk_begin;
   ea.chunk_begin = sh.chunk_begin;
   ea.n_chunks = sh.n_chunks;
   ea.chunks = p->chunks;
@@ -1633,20 +1670,22 @@ sic_status pool_get_state(Pool *p, int32_t slot, double *x, double *v, int64_t *
   ea.v_out = dv;
   ea.c_out = nullptr;
   int le = launch_extract(p->prec, ea, p->stream);
-  hipError_t e = hipStreamSynchronize(p->stream);
+  sic_status st = SIC_OK;
+  if (step && p->batch) {  // a batch's slots count their steps on the device
+    InstDesc I;
+    st = export_slot(p, slot, false, 0, &I);
+    if (st == SIC_OK) *step = I.step;
+  }
+  hipError_t e = (step && p->batch && st == SIC_OK) ? hipSuccess : hipStreamSynchronize(p->stream);
   if (le == 0 && e == hipSuccess && stage && x)
     e = hipMemcpy(x, dx, sizeof(double) * (size_t)sh.n_tracers, hipMemcpyDeviceToHost);
   if (le == 0 && e == hipSuccess && stage && v)
     e = hipMemcpy(v, dv, sizeof(double) * (size_t)sh.n_tracers, hipMemcpyDeviceToHost);
   if (stage) hipFree(stage);
   if (le != 0) return fail(p, SIC_EDEVICE, std::string("extract: ") + hipGetErrorString((hipError_t)le));
+  if (st != SIC_OK) return st;
   if (e != hipSuccess) return fail(p, SIC_EDEVICE, std::string("get_state: ") + hipGetErrorString(e));
-  if (step) {
-    InstDesc I;
-    sic_status st = read_inst(p, slot, &I);
-    if (st != SIC_OK) return st;
-    *step = I.step;
-  }
+  if (step && !p->batch) *step = sh.step;
   return SIC_OK;
 }
 
@@ -1672,7 +1711,7 @@ sic_status pool_get_charges(Pool *p, int32_t slot, double *c, int32_t mem_kind) 
   double *stage = nullptr;
   HIPCHK(p, hipMalloc((void **)&stage, sizeof(double) * 3 * std::max<size_t>(n, 1)));
   ExtractArgs ea;
-  ea.chunk_in_off = sh.d_in_off;
+  ea.chunk_in_off = p->in_off + sh.chunk_begin;
   ea.chunk_begin = sh.chunk_begin;
   ea.n_chunks = sh.n_chunks;
   ea.chunks = p->chunks;
@@ -1744,10 +1783,6 @@ sic_status pool_set_state(Pool *p, int32_t slot, int64_t step, const double *x, 
   SlotHost &sh = p->slots[slot];
   if (mem_kind == SIC_MEM_HOST && (!all_finite_host(x, sh.n_tracers) || !all_finite_host(v, sh.n_tracers)))
     return fail(p, SIC_EINVAL, "non-finite state");
-  InstDesc I;
-  sic_status st = read_inst(p, slot, &I);
-  if (st != SIC_OK) return st;
-  I.step = step;
   double *stage = nullptr;  // allocated here (freed below)
   const double *dx = x, *dv = v;
   if (mem_kind == SIC_MEM_HOST) {
@@ -1761,15 +1796,15 @@ sic_status pool_set_state(Pool *p, int32_t slot, int64_t step, const double *x, 
     dx = buf;
     dv = buf + sh.n_tracers;
   }
-  hipError_t e = hipMemcpyAsync(p->inst + slot, &I, sizeof(I), hipMemcpyHostToDevice, p->stream);
   // positions and velocities only: the layout and the charges stay
-  int le = (e == hipSuccess) ? ingest_slot(p, slot, dx, nullptr, dv, nullptr, nullptr, true) : 0;
-  if (le == 0 && e == hipSuccess)
+  int le = ingest_slot(p, slot, dx, nullptr, dv, nullptr, nullptr, true);
+  if (le == 0)
     le = launch_zero_mesh(p->prec, p->meshP, p->meshD, p->meshR, p->inst, p->slot_ids + slot, 1, p->rep,
-                                         mesh_words(p), p->stream);
-  hipError_t e2 = hipStreamSynchronize(p->stream);
+                          mesh_words(p), p->stream, step);
+  const hipError_t e = hipStreamSynchronize(p->stream);
   if (stage) hipFree(stage);
-  if (e != hipSuccess || e2 != hipSuccess || le != 0) return fail(p, SIC_EDEVICE, "set_state failed");
+  if (e != hipSuccess || le != 0) return fail(p, SIC_EDEVICE, "set_state failed");
+  sh.step = step;
   sh.state = kStale;
   sh.pending_push = sh.pending_dep = false;
   sh.hist_from = step;
@@ -1797,6 +1832,7 @@ sic_status sim_solve(Pool *p) {
   sic_status st = launch_solve_mode(p, flags, -1, p->stream);
   if (st != SIC_OK) return st;
   sh.state = kField;
+  if (sh.pending_push) sh.step += 1;
   sh.pending_push = sh.pending_dep = false;
   return SIC_OK;
 }
@@ -1920,7 +1956,7 @@ sic_status dev_refine_end(Pool *p) {
   sh.n_tracers_s = nt;
   sh.chunk_in_off = L.in_off;
   sh.n_chunks = (int32_t)L.cd.size();
-  hipError_t e = upload_layout(p, sh, sh.chunk_begin, L);
+  hipError_t e = upload_layout(p, sh.chunk_begin, L);
   if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
   if (e != hipSuccess) return fail(p, SIC_EDEVICE, std::string("layout upload: ") + hipGetErrorString(e));
   sic_status st = SIC_OK;
@@ -2078,7 +2114,10 @@ sic_status sim_step_refining(Pool *p, int64_t n) {
   // inactive): the halo buffers alternate only for the steps that ran
   InstDesc I1;
   const sic_status st3 = read_inst(p, 0, &I1);
-  if (st3 == SIC_OK) p->parity = parity0 ^ (int)((I1.step - I0.step) & 1);
+  if (st3 == SIC_OK) {
+    p->parity = parity0 ^ (int)((I1.step - I0.step) & 1);
+    sh.step = I1.step;
+  }
   if (st != SIC_OK) return st;
   return st2 != SIC_OK ? st2 : st3;
 }
@@ -2099,6 +2138,7 @@ sic_status sim_step(Pool *p, int64_t n) {
     if (p->timing) {
       for (int64_t i = 0; i < n && st == SIC_OK; ++i) {
         st = run_fused(p, 1);
+        if (st == SIC_OK) sh.step += 1;
         if (st == SIC_OK) st = pool_refine(p, 0, sh.l_max, nullptr);
       }
       return st;
@@ -2107,10 +2147,13 @@ sic_status sim_step(Pool *p, int64_t n) {
   }
   if (!p->timing && !p->tune.fused_only && resident_supported(p->order, sh.n_chunks, sh.n_cells)) {
     p->last_path = SIC_PATH_RESIDENT;
-    return run_resident(p, n);
+    st = run_resident(p, n);
+  } else {
+    p->last_path = sf_ready(p) ? SIC_PATH_SOLVE_FIRST : SIC_PATH_FUSED;
+    st = run_fused(p, n);
   }
-  p->last_path = sf_ready(p) ? SIC_PATH_SOLVE_FIRST : SIC_PATH_FUSED;
-  return run_fused(p, n);
+  if (st == SIC_OK) sh.step += n;
+  return st;
 }
 
 const char *status_str(sic_status s) {
@@ -2393,8 +2436,8 @@ sic_status sic_batch_poll(sic_batch *b, int32_t *done_slots, int32_t cap, int32_
   if (!b || !n_done) return SIC_EINVAL;
   Pool *p = b->pool;
   std::vector<int32_t> d((size_t)p->slot_cap);
+  HIPCHK(p, hipMemcpyAsync(d.data(), p->done, sizeof(int32_t) * d.size(), hipMemcpyDeviceToHost, p->stream));
   HIPCHK(p, hipStreamSynchronize(p->stream));
-  HIPCHK(p, hipMemcpy(d.data(), p->done, sizeof(int32_t) * d.size(), hipMemcpyDeviceToHost));
   int32_t n = 0;
   for (int32_t i = 0; i < p->slot_cap; ++i) {
     if (p->slots[i].live && d[i] && !p->slots[i].reported) {

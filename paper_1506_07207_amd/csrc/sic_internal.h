@@ -232,6 +232,21 @@ struct ExtractArgs {
   double *c_out;         // NULL: positions and velocities only
 };
 
+// What a diagnostics call reads of a slot, written in one launch to a block
+// of host memory: its descriptor (at 0), the newest row (kExportRow), the
+// density and the field (kExportMesh, nc words each; where wanted) and the
+// newest max_rows rows of the history, oldest first.
+constexpr size_t kExportRow = 128, kExportMesh = 192;
+struct ExportArgs {
+  const InstDesc *inst;    // the slot's
+  const DiagRow *hist;     // the slot's ring
+  const double *rho, *E;   // both or neither
+  int32_t nc;
+  int64_t hist_from;       // the step the history starts at
+  int64_t max_rows;
+  unsigned char *out;
+};
+
 // Refinement (section 2.6) of one slot's chunk range: a marking pass counts
 // per chunk the segments longer than l_max (and keeps their lane mask); the
 // scatter pass writes every tracer, plus a centre tracer after each marked
@@ -306,9 +321,12 @@ size_t tracer_lds_size(int prec, int order, bool seg, int mesh_cells, int tile_c
 int launch_solve(int prec, const SolveArgs &a, int n_blocks, int max_cells, void *stream);
 int launch_ingest(int prec, const IngestArgs &a, void *stream);
 int launch_extract(int prec, const ExtractArgs &a, void *stream);
-// Clears the meshes of the listed slots in all rep copies (rep_stride words apart).
-int launch_zero_mesh(int prec, void *meshP, void *meshD, void *meshR, const InstDesc *inst,
-                     const int32_t *slot_list, int n_blocks, int rep, int64_t rep_stride, void *stream);
+// Clears the meshes of the listed slots in all rep copies (rep_stride words
+// apart); step >= 0 sets their step.
+int launch_zero_mesh(int prec, void *meshP, void *meshD, void *meshR, InstDesc *inst,
+                     const int32_t *slot_list, int n_blocks, int rep, int64_t rep_stride, void *stream,
+                     int64_t step = -1);
+int launch_export(const ExportArgs &a, void *stream);
 // grid: workgroups of 256 threads
 int launch_copy_bench(const double *src, double *dst, int64_t n, int grid, void *stream);
 // Charge edges of chunks [chunk_begin, chunk_begin + n_chunks): prev_slot[c]

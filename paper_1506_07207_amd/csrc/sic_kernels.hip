@@ -2968,11 +2968,13 @@ __global__ void __launch_bounds__(256) k_refine_layout(RefinePlanArgs a) {
 }
 
 template <int PREC>
-__global__ void __launch_bounds__(256) k_zero_mesh(void *meshP, void *meshD, void *meshR, const InstDesc *inst,
-                                                   const int32_t *slot_list, int rep, int64_t rep_stride) {
+__global__ void __launch_bounds__(256) k_zero_mesh(void *meshP, void *meshD, void *meshR, InstDesc *inst,
+                                                   const int32_t *slot_list, int rep, int64_t rep_stride,
+                                                   int64_t step) {
   using acc_t = typename std::conditional<PREC == kFP64, double, long long>::type;
   const int slot = slot_list ? slot_list[blockIdx.x] : (int)blockIdx.x;
   const InstDesc &I = inst[slot];
+  if (step >= 0 && threadIdx.x == 0) inst[slot].step = step;
   for (int r = 0; r < rep; ++r) {
     const int64_t off = I.mesh_off + r * rep_stride;
     acc_t *P = reinterpret_cast<acc_t *>(meshP) + off;
@@ -2983,6 +2985,37 @@ __global__ void __launch_bounds__(256) k_zero_mesh(void *meshP, void *meshD, voi
       D[j] = (acc_t)0;
       if (R) R[j] = (acc_t)0;
     }
+  }
+}
+
+// The reads of a diagnostics call in one launch, to host memory: a call then
+// waits for the stream once, where a copy per item waited for each (one step
+// and its diagnostics on 50 cells: six waits of 10 to 15 us).
+__global__ void __launch_bounds__(256) k_export(ExportArgs a) {
+  const int tid = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+  const InstDesc &I = *a.inst;
+  const int64_t step = I.step, cap = I.hist_cap;
+  const uint64_t *src = reinterpret_cast<const uint64_t *>(a.inst);
+  uint64_t *out = reinterpret_cast<uint64_t *>(a.out);
+  constexpr int kRowWords = sizeof(DiagRow) / 8;
+  static_assert(sizeof(InstDesc) <= kExportRow && kExportRow + sizeof(DiagRow) <= kExportMesh, "export layout");
+  for (int i = tid; i < (int)(sizeof(InstDesc) / 8); i += nt) out[i] = src[i];
+  const uint64_t *newest = reinterpret_cast<const uint64_t *>(a.hist + row_of(step, cap));
+  for (int i = tid; i < kRowWords; i += nt) out[kExportRow / 8 + i] = newest[i];
+  out += kExportMesh / 8;
+  if (a.rho != nullptr) {
+    double *m = reinterpret_cast<double *>(out);
+    for (int i = tid; i < a.nc; i += nt) {
+      m[i] = a.rho[i];
+      m[a.nc + i] = a.E[i];
+    }
+    out += 2 * a.nc;
+  }
+  const int64_t avail = min(step + 1 - min(step, a.hist_from), cap);
+  const int64_t rows = min(avail, a.max_rows);
+  for (int64_t i = tid; i < rows * kRowWords; i += nt) {
+    const DiagRow *r = a.hist + row_of(step + 1 - rows + i / kRowWords, cap);
+    out[i] = reinterpret_cast<const uint64_t *>(r)[i % kRowWords];
   }
 }
 
@@ -3293,17 +3326,25 @@ int launch_extract(int prec, const ExtractArgs &a, void *stream) {
   return (int)hipGetLastError();
 }
 
-int launch_zero_mesh(int prec, void *meshP, void *meshD, void *meshR, const InstDesc *inst,
-                     const int32_t *slot_list, int n_blocks, int rep, int64_t rep_stride, void *stream) {
+int launch_export(const ExportArgs &a, void *stream) {
+  const int64_t words = std::max<int64_t>(2 * a.nc, 8 * a.max_rows);
+  const int grid = (int)std::min<int64_t>(32, (words + 255) / 256 + 1);
+  hipLaunchKernelGGL(k_export, dim3(grid), dim3(256), 0, (hipStream_t)stream, a);
+  return (int)hipGetLastError();
+}
+
+int launch_zero_mesh(int prec, void *meshP, void *meshD, void *meshR, InstDesc *inst,
+                     const int32_t *slot_list, int n_blocks, int rep, int64_t rep_stride, void *stream,
+                     int64_t step) {
   hipStream_t st = (hipStream_t)stream;
   if (n_blocks <= 0) return 0;
   if (rep < 1) return (int)hipErrorInvalidValue;
   if (prec == kFP64)
     hipLaunchKernelGGL(k_zero_mesh<kFP64>, dim3(n_blocks), dim3(256), 0, st, meshP, meshD, meshR, inst, slot_list,
-                       rep, rep_stride);
+                       rep, rep_stride, step);
   else
     hipLaunchKernelGGL(k_zero_mesh<kSplitF32>, dim3(n_blocks), dim3(256), 0, st, meshP, meshD, meshR, inst,
-                       slot_list, rep, rep_stride);
+                       slot_list, rep, rep_stride, step);
   return (int)hipGetLastError();
 }
 
