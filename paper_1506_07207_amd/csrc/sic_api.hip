@@ -176,10 +176,17 @@ struct Pool {
   int32_t *dr_nt = nullptr;      // per sheet: tracers now
   int32_t *dr_closed = nullptr;  // per sheet
   double *dr_q = nullptr;        // per sheet
-  int64_t *dr_work = nullptr;    // plan scratch, 3 n_sheets + 3
+  int64_t *dr_work = nullptr;    // plan scratch, 4 n_sheets + 2
   int32_t *dr_state = nullptr;   // RefineState words
-  int64_t *dr_in_off = nullptr;  // per chunk of the reservation: first staging index
-  int32_t dr_sheets = 0, dr_chunks = 0;
+  Partial *dr_part = nullptr;    // work-item partials of refined deposits
+  int32_t dr_sheets = 0;
+  // the other set of state arrays (a pass reads one set and writes the other);
+  // alt_swapped counts the exchanges with xs, vs, segq and chunks, mod 2
+  uint64_t *alt_xs = nullptr;
+  double *alt_vs = nullptr;
+  uint64_t *alt_segq = nullptr;
+  ChunkDesc *alt_chunks = nullptr;
+  int alt_swapped = 0;
   // solve-first steps of a single simulation (allocated on first use): two
   // more accumulator sets (the pool's own is the third) and a second set of
   // work-item partials
@@ -294,7 +301,8 @@ void pool_free(Pool *p) {
                   p->partials,  p->meshP,    p->meshE,    p->meshRho,
                   p->hist,      p->done,     p->slot_ids, p->segq,     p->cedge,     p->edge_prev,
                   p->ref_cnt,   p->ref_mask, p->ref_off,  p->ref_w,    p->ref_v,     p->ref_c,
-                  p->dr_nt,     p->dr_closed, p->dr_q,    p->dr_work,  p->dr_state,  p->dr_in_off,
+                  p->dr_nt,     p->dr_closed, p->dr_q,    p->dr_work,  p->dr_state,  p->dr_part,
+                  p->alt_xs,    p->alt_vs,   p->alt_segq, p->alt_chunks,
                   p->sf_mesh,   p->sf_part,  p->in_off};
   for (void *b : bufs)
     if (b) hipFree(b);
@@ -432,10 +440,9 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
 // compute unit.  Atomics on one address serialise (about 22 ns each), so a
 // small mesh also caps the items that merge into one accumulator copy: at
 // most max(256, cells x copies / 2) items (a million tracers on 100 cells:
-// 256 items of 64 chunks, not 2048 of 8); not for the layout of a refining
-// simulation's whole reservation (cap_items false), whose items are mostly
-// empty while it grows.
-int slot_tile(const Pool *p, int64_t n_chunks, bool cap_items = true) {
+// 256 items of 64 chunks, not 2048 of 8).  (A simulation that refines on the
+// device has its own rule, refine_tile, for the chunks that it holds so far.)
+int slot_tile(const Pool *p, int64_t n_chunks) {
   if (p->tune.tile_chunks > 0) return std::max(kMinTile, std::min(kMaxTile, (int)p->tune.tile_chunks));
   const int wave_min = p->block / kChunk;
   if (p->batch) {
@@ -445,7 +452,7 @@ int slot_tile(const Pool *p, int64_t n_chunks, bool cap_items = true) {
   const int64_t per = (n_chunks + 2047) / 2048;
   const int64_t mesh_min = (4 * (int64_t)p->max_cells + kChunk - 1) / kChunk;
   const int64_t max_items = std::max<int64_t>(256, (int64_t)p->max_cells * p->rep / 2);
-  const int64_t contention = cap_items ? (n_chunks + max_items - 1) / max_items : 1;
+  const int64_t contention = (n_chunks + max_items - 1) / max_items;
   const int64_t want = std::max(std::max(per, contention), std::min(mesh_min, n_chunks / 256));
   int t = (int)std::max<int64_t>(kMinTile, std::min<int64_t>(kMaxTile, want));
   t = (t + 3) / 4 * 4;
@@ -563,6 +570,7 @@ sic_status run_fused(Pool *p, int64_t n);
 // Re-lays out every live slot's items (after a tuning change) in one upload.
 sic_status relayout_items(Pool *p) {
   HIPCHK(p, hipStreamSynchronize(p->stream));
+  p->dr_items = false;
   p->item_alloc.init(p->item_cap);
   std::vector<Item> its;
   int tile = p->tile;
@@ -737,6 +745,29 @@ int64_t mesh_words(const Pool *p) { return (int64_t)p->slot_cap * p->max_cells; 
 // Words of all accumulators: P, D (and R) in all copies.
 int64_t acc_words(const Pool *p) { return (p->order == 1 ? 3 : 2) * p->rep * mesh_words(p); }
 
+// The second set of state arrays and the state words of a simulation that
+// refines on the device.
+RefineSel refine_sel(const Pool *p) {
+  RefineSel r;
+  r.state = p->dr_state;
+  r.xs = p->alt_xs;
+  r.vs = p->alt_vs;
+  r.segq = p->alt_segq;
+  r.chunks = p->alt_chunks;
+  return r;
+}
+
+// Where its steps mark the segments to split.
+MarkArgs mark_args(const Pool *p) {
+  MarkArgs m;
+  m.cnt = p->ref_cnt;
+  m.mask = p->ref_mask;
+  m.total = p->dr_state + kRefMarks;
+  m.l_max = p->slots[0].l_max;
+  m.chunk_begin = p->slots[0].chunk_begin;
+  return m;
+}
+
 TracerArgs tracer_args(Pool *p, int mode, int slot) {
   TracerArgs a;
   const bool one = slot >= 0;
@@ -767,6 +798,10 @@ TracerArgs tracer_args(Pool *p, int mode, int slot) {
   // batches skip finished slots; a single simulation refining on the device
   // is made inactive when a pass would exceed its capacity
   a.respect_active = ((p->batch || p->dev_refine) && !one) ? 1 : 0;
+  if (p->dev_refine) {
+    a.sel = refine_sel(p);
+    if (mode == (kPush | kDeposit)) a.mark = mark_args(p);
+  }
   return a;
 }
 
@@ -865,13 +900,14 @@ sic_status get_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
 // as the other paths expect.  The bits are those of the tracer/solve launch
 // pairs: the same solve code, the same sums in the same order.
 bool sf_ready(Pool *p) {
-  if (p->batch || p->timing || p->dev_refine || p->tune.fused_only || p->block < kSolveThreads ||
+  if (p->batch || p->timing || p->tune.fused_only || p->block < kSolveThreads ||
       !step_supported(p->order, p->max_cells) || p->tile > p->block)
     return false;
+  // (refining on the device, the launch has at most kRefineGroups + 1)
   // every workgroup solves first: worth it while the workgroups run in one
   // round on the machine, not when each CU works through several in turn
   // (a 33.5M-tracer job's 2048 workgroups: 400 against 290 us per step)
-  if (grid_for(p, -1) > kSfMaxGrid) return false;
+  if (!p->dev_refine && grid_for(p, -1) > kSfMaxGrid) return false;
   if (!p->sf_mesh) {
     const size_t bytes = sizeof(double) * 2 * (size_t)acc_words(p);
     if (hipMalloc(&p->sf_mesh, bytes) != hipSuccess) {
@@ -927,13 +963,22 @@ sic_status enqueue_sf(Pool *p, int64_t i, hipStream_t st) {
   a.part_in = part[(i + 1) % 2];
   a.part_out = part[i % 2];
   a.sf = solve_args(p, kHavePush | kHaveDeposit, -1);
-  LAUNCHCHK(p, launch_step(p->prec, p->order, p->seg, a, std::min(grid_for(p, -1), sh.n_items), p->block, st));
+  int grid = std::min(grid_for(p, -1), sh.n_items);
+  if (p->dev_refine) {
+    a.sel = refine_sel(p);
+    a.mark = mark_args(p);
+    a.tile_fixed = p->tune.tile_chunks > 0 ? p->tile : 0;
+    a.part_ref = p->dr_part;
+    grid = std::min(grid, kRefineGroups);
+  }
+  LAUNCHCHK(p, launch_step(p->prec, p->order, p->seg, a, grid, p->block, st));
   p->parity ^= 1;
   return SIC_OK;
 }
 
-// The solve launch that ends a run of k solve-first steps.
-sic_status close_sf(Pool *p, int64_t k, hipStream_t st) {
+// The solve launch that ends a run of k solve-first steps (refining: rs, the
+// state words after it).
+sic_status close_sf(Pool *p, int64_t k, hipStream_t st, const int32_t *rs = nullptr) {
   const int64_t arr = (int64_t)p->rep * mesh_words(p);
   Partial *part[2] = {p->partials, p->sf_part};
   long long *set = sf_set(p, k - 1);
@@ -945,6 +990,15 @@ sic_status close_sf(Pool *p, int64_t k, hipStream_t st) {
   if (k >= 2) {
     sa.zero = sf_set(p, k - 2);
     sa.zero_words = acc_words(p);
+  }
+  if (rs) {
+    const int fixed = p->tune.tile_chunks > 0 ? p->tile : 0;
+    sa.respect_active = 0;
+    sa.n_partials = refine_items(rs[kRefStepChunks], fixed);
+    if (rs[kRefInserted] > 0) {
+      sa.refined = p->dr_part;
+      sa.n_refined = refine_items(rs[kRefChunks], fixed);
+    }
   }
   LAUNCHCHK(p, launch_solve(p->prec, sa, p->solve_grid, p->max_cells, st));
   return SIC_OK;
@@ -1849,32 +1903,37 @@ sic_status sim_push(Pool *p) {
 
 // ---- refinement on the device (single simulation) ----
 //
-// Every step: the fused step and its solve, then a marking pass, the plan
-// (flat staging offsets, new sheet sizes, capacity), the scatter into the
-// flat staging, the new layout (descriptors, links, charge edges, work
-// items), the re-ingest, and a deposit and solve of the refined state - each
-// launch reading the counts the previous ones left on the device, the
-// launches sized for the simulation's reservation, and the ones after the
-// plan doing nothing when no segment was split.  No host round trip per
-// step: the host layout is brought up to date once at the end.
+// Every step marks the segments longer than l_max as it deposits them; then
+// come the plan (the new order's indices, the sheets' sizes, the capacity
+// check), the rebuild (the tracers and their centres into the other set of
+// state arrays, the new layout) and a deposit of the refined state, each
+// reading the counts the launches before it left on the device and doing
+// nothing when no segment was marked.  The step is the solve-first launch
+// (four launches per refining step) or, where that does not apply, the
+// tracer/solve pair with a solve of the refined state (six).  No host round
+// trip per step: the host layout is brought up to date once at the end.
 
-// Work items for the whole reservation (tile fixed for it), the first
-// ceil(n_chunks / tile) of them live; the rest are written by the device as
-// the simulation grows.
+// Room in the item arena for the whole reservation; the items are those of
+// the chunks so far (refine_tile), rewritten by the device as they grow.
 sic_status place_slot_items_reserved(Pool *p, int32_t slot) {
   SlotHost &s = p->slots[slot];
   sic_status st = clear_slot_items(p, slot);
   if (st != SIC_OK) return st;
-  const int tile = slot_tile(p, s.n_chunks_res, false);
-  p->tile = tile;
-  const int32_t cap = (s.n_chunks_res + tile - 1) / tile;
-  const int32_t now = (s.n_chunks + tile - 1) / tile;
+  const int fixed = p->tune.tile_chunks > 0 ? slot_tile(p, s.n_chunks_res) : 0;
+  p->tile = fixed > 0 ? fixed : kRefineMaxTile;
+  // the most items on the way to the reservation
+  const int32_t cap =
+      fixed > 0 ? refine_items(s.n_chunks_res, fixed)
+                : std::min((s.n_chunks_res + 7) / 8,
+                           std::max(kRefineGroups, (s.n_chunks_res + kRefineMaxTile - 1) / kRefineMaxTile));
+  const int tile = refine_tile(s.n_chunks, fixed);
+  const int32_t now = refine_items(s.n_chunks, fixed);
   const int64_t ib = p->item_alloc.alloc(cap);
   if (ib < 0) return fail(p, SIC_EBUSY, "work-item arena full");
   std::vector<Item> its((size_t)cap);
   for (int32_t k = 0; k < cap; ++k) {
     its[k].inst = k < now ? slot : -1;
-    its[k].chunk_begin = s.chunk_begin + k * tile;
+    its[k].chunk_begin = s.chunk_begin + std::min(s.n_chunks, k * tile);
     its[k].chunk_end = s.chunk_begin + std::min(s.n_chunks, (k + 1) * tile);
     its[k].pad = 0;
   }
@@ -1895,28 +1954,33 @@ sic_status place_slot_items_reserved(Pool *p, int32_t slot) {
 
 sic_status dev_refine_begin(Pool *p) {
   SlotHost &sh = p->slots[0];
-  sic_status st = ensure_refine_scratch(p, sh.max_tracers);
+  sic_status st = ensure_refine_scratch(p, 0);
   if (st != SIC_OK) return st;
   const int32_t S = (int32_t)sh.n_tracers_s.size();
-  if (p->dr_sheets < S || p->dr_chunks < sh.n_chunks_res) {
-    for (void *b : {(void *)p->dr_nt, (void *)p->dr_closed, (void *)p->dr_q, (void *)p->dr_work, (void *)p->dr_state,
-                    (void *)p->dr_in_off})
+  if (!p->alt_xs) {
+    const size_t slotsz = (size_t)p->chunk_cap * kChunk;
+    HIPCHK(p, dalloc(&p->alt_vs, slotsz));
+    HIPCHK(p, dalloc(&p->alt_segq, slotsz));
+    HIPCHK(p, dalloc(&p->alt_chunks, (size_t)p->chunk_cap));
+    HIPCHK(p, dalloc(&p->dr_state, (size_t)kRefWords));
+    HIPCHK(p, dalloc(&p->dr_part, (size_t)p->item_cap));
+    HIPCHK(p, dalloc(&p->alt_xs, slotsz));
+  }
+  if (p->dr_sheets < S) {
+    for (void *b : {(void *)p->dr_nt, (void *)p->dr_closed, (void *)p->dr_q, (void *)p->dr_work})
       if (b) hipFree(b);
-    p->dr_nt = p->dr_closed = p->dr_state = nullptr;
+    p->dr_nt = p->dr_closed = nullptr;
     p->dr_q = nullptr;
-    p->dr_work = p->dr_in_off = nullptr;
-    p->dr_sheets = p->dr_chunks = 0;
+    p->dr_work = nullptr;
+    p->dr_sheets = 0;
     HIPCHK(p, dalloc(&p->dr_nt, (size_t)S));
     HIPCHK(p, dalloc(&p->dr_closed, (size_t)S));
     HIPCHK(p, dalloc(&p->dr_q, (size_t)S));
-    HIPCHK(p, dalloc(&p->dr_work, 3 * (size_t)S + 3));
-    HIPCHK(p, dalloc(&p->dr_state, (size_t)kRefWords));
-    HIPCHK(p, dalloc(&p->dr_in_off, (size_t)sh.n_chunks_res));
+    HIPCHK(p, dalloc(&p->dr_work, 4 * (size_t)S + 2));
     p->dr_sheets = S;
-    p->dr_chunks = sh.n_chunks_res;
   }
   int32_t stw[kRefWords] = {};
-  stw[kRefChunks] = sh.n_chunks;
+  stw[kRefChunks] = stw[kRefStepChunks] = sh.n_chunks;
   HIPCHK(p, hipMemcpyAsync(p->dr_nt, sh.n_tracers_s.data(), sizeof(int32_t) * (size_t)S, hipMemcpyHostToDevice,
                            p->stream));
   HIPCHK(p, hipMemcpyAsync(p->dr_closed, sh.closed_s.data(), sizeof(int32_t) * (size_t)S, hipMemcpyHostToDevice,
@@ -1934,13 +1998,13 @@ sic_status dev_refine_begin(Pool *p) {
   return SIC_OK;
 }
 
-// The host mirror of the layout after device refinement: the sheets' sizes
-// come back and the layout is rebuilt as the host builds it (the same
-// content; uploaded again, which also sizes the host's chunk offsets); the
-// work items stay laid out for the reservation, so the next refining call
-// reuses them and its captured step.  Returns SIC_ENOMEM when a pass was
-// refused for capacity.
-sic_status dev_refine_end(Pool *p) {
+// The host mirror of the layout after device refinement: the state words and
+// the sheets' sizes come back and the layout is rebuilt as the host builds it
+// (the same content; uploaded again, with the host's chunk offsets); the work
+// items stay laid out for the reservation, so the next refining call reuses
+// them and its captured step.  sf: the steps were solve-first, and their run
+// is closed here.  Returns SIC_ENOMEM when a pass was refused for capacity.
+sic_status dev_refine_end(Pool *p, int parity0, bool sf) {
   SlotHost &sh = p->slots[0];
   p->dev_refine = false;
   std::vector<int32_t> nt(sh.n_tracers_s.size());
@@ -1948,6 +2012,22 @@ sic_status dev_refine_end(Pool *p) {
   HIPCHK(p, hipMemcpyAsync(nt.data(), p->dr_nt, sizeof(int32_t) * nt.size(), hipMemcpyDeviceToHost, p->stream));
   HIPCHK(p, hipMemcpyAsync(stw, p->dr_state, sizeof(stw), hipMemcpyDeviceToHost, p->stream));
   HIPCHK(p, hipStreamSynchronize(p->stream));
+  // after a refused pass the remaining steps did nothing: the halo buffers
+  // alternate only for the steps that ran
+  const int64_t steps = stw[kRefSteps];
+  p->parity = parity0 ^ (int)(steps & 1);
+  sh.step += steps;
+  if (sf && steps > 0) {
+    sic_status st = close_sf(p, steps, p->stream, stw);
+    if (st != SIC_OK) return st;
+  }
+  if (stw[kRefCur] != 0) {
+    std::swap(p->xs, p->alt_xs);
+    std::swap(p->vs, p->alt_vs);
+    std::swap(p->segq, p->alt_segq);
+    std::swap(p->chunks, p->alt_chunks);
+    p->alt_swapped ^= 1;
+  }
   int64_t n_tr = 0;
   for (int32_t t : nt) n_tr += t;
   Layout L;
@@ -1959,12 +2039,11 @@ sic_status dev_refine_end(Pool *p) {
   hipError_t e = upload_layout(p, sh.chunk_begin, L);
   if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
   if (e != hipSuccess) return fail(p, SIC_EDEVICE, std::string("layout upload: ") + hipGetErrorString(e));
-  sic_status st = SIC_OK;
   if (stw[kRefHalt] != 0) {
     // the pass that did not fit inserted nothing; the simulation stays at
     // that step, active again for the caller
     InstDesc I;
-    st = read_inst(p, 0, &I);
+    sic_status st = read_inst(p, 0, &I);
     if (st != SIC_OK) return st;
     I.active = 1;
     HIPCHK(p, hipMemcpyAsync(p->inst, &I, sizeof(I), hipMemcpyHostToDevice, p->stream));
@@ -1974,92 +2053,75 @@ sic_status dev_refine_end(Pool *p) {
   return SIC_OK;
 }
 
-// One refinement pass of slot 0 on the device, after its fused step, on
-// stream st.
-sic_status dev_refine_pass(Pool *p, double l_max, hipStream_t st) {
+// One refining step of slot 0 on stream st: step i of a run of solve-first
+// steps, or (i < 0) a tracer/solve pair.
+sic_status enqueue_refining(Pool *p, int64_t i, hipStream_t st) {
   SlotHost &sh = p->slots[0];
-  RefineArgs ra;
-  ra.chunks = p->chunks;
-  ra.inst = p->inst;
-  ra.xs = p->xs;
-  ra.vs = p->vs;
-  ra.segq = p->segq;
-  ra.chunk_begin = sh.chunk_begin;
-  ra.n_chunks = sh.n_chunks_res;
-  ra.l_max = l_max;
-  ra.cnt = p->ref_cnt;
-  ra.mask = p->ref_mask;
-  ra.out_off = p->ref_off;
-  ra.w_out = p->ref_w;
-  ra.v_out = p->ref_v;
-  ra.c_out = p->ref_c;
-  ra.state = p->dr_state;
-  RefinePlanArgs pa;
-  pa.chunks = p->chunks;
-  pa.links = p->order == 1 ? p->links : nullptr;
-  pa.edge_prev = p->edge_prev;
-  pa.in_off = p->dr_in_off;
-  pa.items = p->items;
-  pa.slot_items = p->slot_items;
-  pa.n_items = p->n_items;
-  pa.inst = p->inst;
-  pa.cnt = p->ref_cnt;
-  pa.out_off = p->ref_off;
-  pa.nt = p->dr_nt;
-  pa.closed = p->dr_closed;
-  pa.q = p->dr_q;
-  pa.work = p->dr_work;
-  pa.state = p->dr_state;
-  pa.max_tracers = sh.max_tracers;
-  pa.q_scale = sh.q_scale;
-  pa.n_sheets = (int32_t)sh.n_tracers_s.size();
-  pa.chunk_begin = sh.chunk_begin;
-  pa.chunk_cap = sh.n_chunks_res;
-  pa.tile = p->tile;
-  pa.slot = 0;
-  pa.item_begin = sh.item_begin;
-  pa.order = p->order;
-  pa.fixed = p->prec != kFP64 ? 1 : 0;
-  LAUNCHCHK(p, launch_refine_mark(p->prec, ra, st));
-  LAUNCHCHK(p, launch_refine_plan(pa, st));
-  LAUNCHCHK(p, launch_refine_scatter(p->prec, ra, st));
-  LAUNCHCHK(p, launch_refine_layout(pa, st));
-  IngestArgs ia;
-  ia.x_in = nullptr;
-  ia.w_in = p->ref_w;
-  ia.v_in = p->ref_v;
-  ia.c_in = nullptr;
-  ia.cw_in = p->ref_c;
-  ia.segq = p->segq;
-  ia.q_scale = sh.q_scale;
-  ia.chunk_in_off = p->dr_in_off;
-  ia.chunk_begin = sh.chunk_begin;
-  ia.n_chunks = sh.n_chunks_res;
-  ia.chunks = p->chunks;
-  ia.inst = p->inst;
-  ia.xs = p->xs;
-  ia.vs = p->vs;
-  ia.halo = p->halo[p->parity];
-  ia.halo3 = p->halo3[p->parity];
-  ia.state = p->dr_state;
-  LAUNCHCHK(p, launch_ingest(p->prec, ia, st));
-  LAUNCHCHK(p, launch_charge_edges(p->chunks, p->edge_prev, p->segq, p->cedge, sh.chunk_begin, sh.n_chunks_res,
-                                   st, p->dr_state));
+  const bool sf = i >= 0;
+  sic_status rc = sf ? enqueue_sf(p, i, st) : enqueue_fused(p, st);
+  if (rc != SIC_OK) return rc;
+  RefinePassArgs a;
+  a.chunks[0] = p->chunks;
+  a.chunks[1] = p->alt_chunks;
+  a.xs[0] = p->xs;
+  a.xs[1] = p->alt_xs;
+  a.vs[0] = p->vs;
+  a.vs[1] = p->alt_vs;
+  a.segq[0] = p->segq;
+  a.segq[1] = p->alt_segq;
+  a.halo = p->order == 1 ? p->halo3[p->parity] : p->halo[p->parity];
+  a.cedge = p->cedge;
+  a.links = p->order == 1 ? p->links : nullptr;
+  a.items = p->items;
+  a.slot_items = p->slot_items;
+  a.n_items = p->n_items;
+  a.inst = p->inst;
+  a.cnt = p->ref_cnt;
+  a.mask = p->ref_mask;
+  a.out_off = p->ref_off;
+  a.nt = p->dr_nt;
+  a.closed = p->dr_closed;
+  a.q = p->dr_q;
+  a.work = p->dr_work;
+  a.state = p->dr_state;
+  a.acc_zero = sf ? sf_set(p, i) : nullptr;  // a pair's solve has cleared its own
+  a.acc_words = acc_words(p);
+  a.max_tracers = sh.max_tracers;
+  a.q_scale = sh.q_scale;
+  a.n_sheets = (int32_t)sh.n_tracers_s.size();
+  a.chunk_begin = sh.chunk_begin;
+  a.chunk_cap = sh.n_chunks_res;
+  a.tile_fixed = p->tune.tile_chunks > 0 ? p->tile : 0;
+  a.slot = 0;
+  a.item_begin = sh.item_begin;
+  a.order = p->order;
+  a.fixed = p->prec != kFP64 ? 1 : 0;
+  LAUNCHCHK(p, launch_refine_plan(a, st));
+  LAUNCHCHK(p, launch_refine_rebuild(p->prec, a, st));
   // the refined state's charge and field (only when a segment was split)
   TracerArgs ta = tracer_args(p, kDeposit, 0);
   ta.gate = p->dr_state + kRefInserted;
+  if (sf) {
+    const int64_t arr = (int64_t)p->rep * mesh_words(p);
+    ta.meshP = sf_set(p, i);
+    ta.meshD = sf_set(p, i) + arr;
+    if (p->order == 1) ta.meshR = sf_set(p, i) + 2 * arr;
+    ta.partials = p->dr_part;
+  }
   const size_t lds = tracer_lds_size(p->prec, p->order, p->seg, p->max_cells, p->tile);
   LAUNCHCHK(p, launch_tracers(p->prec, kDeposit, p->order, p->seg, ta, grid_for(p, 0), p->block, lds, st));
-  SolveArgs sa = solve_args(p, kHaveDeposit, 0);
-  sa.gate = p->dr_state + kRefInserted;
-  LAUNCHCHK(p, launch_solve(p->prec, sa, 1, p->max_cells, st));
+  if (!sf) {
+    SolveArgs sa = solve_args(p, kHaveDeposit, 0);
+    sa.gate = p->dr_state + kRefInserted;
+    LAUNCHCHK(p, launch_solve(p->prec, sa, 1, p->max_cells, st));
+  }
   return SIC_OK;
 }
 
-// Graphs of k refining steps (fused step, solve, refinement pass), keyed
-// apart from the plain step graphs.
-sic_status get_refine_graph(Pool *p, int64_t k, double l_max, hipGraphExec_t *out) {
-  auto key = std::make_tuple(k, p->parity, p->grid, p->solve_grid, 2);
+// Graphs of k refining steps, keyed apart from the plain step graphs; sf: the
+// first is step 1 (mod 6) of a run of solve-first steps.
+sic_status get_refine_graph(Pool *p, int64_t k, bool sf, hipGraphExec_t *out) {
+  auto key = std::make_tuple(k, p->parity, p->grid, p->solve_grid, 4 + 2 * p->alt_swapped + (sf ? 1 : 0));
   auto it = p->graphs.find(key);
   if (it != p->graphs.end()) {
     *out = it->second;
@@ -2068,10 +2130,7 @@ sic_status get_refine_graph(Pool *p, int64_t k, double l_max, hipGraphExec_t *ou
   const int parity0 = p->parity;
   HIPCHK(p, hipStreamBeginCapture(p->cap, hipStreamCaptureModeRelaxed));
   sic_status s = SIC_OK;
-  for (int64_t i = 0; i < k && s == SIC_OK; ++i) {
-    s = enqueue_fused(p, p->cap);
-    if (s == SIC_OK) s = dev_refine_pass(p, l_max, p->cap);
-  }
+  for (int64_t i = 0; i < k && s == SIC_OK; ++i) s = enqueue_refining(p, sf ? 1 + i : -1, p->cap);
   p->parity = parity0;
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(p->cap, &g);
@@ -2093,33 +2152,29 @@ sic_status get_refine_graph(Pool *p, int64_t k, double l_max, hipGraphExec_t *ou
 }
 
 sic_status sim_step_refining(Pool *p, int64_t n) {
-  SlotHost &sh = p->slots[0];
-  InstDesc I0;
-  sic_status st = read_inst(p, 0, &I0);
-  if (st == SIC_OK) st = dev_refine_begin(p);
+  if (n == 0) return SIC_OK;
+  sic_status st = dev_refine_begin(p);
+  if (st != SIC_OK) return st;
   const int parity0 = p->parity;
-  while (n > 0 && st == SIC_OK) {
-    const int64_t k = std::min<int64_t>(n, kGraphSteps);
+  const bool sf = sf_ready(p);
+  int64_t i = 0;
+  if (sf) st = enqueue_refining(p, i++, p->stream);
+  while (i < n && st == SIC_OK) {
+    const int64_t k = std::min<int64_t>(n - i, kSfGraphSteps);
+    if (sf && k <= kSfDirectSteps) {
+      st = enqueue_refining(p, i++, p->stream);
+      continue;
+    }
     hipGraphExec_t ex;
-    st = get_refine_graph(p, k, sh.l_max, &ex);
+    st = get_refine_graph(p, k, sf, &ex);
     if (st != SIC_OK) break;
     const hipError_t e = hipGraphLaunch(ex, p->stream);
     if (e != hipSuccess) st = fail(p, SIC_EDEVICE, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
     if (k & 1) p->parity ^= 1;
-    n -= k;
+    i += k;
   }
-  if (!p->dev_refine) return st;
-  sic_status st2 = dev_refine_end(p);
-  // after a refused pass the remaining steps did nothing (the slot was
-  // inactive): the halo buffers alternate only for the steps that ran
-  InstDesc I1;
-  const sic_status st3 = read_inst(p, 0, &I1);
-  if (st3 == SIC_OK) {
-    p->parity = parity0 ^ (int)((I1.step - I0.step) & 1);
-    sh.step = I1.step;
-  }
-  if (st != SIC_OK) return st;
-  return st2 != SIC_OK ? st2 : st3;
+  sic_status st2 = dev_refine_end(p, parity0, sf);
+  return st != SIC_OK ? st : st2;
 }
 
 sic_status sim_step(Pool *p, int64_t n) {

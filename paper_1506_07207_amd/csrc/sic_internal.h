@@ -138,7 +138,67 @@ struct SolveArgs {
   // solve-first steps read)
   void *zero = nullptr;
   int64_t zero_words = 0;
+  // the end of a run of refining solve-first steps: the partials' count (>= 0)
+  // and, where the last step refined, the partials of the refined deposit
+  int32_t n_partials = -1;
+  int32_t n_refined = 0;
+  const Partial *refined = nullptr;
 };
+
+// Refinement done entirely on the device (one simulation, steps in a row):
+// int32 words of its state.
+//   kRefChunks      chunks of the slot now
+//   kRefInserted    tracers the last pass inserted (0: nothing re-laid out)
+//   kRefHalt        set when a pass would exceed the capacity (sticky; the
+//                   following steps do nothing)
+//   kRefMarks       segments marked since the last plan
+//   kRefCur         which of the two sets of state arrays holds the state
+//   kRefSteps       steps taken
+//   kRefStepChunks  chunks at the newest step, before its refinement
+enum RefineState : int {
+  kRefChunks = 0,
+  kRefInserted = 1,
+  kRefHalt = 2,
+  kRefMarks = 3,
+  kRefCur = 4,
+  kRefSteps = 5,
+  kRefStepChunks = 6,
+  kRefWords = 8
+};
+
+// The second set of a refining simulation's state arrays and its state
+// words; state NULL: the launch does not refine.
+struct RefineSel {
+  const int32_t *state = nullptr;
+  uint64_t *xs = nullptr;
+  double *vs = nullptr;
+  uint64_t *segq = nullptr;
+  ChunkDesc *chunks = nullptr;
+};
+
+// Where a step marks the segments longer than l_max: per chunk from
+// chunk_begin on their count and lane mask, and their total; cnt NULL: none.
+struct MarkArgs {
+  int32_t *cnt = nullptr;
+  uint64_t *mask = nullptr;
+  int32_t *total = nullptr;
+  double l_max = 0.0;
+  int32_t chunk_begin = 0;
+};
+
+// Work items of a simulation that refines on the device: enough for one per
+// compute unit but one (which writes the rows), of 8 to kRefineMaxTile chunks.
+constexpr int kRefineGroups = kComputeUnits - 1;
+constexpr int kRefineMaxTile = 256;
+__host__ __device__ inline int refine_tile(int n_chunks, int fixed) {
+  if (fixed > 0) return fixed;
+  const int t = ((n_chunks + kRefineGroups - 1) / kRefineGroups + 7) / 8 * 8;
+  return t < 8 ? 8 : (t > kRefineMaxTile ? kRefineMaxTile : t);
+}
+__host__ __device__ inline int refine_items(int n_chunks, int fixed) {
+  const int t = refine_tile(n_chunks, fixed);
+  return (n_chunks + t - 1) / t;
+}
 
 struct TracerArgs {
   const Item *items;
@@ -168,6 +228,8 @@ struct TracerArgs {
   // mesh)
   int32_t rep = 1;
   int64_t rep_stride = 0;
+  RefineSel sel;           // per-segment pools
+  MarkArgs mark;
 };
 
 // A solve-first step of a single simulation (slot 0).  The accumulators of a
@@ -193,6 +255,12 @@ struct StepArgs {
   const Partial *part_in;         // the previous step's work-item partials
   Partial *part_out;
   SolveArgs sf;                   // what the diagnostics go to
+  // refining on the device (per-segment pools; sel.state set): the chunk count
+  // is the device's, the items are those of refine_tile(count, tile_fixed)
+  RefineSel sel;
+  MarkArgs mark;
+  int32_t tile_fixed = 0;
+  const Partial *part_ref = nullptr;  // partials of the refined state's deposit
   int32_t row_group = 0;          // set by launch_step: workgroup 0 has no item
   int32_t zero_slice = 0;         // words of acc_zero per workgroup
 };
@@ -214,8 +282,6 @@ struct IngestArgs {
   double *vs;
   double2 *halo;
   double2 *halo3;  // order 1 (NULL otherwise)
-  const int32_t *state = nullptr;  // device refinement: skip unless state[kRefInserted] > 0, chunk
-                                   // count state[kRefChunks] (the launch covers the capacity)
 };
 
 struct ExtractArgs {
@@ -266,42 +332,40 @@ struct RefineArgs {
   uint64_t *w_out;
   double *v_out;
   uint64_t *c_out;
-  const int32_t *state = nullptr;  // device refinement: chunk count state[kRefChunks]; the marking pass
-                                   // skips after a halt, the scatter unless state[kRefInserted] > 0
 };
 
-// Refinement done entirely on the device (one simulation, steps in a row):
-// int32 words of its state.  kRefChunks: chunks of the slot now;
-// kRefInserted: tracers the last pass inserted (0: nothing to re-lay out);
-// kRefHalt: set when a pass would exceed the capacity (sticky; the slot is
-// made inactive, so the following steps do nothing); kRefNextChunks: chunks
-// after the pending re-layout.
-enum RefineState : int { kRefChunks = 0, kRefInserted = 1, kRefHalt = 2, kRefNextChunks = 3, kRefWords = 8 };
-
-// The re-layout of one simulation after a refinement pass, planned and
-// written on the device (the counterpart of the host's layout building).
-struct RefinePlanArgs {
-  ChunkDesc *chunks;       // pool descriptors; the slot's range is rewritten
+// A refinement pass of one simulation on the device, after a step that
+// marked its segments: the plan and the rebuild.  State arrays come in two
+// sets; the rebuild reads one and writes the other.
+struct RefinePassArgs {
+  ChunkDesc *chunks[2];
+  uint64_t *xs[2];
+  double *vs[2];
+  uint64_t *segq[2];
+  double2 *halo;           // the halo copies the next step reads (orders 0, 2: one per chunk, 1: three)
+  uint64_t *cedge;
   int2 *links;             // order 1 (NULL otherwise)
-  int64_t *edge_prev;      // per chunk: slot of the tracer before its first one
-  int64_t *in_off;         // per chunk of the range: first index in the flat staging
   Item *items;             // the slot's item range (room for the capacity)
   int2 *slot_items;        // per slot: (first item, item count)
   int32_t *n_items;        // item count the tracer kernel walks
   InstDesc *inst;
   const int32_t *cnt;      // per chunk of the range: segments to split
-  int64_t *out_off;        // per chunk of the range: first index in the flat staging
+  const uint64_t *mask;    // per chunk of the range: their lanes
+  int64_t *out_off;        // per chunk of the range: its first tracer's index in the new order
   int32_t *nt;             // per sheet: tracers now
   const int32_t *closed;   // per sheet
   const double *q;         // per sheet: charge kept in the descriptors
-  int64_t *work;           // 3 n_sheets + 3 entries (per sheet: new count, new first chunk, flat start)
+  int64_t *work;           // 4 n_sheets + 2 entries (per sheet: new count, new first chunk, index of its
+                           // first tracer, old first chunk)
   int32_t *state;          // RefineState words
+  void *acc_zero;          // accumulators to clear when the pass inserts, or NULL
+  int64_t acc_words;
   int64_t max_tracers;
   double q_scale;
   int32_t n_sheets;
   int32_t chunk_begin;
   int32_t chunk_cap;       // chunks reserved for the slot
-  int32_t tile;            // chunks per work item
+  int32_t tile_fixed;      // refine_tile
   int32_t slot;
   int32_t item_begin;
   int32_t order;
@@ -332,7 +396,7 @@ int launch_copy_bench(const double *src, double *dst, int64_t n, int grid, void 
 // Charge edges of chunks [chunk_begin, chunk_begin + n_chunks): prev_slot[c]
 // is the slot of the tracer before chunk c's first one (-1: none).
 int launch_charge_edges(const ChunkDesc *chunks, const int64_t *prev_slot, const uint64_t *segq, uint64_t *cedge,
-                        int32_t chunk_begin, int32_t n_chunks, void *stream, const int32_t *state = nullptr);
+                        int32_t chunk_begin, int32_t n_chunks, void *stream);
 // A small simulation's n_steps fused steps (push, deposit, solve) in one
 // launch of one workgroup; chunks [chunk_begin, chunk_begin + n_chunks) of
 // slot 0.  a.halo_out (order 1: a.halo3_out) receives the halos of the final
@@ -340,13 +404,10 @@ int launch_charge_edges(const ChunkDesc *chunks, const int64_t *prev_slot, const
 bool resident_supported(int order, int n_chunks, int n_cells);
 int launch_resident(int prec, int order, bool seg, const TracerArgs &a, const SolveArgs &sa, int chunk_begin,
                     int n_chunks, int n_cells, int64_t n_steps, void *stream);
-// With a.state the launches cover a.n_chunks chunks (the capacity) and read
-// the count from the device.
 int launch_refine_mark(int prec, const RefineArgs &a, void *stream);
 int launch_refine_scatter(int prec, const RefineArgs &a, void *stream);
-// Device re-layout: the plan (one workgroup) and the descriptor/item writer
-// (covers chunk_cap chunks).
-int launch_refine_plan(const RefinePlanArgs &a, void *stream);
-int launch_refine_layout(const RefinePlanArgs &a, void *stream);
+// A pass on the device: the plan (one workgroup) and the rebuild.
+int launch_refine_plan(const RefinePassArgs &a, void *stream);
+int launch_refine_rebuild(int prec, const RefinePassArgs &a, void *stream);
 
 }  // namespace sic

@@ -1344,6 +1344,21 @@ __device__ __forceinline__ void stage_linear(const Geo &g, const double *sE, boo
   *wn = wn1;
 }
 
+// Length of the segment between two state words as refinement measures it:
+// float64 positions by the physical minimum image, split ones in mesh units.
+template <int PREC>
+__device__ __forceinline__ double mark_length(uint64_t wa, uint64_t wb, const Geo &g) {
+  if constexpr (PREC == kFP64) {
+    double d = __longlong_as_double((long long)wb) - __longlong_as_double((long long)wa);
+    if (d >= g.half_L) d -= g.L;
+    else if (d < -g.half_L) d += g.L;
+    return fabs(d);
+  } else {
+    const double dm = mesh_pos<PREC>(wb, g.inv_dx) - mesh_pos<PREC>(wa, g.inv_dx);
+    return fabs(min_image_cells(dm, 0.5 * (double)g.nc, (double)g.nc)) * g.dx;
+  }
+}
+
 // A chunk's table entry: its descriptor, the charge word of the segment that
 // ends at its first tracer (per-segment charges), the word of the tracer
 // after it (moved when the step moves) and, for linear segments, the segments
@@ -1430,7 +1445,7 @@ template <int PREC, int MODE, int ORDER, bool SEG, bool STORE = true>
 __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t, const Geo &g, double q_unit,
                                               uint64_t *xs, double *vs, double2 *halo_out, const ChunkTab &tab,
                                               size_t chunk, int lane, uint64_t &xw, double &v, uint64_t cw, double &ke,
-                                              double &mom, double &ms) {
+                                              double &mom, double &ms, const MarkArgs &mark = MarkArgs()) {
   constexpr bool kLin = ORDER == 1;
   constexpr bool kDep = (MODE & kDeposit) != 0;
   constexpr bool kKick = (MODE & kKickHalf) != 0;
@@ -1579,6 +1594,22 @@ __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t
       ms = nan_max(ms, len);
     }
   }
+  if constexpr (SEG && MODE == (kPush | kDeposit)) {
+    if (mark.cnt != nullptr) {
+      // segments to split, by the length that the marking pass takes
+      const uint64_t dn = lane_down1(xw);
+      const bool tail = lane == n_valid - 1;
+      const bool has = valid && !(tail && ch.partner < 0);
+      const bool split = has && mark_length<PREC>(xw, tail ? tab.next : dn, g) > mark.l_max;
+      const uint64_t lanes = __builtin_amdgcn_ballot_w64(split);
+      if (lane == 0) {
+        const int n = __builtin_popcountll(lanes);
+        mark.cnt[chunk - mark.chunk_begin] = n;
+        mark.mask[chunk - mark.chunk_begin] = lanes;
+        if (n) atomicAdd(mark.total, n);
+      }
+    }
+  }
 }
 
 // Work-item partial sums in a fixed order (deterministic for a fixed item
@@ -1638,9 +1669,21 @@ __device__ __forceinline__ void merge_mesh(const ItemLds<PREC, ORDER, SEG> &t, A
   }
 }
 
+// The set of state arrays that holds a refining simulation's state.
+template <class Args>
+__device__ __forceinline__ void select_state(Args &a) {
+  if (a.sel.state != nullptr && a.sel.state[kRefCur] != 0) {
+    a.xs = a.sel.xs;
+    a.vs = a.sel.vs;
+    a.segq = a.sel.segq;
+    a.chunks = a.sel.chunks;
+  }
+}
+
 template <int PREC, int MODE, int ORDER, bool SEG>
 __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
   using acc_t = typename std::conditional<PREC == kFP64, double, unsigned long long>::type;
+  if constexpr (SEG) select_state(a);
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr bool kLin = ORDER == 1;
   const ItemLds<PREC, ORDER, SEG> t(smem, a.mesh_cells, a.tile_cap);
@@ -1781,7 +1824,7 @@ __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
             tab.next = (uint64_t)__double_as_longlong(t.sHalo[kk].x);
           }
           process_chunk<PREC, MODE, ORDER, SEG>(t, g, I.q_unit, a.xs, a.vs, kLin ? a.halo3_out : a.halo_out, tab,
-                                                (size_t)(cb + kk), lane, xr[j], vr[j], cr_[j], ke, mom, ms);
+                                                (size_t)(cb + kk), lane, xr[j], vr[j], cr_[j], ke, mom, ms, a.mark);
         }
         load_state(k + (j + kPrefetch) * nwaves, xr[j], vr[j], cr_[j]);
       }
@@ -1836,7 +1879,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
   constexpr int kRep = single_rep(CELLS * kSolveThreads);
   constexpr int kPrefetch = 3;
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double sRow[4][4];  // workgroup 0: the row's sums by wavefront
+  __shared__ double sRow[5][4];  // workgroup 0: the row's sums by wavefront
   const ItemLds<PREC, ORDER, SEG> t(smem, a.nc, 0);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -1854,13 +1897,37 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
   const int nc = a.nc;
   const SlotConst kc = {nc, a.L, a.dx, a.dt, a.q_unit, 0, 0, a.hist_cap};
 
+  // items now and of the launch before (whose partials these are), and of the
+  // deposit after that one's refinement
+  int n_chunks = a.n_chunks, tile = a.tile, n_items = a.n_items, n_prev = a.n_items, n_ref = 0;
+  if constexpr (SEG) {
+    if (a.sel.state != nullptr) {
+      const int32_t *st = a.sel.state;
+      if (st[kRefHalt] != 0) return;
+      n_chunks = st[kRefChunks];
+      tile = refine_tile(n_chunks, a.tile_fixed);
+      n_items = refine_items(n_chunks, a.tile_fixed);
+      n_prev = refine_items(st[kRefStepChunks], a.tile_fixed);
+      n_ref = st[kRefInserted] > 0 ? n_items : 0;
+      select_state(a);
+    }
+  }
+  auto clear_slice = [&]() {
+    acc_t *z = reinterpret_cast<acc_t *>(a.acc_zero);
+    const int z1 = min(kArrays * kRep * nc, ((int)blockIdx.x + 1) * a.zero_slice);
+    for (int i = (int)blockIdx.x * a.zero_slice + tid; i < z1; i += nt) z[i] = (acc_t)0;
+  };
   const int it0 = a.row_group ? -1 : 0;  // workgroup 0's item; -1: it has none
   int it = (int)blockIdx.x + it0;
+  if (it >= n_items) {  // refining: more workgroups than items so far
+    if (a.acc_zero != nullptr) clear_slice();
+    return;
+  }
   int cb = 0, nch = 0;
   auto range = [&]() {  // a workgroup without an item loads the first one's
     const int i = max(it, 0);
-    cb = a.chunk_begin + i * a.tile;
-    nch = min(a.tile, a.n_chunks - i * a.tile);
+    cb = a.chunk_begin + i * tile;
+    nch = min(tile, n_chunks - i * tile);
   };
   // Lane i of wavefront w holds the tables of chunk w + i * waves, the i-th
   // of the wavefront's (an item has at most 64 chunks per wavefront).
@@ -1920,8 +1987,8 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
     if (row) {
       step0 = a.sf.inst[0].step;
       flags0 = a.sf.inst[0].flags;
-      pr[0] = a.part_in[min(tid, a.n_items - 1)];
-      pr[1] = a.part_in[min(tid + kSolveThreads, a.n_items - 1)];
+      pr[0] = a.part_in[min(tid, n_prev - 1)];
+      pr[1] = a.part_in[min(tid + kSolveThreads, n_prev - 1)];
     }
     if (tid < nc) sum_acc(tid);
     for (int j = tid + nt; j < nc; j += nt) {
@@ -1948,9 +2015,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
                                   (double *)nullptr, (double *)nullptr);
     // The accumulators that the launch before read are cleared, a slice per
     // workgroup (the next launch merges into them).
-    acc_t *z = reinterpret_cast<acc_t *>(a.acc_zero);
-    const int z1 = min(kArrays * kRep * nc, ((int)blockIdx.x + 1) * a.zero_slice);
-    for (int i = (int)blockIdx.x * a.zero_slice + tid; i < z1; i += nt) z[i] = (acc_t)0;
+    clear_slice();
   } else {
     // the first step of a run: the field is in global memory
     halos = tabs.halos(a.halo_in, lane_chunk(), 0);
@@ -1981,7 +2046,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
           if (k + j * nwaves < nch)
             process_chunk<PREC, kMode, ORDER, SEG>(t, g, a.q_unit, a.xs, a.vs, a.halo_out, tabs.entry(i++),
                                                    (size_t)(cb + k + j * nwaves), lane, xr[j], vr[j], cr_[j], ke, mom,
-                                                   ms);
+                                                   ms, a.mark);
           load_state(k + (j + kPrefetch) * nwaves, xr[j], vr[j], cr_[j]);
         }
       }
@@ -1996,15 +2061,18 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
         pmom += p.mom;
         pms = nan_max(pms, p.maxseg);
       };
-      if (tid < a.n_items) add(pr[0]);
-      if (tid + kSolveThreads < a.n_items) add(pr[1]);
-      for (int i = tid + 2 * kSolveThreads; i < a.n_items; i += kSolveThreads) add(a.part_in[i]);
-      const double w = wave_sum(fs.w2), k = wave_sum(pke), m = wave_sum(pmom), x = wave_max(pms);
+      if (tid < n_prev) add(pr[0]);
+      if (tid + kSolveThreads < n_prev) add(pr[1]);
+      for (int i = tid + 2 * kSolveThreads; i < n_prev; i += kSolveThreads) add(a.part_in[i]);
+      double pref = 0.0;
+      for (int i = tid; i < n_ref; i += kSolveThreads) pref = nan_max(pref, a.part_ref[i].maxseg);
+      const double w = wave_sum(fs.w2), k = wave_sum(pke), m = wave_sum(pmom), x = wave_max(pms), y = wave_max(pref);
       if (lane == 0) {
         sRow[0][wave] = w;
         sRow[1][wave] = k;
         sRow[2][wave] = m;
         sRow[3][wave] = x;
+        sRow[4][wave] = y;
       }
     }
     if (it >= 0) item_partial<kMode>(ke, mom, ms, t.sRed, a.part_out + it);
@@ -2014,14 +2082,20 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
       const double k = sRow[1][0] + sRow[1][1] + sRow[1][2] + sRow[1][3];
       const double m = sRow[2][0] + sRow[2][1] + sRow[2][2] + sRow[2][3];
       const double x = nan_max(nan_max(sRow[3][0], sRow[3][1]), nan_max(sRow[3][2], sRow[3][3]));
-      write_row(a.sf, 0, kc, step0, solve_flags(a.sf.flags, flags0, a.L, W, k, m, x), W, fs.Qtot, k, m, x);
+      int flags = solve_flags(a.sf.flags, flags0, a.L, W, k, m, x);
+      double longest = x;
+      if (n_ref > 0) {  // as k_solve: the row is the refined state's
+        longest = nan_max(nan_max(sRow[4][0], sRow[4][1]), nan_max(sRow[4][2], sRow[4][3]));
+        flags = solve_flags(a.sf.flags, flags, a.L, W, k, m, longest);
+      }
+      write_row(a.sf, 0, kc, step0, flags, W, fs.Qtot, k, m, longest);
     }
     if (it < 0) return;
     acc_t *out = reinterpret_cast<acc_t *>(a.acc_out) + (int64_t)(it % kRep) * nc;
     const int64_t arr = (int64_t)kRep * nc;
     merge_mesh<PREC, ORDER, SEG>(t, out, out + arr, out + 2 * arr, nc);
     it += (int)gridDim.x + it0;
-    if (it >= a.n_items) break;
+    if (it >= n_items) break;
     range();
     tabs.load(a.chunks, a.links, a.cedge, lane_chunk());
     halos = tabs.halos(a.halo_in, lane_chunk(), 0);
@@ -2122,6 +2196,7 @@ k_deposit_faces(TracerArgs a) {
   using acc_t = typename std::conditional<PREC == kFP64, double, unsigned long long>::type;
   extern __shared__ __align__(16) unsigned char smem[];
   if (a.gate != nullptr && *a.gate <= 0) return;
+  if constexpr (SEG) select_state(a);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2342,7 +2417,7 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(SolveArgs a) {
   if (a.respect_active && !Ip->active) return;
   const int tid = threadIdx.x;
   const int2 si = a.slot_items[slot];
-  const int item_begin = si.x, item_count = si.y;
+  const int item_begin = si.x, item_count = a.n_partials >= 0 ? a.n_partials : si.y;
   const SlotConst kc = slot_const(*Ip);
   acc_t *gP = reinterpret_cast<acc_t *>(a.meshP) + kc.mesh_off;
   acc_t *gD = reinterpret_cast<acc_t *>(a.meshD) + kc.mesh_off;
@@ -2388,8 +2463,20 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(SolveArgs a) {
   const FieldSums f = solve_field<PREC, CELLS, REP>(kc, pv, dv, gRamp, a.rep_stride, (double *)nullptr, false,
                                                     a.meshE + kc.mesh_off, a.meshRho + kc.mesh_off);
   const double W = field_energy(f, kc.dx);
+  int flags = Ip->flags;
+  if (a.refined != nullptr) {
+    // the row is the refined state's; the flags are also those of the state
+    // before its refinement
+    flags = solve_flags(a.flags, flags, kc.L, W, ke, mom, ms);
+    ms = 0.0;
+    for (int i = tid; i < a.n_refined; i += kSolveThreads) ms = nan_max(ms, a.refined[i].maxseg);
+    ms = wave_max(ms);
+    if ((tid & 63) == 0) sMs[wave] = ms;
+    __syncthreads();
+    ms = nan_max(nan_max(sMs[0], sMs[1]), nan_max(sMs[2], sMs[3]));
+  }
   if (tid == 0)
-    write_row(a, slot, kc, Ip->step, solve_flags(a.flags, Ip->flags, kc.L, W, ke, mom, ms), W, f.Qtot, ke, mom, ms);
+    write_row(a, slot, kc, Ip->step, solve_flags(a.flags, flags, kc.L, W, ke, mom, ms), W, f.Qtot, ke, mom, ms);
   acc_t *z = reinterpret_cast<acc_t *>(a.zero);
   for (int64_t i = tid; i < a.zero_words; i += kSolveThreads) z[i] = (acc_t)0;
 }
@@ -2578,7 +2665,6 @@ __global__ void __launch_bounds__((NW + 1) * kChunk) k_resident(TracerArgs a, So
 template <int PREC>
 __global__ void __launch_bounds__(256) k_ingest(IngestArgs a) {
   const int cl = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (a.state != nullptr && (a.state[kRefInserted] <= 0 || cl >= a.state[kRefChunks])) return;
   if (cl >= a.n_chunks) return;
   const int lane = threadIdx.x & 63;
   const int c = a.chunk_begin + cl;
@@ -2655,9 +2741,8 @@ __global__ void __launch_bounds__(256) k_extract(ExtractArgs a) {
 // its partner tracer.
 __global__ void __launch_bounds__(256) k_charge_edges(const ChunkDesc *chunks, const int64_t *prev_slot,
                                                       const uint64_t *segq, uint64_t *cedge, int32_t chunk_begin,
-                                                      int32_t n_chunks, const int32_t *state) {
+                                                      int32_t n_chunks) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (state != nullptr && (state[kRefInserted] <= 0 || i >= state[kRefChunks])) return;
   if (i >= n_chunks) return;
   const int c = chunk_begin + i;
   const int64_t pv = prev_slot[c];
@@ -2671,13 +2756,14 @@ __global__ void __launch_bounds__(256) k_charge_edges(const ChunkDesc *chunks, c
 // an open sheet's end) and marks it when its minimum-image length exceeds
 // l_max.
 template <int PREC>
-__device__ __forceinline__ bool refine_segment(const RefineArgs &a, const ChunkDesc &ch, const InstDesc &I,
-                                               int lane, uint64_t w, uint64_t &wn, double &vn, double &du) {
+__device__ __forceinline__ bool refine_segment(const uint64_t *xs, const double *vs, const ChunkDesc &ch,
+                                               const InstDesc &I, int lane, uint64_t w, uint64_t &wn, double &vn,
+                                               double &du, double l_max) {
   bool has = lane < ch.n_valid;
   if (lane == ch.n_valid - 1) {
     if (ch.partner >= 0) {
-      wn = a.xs[(size_t)ch.partner * kChunk];
-      vn = a.vs[(size_t)ch.partner * kChunk];
+      wn = xs[(size_t)ch.partner * kChunk];
+      vn = vs[(size_t)ch.partner * kChunk];
     } else {
       has = false;
     }
@@ -2697,13 +2783,31 @@ __device__ __forceinline__ bool refine_segment(const RefineArgs &a, const ChunkD
     du = dm;
     len = fabs(dm) * I.dx;
   }
-  return len > a.l_max;
+  return len > l_max;
+}
+
+// The centre of a split segment and the charges of its halves (fixed point:
+// they differ by at most one unit and sum exactly).
+template <int PREC>
+__device__ __forceinline__ void refine_split(uint64_t w, uint64_t cq, double du, const InstDesc &I, uint64_t *wm,
+                                             uint64_t *c0, uint64_t *c1) {
+  if constexpr (PREC == kFP64) {
+    const double h = 0.5 * __longlong_as_double((long long)cq);
+    *c0 = *c1 = (uint64_t)__double_as_longlong(h);
+    const double xa = __longlong_as_double((long long)w);
+    *wm = (uint64_t)__double_as_longlong(wrap_into_box(xa + 0.5 * du, I.L));
+  } else {
+    const long long q = (long long)cq;
+    const long long q1 = q >> 1;
+    *c0 = (uint64_t)(q - q1);
+    *c1 = (uint64_t)q1;
+    *wm = advance_split<PREC>(w, 0.5 * du, I.n_cells);
+  }
 }
 
 template <int PREC>
 __global__ void __launch_bounds__(256) k_refine_mark(RefineArgs a) {
   const int cl = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (a.state != nullptr && (a.state[kRefHalt] != 0 || cl >= a.state[kRefChunks])) return;
   if (cl >= a.n_chunks) return;  // uniform per wavefront
   const int lane = threadIdx.x & 63;
   const int c = a.chunk_begin + cl;
@@ -2713,7 +2817,7 @@ __global__ void __launch_bounds__(256) k_refine_mark(RefineArgs a) {
   const uint64_t w = a.xs[s];
   uint64_t wn = lane_down1(w);
   double vn = 0.0, du = 0.0;
-  const bool flag = refine_segment<PREC>(a, ch, I, lane, w, wn, vn, du);
+  const bool flag = refine_segment<PREC>(a.xs, a.vs, ch, I, lane, w, wn, vn, du, a.l_max);
   const uint64_t mask = __ballot(flag);
   if (lane == 0) {
     a.cnt[cl] = __popcll(mask);
@@ -2727,7 +2831,6 @@ __global__ void __launch_bounds__(256) k_refine_mark(RefineArgs a) {
 template <int PREC>
 __global__ void __launch_bounds__(256) k_refine_scatter(RefineArgs a) {
   const int cl = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (a.state != nullptr && (a.state[kRefInserted] <= 0 || cl >= a.state[kRefChunks])) return;
   if (cl >= a.n_chunks) return;  // uniform per wavefront
   const int lane = threadIdx.x & 63;
   const int c = a.chunk_begin + cl;
@@ -2740,7 +2843,7 @@ __global__ void __launch_bounds__(256) k_refine_scatter(RefineArgs a) {
   uint64_t wn = lane_down1(w);
   double vn = lane_down1(v);
   double du = 0.0;
-  refine_segment<PREC>(a, ch, I, lane, w, wn, vn, du);
+  refine_segment<PREC>(a.xs, a.vs, ch, I, lane, w, wn, vn, du, a.l_max);
   // the marking pass decided (the host sized the output from its counts)
   const uint64_t mask = a.mask[cl];
   const bool flag = ((mask >> lane) & 1ull) != 0;
@@ -2749,18 +2852,7 @@ __global__ void __launch_bounds__(256) k_refine_scatter(RefineArgs a) {
   uint64_t c0 = cq;
   if (flag) {
     uint64_t c1, wm;
-    if constexpr (PREC == kFP64) {
-      const double h = 0.5 * __longlong_as_double((long long)cq);
-      c0 = c1 = (uint64_t)__double_as_longlong(h);
-      const double xa = __longlong_as_double((long long)w);
-      wm = (uint64_t)__double_as_longlong(wrap_into_box(xa + 0.5 * du, I.L));
-    } else {
-      const long long q = (long long)cq;
-      const long long q1 = q >> 1;
-      c0 = (uint64_t)(q - q1);
-      c1 = (uint64_t)q1;
-      wm = advance_split<PREC>(w, 0.5 * du, I.n_cells);
-    }
+    refine_split<PREC>(w, cq, du, I, &wm, &c0, &c1);
     a.w_out[out + 1] = wm;
     a.v_out[out + 1] = 0.5 * (v + vn);
     a.c_out[out + 1] = c1;
@@ -2770,14 +2862,16 @@ __global__ void __launch_bounds__(256) k_refine_scatter(RefineArgs a) {
   a.c_out[out] = c0;
 }
 
-// Device re-layout after a marking pass (one simulation; the host's layout
-// building done on the device, so that refining steps need no round trip).
-// The plan, one workgroup: the flat staging offset of every chunk (the old
-// tracers plus the inserted ones, sheet-major), each sheet's new tracer
-// count, its first chunk in the new layout and its first staging index, and
-// the capacity check.  A pass that would exceed the capacity inserts nothing
-// and halts the simulation (inactive; the host reports it).
-__global__ void __launch_bounds__(1024) k_refine_plan(RefinePlanArgs a) {
+// A refinement pass on the device (one simulation, whose step marked its
+// segments; the host's layout building done on the device, so that refining
+// steps need no round trip).  The plan, one workgroup: every chunk's first
+// tracer's index in the new order (the old tracers plus the inserted ones,
+// sheet-major), each sheet's new tracer count, its first chunk in the new
+// layout and its first index, and the capacity check.  A step that marked
+// nothing (most, before the sheets fold) ends it at once.  A pass that would
+// exceed the capacity inserts nothing and halts the simulation (inactive; the
+// host reports it).
+__global__ void __launch_bounds__(1024) k_refine_plan(RefinePassArgs a) {
   __shared__ long long sW[16];
   __shared__ long long sTk[16];
   __shared__ long long sTot[2];
@@ -2785,12 +2879,19 @@ __global__ void __launch_bounds__(1024) k_refine_plan(RefinePlanArgs a) {
   const int tid = threadIdx.x;
   const int nth = blockDim.x;
   int32_t *st = a.state;
-  if (st[kRefHalt] != 0) {
-    if (tid == 0) st[kRefInserted] = 0;
-    return;
+  const int halted = st[kRefHalt], marks = st[kRefMarks], n = st[kRefChunks];
+  const ChunkDesc *chunks = st[kRefCur] ? a.chunks[1] : a.chunks[0];
+  __syncthreads();
+  if (tid == 0) {
+    sOver = 0;
+    st[kRefMarks] = 0;
+    if (!halted) {
+      st[kRefSteps] += 1;
+      st[kRefStepChunks] = n;
+    }
+    if (halted || marks == 0) st[kRefInserted] = 0;
   }
-  if (tid == 0) sOver = 0;
-  const int n = st[kRefChunks];
+  if (halted || marks == 0) return;
   // Each wavefront takes a contiguous range of chunks and walks it 64 chunks
   // (one per lane, coalesced) at a time, kB groups of loads in flight
   // together: a wavefront scan gives each chunk its offset within the range
@@ -2808,7 +2909,7 @@ __global__ void __launch_bounds__(1024) k_refine_plan(RefinePlanArgs a) {
       const int c = gb + u * 64 + lane;
       const int cc = min(c, w1 - 1);
       const long long k = a.cnt[cc];
-      const long long v = (long long)a.chunks[a.chunk_begin + cc].n_valid + k;
+      const long long v = (long long)chunks[a.chunk_begin + cc].n_valid + k;
       kv[u] = c < w1 ? k : 0;
       vv[u] = c < w1 ? v : 0;
     }
@@ -2846,6 +2947,7 @@ __global__ void __launch_bounds__(1024) k_refine_plan(RefinePlanArgs a) {
   int64_t *newnt = a.work;
   int64_t *first2 = a.work + S;  // S + 1 entries
   int64_t *flat0 = a.work + 2 * S + 1;
+  int64_t *first1 = a.work + 3 * S + 1;  // S + 1 entries
   long long old_first = 0, new_first = 0;
   for (int base = 0; base < S; base += nth) {
     const int s = base + tid;
@@ -2865,6 +2967,7 @@ __global__ void __launch_bounds__(1024) k_refine_plan(RefinePlanArgs a) {
       newnt[s] = nn;
       first2[s] = new_first + in2 - nch;
       flat0[s] = o0;
+      first1[s] = old_first + io - och;
     }
     if (tid == nth - 1) {
       sTot[0] = io;
@@ -2877,6 +2980,7 @@ __global__ void __launch_bounds__(1024) k_refine_plan(RefinePlanArgs a) {
   }
   if (tid == 0) {
     first2[S] = new_first;
+    first1[S] = old_first;
     const bool over = sOver != 0 || total_new > a.max_tracers || new_first > a.chunk_cap;
     if (over) {
       st[kRefHalt] = 1;
@@ -2884,54 +2988,127 @@ __global__ void __launch_bounds__(1024) k_refine_plan(RefinePlanArgs a) {
       a.inst[a.slot].active = 0;
     } else {
       st[kRefInserted] = (int32_t)(inserted < 0x7fffffffll ? inserted : 0x7fffffffll);
-      st[kRefNextChunks] = (int32_t)new_first;
+      st[kRefChunks] = (int32_t)new_first;
+      st[kRefCur] ^= 1;
     }
   }
 }
 
-// Writes the planned layout: per new chunk its descriptor (sheet charge,
-// fixed-point charge, valid count, partner chunk, open-sheet start), its
-// first staging index, the slot of the tracer before it (charge edges) and,
-// for piecewise-linear segments, its links; the slot's work items (runs of
-// tile chunks); the new counts.  Mirrors the host's layout building.
-__global__ void __launch_bounds__(256) k_refine_layout(RefinePlanArgs a) {
-  int32_t *st = a.state;
+// The planned pass: every old chunk's wavefront writes its tracers, and the
+// centre tracer after each marked one, to their slots in the other set of
+// state arrays, with the halo copies and charge edges that they are (one
+// launch and one pass over the tracers; a flat staging array, a re-ingest
+// from it and a pass for the edges took three launches and two).  A thread
+// per new chunk writes its descriptor, its links and its work item; the
+// accumulators of the unrefined deposit are cleared for the refined one.
+template <int PREC>
+__global__ void __launch_bounds__(256) k_refine_rebuild(RefinePassArgs a) {
+  const int32_t *st = a.state;
   if (st[kRefInserted] <= 0) return;
+  const int to = st[kRefCur], from = to ^ 1;  // the plan made the new set current
+  const int n1 = st[kRefStepChunks], n2 = st[kRefChunks];
   const int S = a.n_sheets;
   const int64_t *newnt = a.work;
   const int64_t *first2 = a.work + S;
   const int64_t *flat0 = a.work + 2 * S + 1;
-  const int n2 = st[kRefNextChunks];
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  auto n_valid_of = [](long long n, long long k) { return (int32_t)min((long long)kChunk, n - k * kChunk); };
-  if (c < n2) {
-    int lo = 0, hi = S - 1;  // the sheet holding new chunk c: last s with first2[s] <= c
+  const int64_t *first1 = a.work + 3 * S + 1;
+  const InstDesc &I = a.inst[a.slot];
+  auto sheet_of = [S](const int64_t *first, int c) {  // the sheet holding chunk c: last s with first[s] <= c
+    int lo = 0, hi = S - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
-      if (first2[mid] <= c) lo = mid;
+      if (first[mid] <= c) lo = mid;
       else hi = mid - 1;
     }
-    const int s = lo;
-    const long long k = c - first2[s];
-    const long long n = newnt[s];
+    return lo;
+  };
+  const uint64_t *xs = from ? a.xs[1] : a.xs[0];
+  const double *vs = from ? a.vs[1] : a.vs[0];
+  const uint64_t *segq = from ? a.segq[1] : a.segq[0];
+  const ChunkDesc *chunks = from ? a.chunks[1] : a.chunks[0];
+  uint64_t *xo = to ? a.xs[1] : a.xs[0];
+  double *vo = to ? a.vs[1] : a.vs[0];
+  uint64_t *co = to ? a.segq[1] : a.segq[0];
+  ChunkDesc *chunks_out = to ? a.chunks[1] : a.chunks[0];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
+  const int nwaves = gridDim.x * (blockDim.x >> 6);
+  for (int cl = wave; cl < n1; cl += nwaves) {
+    const int sh = sheet_of(first1, cl);
+    const int64_t n = newnt[sh], f0 = flat0[sh];
+    const int64_t base = a.chunk_begin + first2[sh];  // the sheet's first chunk
+    const int64_t last = base + (n - 1) / kChunk;     // and its last one
+    const bool closed = a.closed[sh] != 0;
+    const ChunkDesc ch = chunks[a.chunk_begin + cl];
+    const size_t s = (size_t)(a.chunk_begin + cl) * kChunk + lane;
+    const uint64_t w = xs[s], cq = segq[s];
+    const double v = vs[s];
+    uint64_t wn = lane_down1(w);
+    double vn = lane_down1(v), du = 0.0;
+    refine_segment<PREC>(xs, vs, ch, I, lane, w, wn, vn, du, 0.0);
+    const uint64_t mask = a.mask[cl];
+    // tracer r of the sheet
+    auto place = [&](int64_t r, uint64_t pw, double pv, uint64_t pc) {
+      const int64_t c = base + (r >> 6);
+      const int l = (int)(r & 63);
+      const size_t at = (size_t)base * kChunk + (size_t)r;
+      xo[at] = pw;
+      vo[at] = pv;
+      co[at] = pc;
+      const double2 h = make_double2(__longlong_as_double((long long)pw), pv);
+      const bool end = r == n - 1;
+      if (a.order == 1) {
+        if (l == 0) a.halo[3 * c + kHaloFirst] = h;
+        if (l == 1) a.halo[3 * c + kHaloSecond] = h;
+        if (l == 63 || end) a.halo[3 * c + kHaloLast] = h;
+      } else if (l == 0) {
+        a.halo[c] = h;
+      }
+      // its segment starts at the partner of the chunk before it, and ends at
+      // the first tracer of the chunk after it
+      if (l == 0 && (r > 0 || closed)) a.cedge[2 * (r > 0 ? c - 1 : last) + 1] = pc;
+      if (end) a.cedge[2 * base] = closed ? pc : 0ull;
+      else if (l == 63) a.cedge[2 * (c + 1)] = pc;
+      if (end && !closed) a.cedge[2 * last + 1] = 0ull;
+    };
+    if (lane < ch.n_valid) {
+      const bool flag = ((mask >> lane) & 1ull) != 0;
+      const int64_t r = a.out_off[cl] - f0 + lane + __popcll(mask & ((1ull << lane) - 1ull));
+      uint64_t c0 = cq;
+      if (flag) {
+        uint64_t c1, wm;
+        refine_split<PREC>(w, cq, du, I, &wm, &c0, &c1);
+        place(r + 1, wm, 0.5 * (v + vn), c1);
+      }
+      place(r, w, v, c0);
+    }
+    if (cl + 1 == first1[sh + 1]) {  // the sheet's last old chunk clears the padding of its last new one
+      const int64_t r = n + lane;
+      if (r < (last - base + 1) * kChunk) {
+        const size_t at = (size_t)base * kChunk + (size_t)r;
+        xo[at] = 0;
+        vo[at] = 0.0;
+        co[at] = 0;
+      }
+    }
+  }
+  const int tid = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+  auto n_valid_of = [](long long n, long long k) { return (int32_t)min((long long)kChunk, n - k * kChunk); };
+  for (int c = tid; c < n2; c += nt) {
+    const int sh = sheet_of(first2, c);
+    const long long k = c - first2[sh];
+    const long long n = newnt[sh];
     const long long nch = (n + kChunk - 1) / kChunk;
-    const int32_t first = a.chunk_begin + (int32_t)first2[s];
-    const bool cl = a.closed[s] != 0;
+    const int32_t first = a.chunk_begin + (int32_t)first2[sh];
+    const bool cl = a.closed[sh] != 0;
     ChunkDesc d;
-    d.q = a.q[s];
-    d.q_fix = a.fixed ? (int64_t)llrint(a.q[s] * a.q_scale) : 0;
+    d.q = a.q[sh];
+    d.q_fix = a.fixed ? (int64_t)llrint(a.q[sh] * a.q_scale) : 0;
     d.n_valid = n_valid_of(n, k);
     d.inst = a.slot;
     d.flags = (k == 0 && !cl) ? kChunkOpenStart : 0;
     d.partner = (k + 1 < nch) ? (int32_t)(first + k + 1) : (cl ? first : -1);
-    a.chunks[first + k] = d;
-    a.in_off[c] = flat0[s] + k * kChunk;
-    if (a.edge_prev) {
-      int64_t pv = -1;
-      if (k > 0) pv = (int64_t)(first + k - 1) * kChunk + (kChunk - 1);
-      else if (cl) pv = (int64_t)(first + nch - 1) * kChunk + (n - (nch - 1) * kChunk - 1);
-      a.edge_prev[first + k] = pv;
-    }
+    chunks_out[first + k] = d;
     if (a.links) {
       int2 lk = make_int2(-1, -1);
       if (!cl || n >= 3) {
@@ -2950,18 +3127,20 @@ __global__ void __launch_bounds__(256) k_refine_layout(RefinePlanArgs a) {
       a.links[first + k] = lk;
     }
   }
-  const int n_items = (n2 + a.tile - 1) / a.tile;
-  if (c < n_items) {
+  const int tile = refine_tile(n2, a.tile_fixed), n_items = refine_items(n2, a.tile_fixed);
+  for (int c = tid; c < n_items; c += nt) {
     Item it;
     it.inst = a.slot;
-    it.chunk_begin = a.chunk_begin + c * a.tile;
-    it.chunk_end = a.chunk_begin + min(n2, (c + 1) * a.tile);
+    it.chunk_begin = a.chunk_begin + c * tile;
+    it.chunk_end = a.chunk_begin + min(n2, (c + 1) * tile);
     it.pad = 0;
     a.items[a.item_begin + c] = it;
   }
-  for (int s = c; s < S; s += gridDim.x * blockDim.x) a.nt[s] = (int32_t)newnt[s];
-  if (c == 0) {
-    st[kRefChunks] = n2;
+  for (int sh = tid; sh < S; sh += nt) a.nt[sh] = (int32_t)newnt[sh];
+  uint64_t *z = reinterpret_cast<uint64_t *>(a.acc_zero);
+  if (z != nullptr)
+    for (int64_t i = tid; i < a.acc_words; i += nt) z[i] = 0;
+  if (tid == 0) {
     a.slot_items[a.slot].y = n_items;
     *a.n_items = a.item_begin + n_items;
   }
@@ -3187,7 +3366,7 @@ struct LaunchStep {
 int launch_step(int prec, int order, bool seg, const StepArgs &a, int grid, int block, void *stream) {
   // a wavefront stages at most 64 chunks of an item: a.tile <= block
   if (!step_supported(order, a.nc) || block < kSolveThreads || a.tile < 1 || a.tile > block || a.n_items < 1 ||
-      grid < 1 || grid > a.n_items)
+      grid < 1 || grid > a.n_items || (a.sel.state != nullptr && !seg))
     return (int)hipErrorInvalidValue;
   // the chunks' tables are in registers: the mesh, the field and the sums only
   const size_t lds = tracer_lds_size(prec, order, seg, a.nc, 0);
@@ -3349,10 +3528,10 @@ int launch_zero_mesh(int prec, void *meshP, void *meshD, void *meshR, InstDesc *
 }
 
 int launch_charge_edges(const ChunkDesc *chunks, const int64_t *prev_slot, const uint64_t *segq, uint64_t *cedge,
-                        int32_t chunk_begin, int32_t n_chunks, void *stream, const int32_t *state) {
+                        int32_t chunk_begin, int32_t n_chunks, void *stream) {
   if (n_chunks <= 0) return 0;
   hipLaunchKernelGGL(k_charge_edges, dim3((n_chunks + 255) / 256), dim3(256), 0, (hipStream_t)stream, chunks,
-                     prev_slot, segq, cedge, chunk_begin, n_chunks, state);
+                     prev_slot, segq, cedge, chunk_begin, n_chunks);
   return (int)hipGetLastError();
 }
 
@@ -3382,14 +3561,23 @@ int launch_refine_scatter(int prec, const RefineArgs &a, void *stream) {
   return (int)hipGetLastError();
 }
 
-int launch_refine_plan(const RefinePlanArgs &a, void *stream) {
+int launch_refine_plan(const RefinePassArgs &a, void *stream) {
   hipLaunchKernelGGL(k_refine_plan, dim3(1), dim3(1024), 0, (hipStream_t)stream, a);
   return (int)hipGetLastError();
 }
 
-int launch_refine_layout(const RefinePlanArgs &a, void *stream) {
-  const int grid = std::max(1, (a.chunk_cap + 255) / 256);
-  hipLaunchKernelGGL(k_refine_layout, dim3(grid), dim3(256), 0, (hipStream_t)stream, a);
+int launch_refine_rebuild(int prec, const RefinePassArgs &a, void *stream) {
+  hipStream_t st = (hipStream_t)stream;
+  // the capacity at a wavefront per chunk, up to two workgroups per compute
+  // unit (a simulation holds far fewer chunks than its capacity for most of a
+  // run, and a launch pays for the workgroups that find nothing to do)
+  const int grid = std::max(1, std::min((a.chunk_cap + 3) / 4, 2 * kComputeUnits));
+  switch (prec) {
+    case kFP64: hipLaunchKernelGGL(k_refine_rebuild<kFP64>, dim3(grid), dim3(256), 0, st, a); break;
+    case kSplitF32: hipLaunchKernelGGL(k_refine_rebuild<kSplitF32>, dim3(grid), dim3(256), 0, st, a); break;
+    case kSplitU32: hipLaunchKernelGGL(k_refine_rebuild<kSplitU32>, dim3(grid), dim3(256), 0, st, a); break;
+    default: return (int)hipErrorInvalidValue;
+  }
   return (int)hipGetLastError();
 }
 
