@@ -46,6 +46,7 @@ constexpr int kBatchItems = 3072;        // work items a batch's arena is cut in
 constexpr int kMinBatchTile = 48;
 constexpr int kMinTile = 4;             // chunks per work item, lower bound
 constexpr int kMaxTile = 256;
+constexpr int kMaxRun = 16;             // items a deposit's workgroup takes at most
 
 enum SimState { kStale = 0, kDeposited = 1, kField = 2 };
 
@@ -833,24 +834,51 @@ int grid_for(Pool *p, int slot) {
 
 sic_status launch_tracer_mode(Pool *p, int mode, int slot, hipStream_t st) {
   TracerArgs a = tracer_args(p, mode, slot);
+  // a single simulation on its own grid: the items follow one another
+  if (!p->batch && p->tune.grid_blocks == 0 && !p->dev_refine && p->slots[0].n_items == grid_for(p, slot))
+    a.run = kMaxRun;
   const size_t lds = tracer_lds_size(p->prec, p->order, p->seg, p->max_cells, p->tile);
   LAUNCHCHK(p, launch_tracers(p->prec, mode, p->order, p->seg, a, grid_for(p, slot), p->block, lds, st));
   return SIC_OK;
 }
 
-sic_status launch_solve_mode(Pool *p, int flags, int slot, hipStream_t st) {
+// n_partials >= 0: the work-item partials to sum, instead of one per item.
+sic_status launch_solve_mode(Pool *p, int flags, int slot, hipStream_t st, int n_partials = -1) {
   SolveArgs a = solve_args(p, flags, slot);
+  a.n_partials = n_partials;
   LAUNCHCHK(p, launch_solve(p->prec, a, slot >= 0 ? 1 : p->solve_grid, p->max_cells, st));
+  return SIC_OK;
+}
+
+StepArgs step_args(Pool *p);
+
+// The tracer launch of a fused step for the whole pool; *n_partials as
+// launch_solve_mode takes it.  A single simulation of more items than
+// solve-first steps take runs as many workgroups as the machine holds at a
+// time, which go through all chunks together (launch_run): 33.5M tracers on
+// 4096 cells 262 -> 216 us per launch.
+sic_status launch_fused_tracers(Pool *p, hipStream_t st, int *n_partials) {
+  *n_partials = -1;
+  if (p->batch || p->dev_refine || p->tune.grid_blocks > 0 || p->tune.tile_chunks > 0 ||
+      grid_for(p, -1) <= kSfMaxGrid)
+    return launch_tracer_mode(p, kPush | kDeposit, -1, st);
+  StepArgs a = step_args(p);
+  a.acc_out = p->meshP;
+  a.part_out = p->partials;
+  int grid = p->slots[0].n_items;
+  LAUNCHCHK(p, launch_run(p->prec, p->order, p->seg, a, p->block, st, &grid));
+  *n_partials = grid;
   return SIC_OK;
 }
 
 // One fused step for the whole pool (every live slot; batch pools skip
 // finished slots): move + deposit, then solve.
 sic_status enqueue_fused(Pool *p, hipStream_t st) {
-  sic_status s = launch_tracer_mode(p, kPush | kDeposit, -1, st);
+  int n_partials;
+  sic_status s = launch_fused_tracers(p, st, &n_partials);
   if (s != SIC_OK) return s;
   int flags = kHavePush | kHaveDeposit | (p->batch ? kBatchStep : 0);
-  s = launch_solve_mode(p, flags, -1, st);
+  s = launch_solve_mode(p, flags, -1, st, n_partials);
   if (s != SIC_OK) return s;
   p->parity ^= 1;
   return SIC_OK;
@@ -931,10 +959,10 @@ long long *sf_set(Pool *p, int64_t i) {
                     : static_cast<long long *>(p->sf_mesh) + (i % 3 - 1) * acc_words(p);
 }
 
-// Step i of a run of solve-first steps.
-sic_status enqueue_sf(Pool *p, int64_t i, hipStream_t st) {
+// What a step launch of a single simulation reads and writes, but for the
+// accumulators and the partials.
+StepArgs step_args(Pool *p) {
   const SlotHost &sh = p->slots[0];
-  Partial *part[2] = {p->partials, p->sf_part};
   StepArgs a;
   a.L = sh.L;
   a.half_L = 0.5 * sh.L;
@@ -957,12 +985,25 @@ sic_status enqueue_sf(Pool *p, int64_t i, hipStream_t st) {
   a.halo_in = p->order == 1 ? p->halo3[p->parity] : p->halo[p->parity];
   a.halo_out = p->order == 1 ? p->halo3[p->parity ^ 1] : p->halo[p->parity ^ 1];
   a.meshE = p->meshE;
+  a.acc_in = nullptr;
+  a.acc_out = nullptr;
+  a.acc_zero = nullptr;
+  a.part_in = nullptr;
+  a.part_out = nullptr;
+  a.sf = solve_args(p, kHavePush | kHaveDeposit, -1);
+  return a;
+}
+
+// Step i of a run of solve-first steps.
+sic_status enqueue_sf(Pool *p, int64_t i, hipStream_t st) {
+  const SlotHost &sh = p->slots[0];
+  Partial *part[2] = {p->partials, p->sf_part};
+  StepArgs a = step_args(p);
   a.acc_in = i > 0 ? sf_set(p, i - 1) : nullptr;
   a.acc_out = sf_set(p, i);
   a.acc_zero = i > 0 ? sf_set(p, i + 1) : nullptr;
   a.part_in = part[(i + 1) % 2];
   a.part_out = part[i % 2];
-  a.sf = solve_args(p, kHavePush | kHaveDeposit, -1);
   int grid = std::min(grid_for(p, -1), sh.n_items);
   if (p->dev_refine) {
     a.sel = refine_sel(p);
@@ -1073,11 +1114,12 @@ sic_status run_fused(Pool *p, int64_t n) {
     for (int64_t i = 0; i < n && s == SIC_OK && e == hipSuccess; ++i) {
       e = hipEventRecord(ev[3 * i], p->stream);
       if (e != hipSuccess) break;
-      s = launch_tracer_mode(p, kPush | kDeposit, -1, p->stream);
+      int n_partials;
+      s = launch_fused_tracers(p, p->stream, &n_partials);
       if (s != SIC_OK) break;
       e = hipEventRecord(ev[3 * i + 1], p->stream);
       if (e != hipSuccess) break;
-      s = launch_solve_mode(p, kHavePush | kHaveDeposit | (p->batch ? kBatchStep : 0), -1, p->stream);
+      s = launch_solve_mode(p, kHavePush | kHaveDeposit | (p->batch ? kBatchStep : 0), -1, p->stream, n_partials);
       if (s == SIC_OK) e = hipEventRecord(ev[3 * i + 2], p->stream);
       p->parity ^= 1;
     }

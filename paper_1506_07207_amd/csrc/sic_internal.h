@@ -228,6 +228,9 @@ struct TracerArgs {
   // mesh)
   int32_t rep = 1;
   int64_t rep_stride = 0;
+  // deposit alone, one simulation: consecutive items that a workgroup may take
+  // with one clearing and one merge of its mesh (the grid covers the items)
+  int32_t run = 1;
   RefineSel sel;           // per-segment pools
   MarkArgs mark;
 };
@@ -379,6 +382,10 @@ int launch_tracers(int prec, int mode, int order, bool seg, const TracerArgs &a,
 // of block threads, at least kSolveThreads and at least a.tile.
 int launch_step(int prec, int order, bool seg, const StepArgs &a, int grid, int block, void *stream);
 bool step_supported(int order, int max_cells);
+// The tracer launch of a step whose charge a solve launch solves (a.acc_in,
+// acc_zero NULL), in at most *grid workgroups and at most as many as run at a
+// time; *grid: the workgroups launched, each of which writes one partial.
+int launch_run(int prec, int order, bool seg, const StepArgs &a, int block, void *stream, int *grid);
 int set_tracer_lds_limit(int prec, int order, bool seg, size_t lds_bytes);
 size_t tracer_lds_size(int prec, int order, bool seg, int mesh_cells, int tile_cap);
 // max_cells: the largest mesh of the slots the launch may solve.

@@ -990,6 +990,14 @@ __device__ __forceinline__ void solve_take(const SlotConst &kc, Acc *gP, Acc *gD
   }
 }
 
+// Index of a cell in LDS when each solve thread takes up to 16 consecutive
+// ones: a word of padding every 16 keeps the threads of a wavefront, 128 bytes
+// apart, off one another's banks.
+template <int CELLS>
+__device__ __forceinline__ int padded_cell(int j) {
+  return CELLS == 16 ? j + (j >> 4) : j;
+}
+
 // What the solve leaves for the diagnostics row: this thread's field energy
 // sum (threads of the first kSolveThreads; not finite when one of its field
 // values is not) and the total charge (every thread).
@@ -999,12 +1007,12 @@ struct FieldSums {
 
 // The field of pv, dv (this thread's accumulators from solve_take) and the
 // ramps, into sE (LDS, with one ghost cell on each side when ghost is set)
-// and into gE and gR (global field and density) where they are given.  The
-// cells are partitioned over kSolveThreads threads; a wider workgroup's other
+// and into gE and gR (field and density: global memory, or, PADDED, LDS by
+// padded_cell) where they are given.  The cells are partitioned over kSolveThreads threads; a wider workgroup's other
 // wavefronts only pass the barriers, so the bits are those of a workgroup of
 // kSolveThreads.  The field in sE is complete after a barrier following the
 // return.
-template <int PREC, int CELLS, int REP = 1, class Acc, class T>
+template <int PREC, int CELLS, int REP = 1, bool PADDED = false, class Acc, class T>
 __device__ __forceinline__ FieldSums solve_field(const SlotConst &kc, const T (&pv)[CELLS], const T (&dv)[CELLS],
                                                  Acc *gRamp, int64_t ramp_stride, double *sE, bool ghost, double *gE,
                                                  double *gR) {
@@ -1150,8 +1158,9 @@ __device__ __forceinline__ FieldSums solve_field(const SlotConst &kc, const T (&
           }
         }
         if (gE) {
-          gE[j] = e;
-          gR[j] = (Q[k] - qmean) / kc.dx;
+          const int at = PADDED ? padded_cell<CELLS>(j) : j;
+          gE[at] = e;
+          gR[at] = (Q[k] - qmean) / kc.dx;
         }
         out.w2 += e * e;
       }
@@ -1868,7 +1877,17 @@ __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
 // cells, split U32) 11.1 -> 7.3, two-stream (2.1M tracers, 1024 cells, split
 // F32) 26 -> 26.  Of the 8.1 us of Landau's, 1.6 are the launch, 1.2 the
 // charge, 1.2 the solve, 1.7 moving and depositing one chunk per wavefront
-// and 1.2 the merge.  CELLS: cells per solve thread.
+// and 1.2 the merge.
+//
+// CELLS: cells per solve thread; 0: no solve, for simulations of more items
+// than run in one round, whose charge a solve launch solves once.  Their
+// workgroups, as many as run at a time, go through all chunks together: the
+// wavefronts stream on their own, with no barrier, and the mesh is cleared,
+// and merged, once per workgroup (33.5M tracers, 4096 cells: 256
+// merges of 8192 additions instead of 2048, on compute units that hold one
+// workgroup and had nothing to do meanwhile: 262 -> 216 us, 4.1 -> 5.0 TB/s of
+// the state's bytes; a contiguous run for each workgroup instead of all going
+// through memory together: 225).
 template <int PREC, int ORDER, bool SEG, int CELLS>
 __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
   using acc_t = typename std::conditional<PREC == kFP64, double, unsigned long long>::type;
@@ -1876,7 +1895,8 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
   constexpr int kMode = kPush | kDeposit;
   constexpr bool kLin = ORDER == 1;
   constexpr int kArrays = kLin ? 3 : 2;
-  constexpr int kRep = single_rep(CELLS * kSolveThreads);
+  constexpr bool kSolve = CELLS > 0;
+  const int kRep = kSolve ? single_rep(CELLS * kSolveThreads) : single_rep(a.nc);
   constexpr int kPrefetch = 3;
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double sRow[5][4];  // workgroup 0: the row's sums by wavefront
@@ -1886,7 +1906,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nt = blockDim.x;
   const int nwaves = nt >> 6;
-  const bool row = blockIdx.x == 0 && a.acc_in != nullptr;
+  const bool row = kSolve && blockIdx.x == 0 && a.acc_in != nullptr;
   Geo g;
   g.L = a.L;
   g.half_L = a.half_L;
@@ -1923,21 +1943,31 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
     if (a.acc_zero != nullptr) clear_slice();
     return;
   }
-  int cb = 0, nch = 0;
+  // The wavefront's chunks: c0, c0 + stride, ... below cend.  An item's are
+  // consecutive; without the solve the workgroups go through all chunks
+  // together.
+  const int stride = kSolve ? nwaves : nwaves * (int)gridDim.x;
+  int c0 = 0, cend = 0;
   auto range = [&]() {  // a workgroup without an item loads the first one's
-    const int i = max(it, 0);
-    cb = a.chunk_begin + i * tile;
-    nch = min(tile, n_chunks - i * tile);
+    if constexpr (kSolve) {
+      const int i = max(it, 0), cb = a.chunk_begin + i * tile;
+      c0 = cb + wave;
+      cend = cb + min(tile, n_chunks - i * tile);
+    } else {
+      c0 = a.chunk_begin + (int)blockIdx.x * nwaves + wave;
+      cend = a.chunk_begin + a.n_chunks;
+    }
   };
-  // Lane i of wavefront w holds the tables of chunk w + i * waves, the i-th
-  // of the wavefront's (an item has at most 64 chunks per wavefront).
+  // Lane i holds the tables of the wavefront's i-th chunk from c0 on (an item
+  // has at most 64 chunks per wavefront; without the solve, groups of 64).
   WaveTabs<PREC, ORDER, SEG> tabs;
   typename WaveTabs<PREC, ORDER, SEG>::Halos halos;
-  auto lane_chunk = [&]() { return (size_t)(cb + min(wave + lane * nwaves, nch - 1)); };
+  auto lane_chunk = [&]() { return (size_t)min(c0 + lane * stride, cend - 1); };
   uint64_t xr[kPrefetch], cr_[kPrefetch];
   double vr[kPrefetch];
-  auto load_state = [&](int kk, uint64_t &xw, double &v, uint64_t &cw) {  // as in k_tracers
-    const size_t s = kk < nch ? (size_t)(cb + kk) * kChunk + lane : (size_t)cb * kChunk;
+  auto load_state = [&](int c, uint64_t &xw, double &v, uint64_t &cw) {
+    // past the end every lane reads the last chunk's first slot (k_tracers)
+    const size_t s = c < cend ? (size_t)c * kChunk + lane : (size_t)(cend - 1) * kChunk;
     xw = __builtin_nontemporal_load(a.xs + s);
     v = __builtin_nontemporal_load(a.vs + s);
     if constexpr (SEG) cw = a.segq[s];
@@ -1946,7 +1976,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
 #pragma unroll
     for (int j = 0; j < kPrefetch; ++j) {
       xr[j] = cr_[j] = 0;
-      load_state(wave + j * nwaves, xr[j], vr[j], cr_[j]);
+      load_state(c0 + j * stride, xr[j], vr[j], cr_[j]);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -1957,27 +1987,32 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
   Partial pr[2];  // the row: the launch before's partials tid and tid + 256
   int64_t step0 = 0;
   int flags0 = 0;
+  bool solved = false;
+  if constexpr (kSolve) {
   if (a.acc_in != nullptr) {
+    solved = true;
     // The charge: cells tid, tid + threads, ... of every array, the copies
     // summed in copy order (as the solve launch sums them) and passed to the
-    // solve's threads through the item's still unused LDS mesh, so that the
-    // reads are coalesced and spread over all wavefronts.
+    // solve's threads through the item's still unused LDS mesh (with padding,
+    // and the field's room), so that the reads are coalesced and spread over
+    // all wavefronts.
     const sacc_t *in = reinterpret_cast<const sacc_t *>(a.acc_in);
     sacc_t *sAcc = reinterpret_cast<sacc_t *>(t.sP);
-    sacc_t av[kArrays][kRep];
+    constexpr int kCopies = single_rep(CELLS * kSolveThreads);
+    sacc_t av[kArrays][kCopies];
     auto load_acc = [&](int j) {
 #pragma unroll
-      for (int r = 0; r < kRep; ++r)
+      for (int r = 0; r < kCopies; ++r)
 #pragma unroll
-        for (int k = 0; k < kArrays; ++k) av[k][r] = in[(int64_t)(k * kRep + r) * nc + j];
+        for (int k = 0; k < kArrays; ++k) av[k][r] = in[(int64_t)(k * kCopies + r) * nc + j];
     };
     auto sum_acc = [&](int j) {
 #pragma unroll
       for (int k = 0; k < kArrays; ++k) {
         sacc_t sum = (sacc_t)0;
 #pragma unroll
-        for (int r = 0; r < kRep; ++r) sum += av[k][r];
-        sAcc[(int64_t)k * nc + j] = sum;
+        for (int r = 0; r < kCopies; ++r) sum += av[k][r];
+        sAcc[k * padded_cell<CELLS>(nc) + padded_cell<CELLS>(j)] = sum;
       }
     };
     load_acc(min(tid, nc - 1));
@@ -2003,8 +2038,8 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
       for (int k = 0; k < CELLS; ++k) {
         const int j = tid * per + k;
         const bool in_mesh = k < per && j < nc;
-        const int at = in_mesh ? j : 0;
-        const sacc_t p = sAcc[at], d = sAcc[nc + at];
+        const int at = padded_cell<CELLS>(in_mesh ? j : 0);
+        const sacc_t p = sAcc[at], d = sAcc[padded_cell<CELLS>(nc) + at];
         pv[k] = in_mesh ? p : (sacc_t)0;
         dv[k] = in_mesh ? d : (sacc_t)0;
       }
@@ -2016,8 +2051,10 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
     // The accumulators that the launch before read are cleared, a slice per
     // workgroup (the next launch merges into them).
     clear_slice();
-  } else {
-    // the first step of a run: the field is in global memory
+  }
+  }
+  if (!solved) {
+    // the first step of a run (or no solve): the field is in global memory
     halos = tabs.halos(a.halo_in, lane_chunk(), 0);
     load_first_states();
     for (int j = tid; j < nc; j += nt) {
@@ -2038,20 +2075,29 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
     __syncthreads();  // the field, the cleared mesh
     double ke = 0.0, mom = 0.0, ms = 0.0;
     if (it >= 0) {
-      tabs.move(halos, g, t.sE);
-      int i = 0;
-      for (int k = wave; k < nch; k += kPrefetch * nwaves) {
+      for (;;) {
+        tabs.move(halos, g, t.sE);
+        int i = 0;
+        const int gend = kSolve ? cend : min(cend, c0 + kChunk * stride);
+        for (int k = c0; k < gend; k += kPrefetch * stride) {
 #pragma unroll
-        for (int j = 0; j < kPrefetch; ++j) {
-          if (k + j * nwaves < nch)
-            process_chunk<PREC, kMode, ORDER, SEG>(t, g, a.q_unit, a.xs, a.vs, a.halo_out, tabs.entry(i++),
-                                                   (size_t)(cb + k + j * nwaves), lane, xr[j], vr[j], cr_[j], ke, mom,
-                                                   ms, a.mark);
-          load_state(k + (j + kPrefetch) * nwaves, xr[j], vr[j], cr_[j]);
+          for (int j = 0; j < kPrefetch; ++j) {
+            const int c = k + j * stride;
+            if (c < gend)
+              process_chunk<PREC, kMode, ORDER, SEG>(t, g, a.q_unit, a.xs, a.vs, a.halo_out, tabs.entry(i++),
+                                                     (size_t)c, lane, xr[j], vr[j], cr_[j], ke, mom, ms, a.mark);
+            load_state(c + kPrefetch * stride, xr[j], vr[j], cr_[j]);
+          }
         }
+        if constexpr (kSolve) break;
+        c0 += kChunk * stride;
+        if (c0 >= cend) break;
+        tabs.load(a.chunks, a.links, a.cedge, lane_chunk());
+        halos = tabs.halos(a.halo_in, lane_chunk(), 0);
+        load_first_states();
       }
     }
-    const bool with_row = row && it == it0;
+    const bool with_row = kSolve && row && it == it0;
     if (with_row && wave < kSolveThreads / kChunk) {
       // the row's wavefront sums, in the solve launch's order: thread tid
       // sums the items tid, tid + 256, ...
@@ -2212,7 +2258,11 @@ k_deposit_faces(TracerArgs a) {
   qW += wave * kDepQueue;
   const int n_items = *a.n_items;
 
-  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+  // run > 1: a run of consecutive items of one simulation, whose mesh is
+  // cleared before the first and merged after the last
+  const int it_end = a.run > 1 ? min(n_items, ((int)blockIdx.x + 1) * a.run) : n_items;
+  const int it_first = (int)blockIdx.x * a.run, it_step = a.run > 1 ? 1 : gridDim.x;
+  for (int it = it_first; it < it_end; it += it_step) {
     const Item item = a.items[it];
     if (item.inst < 0) continue;  // freed slot
     const InstDesc &I = a.inst[item.inst];
@@ -2227,9 +2277,11 @@ k_deposit_faces(TracerArgs a) {
     const int cb = item.chunk_begin;
     const int nch = item.chunk_end - item.chunk_begin;
 
-    for (int i = tid; i < g.nc; i += blockDim.x) {
-      sP[i] = (acc_t)0;
-      sD[i] = (acc_t)0;
+    if (a.run == 1 || it == it_first) {
+      for (int i = tid; i < g.nc; i += blockDim.x) {
+        sP[i] = (acc_t)0;
+        sD[i] = (acc_t)0;
+      }
     }
     // descriptors, and the word and cell of the tracer after each chunk
     for (int i = tid; i < nch; i += blockDim.x) {
@@ -2384,22 +2436,52 @@ k_deposit_faces(TracerArgs a) {
       for (int w = 0; w < nwaves; ++w) x = nan_max(x, reinterpret_cast<const double *>(qBase + w * kDepQueue)[0]);
       a.partials[it].maxseg = x;
     }
-    const int64_t roff = I.mesh_off + (int64_t)(it % a.rep) * a.rep_stride;
-    acc_t *gP = reinterpret_cast<acc_t *>(a.meshP) + roff;
-    acc_t *gD = reinterpret_cast<acc_t *>(a.meshD) + roff;
-    for (int i = tid; i < g.nc; i += blockDim.x) {
-      const acc_t p = sP[i];
-      const acc_t d = sD[i];
-      if (p != (acc_t)0) {
-        if constexpr (PREC == kFP64) unsafeAtomicAdd(gP + i, p);
-        else atomicAdd(gP + i, p);
-      }
-      if (d != (acc_t)0) {
-        if constexpr (PREC == kFP64) unsafeAtomicAdd(gD + i, d);
-        else atomicAdd(gD + i, d);
+    if (a.run == 1 || it + 1 == it_end) {
+      const int64_t roff = I.mesh_off + (int64_t)((a.run > 1 ? (int)blockIdx.x : it) % a.rep) * a.rep_stride;
+      acc_t *gP = reinterpret_cast<acc_t *>(a.meshP) + roff;
+      acc_t *gD = reinterpret_cast<acc_t *>(a.meshD) + roff;
+      for (int i = tid; i < g.nc; i += blockDim.x) {
+        const acc_t p = sP[i];
+        const acc_t d = sD[i];
+        if (p != (acc_t)0) {
+          if constexpr (PREC == kFP64) unsafeAtomicAdd(gP + i, p);
+          else atomicAdd(gP + i, p);
+        }
+        if (d != (acc_t)0) {
+          if constexpr (PREC == kFP64) unsafeAtomicAdd(gD + i, d);
+          else atomicAdd(gD + i, d);
+        }
       }
     }
     __syncthreads();
+  }
+}
+
+// An accumulator summed over its copies, in copy order, into LDS, and cleared;
+// consecutive threads take consecutive cells, all copies of 16 rows of them in
+// flight together.
+template <class T, int REP>
+__device__ __forceinline__ void take_lds(T *g, int nc, int64_t rep_stride, T *out) {
+  constexpr int kU = 16;
+  for (int j0 = threadIdx.x; j0 < nc; j0 += kU * kSolveThreads) {
+    T v[kU][REP];
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+#pragma unroll
+      for (int r = 0; r < REP; ++r) v[u][r] = g[r * rep_stride + min(j0 + u * kSolveThreads, nc - 1)];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int j = j0 + u * kSolveThreads;
+      if (j < nc) {
+        T sum = (T)0;
+#pragma unroll
+        for (int r = 0; r < REP; ++r) {
+          sum += v[u][r];
+          g[r * rep_stride + j] = (T)0;
+        }
+        out[padded_cell<16>(j)] = sum;
+      }
+    }
   }
 }
 
@@ -2422,7 +2504,19 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(SolveArgs a) {
   acc_t *gP = reinterpret_cast<acc_t *>(a.meshP) + kc.mesh_off;
   acc_t *gD = reinterpret_cast<acc_t *>(a.meshD) + kc.mesh_off;
   acc_t pv[CELLS], dv[CELLS];
-  solve_take<PREC, CELLS, REP>(kc, gP, gD, a.rep_stride, pv, dv);  // in flight with the partial loads below
+  // With 16 cells per thread (128 bytes apart from thread to thread) the
+  // accumulators, the field and the density go through LDS, so that global
+  // memory is read and written in whole lines (4096 cells, two copies: 26 ->
+  // 14 us).
+  constexpr bool kLds = CELLS == 16;
+  extern __shared__ __align__(16) unsigned char smem[];
+  acc_t *sAcc = reinterpret_cast<acc_t *>(smem);
+  if constexpr (kLds) {
+    take_lds<acc_t, REP>(gP, kc.nc, a.rep_stride, sAcc);
+    take_lds<acc_t, REP>(gD, kc.nc, a.rep_stride, sAcc + padded_cell<CELLS>(kc.nc));
+  } else {
+    solve_take<PREC, CELLS, REP>(kc, gP, gD, a.rep_stride, pv, dv);  // in flight with the partial loads below
+  }
 
   // 1. work-item partials, in item order: each thread sums items tid,
   // tid + 256, ... (loads issued four at a time), then the wavefront and
@@ -2460,8 +2554,32 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(SolveArgs a) {
   mom = sMom[0] + sMom[1] + sMom[2] + sMom[3];
   ms = nan_max(nan_max(sMs[0], sMs[1]), nan_max(sMs[2], sMs[3]));
   acc_t *gRamp = (a.order == 1 && a.meshR) ? reinterpret_cast<acc_t *>(a.meshR) + kc.mesh_off : nullptr;
-  const FieldSums f = solve_field<PREC, CELLS, REP>(kc, pv, dv, gRamp, a.rep_stride, (double *)nullptr, false,
-                                                    a.meshE + kc.mesh_off, a.meshRho + kc.mesh_off);
+  FieldSums f;
+  if constexpr (kLds) {
+    const int per = (kc.nc + kSolveThreads - 1) / kSolveThreads;
+#pragma unroll
+    for (int k = 0; k < CELLS; ++k) {
+      const int j = tid * per + k;
+      const bool in = k < per && j < kc.nc;
+      const int at = padded_cell<CELLS>(in ? j : 0);
+      const acc_t pj = sAcc[at], dj = sAcc[padded_cell<CELLS>(kc.nc) + at];
+      pv[k] = in ? pj : (acc_t)0;
+      dv[k] = in ? dj : (acc_t)0;
+    }
+    // the field over the cells' P, the density over their D (the same thread's)
+    double *sE = reinterpret_cast<double *>(smem), *sRho = sE + padded_cell<CELLS>(kc.nc);
+    __syncthreads();
+    f = solve_field<PREC, CELLS, REP, true>(kc, pv, dv, gRamp, a.rep_stride, (double *)nullptr, false, sE, sRho);
+    __syncthreads();
+    double *gE = a.meshE + kc.mesh_off, *gR = a.meshRho + kc.mesh_off;
+    for (int j = tid; j < kc.nc; j += kSolveThreads) {
+      gE[j] = sE[padded_cell<CELLS>(j)];
+      gR[j] = sRho[padded_cell<CELLS>(j)];
+    }
+  } else {
+    f = solve_field<PREC, CELLS, REP>(kc, pv, dv, gRamp, a.rep_stride, (double *)nullptr, false,
+                                      a.meshE + kc.mesh_off, a.meshRho + kc.mesh_off);
+  }
   const double W = field_energy(f, kc.dx);
   int flags = Ip->flags;
   if (a.refined != nullptr) {
@@ -3243,7 +3361,24 @@ static hipError_t deposit_faces(const TracerArgs &a, int grid, int block, hipStr
     lds = dep_lds_bytes<SEG>(a.mesh_cells, a.tile_cap, block / kChunk);
   }
   if (lds > kLdsMax) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_deposit_faces<PREC, SEG>), dim3(grid), dim3(block), lds, st, a);
+  TracerArgs b = a;
+  if (grid <= kComputeUnits) b.run = 1;  // fewer than run at a time in any case
+  if (b.run > 1) {
+    // a.run items per workgroup at most, fewer while workgroups are left that
+    // would run at the same time
+    int per_cu = 1;
+    const hipError_t e =
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k_deposit_faces<PREC, SEG>, block, lds);
+    if (e != hipSuccess) return e;
+    // where the LDS mesh leaves a compute unit one or two workgroups, they
+    // have little to do while one of them clears or merges (67M tracers on
+    // 4096 cells 150 -> 140 us); four overlap one another, and one item at a
+    // time spreads better (1024 cells: 138 us, 143 in runs of four)
+    const int resident = std::max(1, per_cu) * kComputeUnits;
+    b.run = per_cu > 2 ? 1 : std::max(1, std::min(b.run, (grid + resident - 1) / resident));
+    grid = (grid + b.run - 1) / b.run;
+  }
+  hipLaunchKernelGGL((k_deposit_faces<PREC, SEG>), dim3(grid), dim3(block), lds, st, b);
   return hipGetLastError();
 }
 
@@ -3363,6 +3498,38 @@ struct LaunchStep {
   }
 };
 
+template <int PREC, int ORDER, bool SEG>
+struct LaunchRun {
+  static hipError_t run(const StepArgs &a, int block, size_t lds, hipStream_t st, int *grid) {
+    // as many workgroups as run at a time
+    int per_cu = 1;
+    const void *f = (const void *)k_step<PREC, ORDER, SEG, 0>;
+    if (lds > 65536) {
+      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return e;
+      }
+    }
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, block, lds);
+    if (e != hipSuccess) return e;
+    StepArgs b = a;
+    const int n = std::max(1, std::min(*grid, std::max(1, per_cu) * kComputeUnits));
+    b.n_items = n;
+    *grid = n;
+    hipLaunchKernelGGL((k_step<PREC, ORDER, SEG, 0>), dim3(n), dim3(block), lds, st, b);
+    return hipGetLastError();
+  }
+};
+
+int launch_run(int prec, int order, bool seg, const StepArgs &a, int block, void *stream, int *grid) {
+  if (a.nc < 1 || a.nc > kMaxCells || block < kChunk || block > 1024 || a.n_chunks < 1 || *grid < 1 ||
+      a.acc_in != nullptr || a.acc_zero != nullptr || a.sel.state != nullptr)
+    return (int)hipErrorInvalidValue;
+  const size_t lds = tracer_lds_size(prec, order, seg, a.nc, 0);
+  return (int)dispatch<LaunchRun>(prec, order, seg, a, block, lds, (hipStream_t)stream, grid);
+}
+
 int launch_step(int prec, int order, bool seg, const StepArgs &a, int grid, int block, void *stream) {
   // a wavefront stages at most 64 chunks of an item: a.tile <= block
   if (!step_supported(order, a.nc) || block < kSolveThreads || a.tile < 1 || a.tile > block || a.n_items < 1 ||
@@ -3442,21 +3609,32 @@ int launch_resident(int prec, int order, bool seg, const TracerArgs &a, const So
                                        (hipStream_t)stream);
 }
 
+template <int PREC, int CELLS, int REP>
+static hipError_t solve_launch(const SolveArgs &a, int n_blocks, hipStream_t st) {
+  // 16 cells per thread: the accumulators of the largest mesh in LDS, padded
+  // (68 KB beside the static LDS)
+  constexpr size_t lds = CELLS == 16 ? 2 * sizeof(double) * (CELLS + 1) * kSolveThreads : 0;
+  if constexpr (lds > 0) {
+    static std::atomic<bool> limit_set{false};
+    if (!limit_set.load()) {
+      const hipError_t e = hipFuncSetAttribute((const void *)k_solve<PREC, CELLS, REP>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+      limit_set.store(true);
+    }
+  }
+  hipLaunchKernelGGL((k_solve<PREC, CELLS, REP>), dim3(n_blocks), dim3(kSolveThreads), lds, st, a);
+  return hipGetLastError();
+}
+
 template <int CELLS, int REP>
 static hipError_t solve_cells_launch(int prec, const SolveArgs &a, int n_blocks, hipStream_t st) {
   switch (prec) {
-    case kFP64:
-      hipLaunchKernelGGL((k_solve<kFP64, CELLS, REP>), dim3(n_blocks), dim3(kSolveThreads), 0, st, a);
-      break;
-    case kSplitF32:
-      hipLaunchKernelGGL((k_solve<kSplitF32, CELLS, REP>), dim3(n_blocks), dim3(kSolveThreads), 0, st, a);
-      break;
-    case kSplitU32:
-      hipLaunchKernelGGL((k_solve<kSplitU32, CELLS, REP>), dim3(n_blocks), dim3(kSolveThreads), 0, st, a);
-      break;
+    case kFP64: return solve_launch<kFP64, CELLS, REP>(a, n_blocks, st);
+    case kSplitF32: return solve_launch<kSplitF32, CELLS, REP>(a, n_blocks, st);
+    case kSplitU32: return solve_launch<kSplitU32, CELLS, REP>(a, n_blocks, st);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 template <int REP>

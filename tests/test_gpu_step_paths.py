@@ -85,3 +85,41 @@ def test_single_launch_steps_follow_the_launch_pairs(case, prec, order, charges)
     np.testing.assert_allclose(ha["KE"][:-1], hb["KE"][:-1], rtol=1e-11)
     scale = np.max(np.abs(hb["KE"][:-1])) * 2
     assert np.max(np.abs(ha["momentum"][:-1] - hb["momentum"][:-1])) < 1e-11 * scale
+
+
+@pytest.mark.parametrize("order,cells,charges", [(0, 600, False), (0, 600, True), (1, 600, False), (2, 600, True),
+                                                 (0, 3000, False), (1, 3000, False)])
+@pytest.mark.parametrize("prec", [B.SIC_FP64, B.SIC_SPLIT_U32])
+def test_long_runs_of_chunks_follow_the_work_items(prec, order, cells, charges):
+    """A simulation of more than 512 work items steps with as many workgroups
+    as run at a time; a tuned item size keeps the work items.  Several groups
+    of 64 chunks per wavefront on 3000 cells, one on 600."""
+    rng = np.random.default_rng(cells)
+    m = 3000 if cells == 600 else 9000
+    counts = rng.integers(600, 800, m)
+    counts[:3] = (2, 64, 65)
+    p, x, v, c = _problem([int(n) for n in counts], cells, charges)
+    print(f"case runs prec={prec} order={order} cells={cells} charges={charges}", flush=True)
+    res = []
+    for tile in (0, 128):
+        with B.Simulation(p, precision=prec, x0=x, v0=v, deposit_order=order, seg_charges=c, history_rows=16) as s:
+            if tile:
+                B.sic_set_tuning(s.h, tile_chunks=tile)
+            else:
+                assert B.sic_get_tuning(s.h)["grid_blocks"] > 512
+            s.step(4)
+            if not tile:
+                assert B.sic_last_step_path(s.h) == B.SIC_PATH_FUSED
+            res.append((s.state(), s.diagnostics()))
+    (xa, va, na), da = res[0]
+    (xb, vb, nb), db = res[1]
+    assert na == nb == 4
+    if prec == B.SIC_FP64:
+        # float64 sums of up to 1e5 additions per cell in another order
+        assert np.max(periodic_diff(xa, xb, p.L)) < 1e-12 * p.L
+        np.testing.assert_allclose(da["history"]["W_E"], db["history"]["W_E"], rtol=1e-9)
+    else:
+        assert np.array_equal(xa, xb) and np.array_equal(va, vb)
+        assert np.array_equal(da["E"], db["E"])
+        assert np.array_equal(da["history"]["max_segment"], db["history"]["max_segment"])
+    np.testing.assert_allclose(da["history"]["KE"][:-1], db["history"]["KE"][:-1], rtol=1e-11)
