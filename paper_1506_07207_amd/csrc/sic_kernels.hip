@@ -49,11 +49,20 @@ namespace sic {
 
 namespace {
 
+// c reduced by one period either way, for c in [-period, 2 period): of c and
+// c + period the smaller as unsigned integers is the one that is not negative,
+// and so for c and c - period (four instructions where compares and selects
+// take seven).
+__device__ __forceinline__ uint32_t wrap_once(int c, uint32_t period) {
+  const uint32_t r = min((uint32_t)c, (uint32_t)c + period);
+  return min(r, r - period);
+}
+
 // Cell index modulo nc for c in [-nc, 2nc); anything else (only reachable
-// from non-finite data) is clamped to cell 0 so that no access leaves the mesh.
+// from non-finite data) is clamped to the last cell so that no access leaves
+// the mesh.
 __device__ __forceinline__ int wrap_cell(int c, int nc) {
-  c = c < 0 ? c + nc : (c >= nc ? c - nc : c);
-  return ((unsigned)c < (unsigned)nc) ? c : 0;
+  return (int)min(wrap_once(c, (uint32_t)nc), (uint32_t)nc - 1u);
 }
 
 // Periodic reduction of a position into [0, L).  The common case moves at
@@ -135,6 +144,9 @@ template <int PREC>
 __device__ __forceinline__ double mesh_pos(uint64_t w, double inv_dx) {
   if constexpr (PREC == kFP64) {
     return __longlong_as_double((long long)w) * inv_dx;
+  } else if constexpr (PREC == kSplitF32) {
+    // the index with its cell, in sub-cells: one rounding
+    return ((double)(uint32_t)w + (double)__uint_as_float((uint32_t)(w >> 32))) * 0x1p-20;
   } else {
     return (double)split_cell<PREC>(w) + split_frac<PREC>(w);
   }
@@ -176,9 +188,9 @@ __device__ __forceinline__ uint64_t advance_split(uint64_t w, double du, int nc)
   if (!(t - t == 0.0)) return w;
   const double k = floor(t);
   const double r = t - k;
-  // a step of under 2^31 units converts through a 32-bit integer; longer
+  // a step of under 2^30 units converts through a 32-bit integer; longer
   // ones (and their 64-bit conversion) take the rare branch below
-  const bool near = fabs(k) < 0x1p31;
+  const bool near = fabs(k) < 0x1p30;
   long long carry = 0;
   uint32_t bits;
   if constexpr (PREC == kSplitF32) {
@@ -203,11 +215,14 @@ __device__ __forceinline__ uint64_t advance_split(uint64_t w, double du, int nc)
   long long idx = 0;
   if constexpr (PREC == kSplitU32) {
     // the cell index is below 4096: a near move stays in 32-bit integers
-    int c = (int)(uint32_t)w + (int)(near ? k : 0.0) + (int)carry;
-    if (c >= nc) c -= nc;
-    else if (c < 0) c += nc;
-    far = far || (unsigned)c >= (unsigned)nc;
+    const uint32_t c = wrap_once((int)(uint32_t)w + (int)(near ? k : 0.0) + (int)carry, (uint32_t)nc);
+    far = far || c >= (uint32_t)nc;
     idx = c;
+  } else if (nc <= (1 << (30 - kSubBits))) {
+    // and so does one of an index below 2^30
+    const uint32_t i = wrap_once((int)(uint32_t)w + (int)(near ? k : 0.0) + (int)carry, (uint32_t)period);
+    far = far || i >= (uint32_t)period;
+    idx = i;
   } else {
     idx = (long long)(uint32_t)w + (long long)(int)(near ? k : 0.0) + carry;
     if (idx >= period) idx -= period;
@@ -310,14 +325,10 @@ __device__ __forceinline__ double deposit_fp64(double a, double b, double q, con
   return ad;
 }
 
-// Split-form segment; positions in mesh units ua = cell + fraction.
+// Split-form segment from word wa at ua to ub (mesh_pos).
 template <int PREC>
-__device__ __forceinline__ double deposit_split(uint64_t wa, uint64_t wb, long long qf, const Geo &g,
+__device__ __forceinline__ double deposit_split(uint64_t wa, double ua, double ub, long long qf, const Geo &g,
                                                 unsigned long long *sP, unsigned long long *sD) {
-  const int ca = split_cell<PREC>(wa);
-  const double fa = split_frac<PREC>(wa);
-  const double ua = (double)ca + fa;
-  const double ub = mesh_pos<PREC>(wb, g.inv_dx);
   const double half_nc = 0.5 * (double)g.nc;
   double du = ub - ua;
   if (du >= half_nc) du -= (double)g.nc;
@@ -325,7 +336,8 @@ __device__ __forceinline__ double deposit_split(uint64_t wa, uint64_t wb, long l
   const double ad = fabs(du) * g.dx;
   if (!(fabs(du) <= half_nc)) return ad;
   if (du == 0.0) {
-    const int c = wrap_cell(fa == 0.0 ? ca - 1 : ca, g.nc);
+    const int ca = split_cell<PREC>(wa);
+    const int c = wrap_cell(split_frac<PREC>(wa) == 0.0 ? ca - 1 : ca, g.nc);
     lds_add(sP + c, (unsigned long long)qf);
     return 0.0;
   }
@@ -536,6 +548,15 @@ __device__ __forceinline__ SegGeo lin_geo(uint64_t wa, uint64_t wb, const Geo &g
     s.u = mesh_pos<PREC>(wa, g.inv_dx);
     s.d = min_image_cells(mesh_pos<PREC>(wb, g.inv_dx) - s.u, 0.5 * (double)g.nc, (double)g.nc);
   }
+  s.c = s.u + 0.5 * s.d;
+  return s;
+}
+
+// The same of split positions, from their mesh positions.
+__device__ __forceinline__ SegGeo lin_geo_mesh(double ua, double ub, const Geo &g) {
+  SegGeo s;
+  s.u = ua;
+  s.d = min_image_cells(ub - ua, 0.5 * (double)g.nc, (double)g.nc);
   s.c = s.u + 0.5 * s.d;
   return s;
 }
@@ -1375,6 +1396,7 @@ __device__ __forceinline__ double mark_length(uint64_t wa, uint64_t wb, const Ge
 struct ChunkTab {
   ChunkDesc d;
   uint64_t edge, next;
+  double next_u;  // split forms: the mesh position of next
   LinNb before, after;
 };
 
@@ -1386,6 +1408,7 @@ struct WaveTabs {
   int2 lk;                 // order 1
   uint64_t e0, e1;         // per-segment charges
   uint64_t next;           // the moved tracers around the chunk (ChunkTab)
+  double next_u;
   LinNb before, after;
 
   __device__ __forceinline__ void load(const ChunkDesc *chunks, const int2 *links, const uint64_t *cedge, size_t c) {
@@ -1423,6 +1446,7 @@ struct WaveTabs {
     } else {
       next = moved_halo<PREC, kPush | kDeposit>(h.first, g, sE);
     }
+    if constexpr (PREC != kFP64) next_u = mesh_pos<PREC>(next, g.inv_dx);
   }
   // The entry of the wavefront's i-th chunk, from lane i.
   __device__ __forceinline__ ChunkTab entry(int i) const {
@@ -1436,7 +1460,8 @@ struct WaveTabs {
     t.d.n_valid = __builtin_amdgcn_readlane(d.n_valid, i);
     t.d.flags = __builtin_amdgcn_readlane(d.flags, i);
     t.edge = SEG ? read_lane64(e0, i) : 0;
-    t.next = read_lane64(next, i);
+    t.next = read_lane64(next, i);  // not read where the form has no use for it
+    t.next_u = PREC == kFP64 ? 0.0 : f64(next_u);
     if constexpr (ORDER == 1) {
       t.before.d = f64(before.d);
       t.before.r = f64(before.r);
@@ -1472,30 +1497,33 @@ __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t
     cl = lane == 0 ? tab.edge : up;
   }
   if constexpr (kField) {
+    // The padding slots of a sheet's last chunk move with the others (they
+    // start at rest at 0, and nothing reads them); they have no mass.
     const double e = gather_field_ghost(t.sE, mesh_pos<PREC>(xw, g.inv_dx), g.nc);
     if constexpr (kKick) {
-      const double vk = v - (0.5 * g.dt) * e;
-      v = valid ? vk : v;
+      v = v - (0.5 * g.dt) * e;
       vs[s] = v;
     } else {
       const double vn = v + g.dt * e;
-      double m;
+      double qv;
       if constexpr (SEG) {
-        m = tracer_mass<PREC>(cl, cw, q_unit);
+        qv = tracer_mass<PREC>(cl, cw, q_unit);
       } else {
         // half of each segment the tracer bounds: the ends of an open
         // sheet bound one
-        const bool end = (lane == 0 && (ch.flags & kChunkOpenStart)) || (lane == n_valid - 1 && ch.partner < 0);
-        m = end ? 0.5 * ch.q : ch.q;
+        qv = ch.q;
+        if (__builtin_amdgcn_readfirstlane((ch.flags & kChunkOpenStart) | (ch.partner & (int)0x80000000)) != 0) {
+          const bool end = (lane == 0 && (ch.flags & kChunkOpenStart)) || (lane == n_valid - 1 && ch.partner < 0);
+          qv = end ? 0.5 * ch.q : ch.q;
+        }
       }
-      const double qv = valid ? m : 0.0;
+      if (n_valid < kChunk) qv = valid ? qv : 0.0;
       // twice the kinetic energy and momentum: the factor 1/2 is applied
       // to the item's sums (a power of two, so the same bits)
       ke += qv * v * vn;
       mom += qv * (v + vn);
-      const uint64_t xn = drift<PREC>(xw, vn, g.dt, g.L, g.inv_dx, g.nc);
-      xw = valid ? xn : xw;
-      v = valid ? vn : v;
+      xw = drift<PREC>(xw, vn, g.dt, g.L, g.inv_dx, g.nc);
+      v = vn;
       if constexpr (STORE) {
         __builtin_nontemporal_store(xw, xs + s);
         __builtin_nontemporal_store(v, vs + s);
@@ -1511,6 +1539,14 @@ __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t
       if (lane == 0) halo_out[chunk] = hv2;
     }
   }
+  // split forms: a lane's mesh position serves its own segment and the one
+  // before it
+  double ua = 0.0, ub = 0.0;
+  if constexpr (kDep && PREC != kFP64) {
+    ua = mesh_pos<PREC>(xw, g.inv_dx);
+    ub = lane_down1(ua);
+    if (lane == n_valid - 1) ub = tab.next_u;
+  }
   if constexpr (kDep && kLin) {
     // Every lane computes its own segment's geometry and density; the
     // gradient takes the neighbouring segments' from the lanes next to
@@ -1520,7 +1556,9 @@ __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t
     const uint64_t dn1 = lane_down1(xw);  // all lanes active: a DPP move reads its neighbour's register
     const uint64_t xp1 = last ? tab.next : dn1;
     const bool has_seg = valid && (!last || ch.partner >= 0);
-    SegGeo sg = lin_geo<PREC>(xw, xp1, g);
+    SegGeo sg;
+    if constexpr (PREC == kFP64) sg = lin_geo<PREC>(xw, xp1, g);
+    else sg = lin_geo_mesh(ua, ub, g);
     if (!has_seg) sg.d = 0.0;  // a neighbour without a segment drops the gradient
     double q0 = ch.q;
     long long q0_fix = ch.q_fix;
@@ -1575,7 +1613,7 @@ __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t
       if constexpr (ORDER == 2) {
         // first-order weighting: geometry in mesh units, minimum image as
         // for the constant scheme
-        double ua, dm;
+        double dm;
         if constexpr (PREC == kFP64) {
           const double xa = __longlong_as_double((long long)xw);
           double d = __longlong_as_double((long long)pw) - xa;
@@ -1584,8 +1622,7 @@ __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t
           ua = xa * g.inv_dx;
           dm = d * g.inv_dx;
         } else {
-          ua = mesh_pos<PREC>(xw, g.inv_dx);
-          dm = min_image_cells(mesh_pos<PREC>(pw, g.inv_dx) - ua, 0.5 * (double)g.nc, (double)g.nc);
+          dm = min_image_cells(ub - ua, 0.5 * (double)g.nc, (double)g.nc);
         }
         len = fabs(dm) * g.dx;
         if (len <= g.half_L) {
@@ -1597,7 +1634,7 @@ __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t
           len = deposit_fp64(__longlong_as_double((long long)xw), __longlong_as_double((long long)pw), q0, g,
                              t.sP, t.sD);
         } else {
-          len = deposit_split<PREC>(xw, pw, q0_fix, g, t.sP, t.sD);
+          len = deposit_split<PREC>(xw, ua, ub, q0_fix, g, t.sP, t.sD);
         }
       }
       ms = nan_max(ms, len);
@@ -1805,8 +1842,8 @@ __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
                                         t.sPrevNb + i, t.sNextNb + i);
         } else if (pc >= 0) {
           double2 h = (pc == cb + i + 1 && i + 1 < nch) ? t.sHalo[i] : a.halo_in[pc];
-          h.x = __longlong_as_double((long long)moved_halo<PREC, MODE>(h, g, t.sE));
-          t.sHalo[i] = h;
+          const uint64_t w = moved_halo<PREC, MODE>(h, g, t.sE);
+          t.sHalo[i] = make_double2(__longlong_as_double((long long)w), mesh_pos<PREC>(w, g.inv_dx));
         }
       }
       __syncthreads();
@@ -1827,10 +1864,13 @@ __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
           if constexpr (kNeedQ) tab.edge = t.sEdge[2 * kk];
           if constexpr (kDep && kLin) {
             tab.next = t.sNextW[kk];
+            if constexpr (PREC != kFP64) tab.next_u = mesh_pos<PREC>(tab.next, g.inv_dx);
             tab.before = t.sPrevNb[kk];
             tab.after = t.sNextNb[kk];
           } else if constexpr (kDep) {
-            tab.next = (uint64_t)__double_as_longlong(t.sHalo[kk].x);
+            const double2 h = t.sHalo[kk];
+            tab.next = (uint64_t)__double_as_longlong(h.x);
+            tab.next_u = h.y;
           }
           process_chunk<PREC, MODE, ORDER, SEG>(t, g, I.q_unit, a.xs, a.vs, kLin ? a.halo3_out : a.halo_out, tab,
                                                 (size_t)(cb + kk), lane, xr[j], vr[j], cr_[j], ke, mom, ms, a.mark);
