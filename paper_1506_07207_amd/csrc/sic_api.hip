@@ -994,17 +994,37 @@ StepArgs step_args(Pool *p) {
   return a;
 }
 
+// Work items of solve-first steps.  Two items per compute unit are taken as
+// one, by a workgroup of twice the threads: every compute unit solves once
+// instead of twice and merges half as often (2.1M tracers on 1024 cells: 26.0
+// -> 24.8 us per step).  Not with a tuned shape.
+struct SfShape {
+  int n_items, tile, block;
+};
+SfShape sf_shape(const Pool *p) {
+  SfShape s{p->slots[0].n_items, p->tile, p->block};
+  if (!p->dev_refine && p->tune.tile_chunks == 0 && p->tune.block_threads == 0 && p->tune.grid_blocks == 0 &&
+      s.n_items > kComputeUnits && 2 * s.block <= 1024) {
+    s.tile *= 2;
+    s.block *= 2;
+    s.n_items = (s.n_items + 1) / 2;
+  }
+  return s;
+}
+
 // Step i of a run of solve-first steps.
 sic_status enqueue_sf(Pool *p, int64_t i, hipStream_t st) {
-  const SlotHost &sh = p->slots[0];
+  const SfShape shape = sf_shape(p);
   Partial *part[2] = {p->partials, p->sf_part};
   StepArgs a = step_args(p);
+  a.n_items = shape.n_items;
+  a.tile = shape.tile;
   a.acc_in = i > 0 ? sf_set(p, i - 1) : nullptr;
   a.acc_out = sf_set(p, i);
   a.acc_zero = i > 0 ? sf_set(p, i + 1) : nullptr;
   a.part_in = part[(i + 1) % 2];
   a.part_out = part[i % 2];
-  int grid = std::min(grid_for(p, -1), sh.n_items);
+  int grid = std::min(grid_for(p, -1), shape.n_items);
   if (p->dev_refine) {
     a.sel = refine_sel(p);
     a.mark = mark_args(p);
@@ -1012,7 +1032,7 @@ sic_status enqueue_sf(Pool *p, int64_t i, hipStream_t st) {
     a.part_ref = p->dr_part;
     grid = std::min(grid, kRefineGroups);
   }
-  LAUNCHCHK(p, launch_step(p->prec, p->order, p->seg, a, grid, p->block, st));
+  LAUNCHCHK(p, launch_step(p->prec, p->order, p->seg, a, grid, shape.block, st));
   p->parity ^= 1;
   return SIC_OK;
 }
@@ -1032,6 +1052,7 @@ sic_status close_sf(Pool *p, int64_t k, hipStream_t st, const int32_t *rs = null
     sa.zero = sf_set(p, k - 2);
     sa.zero_words = acc_words(p);
   }
+  sa.n_partials = sf_shape(p).n_items;
   if (rs) {
     const int fixed = p->tune.tile_chunks > 0 ? p->tile : 0;
     sa.respect_active = 0;
