@@ -197,6 +197,7 @@ struct Pool {
   // host memory that the device writes a call's results to (allocated on
   // first use), room for pin_rows history rows
   unsigned char *pin = nullptr;
+  size_t pin_bytes = 0;
   int64_t pin_rows = 0;
 
   std::vector<SlotHost> slots;
@@ -280,6 +281,53 @@ hipError_t scratch_address(int device, double **out) {
     }                                                                                            \
   } while (0)
 
+// Blocks of host memory for calls' results, kept for the next simulation when
+// one is destroyed (allocating and freeing such memory takes 60 and 20 us, as
+// long as a small simulation's call): at most kPinKept of them, shared by all
+// threads and devices.
+constexpr size_t kPinKept = 8;
+std::mutex g_pin_mu;
+std::vector<std::pair<unsigned char *, size_t>> g_pin_kept;
+
+hipError_t pin_take(size_t bytes, unsigned char **out, size_t *got) {
+  {
+    std::lock_guard<std::mutex> lock(g_pin_mu);
+    for (size_t i = 0; i < g_pin_kept.size(); ++i) {
+      if (g_pin_kept[i].second >= bytes) {
+        *out = g_pin_kept[i].first;
+        *got = g_pin_kept[i].second;
+        g_pin_kept.erase(g_pin_kept.begin() + (long)i);
+        return hipSuccess;
+      }
+    }
+  }
+  void *ptr = nullptr;
+  const hipError_t e = hipHostMalloc(&ptr, bytes, hipHostMallocPortable);
+  if (e != hipSuccess) return e;
+  *out = static_cast<unsigned char *>(ptr);
+  *got = bytes;
+  return hipSuccess;
+}
+
+void pin_give(unsigned char *ptr, size_t bytes) {
+  if (!ptr) return;
+  unsigned char *drop = ptr;
+  {
+    std::lock_guard<std::mutex> lock(g_pin_mu);
+    if (g_pin_kept.size() < kPinKept) {
+      g_pin_kept.push_back({ptr, bytes});
+      drop = nullptr;
+    } else {  // the smallest goes
+      for (auto &k : g_pin_kept)
+        if (k.second < bytes) {
+          std::swap(k.first, drop);
+          std::swap(k.second, bytes);
+        }
+    }
+  }
+  if (drop) hipHostFree(drop);
+}
+
 template <class T>
 hipError_t dalloc(T **p, size_t n) {
   if (n == 0) n = 1;
@@ -307,7 +355,7 @@ void pool_free(Pool *p) {
                   p->sf_mesh,   p->sf_part,  p->in_off};
   for (void *b : bufs)
     if (b) hipFree(b);
-  if (p->pin) hipHostFree(p->pin);
+  pin_give(p->pin, p->pin_bytes);  // the stream has been waited for: nothing writes it any more
   if (p->cap) hipStreamDestroy(p->cap);
   delete p;
 }
@@ -1689,10 +1737,8 @@ constexpr int64_t kPinRows = 1024;
 sic_status ensure_pin(Pool *p) {
   if (p->pin) return SIC_OK;
   const int64_t rows = std::min(p->hist_rows, kPinRows);
-  void *ptr = nullptr;
-  HIPCHK(p, hipHostMalloc(&ptr, kExportMesh + 2 * sizeof(double) * p->max_cells + sizeof(DiagRow) * (size_t)rows,
-                          hipHostMallocDefault));
-  p->pin = static_cast<unsigned char *>(ptr);
+  HIPCHK(p, pin_take(kExportMesh + 2 * sizeof(double) * p->max_cells + sizeof(DiagRow) * (size_t)rows, &p->pin,
+                     &p->pin_bytes));
   p->pin_rows = rows;
   return SIC_OK;
 }
