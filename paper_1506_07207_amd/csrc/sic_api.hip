@@ -114,7 +114,9 @@ struct SlotHost {
   int32_t item_begin = 0, n_items = 0;
   std::vector<int64_t> chunk_in_off;
   int state = kStale;
-  int64_t step = 0;  // a single simulation's step (a batch's slots count theirs on the device)
+  // a single simulation's step; a batch's slots take every batch step from
+  // admission (the pool's clock0) on until they have run n_run (< 0: no end)
+  int64_t step = 0, clock0 = 0, n_run = -1;
   // the step the diagnostics history starts at: 0, or the step a state was
   // set or loaded at (rows before it were never written by this simulation)
   int64_t hist_from = 0;
@@ -200,6 +202,7 @@ struct Pool {
   size_t pin_bytes = 0;
   int64_t pin_rows = 0;
 
+  int64_t clock = 0;  // steps of a batch so far
   std::vector<SlotHost> slots;
   std::vector<Item> items_up;  // work items being uploaded
   ChunkAllocator alloc;       // tracer chunks
@@ -1481,6 +1484,8 @@ sic_status pool_admit(Pool *p, const sic_config *cfg, const sic_sheet *sheets, i
   sh.max_tracers = reserve_tr;
   sh.hist_from = 0;
   sh.step = 0;
+  sh.clock0 = p->clock;
+  sh.n_run = n_steps;
   sh.chunk_begin = (int32_t)cb;
   sh.n_chunks = (int32_t)n_ch;
   sh.n_chunks_res = (int32_t)n_res;
@@ -1764,6 +1769,14 @@ sic_status export_slot(Pool *p, int32_t slot, bool mesh, int64_t rows, InstDesc 
   return SIC_OK;
 }
 
+// The step that a slot's launches so far take it to.
+int64_t slot_step(const Pool *p, int32_t slot) {
+  const SlotHost &sh = p->slots[slot];
+  if (!p->batch) return sh.step;
+  const int64_t ran = p->clock - sh.clock0;
+  return sh.n_run < 0 ? ran : std::min(ran, sh.n_run);
+}
+
 int64_t history_avail(const Pool *p, int32_t slot, int64_t step) {
   return std::min<int64_t>(step + 1 - std::min(step, p->slots[slot].hist_from), p->hist_rows);
 }
@@ -1771,8 +1784,8 @@ int64_t history_avail(const Pool *p, int32_t slot, int64_t step) {
 sic_status pool_diagnostics(Pool *p, int32_t slot, sic_diag *out, double *rho_out, double *E_out,
                             sic_diag *history_out, int64_t *history_len) {
   if (slot < 0 || slot >= p->slot_cap || !p->slots[slot].live) return fail(p, SIC_EINVAL, "slot not live");
-  if (!p->batch && !out && !rho_out && !E_out && history_len && !history_out) {
-    *history_len = history_avail(p, slot, p->slots[slot].step);
+  if (!out && !rho_out && !E_out && history_len && !history_out) {
+    *history_len = history_avail(p, slot, slot_step(p, slot));
     return SIC_OK;
   }
   InstDesc I;
@@ -1833,22 +1846,15 @@ sic_status pool_get_state(Pool *p, int32_t slot, double *x, double *v, int64_t *
   ea.v_out = dv;
   ea.c_out = nullptr;
   int le = launch_extract(p->prec, ea, p->stream);
-  sic_status st = SIC_OK;
-  if (step && p->batch) {  // a batch's slots count their steps on the device
-    InstDesc I;
-    st = export_slot(p, slot, false, 0, &I);
-    if (st == SIC_OK) *step = I.step;
-  }
-  hipError_t e = (step && p->batch && st == SIC_OK) ? hipSuccess : hipStreamSynchronize(p->stream);
+  hipError_t e = hipStreamSynchronize(p->stream);
   if (le == 0 && e == hipSuccess && stage && x)
     e = hipMemcpy(x, dx, sizeof(double) * (size_t)sh.n_tracers, hipMemcpyDeviceToHost);
   if (le == 0 && e == hipSuccess && stage && v)
     e = hipMemcpy(v, dv, sizeof(double) * (size_t)sh.n_tracers, hipMemcpyDeviceToHost);
   if (stage) hipFree(stage);
   if (le != 0) return fail(p, SIC_EDEVICE, std::string("extract: ") + hipGetErrorString((hipError_t)le));
-  if (st != SIC_OK) return st;
   if (e != hipSuccess) return fail(p, SIC_EDEVICE, std::string("get_state: ") + hipGetErrorString(e));
-  if (step && !p->batch) *step = sh.step;
+  if (step) *step = slot_step(p, slot);
   return SIC_OK;
 }
 
@@ -2337,10 +2343,15 @@ const char *status_str(sic_status s) {
 // With refining slots (l_max > 0): one step at a time, each followed by a
 // refinement pass of every refining slot that took the step.
 sic_status batch_step(Pool *p, int64_t n) {
+  auto run = [p](int64_t k) {
+    const sic_status st = run_fused(p, k);
+    if (st == SIC_OK) p->clock += k;
+    return st;
+  };
   std::vector<int32_t> refining;
   for (int32_t i = 0; i < p->slot_cap; ++i)
     if (p->slots[i].live && p->slots[i].l_max > 0.0) refining.push_back(i);
-  if (refining.empty()) return run_fused(p, n);
+  if (refining.empty()) return run(n);
   for (int64_t k = 0; k < n; ++k) {
     std::vector<int32_t> stepping;
     for (int32_t slot : refining) {
@@ -2349,8 +2360,8 @@ sic_status batch_step(Pool *p, int64_t n) {
       if (st != SIC_OK) return st;
       if (I.active) stepping.push_back(slot);
     }
-    if (stepping.empty()) return run_fused(p, n - k);  // no refining slot left to advance
-    sic_status st = run_fused(p, 1);
+    if (stepping.empty()) return run(n - k);  // no refining slot left to advance
+    sic_status st = run(1);
     if (st != SIC_OK) return st;
     for (int32_t slot : stepping) {
       st = pool_refine(p, slot, p->slots[slot].l_max, nullptr);

@@ -2559,10 +2559,11 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(SolveArgs a) {
   }
 
   // 1. work-item partials, in item order: each thread sums items tid,
-  // tid + 256, ... (loads issued four at a time), then the wavefront and
+  // tid + 256, ... (loads issued kU at a time), then the wavefront and
   // workgroup sums, all three in one pass
   __shared__ double sMom[4], sMs[4];
-  constexpr int kU = 4;
+  // single simulations (copies) hold thousands of items, a batch's a few each
+  constexpr int kU = REP > 1 ? 8 : 4;
   double ke = 0.0, mom = 0.0, ms = 0.0;
   for (int i0 = tid; i0 < item_count; i0 += kU * kSolveThreads) {
     Partial pr[kU];
@@ -3038,7 +3039,18 @@ __global__ void __launch_bounds__(1024) k_refine_plan(RefinePassArgs a) {
   const int nth = blockDim.x;
   int32_t *st = a.state;
   const int halted = st[kRefHalt], marks = st[kRefMarks], n = st[kRefChunks];
-  const ChunkDesc *chunks = st[kRefCur] ? a.chunks[1] : a.chunks[0];
+  const int cur = st[kRefCur];
+  const ChunkDesc *chunks = cur ? a.chunks[1] : a.chunks[0];
+  // a chunk and a sheet per thread, in flight with the state words (both sets'
+  // descriptors: which one is current is among them)
+  const int cap = min(a.chunk_cap, nth);
+  int my_cnt = 0, my_nv0 = 0, my_nv1 = 0, my_nt = 0;
+  if (tid < cap) {
+    my_cnt = a.cnt[tid];
+    my_nv0 = a.chunks[0][a.chunk_begin + tid].n_valid;
+    my_nv1 = a.chunks[1][a.chunk_begin + tid].n_valid;
+  }
+  if (tid < a.n_sheets) my_nt = a.nt[tid];
   __syncthreads();
   if (tid == 0) {
     sOver = 0;
@@ -3050,6 +3062,54 @@ __global__ void __launch_bounds__(1024) k_refine_plan(RefinePassArgs a) {
     if (halted || marks == 0) st[kRefInserted] = 0;
   }
   if (halted || marks == 0) return;
+  if (n <= nth && a.n_sheets <= nth) {
+    // up to 1024 chunks and sheets: one of each per thread, scans of 32-bit
+    // integers (at most 128 tracers per old chunk) and offsets in LDS instead
+    // of a walk over the chunks and reads back from memory (8 -> PLAN us)
+    __shared__ int sOff[1025];
+    __shared__ int sS[3][16];
+    const int lane = tid & 63, wave = tid >> 6, nw = nth >> 6;
+    auto scan = [&](int v, int *s16) {
+      const int i = wave_incl_scan(v, [](int x, int y) { return x + y; });
+      if (lane == 63) s16[wave] = i;
+      __syncthreads();
+      int base = 0;
+      for (int w = 0; w < nw; ++w) base += w < wave ? s16[w] : 0;
+      return base + i;
+    };
+    const int S = a.n_sheets;
+    const int v = tid < n ? (cur ? my_nv1 : my_nv0) + my_cnt : 0;
+    const int end = scan(v, sS[0]);
+    if (tid == 0) sOff[0] = 0;
+    sOff[tid + 1] = end;
+    if (tid < n) a.out_off[tid] = end - v;
+    const int och = tid < S ? (my_nt + kChunk - 1) / kChunk : 0;
+    const int f1 = scan(och, sS[1]), f0 = f1 - och;  // its barrier: sOff
+    const int o0 = tid < S ? sOff[f0] : 0, nn = tid < S ? sOff[f1] - o0 : 0;
+    const int nch = (nn + kChunk - 1) / kChunk;
+    const int l1 = scan(nch, sS[2]);
+    int64_t *first2 = a.work + S, *flat0 = a.work + 2 * S + 1, *first1 = a.work + 3 * S + 1;
+    if (tid < S) {
+      a.work[tid] = nn;
+      first2[tid] = l1 - nch;
+      flat0[tid] = o0;
+      first1[tid] = f0;
+    }
+    if (tid == S - 1) {
+      first2[S] = l1;
+      first1[S] = f1;
+      if (sOff[n] > a.max_tracers || l1 > a.chunk_cap) {
+        st[kRefHalt] = 1;
+        st[kRefInserted] = 0;
+        a.inst[a.slot].active = 0;
+      } else {
+        st[kRefInserted] = marks;
+        st[kRefChunks] = l1;
+        st[kRefCur] ^= 1;
+      }
+    }
+    return;
+  }
   // Each wavefront takes a contiguous range of chunks and walks it 64 chunks
   // (one per lane, coalesced) at a time, kB groups of loads in flight
   // together: a wavefront scan gives each chunk its offset within the range
