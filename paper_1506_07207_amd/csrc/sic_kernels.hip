@@ -3065,7 +3065,7 @@ __global__ void __launch_bounds__(1024) k_refine_plan(RefinePassArgs a) {
   if (n <= nth && a.n_sheets <= nth) {
     // up to 1024 chunks and sheets: one of each per thread, scans of 32-bit
     // integers (at most 128 tracers per old chunk) and offsets in LDS instead
-    // of a walk over the chunks and reads back from memory (8 -> PLAN us)
+    // of a walk over the chunks and reads back from memory (8 -> 5 us)
     __shared__ int sOff[1025];
     __shared__ int sS[3][16];
     const int lane = tid & 63, wave = tid >> 6, nw = nth >> 6;
