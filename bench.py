@@ -226,11 +226,10 @@ def time_single_configs(B, I, torch):
         finally:
             sim.close()
         n = p.total_tracers
-        graphs = math.ceil(p.n_steps / 32)
         if path == B.SIC_PATH_RESIDENT:
             launches = math.ceil(p.n_steps / 8192) / p.n_steps
         elif path == B.SIC_PATH_SOLVE_FIRST:
-            launches = (p.n_steps + 2 * graphs) / p.n_steps
+            launches = (p.n_steps + 1) / p.n_steps  # and the solve that closes the call
         else:
             launches = 2
         names = {B.SIC_PATH_FUSED: "fused launch pairs", B.SIC_PATH_RESIDENT: "resident",
