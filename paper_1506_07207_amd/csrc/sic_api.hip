@@ -966,6 +966,12 @@ sic_status get_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
   return SIC_OK;
 }
 
+// Accumulator set i of the rotation.
+long long *sf_set(Pool *p, int64_t i) {
+  return i % 3 == 0 ? static_cast<long long *>(p->meshP)
+                    : static_cast<long long *>(p->sf_mesh) + (i % 3 - 1) * acc_words(p);
+}
+
 // Solve-first steps: a single simulation (not timed, not refining on the
 // device) runs k steps as k launches of one workgroup per item, whose second
 // and later ones solve the previous step's charge in every workgroup
@@ -993,7 +999,17 @@ bool sf_ready(Pool *p) {
       p->sf_mesh = nullptr;
       return false;
     }
-    if (hipMemsetAsync(p->sf_mesh, 0, bytes, p->stream) != hipSuccess) return false;
+    // by the clearing kernel, not a memset: a caller may be capturing
+    const int64_t arr = (int64_t)p->rep * mesh_words(p);
+    for (int i = 1; i <= 2; ++i) {
+      long long *set = sf_set(p, i);
+      if (launch_zero_mesh(p->prec, set, set + arr, p->order == 1 ? set + 2 * arr : nullptr, p->inst, p->slot_ids, 1,
+                           p->rep, mesh_words(p), p->stream) != 0) {
+        hipFree(p->sf_mesh);
+        p->sf_mesh = nullptr;
+        return false;
+      }
+    }
   }
   if (!p->sf_part) {
     if (hipMalloc((void **)&p->sf_part, sizeof(Partial) * (size_t)p->item_cap) != hipSuccess) {
@@ -1002,12 +1018,6 @@ bool sf_ready(Pool *p) {
     }
   }
   return true;
-}
-
-// Accumulator set i of the rotation.
-long long *sf_set(Pool *p, int64_t i) {
-  return i % 3 == 0 ? static_cast<long long *>(p->meshP)
-                    : static_cast<long long *>(p->sf_mesh) + (i % 3 - 1) * acc_words(p);
 }
 
 // What a step launch of a single simulation reads and writes, but for the
