@@ -153,19 +153,9 @@ __device__ __forceinline__ double mesh_pos(uint64_t w, double inv_dx) {
 }
 
 // Field at a tracer: linear interpolation between the two cell centres
-// around it (first-order weighting).  u is the position in mesh units.
-__device__ __forceinline__ double gather_field(const double *E, double u, int nc) {
-  const double g = u - 0.5;
-  const double f = floor(g);
-  const double s = g - f;
-  const int j0 = wrap_cell((int)f, nc);
-  const int j1 = (j0 + 1 == nc) ? 0 : j0 + 1;
-  return (1.0 - s) * E[j0] + s * E[j1];
-}
-
-// The same interpolation from a field array with one ghost cell on each side
-// (E[-1] = E[nc-1], E[nc] = E[0]): no periodic wrap of the two indices; the
-// clamp keeps non-finite positions inside the array.
+// around it (first-order weighting), from a field array with one ghost cell on
+// each side (E[-1] = E[nc-1], E[nc] = E[0]): no periodic wrap of the two
+// indices.  u is the position in mesh units.  The clamp keeps non-finite positions inside the array.
 __device__ __forceinline__ double gather_field_ghost(const double *E, double u, int nc) {
   const double g = u - 0.5;
   const double f = floor(g);
@@ -900,20 +890,9 @@ __device__ __forceinline__ T block_incl_scan(T v, T *sWave) {
   return v + base;
 }
 
-template <class T>
-__device__ __forceinline__ T block_sum(T v, T *sWave) {
-  v = wave_sum(v);
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) sWave[wave] = v;
-  __syncthreads();
-  const T r = sWave[0] + sWave[1] + sWave[2] + sWave[3];
-  __syncthreads();
-  return r;
-}
-
 // The solve's scan and sum over its kSolveThreads threads (four wavefronts,
 // mine; a wider workgroup's other wavefronts only pass the barrier), with the
-// sums in the order of block_incl_scan and block_sum.  Each call site passes
+// sums in the order of block_incl_scan.  Each call site passes
 // four LDS words of its own, so one barrier per call suffices (nothing
 // writes them again before the next solve).
 template <class T>
@@ -1912,10 +1891,10 @@ __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
 //
 // Per step, before (item list and descriptor read in turn, the row first, a
 // 64-bit division for the slice to clear; orders 1 and 2 as launch pairs) and
-// now: Landau (131072 tracers, 256 cells) 9.3 -> 8.1 us, with linear segments
-// 13.7 -> 10.1, first-order weighting on ragged sheets (47000 tracers, 200
-// cells, split U32) 11.1 -> 7.3, two-stream (2.1M tracers, 1024 cells, split
-// F32) 26 -> 26.  Of the 8.1 us of Landau's, 1.6 are the launch, 1.2 the
+// now: Landau (131072 tracers, 256 cells) 9.3 -> 8.0 us, with linear segments
+// 13.7 -> 9.7, first-order weighting on ragged sheets (47000 tracers, 200
+// cells, split U32) 11.1 -> 7.2, two-stream (2.1M tracers, 1024 cells, split
+// F32) 26 -> 23.  Of the 8.0 us of Landau's, 1.6 are the launch, 1.2 the
 // charge, 1.2 the solve, 1.7 moving and depositing one chunk per wavefront
 // and 1.2 the merge.
 //
@@ -2029,69 +2008,69 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
   int flags0 = 0;
   bool solved = false;
   if constexpr (kSolve) {
-  if (a.acc_in != nullptr) {
-    solved = true;
-    // The charge: cells tid, tid + threads, ... of every array, the copies
-    // summed in copy order (as the solve launch sums them) and passed to the
-    // solve's threads through the item's still unused LDS mesh (with padding,
-    // and the field's room), so that the reads are coalesced and spread over
-    // all wavefronts.
-    const sacc_t *in = reinterpret_cast<const sacc_t *>(a.acc_in);
-    sacc_t *sAcc = reinterpret_cast<sacc_t *>(t.sP);
-    constexpr int kCopies = single_rep(CELLS * kSolveThreads);
-    sacc_t av[kArrays][kCopies];
-    auto load_acc = [&](int j) {
+    if (a.acc_in != nullptr) {
+      solved = true;
+      // The charge: cells tid, tid + threads, ... of every array, the copies
+      // summed in copy order (as the solve launch sums them) and passed to the
+      // solve's threads through the item's still unused LDS mesh (with padding,
+      // and the field's room), so that the reads are coalesced and spread over
+      // all wavefronts.
+      const sacc_t *in = reinterpret_cast<const sacc_t *>(a.acc_in);
+      sacc_t *sAcc = reinterpret_cast<sacc_t *>(t.sP);
+      constexpr int kCopies = single_rep(CELLS * kSolveThreads);
+      sacc_t av[kArrays][kCopies];
+      auto load_acc = [&](int j) {
 #pragma unroll
-      for (int r = 0; r < kCopies; ++r)
+        for (int r = 0; r < kCopies; ++r)
 #pragma unroll
-        for (int k = 0; k < kArrays; ++k) av[k][r] = in[(int64_t)(k * kCopies + r) * nc + j];
-    };
-    auto sum_acc = [&](int j) {
+          for (int k = 0; k < kArrays; ++k) av[k][r] = in[(int64_t)(k * kCopies + r) * nc + j];
+      };
+      auto sum_acc = [&](int j) {
 #pragma unroll
-      for (int k = 0; k < kArrays; ++k) {
-        sacc_t sum = (sacc_t)0;
+        for (int k = 0; k < kArrays; ++k) {
+          sacc_t sum = (sacc_t)0;
 #pragma unroll
-        for (int r = 0; r < kCopies; ++r) sum += av[k][r];
-        sAcc[k * padded_cell<CELLS>(nc) + padded_cell<CELLS>(j)] = sum;
+          for (int r = 0; r < kCopies; ++r) sum += av[k][r];
+          sAcc[k * padded_cell<CELLS>(nc) + padded_cell<CELLS>(j)] = sum;
+        }
+      };
+      load_acc(min(tid, nc - 1));
+      __builtin_amdgcn_sched_barrier(0);
+      halos = tabs.halos(a.halo_in, lane_chunk(), 0);
+      load_first_states();
+      if (row) {
+        step0 = a.sf.inst[0].step;
+        flags0 = a.sf.inst[0].flags;
+        pr[0] = a.part_in[min(tid, n_prev - 1)];
+        pr[1] = a.part_in[min(tid + kSolveThreads, n_prev - 1)];
       }
-    };
-    load_acc(min(tid, nc - 1));
-    __builtin_amdgcn_sched_barrier(0);
-    halos = tabs.halos(a.halo_in, lane_chunk(), 0);
-    load_first_states();
-    if (row) {
-      step0 = a.sf.inst[0].step;
-      flags0 = a.sf.inst[0].flags;
-      pr[0] = a.part_in[min(tid, n_prev - 1)];
-      pr[1] = a.part_in[min(tid + kSolveThreads, n_prev - 1)];
-    }
-    if (tid < nc) sum_acc(tid);
-    for (int j = tid + nt; j < nc; j += nt) {
-      load_acc(j);
-      sum_acc(j);
-    }
-    __syncthreads();
-    sacc_t pv[CELLS], dv[CELLS];
-    if (wave < kSolveThreads / kChunk) {
-      const int per = (nc + kSolveThreads - 1) / kSolveThreads;
-#pragma unroll
-      for (int k = 0; k < CELLS; ++k) {
-        const int j = tid * per + k;
-        const bool in_mesh = k < per && j < nc;
-        const int at = padded_cell<CELLS>(in_mesh ? j : 0);
-        const sacc_t p = sAcc[at], d = sAcc[padded_cell<CELLS>(nc) + at];
-        pv[k] = in_mesh ? p : (sacc_t)0;
-        dv[k] = in_mesh ? d : (sacc_t)0;
+      if (tid < nc) sum_acc(tid);
+      for (int j = tid + nt; j < nc; j += nt) {
+        load_acc(j);
+        sum_acc(j);
       }
+      __syncthreads();
+      sacc_t pv[CELLS], dv[CELLS];
+      if (wave < kSolveThreads / kChunk) {
+        const int per = (nc + kSolveThreads - 1) / kSolveThreads;
+#pragma unroll
+        for (int k = 0; k < CELLS; ++k) {
+          const int j = tid * per + k;
+          const bool in_mesh = k < per && j < nc;
+          const int at = padded_cell<CELLS>(in_mesh ? j : 0);
+          const sacc_t p = sAcc[at], d = sAcc[padded_cell<CELLS>(nc) + at];
+          pv[k] = in_mesh ? p : (sacc_t)0;
+          dv[k] = in_mesh ? d : (sacc_t)0;
+        }
+      }
+      // the field and the density in global memory are written by the solve
+      // launch that ends a run of such steps
+      fs = solve_field<PREC, CELLS>(kc, pv, dv, kLin ? sAcc + 2 * (int64_t)nc : (sacc_t *)nullptr, 0, t.sE, true,
+                                    (double *)nullptr, (double *)nullptr);
+      // The accumulators that the launch before read are cleared, a slice per
+      // workgroup (the next launch merges into them).
+      clear_slice();
     }
-    // the field and the density in global memory are written by the solve
-    // launch that ends a run of such steps
-    fs = solve_field<PREC, CELLS>(kc, pv, dv, kLin ? sAcc + 2 * (int64_t)nc : (sacc_t *)nullptr, 0, t.sE, true,
-                                  (double *)nullptr, (double *)nullptr);
-    // The accumulators that the launch before read are cleared, a slice per
-    // workgroup (the next launch merges into them).
-    clear_slice();
-  }
   }
   if (!solved) {
     // the first step of a run (or no solve): the field is in global memory
@@ -2657,8 +2636,8 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(SolveArgs a) {
 // instead of waiting for the others' moves), and one wavefront more holds no
 // tracers and reduces and writes the diagnostics rows while the others go on
 // with the next step.  Per step (before: two passes, rows in the chain,
-// constant segments only): 1024 tracers on 128 cells 4.8 -> 3.2 us, of which
-// 1.3 the solve; 1280 tracers, linear segments, 12.2 (launch pairs) -> 5.9.
+// constant segments only): 1024 tracers on 128 cells 4.8 -> 3.0 us, of which
+// 1.3 the solve; 1280 tracers, linear segments, 12.2 (launch pairs) -> 5.7.
 
 constexpr int kResidentChunks = 32;  // chunks (2048 tracer slots) a resident launch holds
 
