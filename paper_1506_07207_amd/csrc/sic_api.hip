@@ -126,6 +126,12 @@ struct SlotHost {
 
 }  // namespace
 
+// What a captured launch takes from the pool apart from its fixed buffers: the
+// number of steps, the halo parity, the launch shape (grid, workgroup and item
+// size, from which the LDS tables are sized), the solve grid and which kind of
+// step it is.
+using GraphKey = std::tuple<int64_t, int, int, int, int, int, int>;
+
 struct Pool {
   int prec = 0;
   int order = 0;  // deposit order: 0 piecewise-constant, 1 piecewise-linear, 2 first-order weighting
@@ -213,8 +219,7 @@ struct Pool {
   sic_tuning tune{};  // requested (0 = automatic)
   int block = kDefaultBlock, grid = kDefaultGrid, tile = kMinTile;
   int solve_grid = 1;  // solve workgroups of a whole-pool step: live slot indices, rounded up
-  // (steps, parity, grid, solve grid, device refinement: the launches then skip an inactive slot)
-  std::map<std::tuple<int64_t, int, int, int, int>, hipGraphExec_t> graphs;
+  std::map<GraphKey, hipGraphExec_t> graphs;
   std::vector<hipGraph_t> graph_objs;
   bool timing = false;
   double t_tracer = 0.0, t_solve = 0.0;
@@ -935,8 +940,15 @@ sic_status enqueue_fused(Pool *p, hipStream_t st) {
   return SIC_OK;
 }
 
+// Kinds of captured steps.
+enum GraphKind : int { kPairSteps = 0, kSolveFirstSteps = 1, kRefiningSteps = 2 };
+
+GraphKey graph_key(const Pool *p, int64_t k, int kind) {
+  return GraphKey(k, p->parity, p->grid, p->block, p->tile, p->solve_grid, kind);
+}
+
 sic_status get_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
-  auto key = std::make_tuple(k, p->parity, p->grid, p->solve_grid, p->dev_refine ? 1 : 0);
+  const GraphKey key = graph_key(p, k, kPairSteps);
   auto it = p->graphs.find(key);
   if (it != p->graphs.end()) {
     *out = it->second;
@@ -1130,7 +1142,7 @@ sic_status close_sf(Pool *p, int64_t k, hipStream_t st, const int32_t *rs = null
 // A graph of k solve-first steps, the first of them step 1 (mod kSfPeriod)
 // of its run.
 sic_status get_sf_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
-  auto key = std::make_tuple(k, p->parity, p->grid, p->solve_grid, 3);
+  const GraphKey key = graph_key(p, k, kSolveFirstSteps);
   auto it = p->graphs.find(key);
   if (it != p->graphs.end()) {
     *out = it->second;
@@ -2246,7 +2258,7 @@ sic_status enqueue_refining(Pool *p, int64_t i, hipStream_t st) {
 // Graphs of k refining steps, keyed apart from the plain step graphs; sf: the
 // first is step 1 (mod 6) of a run of solve-first steps.
 sic_status get_refine_graph(Pool *p, int64_t k, bool sf, hipGraphExec_t *out) {
-  auto key = std::make_tuple(k, p->parity, p->grid, p->solve_grid, 4 + 2 * p->alt_swapped + (sf ? 1 : 0));
+  const GraphKey key = graph_key(p, k, kRefiningSteps + 2 * p->alt_swapped + (sf ? 1 : 0));
   auto it = p->graphs.find(key);
   if (it != p->graphs.end()) {
     *out = it->second;

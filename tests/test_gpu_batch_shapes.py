@@ -1,0 +1,46 @@
+"""Launch shapes of batches: what a batch stepped, or held, before a
+simulation was admitted does not change that simulation's steps."""
+import numpy as np
+import pytest
+
+from paper_1506_07207_amd import binding as B
+from paper_1506_07207_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _admit(b, p, order, n_steps=-1):
+    return B.sic_batch_admit(b, p.L, p.n_cells, p.dt, p.n_tracers, p.q, p.closed, p.x0, p.v0, n_steps,
+                             precision=B.SIC_SPLIT_U32, deposit_order=order)
+
+
+def _result(b, slot, p):
+    x, v, step = B.sic_batch_get_state(b, slot, p.total_tracers)
+    return x, v, step, B.sic_batch_result(b, slot, p.n_cells)
+
+
+def _same(a, b):
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and a[2] == b[2]
+    assert np.array_equal(a[3]["E"], b[3]["E"]) and np.array_equal(a[3]["rho"], b[3]["rho"])
+    for col in ("step", "W_E", "total_charge", "max_segment", "flags"):
+        assert np.array_equal(a[3]["history"][col], b[3]["history"][col]), col
+
+
+@pytest.mark.parametrize("steps", [1, 2, 32])
+@pytest.mark.parametrize("order", [0, 1, 2])
+def test_steps_while_empty_do_not_change_what_is_admitted_later(order, steps):
+    # 313 chunks: two items of the largest size, against tables of four chunks
+    p = I.landau(n_sheets=40, n_tracers=500, n_cells=64)
+    print(f"case empty batch order={order} steps={steps}", flush=True)
+    out = []
+    for empty_first in (False, True):
+        b = B.sic_batch_create(40000, 4, 64, precision=B.SIC_SPLIT_U32, deposit_order=order)
+        try:
+            if empty_first:
+                B.sic_batch_step(b, steps)
+            slot = _admit(b, p, order)
+            B.sic_batch_step(b, steps)
+            out.append(_result(b, slot, p))
+        finally:
+            B.sic_batch_destroy(b)
+    _same(*out)
