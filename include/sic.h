@@ -183,7 +183,11 @@ sic_status sic_push(sic_sim *sim);
  * forms.  Timing mode (sic_set_timing) always takes the fused path.  Async;
  * with refinement on (l_max > 0) each step is followed by a refinement pass
  * on the device (SIC_PATH_REFINING: graphs of steps and passes; the host
- * reads the layout back when it needs it). */
+ * reads the layout back when it needs it).
+ * A call whose steps are plain launches (SIC_PATH_RESIDENT; SIC_PATH_SOLVE_FIRST
+ * of up to 7 steps) may be captured from the caller's stream and replayed, an
+ * even number of steps after a first uncaptured call; every call that reports
+ * the step or the history reports the device's, replays included. */
 sic_status sic_step(sic_sim *sim, int64_t n_steps);
 
 enum {

@@ -202,6 +202,23 @@ def make_sheets(n_tracers, q, closed=None):
     return arr
 
 
+def _history(call):
+    """All history rows through call(rows, length): one call where they fit
+    its first buffer (asking for the length first would wait for the device
+    twice), and a second with room for as many as there are."""
+    n = ctypes.c_int64(1024)
+    while True:
+        room = n.value
+        hist = np.zeros(room, dtype=DIAG_DTYPE)
+        call(hist.ctypes.data_as(ctypes.c_void_p), ctypes.byref(n))
+        if n.value < room:
+            return hist[: n.value].copy()
+        call(None, ctypes.byref(n))
+        if n.value <= room:
+            return hist
+        # more rows than the buffer held
+
+
 def _diag_dict(d: sic_diag) -> dict:
     return {n: getattr(d, n) for n in DIAG_DTYPE.names}
 
@@ -262,12 +279,8 @@ def sic_diagnostics(h, n_cells: Optional[int] = None, history: bool = True):
         pE = E.ctypes.data_as(ctypes.c_void_p)
     hist = None
     if history:
-        n = ctypes.c_int64(0)
-        _check(lib.sic_diagnostics(h, None, None, None, None, ctypes.byref(n)), "sic_diagnostics", h)
-        hist = np.zeros(n.value, dtype=DIAG_DTYPE)
-        _check(lib.sic_diagnostics(h, ctypes.byref(last), prho, pE, hist.ctypes.data_as(ctypes.c_void_p),
-                                   ctypes.byref(n)), "sic_diagnostics", h)
-        hist = hist[: n.value]
+        hist = _history(lambda *a: _check(lib.sic_diagnostics(h, ctypes.byref(last), prho, pE, *a),
+                                          "sic_diagnostics", h))
     else:
         _check(lib.sic_diagnostics(h, ctypes.byref(last), prho, pE, None, None), "sic_diagnostics", h)
     return dict(last=_diag_dict(last), rho=rho, E=E, history=hist)
@@ -437,13 +450,8 @@ def sic_batch_result(b, slot: int, n_cells: Optional[int] = None, history: bool 
         pE = E.ctypes.data_as(ctypes.c_void_p)
     hist = None
     if history:
-        n = ctypes.c_int64(0)
-        _check(lib.sic_batch_result(b, int(slot), None, None, None, None, ctypes.byref(n)), "sic_batch_result", b,
-               batch=True)
-        hist = np.zeros(n.value, dtype=DIAG_DTYPE)
-        _check(lib.sic_batch_result(b, int(slot), ctypes.byref(last), prho, pE, hist.ctypes.data_as(ctypes.c_void_p),
-                                    ctypes.byref(n)), "sic_batch_result", b, batch=True)
-        hist = hist[: n.value]
+        hist = _history(lambda *a: _check(lib.sic_batch_result(b, int(slot), ctypes.byref(last), prho, pE, *a),
+                                          "sic_batch_result", b, batch=True))
     else:
         _check(lib.sic_batch_result(b, int(slot), ctypes.byref(last), prho, pE, None, None), "sic_batch_result",
                b, batch=True)

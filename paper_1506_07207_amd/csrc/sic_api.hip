@@ -114,9 +114,6 @@ struct SlotHost {
   int32_t item_begin = 0, n_items = 0;
   std::vector<int64_t> chunk_in_off;
   int state = kStale;
-  // a single simulation's step; a batch's slots take every batch step from
-  // admission (the pool's clock0) on until they have run n_run (< 0: no end)
-  int64_t step = 0, clock0 = 0, n_run = -1;
   // the step the diagnostics history starts at: 0, or the step a state was
   // set or loaded at (rows before it were never written by this simulation)
   int64_t hist_from = 0;
@@ -208,7 +205,6 @@ struct Pool {
   size_t pin_bytes = 0;
   int64_t pin_rows = 0;
 
-  int64_t clock = 0;  // steps of a batch so far
   std::vector<SlotHost> slots;
   std::vector<Item> items_up;  // work items being uploaded
   ChunkAllocator alloc;       // tracer chunks
@@ -1505,9 +1501,6 @@ sic_status pool_admit(Pool *p, const sic_config *cfg, const sic_sheet *sheets, i
   sh.l_max = cfg->l_max;
   sh.max_tracers = reserve_tr;
   sh.hist_from = 0;
-  sh.step = 0;
-  sh.clock0 = p->clock;
-  sh.n_run = n_steps;
   sh.chunk_begin = (int32_t)cb;
   sh.n_chunks = (int32_t)n_ch;
   sh.n_chunks_res = (int32_t)n_res;
@@ -1628,7 +1621,6 @@ sic_status pool_relayout(Pool *p, int32_t slot, const std::vector<int32_t> &nt, 
   // single simulation's solve-first ones its chunk and item counts too
   if (!p->batch || p->tile != tile0 || p->grid != grid0) destroy_graphs(p);
   hipError_t e = upload_layout(p, cb, L);
-  if (step >= 0) sh.step = step;
   if (e != hipSuccess) return fail(p, SIC_EDEVICE, std::string("re-layout copies: ") + hipGetErrorString(e));
   int le = ingest_slot(p, slot, x, w, v, c, cw);
   if (le == 0) le = launch_zero_mesh(p->prec, p->meshP, p->meshD, p->meshR, p->inst, p->slot_ids + slot, 1, p->rep,
@@ -1791,14 +1783,9 @@ sic_status export_slot(Pool *p, int32_t slot, bool mesh, int64_t rows, InstDesc 
   return SIC_OK;
 }
 
-// The step that a slot's launches so far take it to.
-int64_t slot_step(const Pool *p, int32_t slot) {
-  const SlotHost &sh = p->slots[slot];
-  if (!p->batch) return sh.step;
-  const int64_t ran = p->clock - sh.clock0;
-  return sh.n_run < 0 ? ran : std::min(ran, sh.n_run);
-}
-
+// History rows of a slot at a step.  The step comes from the device in every
+// call that reports one: a caller may capture steps and replay them, of which
+// the host learns nothing.
 int64_t history_avail(const Pool *p, int32_t slot, int64_t step) {
   return std::min<int64_t>(step + 1 - std::min(step, p->slots[slot].hist_from), p->hist_rows);
 }
@@ -1806,10 +1793,6 @@ int64_t history_avail(const Pool *p, int32_t slot, int64_t step) {
 sic_status pool_diagnostics(Pool *p, int32_t slot, sic_diag *out, double *rho_out, double *E_out,
                             sic_diag *history_out, int64_t *history_len) {
   if (slot < 0 || slot >= p->slot_cap || !p->slots[slot].live) return fail(p, SIC_EINVAL, "slot not live");
-  if (!out && !rho_out && !E_out && history_len && !history_out) {
-    *history_len = history_avail(p, slot, slot_step(p, slot));
-    return SIC_OK;
-  }
   InstDesc I;
   const bool mesh = rho_out || E_out;
   sic_status st = export_slot(p, slot, mesh, history_len && history_out ? std::max<int64_t>(*history_len, 0) : 0, &I);
@@ -1850,6 +1833,10 @@ sic_status pool_get_state(Pool *p, int32_t slot, double *x, double *v, int64_t *
   if (slot < 0 || slot >= p->slot_cap || !p->slots[slot].live) return fail(p, SIC_EINVAL, "slot not live");
   SlotHost &sh = p->slots[slot];
   double *dx = x, *dv = v, *stage = nullptr;
+  if (step) {
+    sic_status st = ensure_pin(p);
+    if (st != SIC_OK) return st;
+  }
   if (mem_kind == SIC_MEM_HOST) {
     HIPCHK(p, hipMalloc((void **)&stage, sizeof(double) * 2 * (size_t)std::max<int64_t>(sh.n_tracers, 1)));
     dx = stage;
@@ -1867,6 +1854,7 @@ sic_status pool_get_state(Pool *p, int32_t slot, double *x, double *v, int64_t *
   ea.x_out = dx;
   ea.v_out = dv;
   ea.c_out = nullptr;
+  if (step) ea.step_out = reinterpret_cast<int64_t *>(p->pin);
   int le = launch_extract(p->prec, ea, p->stream);
   hipError_t e = hipStreamSynchronize(p->stream);
   if (le == 0 && e == hipSuccess && stage && x)
@@ -1876,7 +1864,7 @@ sic_status pool_get_state(Pool *p, int32_t slot, double *x, double *v, int64_t *
   if (stage) hipFree(stage);
   if (le != 0) return fail(p, SIC_EDEVICE, std::string("extract: ") + hipGetErrorString((hipError_t)le));
   if (e != hipSuccess) return fail(p, SIC_EDEVICE, std::string("get_state: ") + hipGetErrorString(e));
-  if (step) *step = slot_step(p, slot);
+  if (step) std::memcpy(step, p->pin, sizeof(*step));
   return SIC_OK;
 }
 
@@ -1995,7 +1983,6 @@ sic_status pool_set_state(Pool *p, int32_t slot, int64_t step, const double *x, 
   const hipError_t e = hipStreamSynchronize(p->stream);
   if (stage) hipFree(stage);
   if (e != hipSuccess || le != 0) return fail(p, SIC_EDEVICE, "set_state failed");
-  sh.step = step;
   sh.state = kStale;
   sh.pending_push = sh.pending_dep = false;
   sh.hist_from = step;
@@ -2023,7 +2010,6 @@ sic_status sim_solve(Pool *p) {
   sic_status st = launch_solve_mode(p, flags, -1, p->stream);
   if (st != SIC_OK) return st;
   sh.state = kField;
-  if (sh.pending_push) sh.step += 1;
   sh.pending_push = sh.pending_dep = false;
   return SIC_OK;
 }
@@ -2153,7 +2139,6 @@ sic_status dev_refine_end(Pool *p, int parity0, bool sf) {
   // alternate only for the steps that ran
   const int64_t steps = stw[kRefSteps];
   p->parity = parity0 ^ (int)(steps & 1);
-  sh.step += steps;
   if (sf && steps > 0) {
     sic_status st = close_sf(p, steps, p->stream, stw);
     if (st != SIC_OK) return st;
@@ -2330,7 +2315,6 @@ sic_status sim_step(Pool *p, int64_t n) {
     if (p->timing) {
       for (int64_t i = 0; i < n && st == SIC_OK; ++i) {
         st = run_fused(p, 1);
-        if (st == SIC_OK) sh.step += 1;
         if (st == SIC_OK) st = pool_refine(p, 0, sh.l_max, nullptr);
       }
       return st;
@@ -2344,7 +2328,6 @@ sic_status sim_step(Pool *p, int64_t n) {
     p->last_path = sf_ready(p) ? SIC_PATH_SOLVE_FIRST : SIC_PATH_FUSED;
     st = run_fused(p, n);
   }
-  if (st == SIC_OK) sh.step += n;
   return st;
 }
 
@@ -2365,15 +2348,10 @@ const char *status_str(sic_status s) {
 // With refining slots (l_max > 0): one step at a time, each followed by a
 // refinement pass of every refining slot that took the step.
 sic_status batch_step(Pool *p, int64_t n) {
-  auto run = [p](int64_t k) {
-    const sic_status st = run_fused(p, k);
-    if (st == SIC_OK) p->clock += k;
-    return st;
-  };
   std::vector<int32_t> refining;
   for (int32_t i = 0; i < p->slot_cap; ++i)
     if (p->slots[i].live && p->slots[i].l_max > 0.0) refining.push_back(i);
-  if (refining.empty()) return run(n);
+  if (refining.empty()) return run_fused(p, n);
   for (int64_t k = 0; k < n; ++k) {
     std::vector<int32_t> stepping;
     for (int32_t slot : refining) {
@@ -2382,8 +2360,8 @@ sic_status batch_step(Pool *p, int64_t n) {
       if (st != SIC_OK) return st;
       if (I.active) stepping.push_back(slot);
     }
-    if (stepping.empty()) return run(n - k);  // no refining slot left to advance
-    sic_status st = run(1);
+    if (stepping.empty()) return run_fused(p, n - k);  // no refining slot left to advance
+    sic_status st = run_fused(p, 1);
     if (st != SIC_OK) return st;
     for (int32_t slot : stepping) {
       st = pool_refine(p, slot, p->slots[slot].l_max, nullptr);

@@ -299,6 +299,7 @@ struct ExtractArgs {
   double *x_out;
   double *v_out;
   double *c_out;         // NULL: positions and velocities only
+  int64_t *step_out = nullptr;  // host memory that takes the slot's step, or NULL
 };
 
 // What a diagnostics call reads of a slot, written in one launch to a block

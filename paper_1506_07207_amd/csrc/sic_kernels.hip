@@ -2860,6 +2860,7 @@ __global__ void __launch_bounds__(256) k_extract(ExtractArgs a) {
   const ChunkDesc ch = a.chunks[c];
   if (lane >= ch.n_valid) return;
   const InstDesc &I = a.inst[ch.inst];
+  if (a.step_out != nullptr && cl == 0 && lane == 0) *a.step_out = I.step;
   const size_t s = (size_t)c * kChunk + lane;
   const int64_t dst = a.chunk_in_off[cl] + lane;
   const uint64_t w = a.xs[s];

@@ -29,7 +29,7 @@ def _same(a, b):
 @pytest.mark.parametrize("steps", [1, 2, 32])
 @pytest.mark.parametrize("order", [0, 1, 2])
 def test_steps_while_empty_do_not_change_what_is_admitted_later(order, steps):
-    # 313 chunks: two items of the largest size, against tables of four chunks
+    # 320 chunks, items of 48: against the tables of four chunks of an empty batch
     p = I.landau(n_sheets=40, n_tracers=500, n_cells=64)
     print(f"case empty batch order={order} steps={steps}", flush=True)
     out = []
