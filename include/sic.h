@@ -186,8 +186,8 @@ sic_status sic_push(sic_sim *sim);
  * reads the layout back when it needs it).
  * A call whose steps are plain launches (SIC_PATH_RESIDENT; SIC_PATH_SOLVE_FIRST
  * of up to 7 steps) may be captured from the caller's stream and replayed, an
- * even number of steps after a first uncaptured call; every call that reports
- * the step or the history reports the device's, replays included. */
+ * even number of steps from a current field; every call that reports the step
+ * or the history reports the device's, replays included. */
 sic_status sic_step(sic_sim *sim, int64_t n_steps);
 
 enum {

@@ -193,9 +193,9 @@ struct Pool {
   uint64_t *alt_segq = nullptr;
   ChunkDesc *alt_chunks = nullptr;
   int alt_swapped = 0;
-  // solve-first steps of a single simulation (allocated on first use): two
-  // more accumulator sets (the pool's own is the third) and a second set of
-  // work-item partials
+  // solve-first steps of a single simulation (NULL: it has none): two more
+  // accumulator sets (the pool's own is the third) after meshP's block and a
+  // second set of work-item partials after partials
   void *sf_mesh = nullptr;     // acc_words each
   Partial *sf_part = nullptr;  // item_cap
 
@@ -356,7 +356,7 @@ void pool_free(Pool *p) {
                   p->ref_cnt,   p->ref_mask, p->ref_off,  p->ref_w,    p->ref_v,     p->ref_c,
                   p->dr_nt,     p->dr_closed, p->dr_q,    p->dr_work,  p->dr_state,  p->dr_part,
                   p->alt_xs,    p->alt_vs,   p->alt_segq, p->alt_chunks,
-                  p->sf_mesh,   p->sf_part,  p->in_off};
+                  p->in_off};
   for (void *b : bufs)
     if (b) hipFree(b);
   pin_give(p->pin, p->pin_bytes);  // the stream has been waited for: nothing writes it any more
@@ -422,7 +422,12 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
   ALLOC(p->n_items, 1);
   ALLOC(p->inst, (size_t)slot_cap);
   ALLOC(p->slot_items, (size_t)slot_cap);
-  ALLOC(p->partials, (size_t)p->item_cap);
+  // A single simulation's solve-first steps rotate through three accumulator
+  // sets and two of partials.  They are there, and clear, from the start: a
+  // first step call may be captured, and its launches then run later or never.
+  const int sets = !batch && step_supported(order, max_cells) ? 3 : 1;
+  ALLOC(p->partials, (size_t)p->item_cap * (sets > 1 ? 2 : 1));
+  if (sets > 1) p->sf_part = p->partials + p->item_cap;
   {
     // the no-allocation entry points' staging array on this device, looked
     // up here once per device (a failure is reported by those entry points,
@@ -431,16 +436,18 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
     (void)scratch_address(p->device, &sp);
   }
   p->rep = batch ? 1 : single_rep(max_cells);
+  const size_t acc_all = (size_t)slot_cap * max_cells * p->rep * (order == 1 ? 3 : 2);  // words of a set
   {
     const size_t mc = (size_t)slot_cap * max_cells;
     // one block: P, D (and R), each in rep copies.  Float64 and 64-bit integer
     // additions to memory execute at the memory channels, so arrays and copies
     // that follow one another lie on different channels.
     long long *acc = nullptr;
-    ALLOC(acc, mc * p->rep * (order == 1 ? 3 : 2));
+    ALLOC(acc, acc_all * sets);
     p->meshP = acc;
     p->meshD = acc + mc * p->rep;
     if (order == 1) p->meshR = acc + 2 * mc * p->rep;
+    if (sets > 1) p->sf_mesh = acc + acc_all;
     ALLOC(p->meshE, mc);
     ALLOC(p->meshRho, mc);
   }
@@ -452,9 +459,7 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
   if (e != hipSuccess) return bail(std::string("hipStreamCreate: ") + hipGetErrorString(e), SIC_EDEVICE);
   // zero-initialise everything the kernels accumulate into or read as tables
   const size_t mc = (size_t)slot_cap * max_cells;
-  e = hipMemsetAsync(p->meshP, 0, mc * 8 * p->rep, p->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(p->meshD, 0, mc * 8 * p->rep, p->stream);
-  if (e == hipSuccess && p->meshR) e = hipMemsetAsync(p->meshR, 0, mc * 8 * p->rep, p->stream);
+  e = hipMemsetAsync(p->meshP, 0, acc_all * sets * 8, p->stream);
   if (e == hipSuccess) e = hipMemsetAsync(p->meshE, 0, mc * 8, p->stream);
   if (e == hipSuccess) e = hipMemsetAsync(p->meshRho, 0, mc * 8, p->stream);
   if (e == hipSuccess) e = hipMemsetAsync(p->inst, 0, sizeof(InstDesc) * (size_t)slot_cap, p->stream);
@@ -879,7 +884,7 @@ SolveArgs solve_args(Pool *p, int flags, int slot) {
   return a;
 }
 
-int grid_for(Pool *p, int slot) {
+int grid_for(const Pool *p, int slot) {
   if (slot >= 0) return std::max(1, std::min(p->grid, p->slot_items_h[slot].y));
   return p->grid;
 }
@@ -992,40 +997,14 @@ long long *sf_set(Pool *p, int64_t i) {
 // it reads and the set that the last step read, so every set is clear again,
 // as the other paths expect.  The bits are those of the tracer/solve launch
 // pairs: the same solve code, the same sums in the same order.
-bool sf_ready(Pool *p) {
-  if (p->batch || p->timing || p->tune.fused_only || p->block < kSolveThreads ||
-      !step_supported(p->order, p->max_cells) || p->tile > p->block)
+bool sf_ready(const Pool *p) {
+  if (p->batch || p->timing || p->tune.fused_only || p->block < kSolveThreads || !p->sf_mesh || p->tile > p->block)
     return false;
   // (refining on the device, the launch has at most kRefineGroups + 1)
   // every workgroup solves first: worth it while the workgroups run in one
   // round on the machine, not when each CU works through several in turn
   // (a 33.5M-tracer job's 2048 workgroups: 400 against 290 us per step)
-  if (!p->dev_refine && grid_for(p, -1) > kSfMaxGrid) return false;
-  if (!p->sf_mesh) {
-    const size_t bytes = sizeof(double) * 2 * (size_t)acc_words(p);
-    if (hipMalloc(&p->sf_mesh, bytes) != hipSuccess) {
-      p->sf_mesh = nullptr;
-      return false;
-    }
-    // by the clearing kernel, not a memset: a caller may be capturing
-    const int64_t arr = (int64_t)p->rep * mesh_words(p);
-    for (int i = 1; i <= 2; ++i) {
-      long long *set = sf_set(p, i);
-      if (launch_zero_mesh(p->prec, set, set + arr, p->order == 1 ? set + 2 * arr : nullptr, p->inst, p->slot_ids, 1,
-                           p->rep, mesh_words(p), p->stream) != 0) {
-        hipFree(p->sf_mesh);
-        p->sf_mesh = nullptr;
-        return false;
-      }
-    }
-  }
-  if (!p->sf_part) {
-    if (hipMalloc((void **)&p->sf_part, sizeof(Partial) * (size_t)p->item_cap) != hipSuccess) {
-      p->sf_part = nullptr;
-      return false;
-    }
-  }
-  return true;
+  return p->dev_refine || grid_for(p, -1) <= kSfMaxGrid;
 }
 
 // What a step launch of a single simulation reads and writes, but for the

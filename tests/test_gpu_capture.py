@@ -57,3 +57,23 @@ def test_replayed_steps_are_reported(case, order):
             b.step(n)
             at += n
             _equal(a, b, at)
+
+
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_a_first_call_captured_and_dropped_changes_nothing(case):
+    import torch
+
+    sheets, tracers, cells, _ = CASES[case]
+    p = I.landau(n_sheets=sheets, n_tracers=tracers, n_cells=cells, alpha=0.05)
+    print(f"case capture dropped {case}", flush=True)
+    stream = torch.cuda.Stream()
+    with B.Simulation(p, precision=B.SIC_SPLIT_U32, stream=stream) as a, \
+            B.Simulation(p, precision=B.SIC_SPLIT_U32) as b:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream, capture_error_mode="relaxed"):
+            a.step(4)
+        del graph
+        _equal(a, b, 0)
+        a.step(9)
+        b.step(9)
+        _equal(a, b, 9)

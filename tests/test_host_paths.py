@@ -35,3 +35,23 @@ def test_steps_of_an_empty_batch_leave_no_launch_for_the_simulations_admitted_la
         return got
 
     assert run(True) == run(False)
+
+
+def _sim(sheets=40, n=100, cells=64, order=0, **kw):
+    p = I.landau(n_sheets=sheets, n_tracers=n, n_cells=cells, n_steps=1)
+    return B.Simulation(p, precision=B.SIC_SPLIT_U32, deposit_order=order, stream=0, **kw)
+
+
+@pytest.mark.parametrize("sheets,order", [(4, 0), (40, 0), (40, 1), (40, 2)])
+@H.in_child
+def test_a_first_step_call_prepares_nothing(sheets, order):
+    # a caller may capture it: an allocation would fail, and what is only
+    # recorded has not run when the next call starts
+    with _sim(sheets=sheets, order=order) as s:
+        H.rec.rec_clear()
+        s.step(4)
+        first = H.launches()
+        assert "alloc" not in H.events()
+        H.rec.rec_clear()
+        s.step(4)
+        assert H.launches() == first
