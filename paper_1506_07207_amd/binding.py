@@ -207,15 +207,16 @@ def _history(call):
     its first buffer (asking for the length first would wait for the device
     twice), and a second with room for as many as there are."""
     n = ctypes.c_int64(1024)
+    size = DIAG_DTYPE.itemsize
     while True:
         room = n.value
-        hist = np.zeros(room, dtype=DIAG_DTYPE)
-        call(hist.ctypes.data_as(ctypes.c_void_p), ctypes.byref(n))
+        rows = np.empty(room * size, dtype=np.uint8)  # bytes: a copy of rows goes field by field
+        call(rows.ctypes.data, ctypes.byref(n))
         if n.value < room:
-            return hist[: n.value].copy()
+            return rows[: n.value * size].copy().view(DIAG_DTYPE)
         call(None, ctypes.byref(n))
         if n.value <= room:
-            return hist
+            return rows.view(DIAG_DTYPE)
         # more rows than the buffer held
 
 
