@@ -194,10 +194,10 @@ struct Pool {
   ChunkDesc *alt_chunks = nullptr;
   int alt_swapped = 0;
   // solve-first steps of a single simulation (NULL: it has none): two more
-  // accumulator sets (the pool's own is the third) after meshP's block and a
-  // second set of work-item partials after partials
-  void *sf_mesh = nullptr;     // acc_words each
-  Partial *sf_part = nullptr;  // item_cap
+  // accumulator sets (the pool's own is the third) and a second set of
+  // work-item partials
+  long long *sf_mesh = nullptr;  // acc_words each
+  Partial *sf_part = nullptr;    // item_cap
 
   // host memory that the device writes a call's results to (allocated on
   // first use), room for pin_rows history rows
@@ -356,7 +356,7 @@ void pool_free(Pool *p) {
                   p->ref_cnt,   p->ref_mask, p->ref_off,  p->ref_w,    p->ref_v,     p->ref_c,
                   p->dr_nt,     p->dr_closed, p->dr_q,    p->dr_work,  p->dr_state,  p->dr_part,
                   p->alt_xs,    p->alt_vs,   p->alt_segq, p->alt_chunks,
-                  p->in_off};
+                  p->sf_mesh,   p->sf_part,  p->in_off};
   for (void *b : bufs)
     if (b) hipFree(b);
   pin_give(p->pin, p->pin_bytes);  // the stream has been waited for: nothing writes it any more
@@ -398,9 +398,12 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
     return s;
   };
   hipError_t e = hipSuccess;
-#define ALLOC(ptr, n)                                                                  \
-  e = dalloc(&(ptr), (n));                                                             \
-  if (e != hipSuccess) return bail(std::string("hipMalloc ") + #ptr + ": " + hipGetErrorString(e), SIC_ENOMEM);
+#define ALLOC(ptr, n)                                                                                          \
+  do {                                                                                                        \
+    e = dalloc(&(ptr), (n));                                                                                  \
+    if (e != hipSuccess)                                                                                      \
+      return bail(std::string("hipMalloc ") + #ptr + ": " + hipGetErrorString(e), SIC_ENOMEM);                \
+  } while (0)
   const size_t slotsz = (size_t)chunk_cap * kChunk;
   ALLOC(p->xs, slotsz);
   ALLOC(p->vs, slotsz);
@@ -426,8 +429,8 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
   // sets and two of partials.  They are there, and clear, from the start: a
   // first step call may be captured, and its launches then run later or never.
   const int sets = !batch && step_supported(order, max_cells) ? 3 : 1;
-  ALLOC(p->partials, (size_t)p->item_cap * (sets > 1 ? 2 : 1));
-  if (sets > 1) p->sf_part = p->partials + p->item_cap;
+  ALLOC(p->partials, (size_t)p->item_cap);
+  if (sets > 1) ALLOC(p->sf_part, (size_t)p->item_cap);
   {
     // the no-allocation entry points' staging array on this device, looked
     // up here once per device (a failure is reported by those entry points,
@@ -443,11 +446,11 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
     // additions to memory execute at the memory channels, so arrays and copies
     // that follow one another lie on different channels.
     long long *acc = nullptr;
-    ALLOC(acc, acc_all * sets);
+    ALLOC(acc, acc_all);
     p->meshP = acc;
     p->meshD = acc + mc * p->rep;
     if (order == 1) p->meshR = acc + 2 * mc * p->rep;
-    if (sets > 1) p->sf_mesh = acc + acc_all;
+    if (sets > 1) ALLOC(p->sf_mesh, (sets - 1) * acc_all);
     ALLOC(p->meshE, mc);
     ALLOC(p->meshRho, mc);
   }
@@ -459,7 +462,8 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
   if (e != hipSuccess) return bail(std::string("hipStreamCreate: ") + hipGetErrorString(e), SIC_EDEVICE);
   // zero-initialise everything the kernels accumulate into or read as tables
   const size_t mc = (size_t)slot_cap * max_cells;
-  e = hipMemsetAsync(p->meshP, 0, acc_all * sets * 8, p->stream);
+  e = hipMemsetAsync(p->meshP, 0, acc_all * 8, p->stream);
+  if (e == hipSuccess && p->sf_mesh) e = hipMemsetAsync(p->sf_mesh, 0, (sets - 1) * acc_all * 8, p->stream);
   if (e == hipSuccess) e = hipMemsetAsync(p->meshE, 0, mc * 8, p->stream);
   if (e == hipSuccess) e = hipMemsetAsync(p->meshRho, 0, mc * 8, p->stream);
   if (e == hipSuccess) e = hipMemsetAsync(p->inst, 0, sizeof(InstDesc) * (size_t)slot_cap, p->stream);
@@ -982,7 +986,7 @@ sic_status get_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
 // Accumulator set i of the rotation.
 long long *sf_set(Pool *p, int64_t i) {
   return i % 3 == 0 ? static_cast<long long *>(p->meshP)
-                    : static_cast<long long *>(p->sf_mesh) + (i % 3 - 1) * acc_words(p);
+                    : p->sf_mesh + (i % 3 - 1) * acc_words(p);
 }
 
 // Solve-first steps: a single simulation (not timed, not refining on the
