@@ -236,7 +236,10 @@ namespace {
 // sic_last_error(NULL) when no handle exists, e.g. after a failed sic_init).
 thread_local std::string g_last_error;
 
+// A device error is reported here, once: the runtime keeps it until it is
+// asked for, and the next launch would report it as its own.
 sic_status fail(Pool *p, sic_status s, const std::string &msg) {
+  if (s == SIC_EDEVICE || s == SIC_ENOMEM) (void)hipGetLastError();
   if (p) p->err = msg;
   g_last_error = msg;
   return s;
@@ -393,9 +396,8 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
 
   auto bail = [&](const std::string &m, sic_status s) {
     if (err) *err = m;
-    g_last_error = m;
     pool_free(p);
-    return s;
+    return fail(nullptr, s, m);
   };
   hipError_t e = hipSuccess;
 #define ALLOC(ptr, n)                                                                                          \
@@ -2683,10 +2685,11 @@ sic_status sic_copy_bandwidth(int64_t n_bytes, int32_t iters, void *hip_stream, 
   hipStream_t st = (hipStream_t)hip_stream;
   const int64_t n = n_bytes / 16 * 2;  // doubles, even
   double *a = nullptr, *b = nullptr;
-  if (hipMalloc((void **)&a, sizeof(double) * (size_t)n) != hipSuccess) return SIC_ENOMEM;
+  if (hipMalloc((void **)&a, sizeof(double) * (size_t)n) != hipSuccess)
+    return fail(nullptr, SIC_ENOMEM, "no device memory for the copy");
   if (hipMalloc((void **)&b, sizeof(double) * (size_t)n) != hipSuccess) {
     hipFree(a);
-    return SIC_ENOMEM;
+    return fail(nullptr, SIC_ENOMEM, "no device memory for the copy");
   }
   hipMemsetAsync(a, 0, sizeof(double) * (size_t)n, st);
   hipEvent_t e0, e1;

@@ -55,3 +55,16 @@ def test_a_first_step_call_prepares_nothing(sheets, order):
         H.rec.rec_clear()
         s.step(4)
         assert H.launches() == first
+
+
+@H.in_child
+def test_a_failed_allocation_is_not_reported_again():
+    H.rec.rec_fail_alloc(0)
+    with pytest.raises(B.SicError):
+        _sim()
+    with _sim() as s:  # its launches are not blamed
+        s.step(4)
+        H.rec.rec_fail_alloc(0)
+        with pytest.raises(B.SicError):
+            s.set_state(0, s.problem.x0, s.problem.v0)
+        s.step(4)
