@@ -185,7 +185,6 @@ struct Pool {
   int64_t *dr_work = nullptr;    // plan scratch, 4 n_sheets + 2
   int32_t *dr_state = nullptr;   // RefineState words
   Partial *dr_part = nullptr;    // work-item partials of refined deposits
-  int32_t dr_sheets = 0;
   // the other set of state arrays (a pass reads one set and writes the other);
   // alt_swapped counts the exchanges with xs, vs, segq and chunks, mod 2
   uint64_t *alt_xs = nullptr;
@@ -339,6 +338,16 @@ template <class T>
 hipError_t dalloc(T **p, size_t n) {
   if (n == 0) n = 1;
   return hipMalloc((void **)p, n * sizeof(T));
+}
+
+// Allocates an array that is not there yet (an earlier attempt may have got
+// only some of a call's arrays).
+template <class T>
+hipError_t dalloc_once(T **p, size_t n) {
+  if (*p) return hipSuccess;
+  const hipError_t e = dalloc(p, n);
+  if (e != hipSuccess) *p = nullptr;
+  return e;
 }
 
 void destroy_graphs(Pool *p) {
@@ -1625,11 +1634,9 @@ sic_status pool_relayout(Pool *p, int32_t slot, const std::vector<int32_t> &nt, 
 }
 
 sic_status ensure_refine_scratch(Pool *p, int64_t stage_tracers) {
-  if (!p->ref_cnt) {
-    HIPCHK(p, dalloc(&p->ref_cnt, (size_t)p->chunk_cap));
-    HIPCHK(p, dalloc(&p->ref_mask, (size_t)p->chunk_cap));
-    HIPCHK(p, dalloc(&p->ref_off, (size_t)p->chunk_cap));
-  }
+  HIPCHK(p, dalloc_once(&p->ref_cnt, (size_t)p->chunk_cap));
+  HIPCHK(p, dalloc_once(&p->ref_mask, (size_t)p->chunk_cap));
+  HIPCHK(p, dalloc_once(&p->ref_off, (size_t)p->chunk_cap));
   if (stage_tracers > p->ref_stage_cap) {
     if (p->ref_w) hipFree(p->ref_w);
     if (p->ref_v) hipFree(p->ref_v);
@@ -1638,9 +1645,9 @@ sic_status ensure_refine_scratch(Pool *p, int64_t stage_tracers) {
     p->ref_v = nullptr;
     p->ref_c = nullptr;
     p->ref_stage_cap = 0;
-    HIPCHK(p, dalloc(&p->ref_w, (size_t)stage_tracers));
-    HIPCHK(p, dalloc(&p->ref_v, (size_t)stage_tracers));
-    HIPCHK(p, dalloc(&p->ref_c, (size_t)stage_tracers));
+    HIPCHK(p, dalloc_once(&p->ref_w, (size_t)stage_tracers));
+    HIPCHK(p, dalloc_once(&p->ref_v, (size_t)stage_tracers));
+    HIPCHK(p, dalloc_once(&p->ref_c, (size_t)stage_tracers));
     p->ref_stage_cap = stage_tracers;
   }
   return SIC_OK;
@@ -2065,28 +2072,18 @@ sic_status dev_refine_begin(Pool *p) {
   sic_status st = ensure_refine_scratch(p, 0);
   if (st != SIC_OK) return st;
   const int32_t S = (int32_t)sh.n_tracers_s.size();
-  if (!p->alt_xs) {
-    const size_t slotsz = (size_t)p->chunk_cap * kChunk;
-    HIPCHK(p, dalloc(&p->alt_vs, slotsz));
-    HIPCHK(p, dalloc(&p->alt_segq, slotsz));
-    HIPCHK(p, dalloc(&p->alt_chunks, (size_t)p->chunk_cap));
-    HIPCHK(p, dalloc(&p->dr_state, (size_t)kRefWords));
-    HIPCHK(p, dalloc(&p->dr_part, (size_t)p->item_cap));
-    HIPCHK(p, dalloc(&p->alt_xs, slotsz));
-  }
-  if (p->dr_sheets < S) {
-    for (void *b : {(void *)p->dr_nt, (void *)p->dr_closed, (void *)p->dr_q, (void *)p->dr_work})
-      if (b) hipFree(b);
-    p->dr_nt = p->dr_closed = nullptr;
-    p->dr_q = nullptr;
-    p->dr_work = nullptr;
-    p->dr_sheets = 0;
-    HIPCHK(p, dalloc(&p->dr_nt, (size_t)S));
-    HIPCHK(p, dalloc(&p->dr_closed, (size_t)S));
-    HIPCHK(p, dalloc(&p->dr_q, (size_t)S));
-    HIPCHK(p, dalloc(&p->dr_work, 4 * (size_t)S + 2));
-    p->dr_sheets = S;
-  }
+  const size_t slotsz = (size_t)p->chunk_cap * kChunk;
+  HIPCHK(p, dalloc_once(&p->alt_xs, slotsz));
+  HIPCHK(p, dalloc_once(&p->alt_vs, slotsz));
+  HIPCHK(p, dalloc_once(&p->alt_segq, slotsz));
+  HIPCHK(p, dalloc_once(&p->alt_chunks, (size_t)p->chunk_cap));
+  HIPCHK(p, dalloc_once(&p->dr_state, (size_t)kRefWords));
+  HIPCHK(p, dalloc_once(&p->dr_part, (size_t)p->item_cap));
+  // (a simulation keeps the number of sheets that it was created with)
+  HIPCHK(p, dalloc_once(&p->dr_nt, (size_t)S));
+  HIPCHK(p, dalloc_once(&p->dr_closed, (size_t)S));
+  HIPCHK(p, dalloc_once(&p->dr_q, (size_t)S));
+  HIPCHK(p, dalloc_once(&p->dr_work, 4 * (size_t)S + 2));
   int32_t stw[kRefWords] = {};
   stw[kRefChunks] = stw[kRefStepChunks] = sh.n_chunks;
   HIPCHK(p, hipMemcpyAsync(p->dr_nt, sh.n_tracers_s.data(), sizeof(int32_t) * (size_t)S, hipMemcpyHostToDevice,

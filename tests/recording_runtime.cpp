@@ -55,6 +55,15 @@ void run_plan(const sic::RefinePassArgs &a) {
   if (plan_inserts) st[sic::kRefCur] ^= 1;
 }
 
+// Arrays that a refining step writes have to be there.
+void check_step(const sic::StepArgs &a) {
+  if (a.sel.state && !(a.sel.xs && a.sel.vs && a.sel.segq && a.sel.chunks && a.mark.cnt && a.mark.mask && a.part_ref))
+    events.push_back("null");
+}
+void check_plan(const sic::RefinePassArgs &a) {
+  if (!(a.cnt && a.mask && a.out_off && a.nt && a.closed && a.q && a.work)) events.push_back("null");
+}
+
 hipError_t alloc(void **p, size_t n) {
   if (fail_alloc >= 0 && fail_alloc-- == 0) return ret(hipErrorOutOfMemory);
   *p = std::calloc(1, n ? n : 1);
@@ -134,8 +143,11 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
     return hipSuccess;
   }
   ran.push_back(l);
-  if (name.find("k_refine_plan") != std::string::npos)
+  if (name.find("k_step") != std::string::npos) check_step(*static_cast<const sic::StepArgs *>(args[0]));
+  if (name.find("k_refine_plan") != std::string::npos) {
+    check_plan(*static_cast<const sic::RefinePassArgs *>(args[0]));
     run_plan(*static_cast<const sic::RefinePassArgs *>(args[0]));
+  }
   return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void *f, hipFuncAttribute, int value) {

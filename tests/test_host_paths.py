@@ -68,3 +68,17 @@ def test_a_failed_allocation_is_not_reported_again():
         with pytest.raises(B.SicError):
             s.set_state(0, s.problem.x0, s.problem.v0)
         s.step(4)
+
+
+@pytest.mark.parametrize("at", range(13))
+@H.in_child
+def test_a_refining_call_that_finds_no_memory_leaves_nothing_half_done(at):
+    with _sim(l_max=1.0, max_tracers=20000) as s:
+        H.rec.rec_fail_alloc(at)  # one of the arrays of the first refining call
+        with pytest.raises(B.SicError):
+            s.step(3)
+        H.rec.rec_fail_alloc(-1)
+        s.step(3)  # and the next call has them all
+        assert "null" not in H.events()
+        assert H.rec.rec_live() > 0
+    assert H.rec.rec_live() == 0
