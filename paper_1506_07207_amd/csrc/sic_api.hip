@@ -1162,6 +1162,19 @@ sic_status get_sf_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
   return SIC_OK;
 }
 
+// After a run of steps that could not be ended: charge may be left in any
+// accumulator set and the field is not that of the tracers.  Every set is
+// cleared, as all paths expect them, and the next step deposits and solves.
+void drop_charge(Pool *p) {
+  const int64_t arr = (int64_t)p->rep * mesh_words(p);
+  for (int i = 0; i < (p->sf_mesh ? 3 : 1); ++i) {
+    long long *set = sf_set(p, i);
+    (void)launch_zero_mesh(p->prec, set, set + arr, p->order == 1 ? set + 2 * arr : nullptr, p->inst, p->slot_ids, 1,
+                           p->rep, mesh_words(p), p->stream);
+  }
+  p->slots[0].state = kStale;
+}
+
 // A run of n solve-first steps.  The first one is launched by itself (it
 // reads the field instead of solving for it); the graphs of the others hold
 // a multiple of the six steps after which the accumulators, the partials and
@@ -1171,21 +1184,30 @@ constexpr int64_t kSfGraphSteps = 36;
 constexpr int64_t kSfDirectSteps = 6;
 
 sic_status run_sf(Pool *p, int64_t n) {
-  sic_status s = enqueue_sf(p, 0, p->stream);
-  for (int64_t i = 1; i < n && s == SIC_OK;) {
-    const int64_t k = std::min<int64_t>(n - i, kSfGraphSteps);
+  sic_status s = SIC_OK;
+  int64_t i = 0;  // steps launched
+  while (i < n && s == SIC_OK) {
+    const int64_t k = i == 0 ? 1 : std::min<int64_t>(n - i, kSfGraphSteps);
     if (k <= kSfDirectSteps) {
-      s = enqueue_sf(p, i++, p->stream);
-      continue;
+      s = enqueue_sf(p, i, p->stream);
+      if (s == SIC_OK) ++i;
+    } else {
+      hipGraphExec_t ex;
+      s = get_sf_graph(p, k, &ex);
+      if (s != SIC_OK) break;
+      const hipError_t e = hipGraphLaunch(ex, p->stream);
+      if (e != hipSuccess) {
+        s = fail(p, SIC_EDEVICE, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
+        break;
+      }
+      if (k & 1) p->parity ^= 1;
+      i += k;
     }
-    hipGraphExec_t ex;
-    s = get_sf_graph(p, k, &ex);
-    if (s != SIC_OK) break;
-    HIPCHK(p, hipGraphLaunch(ex, p->stream));
-    if (k & 1) p->parity ^= 1;
-    i += k;
   }
-  return s == SIC_OK ? close_sf(p, n, p->stream) : s;
+  // a launch that failed ends the run at the steps before it
+  const sic_status c = i > 0 ? close_sf(p, i, p->stream) : SIC_OK;
+  if (c != SIC_OK) drop_charge(p);
+  return s != SIC_OK ? s : c;
 }
 
 sic_status run_fused(Pool *p, int64_t n) {
@@ -2277,8 +2299,16 @@ sic_status sim_step_refining(Pool *p, int64_t n) {
     if (k & 1) p->parity ^= 1;
     i += k;
   }
-  sic_status st2 = dev_refine_end(p, parity0, sf);
-  return st != SIC_OK ? st : st2;
+  const int parity = p->parity;
+  const sic_status st2 = dev_refine_end(p, parity0, sf);
+  if (st != SIC_OK) {
+    // a step whose later launches failed has moved the tracers (unless the
+    // simulation was halted before it) and left its charge
+    if (st2 == SIC_OK) p->parity = parity;
+    drop_charge(p);
+    return st;
+  }
+  return st2;
 }
 
 sic_status sim_step(Pool *p, int64_t n) {

@@ -82,3 +82,53 @@ def test_a_refining_call_that_finds_no_memory_leaves_nothing_half_done(at):
         assert "null" not in H.events()
         assert H.rec.rec_live() > 0
     assert H.rec.rec_live() == 0
+
+
+def _names(rows):
+    return [next(n for n in ("k_step", "k_solve", "k_zero_mesh", "k_deposit", "k_refine_plan", "k_refine_rebuild")
+                 if n in k) for k, *_ in rows]
+
+
+@pytest.mark.parametrize("at", [0, 1, 4])
+@H.in_child
+def test_a_failed_launch_ends_the_run_at_the_steps_before_it(at):
+    with _sim() as s:
+        s.step(2)
+        H.rec.rec_clear()
+        H.rec.rec_fail_launch(b"k_step", at)
+        with pytest.raises(B.SicError):
+            s.step(6)
+        # the solve that ends a run takes the charge of the last step that was launched
+        assert _names(H.launches()) == ["k_step"] * at + ["k_solve"] * (at > 0)
+        H.rec.rec_clear()
+        s.step(2)
+        assert _names(H.launches()) == ["k_step"] * 2 + ["k_solve"]
+
+
+@H.in_child
+def test_a_run_that_cannot_be_ended_starts_from_the_tracers_again():
+    with _sim() as s:
+        s.step(2)
+        H.rec.rec_clear()
+        H.rec.rec_fail_launch(b"k_solve", 0)
+        with pytest.raises(B.SicError):
+            s.step(3)
+        assert _names(H.launches()) == ["k_step"] * 3 + ["k_zero_mesh"] * 3
+        H.rec.rec_clear()
+        s.step(2)
+        assert _names(H.launches()) == ["k_deposit", "k_solve"] + ["k_step"] * 2 + ["k_solve"]
+
+
+@H.in_child
+def test_a_refining_run_that_cannot_be_ended_starts_from_the_tracers_again():
+    with _sim(l_max=1.0, max_tracers=20000) as s:
+        s.step(2)
+        H.rec.rec_clear()
+        H.rec.rec_fail_launch(b"k_refine_rebuild", 1)
+        with pytest.raises(B.SicError):
+            s.step(3)
+        assert _names(H.launches()) == ["k_step", "k_refine_plan", "k_refine_rebuild", "k_deposit",
+                                        "k_step", "k_refine_plan", "k_solve"] + ["k_zero_mesh"] * 3
+        H.rec.rec_clear()
+        s.step(1)
+        assert _names(H.launches())[:3] == ["k_deposit", "k_solve", "k_step"]
