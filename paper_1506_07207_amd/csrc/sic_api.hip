@@ -141,7 +141,6 @@ struct Pool {
   int64_t chunk_cap = 0, item_cap = 0, hist_rows = 0, budget = 0;
   int64_t used_tracers = 0;
   int32_t used_slots = 0;
-  size_t lds_bytes = 0;
 
   uint64_t *xs = nullptr;
   double *vs = nullptr;
@@ -397,7 +396,6 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
   p->item_cap = chunk_cap / kMinTile + slot_cap + 1;
   p->hist_rows = hist_rows;
   p->budget = budget;
-  p->lds_bytes = tracer_lds_size(prec, order, seg, max_cells, kMaxTile);
   p->slots.resize(slot_cap);
   p->slot_items_h.assign(slot_cap, make_int2(0, 0));
   p->alloc.init(chunk_cap);
@@ -489,10 +487,8 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
                      p->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
   if (e != hipSuccess) return bail(std::string("init copy: ") + hipGetErrorString(e), SIC_EDEVICE);
-  if (p->lds_bytes > 65536) {
-    int le = set_tracer_lds_limit(prec, order, seg, p->lds_bytes);
-    if (le != 0) return bail(std::string("LDS limit: ") + hipGetErrorString((hipError_t)le), SIC_ENOTSUP);
-  }
+  const int le = set_tracer_lds_limit(prec, order, seg);
+  if (le != 0) return bail(std::string("LDS limit: ") + hipGetErrorString((hipError_t)le), SIC_ENOTSUP);
   *out = p;
   return SIC_OK;
 }

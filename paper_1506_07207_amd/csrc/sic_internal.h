@@ -387,7 +387,8 @@ bool step_supported(int order, int max_cells);
 // acc_zero NULL), in at most *grid workgroups and at most as many as run at a
 // time; *grid: the workgroups launched, each of which writes one partial.
 int launch_run(int prec, int order, bool seg, const StepArgs &a, int block, void *stream, int *grid);
-int set_tracer_lds_limit(int prec, int order, bool seg, size_t lds_bytes);
+// The tracer kernels' dynamic LDS limit, for every mesh and item size.
+int set_tracer_lds_limit(int prec, int order, bool seg);
 size_t tracer_lds_size(int prec, int order, bool seg, int mesh_cells, int tile_cap);
 // max_cells: the largest mesh of the slots the launch may solve.
 int launch_solve(int prec, const SolveArgs &a, int n_blocks, int max_cells, void *stream);

@@ -3424,17 +3424,28 @@ __global__ void __launch_bounds__(256) k_copy(const f64x2 *__restrict__ src, f64
 // ---------------------------------------------------------------------------
 constexpr size_t kLdsMax = 160 * 1024;  // per workgroup on gfx950
 
+// Raises a kernel's dynamic LDS limit to bytes, the most that a launch of it
+// asks for, before its first launch on a device (devices: those done).  The
+// limit belongs to the kernel, which all simulations and threads share: set to
+// one launch's size it would refuse a larger launch of another thread.
+static hipError_t allow_lds(const void *f, size_t bytes, std::atomic<uint64_t> &devices) {
+  int device = 0;
+  hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = 1ull << (device & 63);
+  if (devices.load() & bit) return hipSuccess;
+  e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess) devices.fetch_or(bit);
+  return e;
+}
+
 // The deposit-only launch of constant segments: its own LDS layout (no field,
 // a ring per wavefront), with the workgroup narrowed until it fits.
 template <int PREC, bool SEG>
 static hipError_t deposit_faces(const TracerArgs &a, int grid, int block, hipStream_t st) {
-  static bool limit_set = false;
-  if (!limit_set) {
-    const hipError_t e = hipFuncSetAttribute((const void *)k_deposit_faces<PREC, SEG>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
-    if (e != hipSuccess) return e;
-    limit_set = true;
-  }
+  static std::atomic<uint64_t> devices{0};
+  const hipError_t e = allow_lds((const void *)k_deposit_faces<PREC, SEG>, kLdsMax, devices);
+  if (e != hipSuccess) return e;
   size_t lds = dep_lds_bytes<SEG>(a.mesh_cells, a.tile_cap, block / kChunk);
   while (lds > kLdsMax && block > kChunk) {
     block /= 2;
@@ -3487,20 +3498,21 @@ static hipError_t tracers_prec(int mode, const TracerArgs &a, int grid, int bloc
   return hipGetLastError();
 }
 
+constexpr int kMaxItemChunks = 256;  // of a tracer launch's work item
+
 template <int PREC, int ORDER, bool SEG>
-static hipError_t set_lds_limit(size_t bytes) {
-  const int b = (int)bytes;
+static hipError_t set_lds_limit() {
+  static std::atomic<uint64_t> devices[4];
+  constexpr size_t bytes = tracer_lds_bytes<double, ORDER, SEG>(kMaxCells, kMaxItemChunks);
+  static_assert(bytes <= kLdsMax, "the largest item's tables");
   const void *fns[] = {(const void *)k_tracers<PREC, kPush, ORDER, SEG>,
                        (const void *)k_tracers<PREC, kPush | kDeposit, ORDER, SEG>,
                        (const void *)k_tracers<PREC, kKickHalf, ORDER, SEG>};
-  for (const void *f : fns) {
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, b);
+  for (int i = 0; i < 3; ++i) {
+    const hipError_t e = allow_lds(fns[i], bytes, devices[i]);
     if (e != hipSuccess) return e;
   }
-  if constexpr (ORDER != 0) {
-    return hipFuncSetAttribute((const void *)k_tracers<PREC, kDeposit, ORDER, SEG>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, b);
-  }
+  if constexpr (ORDER != 0) return allow_lds((const void *)k_tracers<PREC, kDeposit, ORDER, SEG>, bytes, devices[3]);
   return hipSuccess;
 }
 
@@ -3527,36 +3539,19 @@ struct LaunchTracers {
 
 template <int PREC, int ORDER, bool SEG>
 struct SetLdsLimit {
-  static hipError_t run(size_t bytes) { return set_lds_limit<PREC, ORDER, SEG>(bytes); }
+  static hipError_t run() { return set_lds_limit<PREC, ORDER, SEG>(); }
 };
 
-// The limit is a property of the kernel function, shared by every pool in
-// the process, so it only ever grows.
-int set_tracer_lds_limit(int prec, int order, bool seg, size_t lds) {
-  static size_t granted[3][3][2] = {};
-  if (prec < 0 || prec > 2 || order < 0 || order > 2) return (int)hipErrorInvalidValue;
-  size_t &g = granted[prec][order][seg ? 1 : 0];
-  if (lds <= std::max<size_t>(g, 65536)) return 0;
-  const hipError_t e = dispatch<SetLdsLimit>(prec, order, seg, lds);
-  if (e == hipSuccess) g = lds;
-  return (int)e;
-}
+int set_tracer_lds_limit(int prec, int order, bool seg) { return (int)dispatch<SetLdsLimit>(prec, order, seg); }
 
 // Solve-first steps (single simulations).
 template <int PREC, int ORDER, bool SEG, int CELLS>
 static hipError_t step_launch(const StepArgs &a, int grid, int block, size_t lds, hipStream_t st) {
-  // the dynamic LDS limit is raised to what a launch asks for, not to the
-  // whole 160 KB: the solve's static LDS takes part of it
-  static std::atomic<size_t> granted{65536};
-  if (lds > granted.load()) {
-    const hipError_t e = hipFuncSetAttribute((const void *)k_step<PREC, ORDER, SEG, CELLS>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();  // not left for the next launch to report
-      return e;
-    }
-    granted.store(lds);
-  }
+  // (not the whole 160 KB: the solve's static LDS takes part of it)
+  static std::atomic<uint64_t> devices{0};
+  const hipError_t e = allow_lds((const void *)k_step<PREC, ORDER, SEG, CELLS>,
+                                 tracer_lds_bytes<double, ORDER, SEG>(CELLS * kSolveThreads, 0), devices);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_step<PREC, ORDER, SEG, CELLS>), dim3(grid), dim3(block), lds, st, a);
   return hipGetLastError();
 }
@@ -3584,14 +3579,9 @@ struct LaunchRun {
     // as many workgroups as run at a time
     int per_cu = 1;
     const void *f = (const void *)k_step<PREC, ORDER, SEG, 0>;
-    if (lds > 65536) {
-      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return e;
-      }
-    }
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, block, lds);
+    static std::atomic<uint64_t> devices{0};
+    hipError_t e = allow_lds(f, tracer_lds_bytes<double, ORDER, SEG>(kMaxCells, 0), devices);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, block, lds);
     if (e != hipSuccess) return e;
     StepArgs b = a;
     const int n = std::max(1, std::min(*grid, std::max(1, per_cu) * kComputeUnits));
@@ -3643,14 +3633,10 @@ static hipError_t resident_launch(const TracerArgs &a, const SolveArgs &sa, int 
                                   int n_cells, int64_t n_steps, hipStream_t st) {
   constexpr int NW = CELLS <= 4 ? 12 : kSolveThreads / kChunk;
   const size_t lds = resident_lds_bytes<ORDER>(n_cells);
-  static std::atomic<bool> limit_set{false};
-  if (!limit_set.load()) {
-    const hipError_t e = hipFuncSetAttribute((const void *)k_resident<PREC, ORDER, SEG, CELLS, NW>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)resident_lds_bytes<ORDER>(CELLS * kSolveThreads));
-    if (e != hipSuccess) return e;
-    limit_set.store(true);
-  }
+  static std::atomic<uint64_t> devices{0};
+  const hipError_t e = allow_lds((const void *)k_resident<PREC, ORDER, SEG, CELLS, NW>,
+                                 resident_lds_bytes<ORDER>(CELLS * kSolveThreads), devices);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_resident<PREC, ORDER, SEG, CELLS, NW>), dim3(1), dim3((NW + 1) * kChunk), lds, st, a, sa,
                      chunk_begin, n_chunks, n_steps);
   return hipGetLastError();
@@ -3695,13 +3681,9 @@ static hipError_t solve_launch(const SolveArgs &a, int n_blocks, hipStream_t st)
   // (68 KB beside the static LDS)
   constexpr size_t lds = CELLS == 16 ? 2 * sizeof(double) * (CELLS + 1) * kSolveThreads : 0;
   if constexpr (lds > 0) {
-    static std::atomic<bool> limit_set{false};
-    if (!limit_set.load()) {
-      const hipError_t e = hipFuncSetAttribute((const void *)k_solve<PREC, CELLS, REP>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-      limit_set.store(true);
-    }
+    static std::atomic<uint64_t> devices{0};
+    const hipError_t e = allow_lds((const void *)k_solve<PREC, CELLS, REP>, lds, devices);
+    if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((k_solve<PREC, CELLS, REP>), dim3(n_blocks), dim3(kSolveThreads), lds, st, a);
   return hipGetLastError();

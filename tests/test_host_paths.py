@@ -132,3 +132,19 @@ def test_a_refining_run_that_cannot_be_ended_starts_from_the_tracers_again():
         H.rec.rec_clear()
         s.step(1)
         assert _names(H.launches())[:3] == ["k_deposit", "k_solve", "k_step"]
+
+
+@pytest.mark.parametrize("order", [0, 1])
+@H.in_child
+def test_a_launch_does_not_lower_the_lds_limit_of_larger_ones(order):
+    # more than 512 work items: launches of as many workgroups as run at a time
+    for cells in (4096, 3000, 2800):
+        with _sim(sheets=1100, n=8192, cells=cells, order=order, history_rows=8) as s:
+            s.step(2)
+            assert "k_step" in H.launches()[-2][0]
+    for cells in (4096, 2800, 2000, 300):
+        with _sim(cells=cells, order=order) as s, _sim(sheets=4, cells=cells, order=order) as r:
+            s.step(2)
+            r.step(2)
+            s.deposit()
+    assert not [e for e in H.events() if e.startswith("lowered")]
