@@ -831,7 +831,7 @@ MarkArgs mark_args(const Pool *p) {
   MarkArgs m;
   m.cnt = p->ref_cnt;
   m.mask = p->ref_mask;
-  m.total = p->dr_state + kRefMarks;
+  m.any = p->dr_state + kRefMarks;
   m.l_max = p->slots[0].l_max;
   m.chunk_begin = p->slots[0].chunk_begin;
   return m;

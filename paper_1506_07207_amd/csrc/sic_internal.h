@@ -148,10 +148,11 @@ struct SolveArgs {
 // Refinement done entirely on the device (one simulation, steps in a row):
 // int32 words of its state.
 //   kRefChunks      chunks of the slot now
-//   kRefInserted    tracers the last pass inserted (0: nothing re-laid out)
+//   kRefInserted    whether the last pass inserted tracers (> 0) or re-laid out
+//                   nothing (0)
 //   kRefHalt        set when a pass would exceed the capacity (sticky; the
 //                   following steps do nothing)
-//   kRefMarks       segments marked since the last plan
+//   kRefMarks       set when a segment was marked since the last plan
 //   kRefCur         which of the two sets of state arrays holds the state
 //   kRefSteps       steps taken
 //   kRefStepChunks  chunks at the newest step, before its refinement
@@ -177,11 +178,12 @@ struct RefineSel {
 };
 
 // Where a step marks the segments longer than l_max: per chunk from
-// chunk_begin on their count and lane mask, and their total; cnt NULL: none.
+// chunk_begin on their count and lane mask, and whether there are any; cnt
+// NULL: none.
 struct MarkArgs {
   int32_t *cnt = nullptr;
   uint64_t *mask = nullptr;
-  int32_t *total = nullptr;
+  int32_t *any = nullptr;
   double l_max = 0.0;
   int32_t chunk_begin = 0;
 };
