@@ -184,13 +184,14 @@ struct Pool {
   int64_t *dr_work = nullptr;    // plan scratch, 4 n_sheets + 2
   int32_t *dr_state = nullptr;   // RefineState words
   Partial *dr_part = nullptr;    // work-item partials of refined deposits
-  // the other set of state arrays (a pass reads one set and writes the other);
-  // alt_swapped counts the exchanges with xs, vs, segq and chunks, mod 2
+  // the other set of state arrays (a pass reads one set and writes the other).
+  // The arrays in xs, vs, segq and chunks hold the state between calls: they
+  // are set cur of the two, set 0 those of the pool's creation.
   uint64_t *alt_xs = nullptr;
   double *alt_vs = nullptr;
   uint64_t *alt_segq = nullptr;
   ChunkDesc *alt_chunks = nullptr;
-  int alt_swapped = 0;
+  int cur = 0;
   // solve-first steps of a single simulation (NULL: it has none): two more
   // accumulator sets (the pool's own is the third) and a second set of
   // work-item partials
@@ -814,16 +815,33 @@ int64_t mesh_words(const Pool *p) { return (int64_t)p->slot_cap * p->max_cells; 
 // Words of all accumulators: P, D (and R) in all copies.
 int64_t acc_words(const Pool *p) { return (p->order == 1 ? 3 : 2) * p->rep * mesh_words(p); }
 
-// The second set of state arrays and the state words of a simulation that
-// refines on the device.
-RefineSel refine_sel(const Pool *p) {
-  RefineSel r;
-  r.state = p->dr_state;
-  r.xs = p->alt_xs;
-  r.vs = p->alt_vs;
-  r.segq = p->alt_segq;
-  r.chunks = p->alt_chunks;
-  return r;
+// The two sets of state arrays of a simulation that refines on the device, in
+// the order of their names there (kRefCur), whichever holds the state: captured
+// launches stay right when a later call starts from the other set.
+struct StateSet {
+  uint64_t *xs;
+  double *vs;
+  uint64_t *segq;
+  ChunkDesc *chunks;
+};
+StateSet state_set(const Pool *p, int i) {
+  return i == p->cur ? StateSet{p->xs, p->vs, p->segq, p->chunks}
+                     : StateSet{p->alt_xs, p->alt_vs, p->alt_segq, p->alt_chunks};
+}
+
+// A refining launch's state arrays: set 0, and set 1 beside the state words.
+template <class Args>
+void set_refine_state(const Pool *p, Args *a) {
+  const StateSet s0 = state_set(p, 0), s1 = state_set(p, 1);
+  a->xs = s0.xs;
+  a->vs = s0.vs;
+  a->segq = s0.segq;
+  a->chunks = s0.chunks;
+  a->sel.state = p->dr_state;
+  a->sel.xs = s1.xs;
+  a->sel.vs = s1.vs;
+  a->sel.segq = s1.segq;
+  a->sel.chunks = s1.chunks;
 }
 
 // Where its steps mark the segments to split.
@@ -868,7 +886,7 @@ TracerArgs tracer_args(Pool *p, int mode, int slot) {
   // is made inactive when a pass would exceed its capacity
   a.respect_active = ((p->batch || p->dev_refine) && !one) ? 1 : 0;
   if (p->dev_refine) {
-    a.sel = refine_sel(p);
+    set_refine_state(p, &a);
     if (mode == (kPush | kDeposit)) a.mark = mark_args(p);
   }
   return a;
@@ -1085,7 +1103,7 @@ sic_status enqueue_sf(Pool *p, int64_t i, hipStream_t st) {
   a.part_out = part[i % 2];
   int grid = std::min(grid_for(p, -1), shape.n_items);
   if (p->dev_refine) {
-    a.sel = refine_sel(p);
+    set_refine_state(p, &a);
     a.mark = mark_args(p);
     a.tile_fixed = p->tune.tile_chunks > 0 ? p->tile : 0;
     a.part_ref = p->dr_part;
@@ -2104,6 +2122,7 @@ sic_status dev_refine_begin(Pool *p) {
   HIPCHK(p, dalloc_once(&p->dr_work, 4 * (size_t)S + 2));
   int32_t stw[kRefWords] = {};
   stw[kRefChunks] = stw[kRefStepChunks] = sh.n_chunks;
+  stw[kRefCur] = p->cur;
   HIPCHK(p, hipMemcpyAsync(p->dr_nt, sh.n_tracers_s.data(), sizeof(int32_t) * (size_t)S, hipMemcpyHostToDevice,
                            p->stream));
   HIPCHK(p, hipMemcpyAsync(p->dr_closed, sh.closed_s.data(), sizeof(int32_t) * (size_t)S, hipMemcpyHostToDevice,
@@ -2143,12 +2162,12 @@ sic_status dev_refine_end(Pool *p, int parity0, bool sf) {
     sic_status st = close_sf(p, steps, p->stream, stw);
     if (st != SIC_OK) return st;
   }
-  if (stw[kRefCur] != 0) {
+  if (stw[kRefCur] != p->cur) {
     std::swap(p->xs, p->alt_xs);
     std::swap(p->vs, p->alt_vs);
     std::swap(p->segq, p->alt_segq);
     std::swap(p->chunks, p->alt_chunks);
-    p->alt_swapped ^= 1;
+    p->cur ^= 1;
   }
   int64_t n_tr = 0;
   for (int32_t t : nt) n_tr += t;
@@ -2183,14 +2202,13 @@ sic_status enqueue_refining(Pool *p, int64_t i, hipStream_t st) {
   sic_status rc = sf ? enqueue_sf(p, i, st) : enqueue_fused(p, st);
   if (rc != SIC_OK) return rc;
   RefinePassArgs a;
-  a.chunks[0] = p->chunks;
-  a.chunks[1] = p->alt_chunks;
-  a.xs[0] = p->xs;
-  a.xs[1] = p->alt_xs;
-  a.vs[0] = p->vs;
-  a.vs[1] = p->alt_vs;
-  a.segq[0] = p->segq;
-  a.segq[1] = p->alt_segq;
+  for (int k = 0; k < 2; ++k) {
+    const StateSet set = state_set(p, k);
+    a.chunks[k] = set.chunks;
+    a.xs[k] = set.xs;
+    a.vs[k] = set.vs;
+    a.segq[k] = set.segq;
+  }
   a.halo = p->order == 1 ? p->halo3[p->parity] : p->halo[p->parity];
   a.cedge = p->cedge;
   a.links = p->order == 1 ? p->links : nullptr;
@@ -2243,7 +2261,7 @@ sic_status enqueue_refining(Pool *p, int64_t i, hipStream_t st) {
 // Graphs of k refining steps, keyed apart from the plain step graphs; sf: the
 // first is step 1 (mod 6) of a run of solve-first steps.
 sic_status get_refine_graph(Pool *p, int64_t k, bool sf, hipGraphExec_t *out) {
-  const GraphKey key = graph_key(p, k, kRefiningSteps + 2 * p->alt_swapped + (sf ? 1 : 0));
+  const GraphKey key = graph_key(p, k, kRefiningSteps + (sf ? 1 : 0));
   auto it = p->graphs.find(key);
   if (it != p->graphs.end()) {
     *out = it->second;

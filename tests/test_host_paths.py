@@ -148,3 +148,20 @@ def test_a_launch_does_not_lower_the_lds_limit_of_larger_ones(order):
             r.step(2)
             s.deposit()
     assert not [e for e in H.events() if e.startswith("lowered")]
+
+
+@pytest.mark.parametrize("tuning", [{}, {"fused_only": 1}])
+@H.in_child
+def test_refining_calls_reuse_their_graphs_whichever_set_holds_the_state(tuning):
+    with _sim(l_max=1.0, max_tracers=20000) as s:
+        if tuning:
+            B.sic_set_tuning(s.h, **tuning)
+        for _ in range(2):  # both halo parities
+            s.step(37)
+        H.rec.rec_plan_inserts(1)
+        s.step(37)  # one pass inserts: the other set holds the state
+        H.rec.rec_plan_inserts(0)
+        H.rec.rec_clear()
+        for _ in range(2):
+            s.step(37)
+        assert "instantiate" not in H.events()
