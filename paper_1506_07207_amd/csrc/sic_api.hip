@@ -438,7 +438,9 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
   // A single simulation's solve-first steps rotate through three accumulator
   // sets and two of partials.  They are there, and clear, from the start: a
   // first step call may be captured, and its launches then run later or never.
-  const int sets = !batch && step_supported(order, max_cells) ? 3 : 1;
+  // (One that can only be resident never takes such steps, unless it refines.)
+  const bool resident = resident_supported(order, (int)std::min<int64_t>(chunk_cap, INT32_MAX), max_cells);
+  const int sets = !batch && step_supported(order, max_cells) && (!resident || seg) ? 3 : 1;
   ALLOC(p->partials, (size_t)p->item_cap);
   if (sets > 1) ALLOC(p->sf_part, (size_t)p->item_cap);
   {
