@@ -125,9 +125,9 @@ struct SlotHost {
 
 // What a captured launch takes from the pool apart from its fixed buffers: the
 // number of steps, the halo parity, the launch shape (grid, workgroup and item
-// size, from which the LDS tables are sized), the solve grid and which kind of
-// step it is.
-using GraphKey = std::tuple<int64_t, int, int, int, int, int, int>;
+// size, from which the LDS tables are sized), the solve's shape (grid and cells
+// per thread) and which kind of step it is.
+using GraphKey = std::tuple<int64_t, int, int, int, int, int, int, int>;
 
 struct Pool {
   int prec = 0;
@@ -214,6 +214,8 @@ struct Pool {
   sic_tuning tune{};  // requested (0 = automatic)
   int block = kDefaultBlock, grid = kDefaultGrid, tile = kMinTile;
   int solve_grid = 1;  // solve workgroups of a whole-pool step: live slot indices, rounded up
+  int solve_cells = 1;  // the largest live mesh, rounded up to a size that the solve is built for
+  int32_t live_by_cells[3] = {0, 0, 0};  // live slots by that size (kSolveCells)
   std::map<GraphKey, hipGraphExec_t> graphs;
   std::vector<hipGraph_t> graph_objs;
   bool timing = false;
@@ -566,8 +568,16 @@ void apply_launch_shape(Pool *p) {
 // The whole-pool solve launches one workgroup per slot index up to the
 // highest live one (slots are taken lowest first), rounded up to a power of
 // two so that graphs are captured again only when that crosses one; the
-// workgroups of slots that are not live return at once.
-void update_solve_grid(Pool *p) {
+// workgroups of slots that are not live return at once.  It is built for the
+// largest live mesh, not for the largest that the batch would take: 16 cells
+// per thread need 68 KB of LDS and so leave two workgroups to a compute unit
+// (batches of max_cells 4096, us per solve by 16 cells per thread and by one:
+// 1024 simulations on 64 cells 20 and 10.5, 512 on 256 cells 14 and 8.4).
+void update_solve_shape(Pool *p, int32_t cells, int change) {
+  p->live_by_cells[solve_class(cells)] += change;
+  p->solve_cells = kSolveCells[0];
+  for (int c = 1; c < 3; ++c)
+    if (p->live_by_cells[c] > 0) p->solve_cells = kSolveCells[c];
   int32_t hw = 0;
   for (int32_t i = p->slot_cap - 1; i >= 0; --i)
     if (p->slots[i].live) {
@@ -934,7 +944,8 @@ sic_status launch_tracer_mode(Pool *p, int mode, int slot, hipStream_t st) {
 sic_status launch_solve_mode(Pool *p, int flags, int slot, hipStream_t st, int n_partials = -1) {
   SolveArgs a = solve_args(p, flags, slot);
   a.n_partials = n_partials;
-  LAUNCHCHK(p, launch_solve(p->prec, a, slot >= 0 ? 1 : p->solve_grid, p->max_cells, st));
+  if (slot >= 0) LAUNCHCHK(p, launch_solve(p->prec, a, 1, p->slots[slot].n_cells, st));
+  else LAUNCHCHK(p, launch_solve(p->prec, a, p->solve_grid, p->solve_cells, st));
   return SIC_OK;
 }
 
@@ -976,7 +987,7 @@ sic_status enqueue_fused(Pool *p, hipStream_t st) {
 enum GraphKind : int { kPairSteps = 0, kSolveFirstSteps = 1, kRefiningSteps = 2 };
 
 GraphKey graph_key(const Pool *p, int64_t k, int kind) {
-  return GraphKey(k, p->parity, p->grid, p->block, p->tile, p->solve_grid, kind);
+  return GraphKey(k, p->parity, p->grid, p->block, p->tile, p->solve_grid, p->solve_cells, kind);
 }
 
 sic_status get_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
@@ -1141,7 +1152,7 @@ sic_status close_sf(Pool *p, int64_t k, hipStream_t st, const int32_t *rs = null
       sa.n_refined = refine_items(rs[kRefChunks], fixed);
     }
   }
-  LAUNCHCHK(p, launch_solve(p->prec, sa, p->solve_grid, p->max_cells, st));
+  LAUNCHCHK(p, launch_solve(p->prec, sa, p->solve_grid, p->solve_cells, st));
   return SIC_OK;
 }
 
@@ -1600,7 +1611,7 @@ sic_status pool_admit(Pool *p, const sic_config *cfg, const sic_sheet *sheets, i
   }
   p->used_tracers += reserve_tr;
   p->used_slots += 1;
-  update_solve_grid(p);
+  update_solve_shape(p, sh.n_cells, 1);
   // ingest: place tracers, deposit, solve, half back-kick
   int le = ingest_slot(p, slot, dx0, nullptr, dv0, dc0, nullptr);
   if (le == 0) le = launch_zero_mesh(p->prec, p->meshP, p->meshD, p->meshR, p->inst, p->slot_ids + slot, 1, p->rep,
@@ -1769,7 +1780,7 @@ sic_status pool_release(Pool *p, int32_t slot) {
   p->used_tracers -= sh.max_tracers;
   p->used_slots -= 1;
   sh.live = false;
-  update_solve_grid(p);
+  update_solve_shape(p, sh.n_cells, -1);
   sh.chunk_in_off.clear();
   return SIC_OK;
 }
@@ -2255,7 +2266,7 @@ sic_status enqueue_refining(Pool *p, int64_t i, hipStream_t st) {
   if (!sf) {
     SolveArgs sa = solve_args(p, kHaveDeposit, 0);
     sa.gate = p->dr_state + kRefInserted;
-    LAUNCHCHK(p, launch_solve(p->prec, sa, 1, p->max_cells, st));
+    LAUNCHCHK(p, launch_solve(p->prec, sa, 1, sh.n_cells, st));
   }
   return SIC_OK;
 }

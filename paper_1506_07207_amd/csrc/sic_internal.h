@@ -43,6 +43,10 @@ constexpr int kMaxCells = 4096;     // mirrors SIC_MAX_CELLS
 constexpr int kSmallMeshRep = 4;
 constexpr int single_rep(int max_cells) { return max_cells <= 256 ? kSmallMeshRep : 2; }
 constexpr int kSolveThreads = 256;  // field-solve workgroup
+// The mesh sizes that the solve is built for (1, 4 and 16 cells per thread),
+// and the smallest of them that holds a mesh.
+constexpr int kSolveCells[3] = {kSolveThreads, 4 * kSolveThreads, 16 * kSolveThreads};
+constexpr int solve_class(int n_cells) { return n_cells <= kSolveCells[0] ? 0 : (n_cells <= kSolveCells[1] ? 1 : 2); }
 constexpr int kComputeUnits = 256;  // of an MI355X
 
 enum Prec : int { kFP64 = 0, kSplitF32 = 1, kSplitU32 = 2 };

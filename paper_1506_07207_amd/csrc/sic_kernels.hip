@@ -3656,10 +3656,7 @@ static hipError_t resident_launch(const TracerArgs &a, const SolveArgs &sa, int 
 }
 
 // Cells per solve thread the kernels are built for: 1, 4 or 16.
-static int solve_cells(int max_cells) {
-  const int per = (max_cells + kSolveThreads - 1) / kSolveThreads;
-  return per <= 1 ? 1 : (per <= 4 ? 4 : 16);
-}
+static int solve_cells(int max_cells) { return kSolveCells[solve_class(max_cells)] / kSolveThreads; }
 
 template <int PREC, int ORDER, bool SEG>
 struct LaunchResident {

@@ -44,3 +44,40 @@ def test_steps_while_empty_do_not_change_what_is_admitted_later(order, steps):
         finally:
             B.sic_batch_destroy(b)
     _same(*out)
+
+
+@pytest.mark.parametrize("order", [0, 1, 2])
+def test_larger_meshes_come_and_go(order):
+    # the solve is built for the largest live mesh; every simulation's bits are
+    # those it has alone in a batch
+    sizes = [64, 256, 257, 1024, 1025, 3000]
+    print(f"case batch meshes order={order}", flush=True)
+    probs = [I.landau(n_sheets=4, n_tracers=300 + i, n_cells=c, alpha=0.05) for i, c in enumerate(sizes)]
+    b = B.sic_batch_create(20000, 8, 4096, precision=B.SIC_SPLIT_U32, deposit_order=order)
+    try:
+        slots = []
+        for p in probs:  # 5 steps with each further mesh
+            slots.append(_admit(b, p, order))
+            B.sic_batch_step(b, 5)
+        first = _result(b, slots[0], probs[0])
+        for k in range(len(probs) - 1, 0, -1):
+            last = _result(b, slots[k], probs[k])
+            alone = B.sic_batch_create(20000, 1, sizes[k], precision=B.SIC_SPLIT_U32, deposit_order=order)
+            try:
+                s = _admit(alone, probs[k], order)
+                B.sic_batch_step(alone, last[2])
+                _same(last, _result(alone, s, probs[k]))
+            finally:
+                B.sic_batch_destroy(alone)
+            B.sic_batch_release(b, slots[k])
+            B.sic_batch_step(b, 2)
+        assert _result(b, slots[0], probs[0])[2] == first[2] + 2 * (len(probs) - 1)
+        alone = B.sic_batch_create(20000, 1, sizes[0], precision=B.SIC_SPLIT_U32, deposit_order=order)
+        try:
+            s = _admit(alone, probs[0], order)
+            B.sic_batch_step(alone, first[2] + 2 * (len(probs) - 1))
+            _same(_result(b, slots[0], probs[0]), _result(alone, s, probs[0]))
+        finally:
+            B.sic_batch_destroy(alone)
+    finally:
+        B.sic_batch_destroy(b)

@@ -165,3 +165,20 @@ def test_refining_calls_reuse_their_graphs_whichever_set_holds_the_state(tuning)
         for _ in range(2):
             s.step(37)
         assert "instantiate" not in H.events()
+
+
+@H.in_child
+def test_a_batch_solves_for_its_largest_live_mesh():
+    def lds(b):
+        H.rec.rec_clear()
+        B.sic_batch_step(b, 2)
+        return {row[3] for row in H.launches() if "k_solve" in row[0]}
+
+    b = _batch(max_cells=4096)
+    _admit(b, cells=64)
+    assert lds(b) == {0}  # the solve of 16 cells per thread has its charge in LDS
+    big = _admit(b, cells=1025)
+    assert lds(b) == {2 * 8 * 17 * 256}
+    B.sic_batch_release(b, big)
+    assert lds(b) == {0}
+    B.sic_batch_destroy(b)
