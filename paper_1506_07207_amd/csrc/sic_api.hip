@@ -42,7 +42,10 @@ constexpr int kDefaultBatchBlock = 512;  // batches
 constexpr int kDefaultBatchTile = 256;   // chunks per batch work item (16k tracers per LDS mesh merge)
 constexpr int kLinearBatchTile = 192;    // piecewise-linear segments: three workgroups per CU in LDS
 // (batch defaults: the autotuner's choice on the 4096-instance mixed batch)
-constexpr int kBatchItems = 3072;        // work items a batch's arena is cut into at least (slot_tile)
+// work items a batch's arena is cut into at least (slot_tile): constant segments
+// and first-order weighting, piecewise-linear ones, meshes that leave a compute
+// unit one workgroup
+constexpr int kBatchItems = 3072, kLinearBatchItems = 1024, kBatchItemsAlone = 192;
 constexpr int kMinBatchTile = 48;
 constexpr int kMinTile = 4;             // chunks per work item, lower bound
 constexpr int kMaxTile = 256;
@@ -498,6 +501,8 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
   return SIC_OK;
 }
 
+constexpr size_t kLdsPerCU = 160 * 1024;
+
 // Work-item size in chunks for a slot of n_chunks chunks.  A batch uses one
 // size for every slot: its default, or, where a batch's whole arena is fewer
 // than kBatchItems such items (12 per compute unit), the size that gives it
@@ -505,7 +510,15 @@ sic_status pool_create(int prec, int order, bool seg, bool batch, int32_t slot_c
 // tracers).  Large items leave compute units idle in the last round: us per
 // step with 256 chunks and with this rule's size, 3 simulations of 10900
 // chunks in all 44 -> 19, 14 of 81000 60 -> 48, 16 of 95000 65 -> 57; 96 of
-// 508000, 222, keep 256.  A single simulation sizes its items to give the
+// 508000, 222, keep 256.  Piecewise-linear items cost more before their first
+// chunk (three meshes, the neighbours of every chunk): four per compute unit
+// (24 simulations of 147000 chunks on 256 cells, items of 56, 168 and 192
+// chunks: 104, 94 and 98).  Where the mesh leaves a compute unit one
+// workgroup, nothing overlaps its clear and merge: items for three quarters of
+// the compute units, about one round (4096 cells, 48 or 56 chunks and this
+// rule's: 64 simulations of 22000 chunks 44 -> 37, 256 of 60000 96 -> 78, 24 of
+// 147000 136 -> 105; 192 or 256 chunks throughout: 53, 100, 115).  A single
+// simulation sizes its items to give the
 // machine about 2048 of them, up to the largest item (fewer, larger items
 // spend less on zeroing and merging the item's LDS mesh).  An item clears
 // and scans its whole LDS mesh, and once a sheet has folded over the box it
@@ -520,7 +533,9 @@ int slot_tile(const Pool *p, int64_t n_chunks) {
   if (p->tune.tile_chunks > 0) return std::max(kMinTile, std::min(kMaxTile, (int)p->tune.tile_chunks));
   const int wave_min = p->block / kChunk;
   if (p->batch) {
-    const int64_t fit = std::max<int64_t>(kMinBatchTile, (p->chunk_cap / kBatchItems + 7) / 8 * 8);
+    const bool alone = tracer_lds_size(p->prec, p->order, p->seg, p->max_cells, kMinBatchTile) > kLdsPerCU / 2;
+    const int items = alone ? kBatchItemsAlone : (p->order == 1 ? kLinearBatchItems : kBatchItems);
+    const int64_t fit = std::max<int64_t>(kMinBatchTile, (p->chunk_cap / items + 7) / 8 * 8);
     return std::max((int)std::min<int64_t>(fit, p->order == 1 ? kLinearBatchTile : kDefaultBatchTile), wave_min);
   }
   const int64_t per = (n_chunks + 2047) / 2048;
@@ -532,8 +547,6 @@ int slot_tile(const Pool *p, int64_t n_chunks) {
   t = (t + 3) / 4 * 4;
   return std::max(t, wave_min);
 }
-
-constexpr size_t kLdsPerCU = 160 * 1024;
 
 void apply_launch_shape(Pool *p) {
   if (p->tune.block_threads > 0) {

@@ -182,3 +182,20 @@ def test_a_batch_solves_for_its_largest_live_mesh():
     B.sic_batch_release(b, big)
     assert lds(b) == {0}
     B.sic_batch_destroy(b)
+
+
+@pytest.mark.parametrize("order,cells,chunks,size", [
+    # twelve items per compute unit, from 48 chunks to 256
+    (0, 1024, 20000, 48), (0, 1024, 150000, 56), (0, 1024, 900000, 256), (2, 256, 150000, 56),
+    # four of piecewise-linear segments, up to 192 chunks
+    (1, 1024, 20000, 48), (1, 1024, 150000, 168), (1, 1024, 900000, 192),
+    # three quarters of one where the mesh leaves room for one workgroup
+    (0, 4096, 10000, 64), (0, 4096, 20000, 120), (0, 4096, 150000, 256), (1, 3000, 10000, 64), (1, 3000, 150000, 192),
+])
+@H.in_child
+def test_a_batch_sizes_its_items_by_arena_order_and_mesh(order, cells, chunks, size):
+    b = B.sic_batch_create(chunks * 64, 1, cells, precision=B.SIC_SPLIT_U32, deposit_order=order, history_rows=8,
+                           stream=0)
+    _admit(b, cells=64, order=order)
+    assert B.sic_batch_get_tuning(b)["tile_chunks"] == size
+    B.sic_batch_destroy(b)
