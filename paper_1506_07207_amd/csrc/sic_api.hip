@@ -1885,6 +1885,8 @@ sic_status pool_diagnostics(Pool *p, int32_t slot, sic_diag *out, double *rho_ou
 
 sic_status pool_get_state(Pool *p, int32_t slot, double *x, double *v, int64_t *step, int32_t mem_kind) {
   if (slot < 0 || slot >= p->slot_cap || !p->slots[slot].live) return fail(p, SIC_EINVAL, "slot not live");
+  // (host memory: either may be NULL, what is not wanted is not copied)
+  if (mem_kind != SIC_MEM_HOST && (!x || !v)) return fail(p, SIC_EINVAL, "null device output");
   SlotHost &sh = p->slots[slot];
   double *dx = x, *dv = v, *stage = nullptr;
   if (step) {

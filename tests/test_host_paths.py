@@ -199,3 +199,14 @@ def test_a_batch_sizes_its_items_by_arena_order_and_mesh(order, cells, chunks, s
     _admit(b, cells=64, order=order)
     assert B.sic_batch_get_tuning(b)["tile_chunks"] == size
     B.sic_batch_destroy(b)
+
+
+@H.in_child
+def test_missing_device_outputs_are_refused_before_any_launch():
+    with _sim() as s:
+        H.rec.rec_clear()
+        some = np.zeros(s.n).ctypes.data
+        for x, v in ((None, None), (some, None), (None, some)):
+            assert B.load().sic_get_state(s.h, x, v, None, B.SIC_MEM_DEVICE) == 1
+        assert H.launches() == []
+        assert B.load().sic_get_state(s.h, None, None, None, B.SIC_MEM_HOST) == 0
