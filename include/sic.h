@@ -178,9 +178,10 @@ sic_status sic_push(sic_sim *sim);
  * every workgroup, and one solve launch closes the call
  * (SIC_PATH_SOLVE_FIRST); a small simulation (at most 32 chunks of 64 tracer
  * slots, linear segments: on at most 1024 cells) runs its steps in one launch
- * of a single workgroup
- * (SIC_PATH_RESIDENT).  All give the bits of the fused path in the split
- * forms.  Timing mode (sic_set_timing) always takes the fused path.  Async;
+ * of a single workgroup (SIC_PATH_RESIDENT).  In the split forms all give the
+ * fused path's bits of the state, the field, the density and the rows' W_E,
+ * total_charge, max_segment and flags; the rows' KE and momentum, and all sums
+ * in FP64, are equal to rounding (summed in another order).  Timing mode (sic_set_timing) always takes the fused path.  Async;
  * with refinement on (l_max > 0) each step is followed by a refinement pass
  * on the device (SIC_PATH_REFINING: graphs of steps and passes; the host
  * reads the layout back when it needs it).

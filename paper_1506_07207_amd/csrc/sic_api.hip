@@ -6,12 +6,15 @@
 // tracer kernel walks.  A sic_sim is a pool with one slot; a sic_batch is a
 // pool with many slots whose simulations advance in shared launches.
 //
-// Per step the device runs two kernels: the tracer kernel (gather, leapfrog
-// move, deposit of the new positions into the mesh) and the field solve (one
-// workgroup per slot).  Runs of steps are captured once into HIP graphs on a
-// private stream and replayed on the caller's stream; the graphs read the
-// item list and slot table from device memory, so admitting or retiring a
-// simulation never needs a new capture.
+// A batch's step is two kernels: the tracer kernel (gather, leapfrog move,
+// deposit of the new positions into the mesh) and the field solve (one
+// workgroup per slot).  A single simulation's step is one kernel that solves
+// the previous step's charge first, or, of a small one, part of a launch that
+// takes many steps; above 512 work items it is a pair as a batch's.  Runs of
+// steps are captured into HIP graphs on a private stream and replayed on the
+// caller's stream; the graphs read a batch's item list and slot table from
+// device memory, so admitting or retiring a simulation needs a new capture only
+// when the launch shape changes (graph_key).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1040,9 +1043,9 @@ long long *sf_set(Pool *p, int64_t i) {
                     : p->sf_mesh + (i % 3 - 1) * acc_words(p);
 }
 
-// Solve-first steps: a single simulation (not timed, not refining on the
-// device) runs k steps as k launches of one workgroup per item, whose second
-// and later ones solve the previous step's charge in every workgroup
+// Solve-first steps: a single simulation (not timed) runs k steps as k launches
+// of one workgroup per item or pair of items (sf_shape), whose second and later
+// ones solve the previous step's charge in every workgroup
 // (launch_step), then one solve launch for the last step.  The charge
 // rotates through three accumulator sets A0 (the pool's own), A1, A2 and the
 // partials through two buffers: step i of the run (from 0) merges into
@@ -1050,8 +1053,11 @@ long long *sf_set(Pool *p, int64_t i) {
 // (i - 1) mod 2, and clears A[(i + 1) mod 3], which step i - 1 read and step
 // i + 1 merges into after this one has ended.  The closing solve clears what
 // it reads and the set that the last step read, so every set is clear again,
-// as the other paths expect.  The bits are those of the tracer/solve launch
-// pairs: the same solve code, the same sums in the same order.
+// as the other paths expect.  In the split forms the state, the field, the
+// density and the rows' field energy, charge and longest segment have the bits
+// of the tracer/solve launch pairs (fixed-point sums in any order, the same
+// solve code); the rows' kinetic energy and momentum, and every sum in FP64, are
+// equal to rounding, as the items are summed in another order.
 bool sf_ready(const Pool *p) {
   if (p->batch || p->timing || p->tune.fused_only || p->block < kSolveThreads || !p->sf_mesh || p->tile > p->block)
     return false;
@@ -1169,8 +1175,7 @@ sic_status close_sf(Pool *p, int64_t k, hipStream_t st, const int32_t *rs = null
   return SIC_OK;
 }
 
-// A graph of k solve-first steps, the first of them step 1 (mod kSfPeriod)
-// of its run.
+// A graph of k solve-first steps, the first of them step 1 (mod 6) of its run.
 sic_status get_sf_graph(Pool *p, int64_t k, hipGraphExec_t *out) {
   const GraphKey key = graph_key(p, k, kSolveFirstSteps);
   auto it = p->graphs.find(key);

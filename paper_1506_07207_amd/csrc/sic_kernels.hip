@@ -1753,8 +1753,8 @@ __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
     const int nch = item.chunk_end - item.chunk_begin;
 
     // Loads and stores are unconditional (a chunk always has 64 slots; the
-    // padding slots of a sheet's last chunk are read and written back
-    // unchanged), so the only branches around memory operations are uniform.
+    // padding slots of a sheet's last chunk move with the others, see
+    // process_chunk), so the only branches around memory operations are uniform.
     // The state is streamed once per step: non-temporal loads and stores
     // keep it from displacing the meshes and tables in the caches.
     auto load_state = [&](int kk, uint64_t &xw, double &v, uint64_t &cw) {
@@ -3475,9 +3475,11 @@ static hipError_t deposit_faces(const TracerArgs &a, int grid, int block, hipStr
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k_deposit_faces<PREC, SEG>, block, lds);
     if (e != hipSuccess) return e;
     // where the LDS mesh leaves a compute unit one or two workgroups, they
-    // have little to do while one of them clears or merges (67M tracers on
-    // 4096 cells 150 -> 140 us); four overlap one another, and one item at a
-    // time spreads better (1024 cells: 138 us, 143 in runs of four)
+    // have little to do while one of them clears or merges (33.5M tracers, one
+    // item at a time and in runs: 2048 cells 111 and 107 us, 2500 116 and 111,
+    // 3000 155 and 137, 4096 192 and 170); four overlap one another, and one
+    // item at a time spreads better (67M tracers, 1024 cells: 138 us, 143 in
+    // runs of four)
     const int resident = std::max(1, per_cu) * kComputeUnits;
     b.run = per_cu > 2 ? 1 : std::max(1, std::min(b.run, (grid + resident - 1) / resident));
     grid = (grid + b.run - 1) / b.run;
@@ -3638,9 +3640,10 @@ int launch_tracers(int prec, int mode, int order, bool seg, const TracerArgs &a,
 // up to three chunks each and one for the rows (a pass of 100 steps of 32
 // chunks on 128 cells: 619 us; 8 wavefronts 692, 11 674, 15 651; of one chunk:
 // 424, and 409 with 8); larger ones, whose solve holds 16 cells per thread in
-// registers, with four (2 x 1000 tracers on 4096 cells, 100 steps: 1.69 ms,
-// 1.77 as solve-first launches) and, with a third array, not with linear
-// segments.
+// registers, with four (us per step, with the rows in the chain before and now:
+// 64 tracers on 1100, 2048 and 4096 cells 4.9, 6.1, 10.7 and 3.9, 5.3, 10.2;
+// 2 x 1000 tracers 12.0, 13.1, 17.9 and 8.3, 9.7, 14.6; as solve-first launches
+// the last one takes 17.7) and, with a third array, not with linear segments.
 template <int PREC, int ORDER, bool SEG, int CELLS>
 static hipError_t resident_launch(const TracerArgs &a, const SolveArgs &sa, int chunk_begin, int n_chunks,
                                   int n_cells, int64_t n_steps, hipStream_t st) {
