@@ -3762,7 +3762,7 @@ int launch_export(const ExportArgs &a, void *stream) {
   // max_rows is the room for rows, most of it often unused: a thread for every
   // four words that there may be
   const int64_t words = std::max<int64_t>(2 * a.nc, 8 * a.max_rows);
-  const int grid = (int)std::min<int64_t>(8, (words + 1023) / 1024);
+  const int grid = (int)std::min<int64_t>(8, words / 1024 + 1);  // at least one: the descriptor and the row
   hipLaunchKernelGGL(k_export, dim3(grid), dim3(256), 0, (hipStream_t)stream, a);
   return (int)hipGetLastError();
 }

@@ -135,6 +135,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
   const std::string &name = names[f];
   const size_t limit = limits.count(f) ? limits[f] : 65536;
   if (lds > limit) return ret(hipErrorInvalidValue);
+  if (grid.x == 0 || block.x == 0) return ret(hipErrorInvalidConfiguration);
   if (fail_launch >= 0 && name.find(fail_kernel) != std::string::npos && fail_launch-- == 0)
     return ret(hipErrorLaunchFailure);
   const Launch l = {name, grid.x, block.x, lds};

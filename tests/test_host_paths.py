@@ -1,5 +1,7 @@
 """What the host code launches, allocates and releases, on the CPU: libsic
 bound to a runtime that records calls and runs nothing."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -210,3 +212,22 @@ def test_missing_device_outputs_are_refused_before_any_launch():
             assert B.load().sic_get_state(s.h, x, v, None, B.SIC_MEM_DEVICE) == 1
         assert H.launches() == []
         assert B.load().sic_get_state(s.h, None, None, None, B.SIC_MEM_HOST) == 0
+
+
+@H.in_child
+def test_diagnostics_of_any_part_alone():
+    lib, n = B.load(), ctypes.c_int64(0)
+    rows = np.zeros(8, dtype=B.DIAG_DTYPE).ctypes.data
+    mesh, last = np.zeros(64).ctypes.data, B.sic_diag()
+    with _sim() as s:
+        s.step(3)
+        for args in ((None, None, None, None, ctypes.byref(n)), (ctypes.byref(last), None, None, None, None),
+                     (None, mesh, None, None, None), (None, None, mesh, None, None),
+                     (None, None, None, rows, ctypes.byref(n)), (None, None, None, None, None)):
+            n.value = 8
+            assert lib.sic_diagnostics(s.h, *args) == 0, args
+    b = _batch()
+    slot = _admit(b)
+    assert lib.sic_batch_result(b, slot, None, None, None, None, ctypes.byref(n)) == 0
+    B.sic_batch_result(b, slot, history=False)
+    B.sic_batch_destroy(b)
