@@ -77,15 +77,3 @@ def test_a_first_call_captured_and_dropped_changes_nothing(case):
         a.step(9)
         b.step(9)
         _equal(a, b, 9)
-
-
-def test_length_and_newest_row_alone():
-    import ctypes
-
-    p = I.landau(n_sheets=4, n_tracers=50, n_cells=33, alpha=0.05)
-    with B.Simulation(p) as s:
-        s.step(5)
-        n = ctypes.c_int64(0)
-        assert B.load().sic_diagnostics(s.h, None, None, None, None, ctypes.byref(n)) == 0 and n.value == 6
-        d = B.sic_diagnostics(s.h, history=False)
-        assert d["last"]["step"] == 5 and d["last"]["W_E"] == s.diagnostics()["last"]["W_E"]
