@@ -14,9 +14,12 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 rec = None  # the recording runtime, in the child
 
 
+_folder = tempfile.TemporaryDirectory(prefix="sic_rec_")  # removed when the tests end
+
+
 @functools.lru_cache(maxsize=None)
 def _runtime() -> str:
-    out = os.path.join(tempfile.mkdtemp(prefix="sic_rec_"), "librec.so")
+    out = os.path.join(_folder.name, "librec.so")
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__",
                     "-I", os.path.join(ROCM, "include"), "-I", os.path.join(ROOT, "paper_1506_07207_amd", "csrc"),
                     "-o", out, os.path.join(HERE, "recording_runtime.cpp")], check=True)
