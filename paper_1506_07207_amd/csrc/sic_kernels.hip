@@ -1453,14 +1453,12 @@ struct WaveTabs {
 
 // One chunk of a work item: the move (or half kick) and the deposit of its
 // segments.  halo_out: orders 0, 2 one copy per chunk, order 1 three.  STORE
-// false: the moved state stays in xw and v.  marked: set where a segment of
-// the chunk is marked (mark given).
+// false: the moved state stays in xw and v.
 template <int PREC, int MODE, int ORDER, bool SEG, bool STORE = true>
 __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t, const Geo &g, double q_unit,
                                               uint64_t *xs, double *vs, double2 *halo_out, const ChunkTab &tab,
                                               size_t chunk, int lane, uint64_t &xw, double &v, uint64_t cw, double &ke,
-                                              double &mom, double &ms, const MarkArgs &mark = MarkArgs(),
-                                              bool *marked = nullptr) {
+                                              double &mom, double &ms, const MarkArgs &mark = MarkArgs()) {
   constexpr bool kLin = ORDER == 1;
   constexpr bool kDep = (MODE & kDeposit) != 0;
   constexpr bool kKick = (MODE & kKickHalf) != 0;
@@ -1629,21 +1627,18 @@ __device__ __forceinline__ void process_chunk(const ItemLds<PREC, ORDER, SEG> &t
       const bool has = valid && !(tail && ch.partner < 0);
       const bool split = has && mark_length<PREC>(xw, tail ? tab.next : dn, g) > mark.l_max;
       const uint64_t lanes = __builtin_amdgcn_ballot_w64(split);
-      *marked = *marked || lanes != 0;
       if (lane == 0) {
         mark.cnt[chunk - mark.chunk_begin] = __builtin_popcountll(lanes);
         mark.mask[chunk - mark.chunk_begin] = lanes;
+        // A plain store, the same from every chunk.  (A count would need an
+        // atomic on one word, which the marked chunks then wait for in turn:
+        // 1.04M tracers, 16000 chunks, took 60 us per step launch, 15 with
+        // this; a flag per wavefront, stored once, cost 1 to 7 % of every
+        // step with per-segment charges in scalar registers.)
+        if (lanes) *mark.any = 1;
       }
     }
   }
-}
-
-// Tells the plan that a wavefront's chunks hold marked segments: a store per
-// wavefront and step.  (A count would need an atomic on one word, which every
-// marked chunk then waits for in turn: 1.04M tracers, 16000 chunks, most of
-// them marked, took 60 us per step launch, 15 with this.)
-__device__ __forceinline__ void report_marks(const MarkArgs &mark, bool marked, int lane) {
-  if (marked && lane == 0) *mark.any = 1;
 }
 
 // Work-item partial sums in a fixed order (deterministic for a fixed item
@@ -1842,7 +1837,6 @@ __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
     // the next two chunks is in flight while the current one is processed
     // (moving a register whose load is pending would force a wait).
     double ke = 0.0, mom = 0.0, ms = 0.0;
-    bool marked = false;
     for (int k = wave; k < nch; k += kPrefetch * nwaves) {
 #pragma unroll
       for (int j = 0; j < kPrefetch; ++j) {
@@ -1862,13 +1856,12 @@ __global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
             tab.next_u = h.y;
           }
           process_chunk<PREC, MODE, ORDER, SEG>(t, g, I.q_unit, a.xs, a.vs, kLin ? a.halo3_out : a.halo_out, tab,
-                                                (size_t)(cb + kk), lane, xr[j], vr[j], cr_[j], ke, mom, ms, a.mark, &marked);
+                                                (size_t)(cb + kk), lane, xr[j], vr[j], cr_[j], ke, mom, ms, a.mark);
         }
         load_state(k + (j + kPrefetch) * nwaves, xr[j], vr[j], cr_[j]);
       }
     }
 
-    if constexpr (SEG && MODE == (kPush | kDeposit)) report_marks(a.mark, marked, lane);
     item_partial<MODE>(ke, mom, ms, t.sRed, a.partials + it);
     if constexpr (kDep) {
       const int64_t roff = I.mesh_off + (int64_t)(it % a.rep) * a.rep_stride;
@@ -2104,7 +2097,6 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
     }
     __syncthreads();  // the field, the cleared mesh
     double ke = 0.0, mom = 0.0, ms = 0.0;
-    bool marked = false;
     if (it >= 0) {
       for (;;) {
         tabs.move(halos, g, t.sE);
@@ -2116,7 +2108,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
             const int c = k + j * stride;
             if (c < gend)
               process_chunk<PREC, kMode, ORDER, SEG>(t, g, a.q_unit, a.xs, a.vs, a.halo_out, tabs.entry(i++),
-                                                     (size_t)c, lane, xr[j], vr[j], cr_[j], ke, mom, ms, a.mark, &marked);
+                                                     (size_t)c, lane, xr[j], vr[j], cr_[j], ke, mom, ms, a.mark);
             load_state(c + kPrefetch * stride, xr[j], vr[j], cr_[j]);
           }
         }
@@ -2128,7 +2120,6 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
         load_first_states();
       }
     }
-    if constexpr (SEG && kSolve) report_marks(a.mark, marked, lane);
     const bool with_row = kSolve && row && it == it0;
     if (with_row && wave < kSolveThreads / kChunk) {
       // the row's wavefront sums, in the solve launch's order: thread tid
