@@ -204,16 +204,20 @@ def make_sheets(n_tracers, q, closed=None):
 
 def _history(call):
     """All history rows through call(rows, length): one call where they fit
-    its first buffer (asking for the length first would wait for the device
-    twice), and a second with room for as many as there are."""
-    n = ctypes.c_int64(1024)
+    its first buffer, which has room for a simulation's default ring (asking
+    for the length first would wait for the device twice), and a second with
+    room for as many as there are."""
+    n = ctypes.c_int64(65536)
     size = DIAG_DTYPE.itemsize
     while True:
         room = n.value
         rows = np.empty(room * size, dtype=np.uint8)  # bytes: a copy of rows goes field by field
         call(rows.ctypes.data, ctypes.byref(n))
         if n.value < room:
-            return rows[: n.value * size].copy().view(DIAG_DTYPE)
+            rows = rows[: n.value * size]
+            # few rows do not keep the buffer; of one that stays only the
+            # pages written are in memory
+            return (rows.copy() if n.value < 4096 else rows).view(DIAG_DTYPE)
         call(None, ctypes.byref(n))
         if n.value <= room:
             return rows.view(DIAG_DTYPE)

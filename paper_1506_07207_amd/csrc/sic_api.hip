@@ -1822,7 +1822,8 @@ sic_status ensure_pin(Pool *p) {
 }
 
 // A slot's descriptor, newest row, mesh (with mesh) and up to rows history
-// rows into p->pin; waits for the stream.
+// rows (no more than the block holds, else none) into p->pin; waits for the
+// stream.
 sic_status export_slot(Pool *p, int32_t slot, bool mesh, int64_t rows, InstDesc *I) {
   sic_status st = ensure_pin(p);
   if (st != SIC_OK) return st;
@@ -1834,7 +1835,8 @@ sic_status export_slot(Pool *p, int32_t slot, bool mesh, int64_t rows, InstDesc 
   a.E = mesh ? p->meshE + mesh_off : nullptr;
   a.nc = mesh ? p->slots[slot].n_cells : 0;
   a.hist_from = p->slots[slot].hist_from;
-  a.max_rows = std::min(rows, p->pin_rows);
+  a.rows = rows;
+  a.max_rows = p->pin_rows;
   a.out = p->pin;
   LAUNCHCHK(p, launch_export(a, p->stream));
   HIPCHK(p, hipStreamSynchronize(p->stream));

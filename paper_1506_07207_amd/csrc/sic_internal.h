@@ -311,7 +311,8 @@ struct ExtractArgs {
 // What a diagnostics call reads of a slot, written in one launch to a block
 // of host memory: its descriptor (at 0), the newest row (kExportRow), the
 // density and the field (kExportMesh, nc words each; where wanted) and the
-// newest max_rows rows of the history, oldest first.
+// newest rows of the history that the call takes, oldest first, unless they
+// are more than max_rows.
 constexpr size_t kExportRow = 128, kExportMesh = 192;
 struct ExportArgs {
   const InstDesc *inst;    // the slot's
@@ -319,7 +320,8 @@ struct ExportArgs {
   const double *rho, *E;   // both or neither
   int32_t nc;
   int64_t hist_from;       // the step the history starts at
-  int64_t max_rows;
+  int64_t rows;            // that the call takes at most
+  int64_t max_rows;        // that the block has room for
   unsigned char *out;
 };
 

@@ -3393,7 +3393,8 @@ __global__ void __launch_bounds__(256) k_export(ExportArgs a) {
     out += 2 * a.nc;
   }
   const int64_t avail = min(step + 1 - min(step, a.hist_from), cap);
-  const int64_t rows = min(avail, a.max_rows);
+  int64_t rows = min(avail, a.rows);
+  if (rows > a.max_rows) rows = 0;  // the caller copies them
   for (int64_t i = tid; i < rows * kRowWords; i += nt) {
     const DiagRow *r = a.hist + row_of(step + 1 - rows + i / kRowWords, cap);
     out[i] = reinterpret_cast<const uint64_t *>(r)[i % kRowWords];
@@ -3750,9 +3751,9 @@ int launch_extract(int prec, const ExtractArgs &a, void *stream) {
 }
 
 int launch_export(const ExportArgs &a, void *stream) {
-  // max_rows is the room for rows, most of it often unused: a thread for every
-  // four words that there may be
-  const int64_t words = std::max<int64_t>(2 * a.nc, 8 * a.max_rows);
+  // most of the room for rows is often unused: a thread for every four words
+  // that there may be
+  const int64_t words = std::max<int64_t>(2 * a.nc, 8 * std::min(a.rows, a.max_rows));
   const int grid = (int)std::min<int64_t>(8, words / 1024 + 1);  // at least one: the descriptor and the row
   hipLaunchKernelGGL(k_export, dim3(grid), dim3(256), 0, (hipStream_t)stream, a);
   return (int)hipGetLastError();
