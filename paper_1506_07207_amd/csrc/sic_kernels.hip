@@ -1709,8 +1709,16 @@ __device__ __forceinline__ void select_state(Args &a) {
   }
 }
 
+// Held to the registers of six wavefronts per SIMD (80), so that three
+// workgroups of 512 threads share a compute unit; a few more leave room for
+// two (first-order weighting, split U32, per-segment charges, 30.7M tracers at
+// 82 registers 301 us, at 80 and 8 bytes of scratch 281; linear segments,
+// split U32 272 and 249, FP64 with charges 141 and 133).  Linear segments with
+// charges in the split forms take 93: at 80 they spill 64 bytes in the chunk
+// loop (310 us, 395 at 80).
 template <int PREC, int MODE, int ORDER, bool SEG>
-__global__ void __launch_bounds__(1024) k_tracers(TracerArgs a) {
+__global__ void __launch_bounds__(1024)
+    __attribute__((amdgpu_waves_per_eu(ORDER == 1 && SEG && PREC != kFP64 ? 5 : 6))) k_tracers(TracerArgs a) {
   using acc_t = typename std::conditional<PREC == kFP64, double, unsigned long long>::type;
   if constexpr (SEG) select_state(a);
   extern __shared__ __align__(16) unsigned char smem[];
