@@ -967,15 +967,34 @@ sic_status launch_solve_mode(Pool *p, int flags, int slot, hipStream_t st, int n
 
 StepArgs step_args(Pool *p);
 
+// Whether a single simulation of more items than solve-first steps take steps
+// as one workgroup per item or as many workgroups as the machine holds at a
+// time, which go through all chunks together (launch_run).  A run clears and
+// merges each workgroup's mesh once, but its kernel leaves a compute unit two
+// workgroups of 512 threads where the items' leaves three.  So runs are taken
+// where the mesh leaves the items' kernel one workgroup as well (us per step
+// as items and in runs, 33.5M tracers: 3000 cells 266 and 224, linear 307 and
+// 282, first-order 272 and 233), and otherwise where an item holds few tracers
+// per cell: up to nine with constant segments and FP64 first-order weighting,
+// which memory bounds (8 tracers: 66 and 63, 75 and 71; 14: 226 and 228), six
+// with first-order weighting in the split forms and with linear segments with
+// charges (6: 79 and 76, 96 and 90; 8: 71 and 74, 89 and 89), five with linear
+// segments, which instruction issue bounds (4: 57 and 56; 6: 85 and 87; 8: 78
+// and 86; 16: 255 and 289).
+bool runs_pay(const Pool *p) {
+  if (2 * tracer_lds_size(p->prec, p->order, p->seg, p->max_cells, p->tile) > kLdsPerCU) return true;
+  int most = 9;
+  if (p->order == 1) most = p->seg ? 6 : 5;
+  else if (p->order == 2 && p->prec != kFP64) most = 6;
+  return kChunk * p->tile <= most * p->max_cells;
+}
+
 // The tracer launch of a fused step for the whole pool; *n_partials as
-// launch_solve_mode takes it.  A single simulation of more items than
-// solve-first steps take runs as many workgroups as the machine holds at a
-// time, which go through all chunks together (launch_run): 33.5M tracers on
-// 4096 cells 262 -> 216 us per launch.
+// launch_solve_mode takes it.
 sic_status launch_fused_tracers(Pool *p, hipStream_t st, int *n_partials) {
   *n_partials = -1;
   if (p->batch || p->dev_refine || p->tune.grid_blocks > 0 || p->tune.tile_chunks > 0 ||
-      grid_for(p, -1) <= kSfMaxGrid)
+      grid_for(p, -1) <= kSfMaxGrid || !runs_pay(p))
     return launch_tracer_mode(p, kPush | kDeposit, -1, st);
   StepArgs a = step_args(p);
   a.acc_out = p->meshP;
