@@ -3482,6 +3482,11 @@ static hipError_t deposit_faces(const TracerArgs &a, int grid, int block, hipStr
     // runs of four)
     const int resident = std::max(1, per_cu) * kComputeUnits;
     b.run = per_cu > 2 ? 1 : std::max(1, std::min(b.run, (grid + resident - 1) / resident));
+    // Of two workgroups per compute unit, runs that leave many of the places
+    // empty lose more than they save: 600 items in 300 pairs (2048 cells, with
+    // charges) 38 -> 42 us, 698 in 349 (3000 cells) 50 -> 52 to 57; 820 in 410
+    // 50 -> 44, with charges 58 -> 53 but 1639 in runs of four 96 -> 101.
+    if (per_cu == 2 && (SEG ? 10 : 4) * grid < (SEG ? 9 : 3) * resident * b.run) b.run = 1;
     grid = (grid + b.run - 1) / b.run;
   }
   hipLaunchKernelGGL((k_deposit_faces<PREC, SEG>), dim3(grid), dim3(block), lds, st, b);

@@ -34,6 +34,7 @@ hipStream_t capture_stream = nullptr;
 long fail_alloc = -1, fail_launch = -1;
 std::string fail_kernel;
 bool plan_inserts = false;
+int occupancy = 1;
 hipError_t last = hipSuccess;
 struct {
   dim3 grid, block;
@@ -96,6 +97,7 @@ void rec_fail_launch(const char *kernel, long n) {
   fail_launch = n;
 }
 void rec_plan_inserts(int on) { plan_inserts = on != 0; }
+void rec_occupancy(int n) { occupancy = n; }  // workgroups that a compute unit holds
 long rec_live() { return (long)live.size(); }
 void rec_clear() {
   ran.clear();
@@ -157,7 +159,7 @@ hipError_t hipFuncSetAttribute(const void *f, hipFuncAttribute, int value) {
   return hipSuccess;
 }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) {
-  *n = 1;
+  *n = occupancy;
   return hipSuccess;
 }
 hipError_t hipMalloc(void **p, size_t n) { return alloc(p, n); }

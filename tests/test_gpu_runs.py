@@ -34,6 +34,24 @@ def test_runs_are_taken_where_they_pay(order, prec, charges, cells, runs):
     B.sic_destroy(h)
 
 
+@pytest.mark.parametrize("items,charges,per_cu,grid", [
+    (600, False, 1, 200), (600, False, 2, 600), (600, False, 3, 600), (600, True, 2, 600),
+    (820, False, 2, 410), (820, True, 2, 820), (1024, False, 2, 512), (1024, True, 2, 512), (1024, False, 1, 256),
+])
+@H.in_child
+def test_deposits_run_where_the_runs_fill_the_machine(items, charges, per_cu, grid):
+    n = items * 128 * 64  # 2048 cells: items of 128 chunks
+    x, v = np.linspace(0.0, 12.0, n, endpoint=False), np.zeros(n)
+    c = np.full(n, 1.0 / n) if charges else None
+    h = B.sic_init(12.0, 2048, 0.05, [n], [1.0 / n], [1], x, v, seg_charges=c, history_rows=8, stream=0)
+    assert B.sic_get_tuning(h)["grid_blocks"] == items
+    H.rec.rec_clear()
+    H.rec.rec_occupancy(per_cu)
+    B.sic_deposit(h)
+    assert H.launches()[-1][1] == grid
+    B.sic_destroy(h)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("order,charges", [(0, True), (1, False), (1, True), (2, False), (2, True)])
 @pytest.mark.parametrize("prec", [B.SIC_FP64, B.SIC_SPLIT_F32, B.SIC_SPLIT_U32])
